@@ -7,6 +7,7 @@
 #include "ppd_kernels.h"
 #include "ppd_launch.h"
 #include "ppd_prefill.h"
+#include "ppd_fused.h"
 
 #include <math.h>
 #include <stdlib.h>
@@ -14,6 +15,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <mutex>
 
 #include <new>
 #include <vector>
@@ -95,6 +97,11 @@ struct ppd_ctx {
   int graph_chunks[4];   // attention grid (64-position chunks) each graph was captured with
   int gmax1, gmax2;      // workgroup budget of an fp32 GEMM launch: one group / per group of a two-group launch
   int nchunk_max;
+  // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
+  int fused, fused_grid, fused_lds, device;
+  FusedArgs fused_args;
+  FLayer* fl_tab;        // [n_layers] in device memory
+  float *fl_ex, *fl_part, *h_save;   // outputs of the steps [n_layers], attention partials, the rows as the round found them
   // round state
   int n_ctx;      // absolute position of the pending token x_t (-1: no prefill yet)
   int matched;    // the pending token already went through layers 1..nb (its h is row 0)
@@ -123,6 +130,13 @@ int g_create_hip_error = 0;   // hipError_t of the last context-free call (ppd_c
       return PPD_EHIP;                          \
     }                                           \
   } while (0)
+
+int env_int(const char* name, int dflt) {
+  const char* v = getenv(name);
+  if (!v || !*v) return dflt;
+  int x = atoi(v);
+  return x > 0 ? x : dflt;
+}
 
 inline size_t cache_head_floats(const ppd_ctx* c) { return kv_blocks(c->d.max_ctx) * KV_BLOCK * c->d.head_dim; }
 inline size_t cache_layer_bytes(const ppd_ctx* c) { return (size_t)c->d.n_heads * cache_head_floats(c) * sizeof(float); }
@@ -447,6 +461,59 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
   return PPD_OK;
 }
 
+// The arguments of a one-launch chain of layers on row 0 that do not change, and its layout of a compute unit's LDS; false: it does
+// not fit.
+bool fused_plan(ppd_ctx* c) {
+  const ppd_model_dims& d = c->d;
+  const int dm = d.d_model, F = d.d_ff, G = c->fused_grid;
+  const bool swiglu = d.act == 2;
+  FusedArgs& a = c->fused_args;
+  memset(&a, 0, sizeof a);
+  int tiles = 0, xmax = 0;
+  auto ph = [&](int i, int K, int ntot, int norm, bool paired, int act) {
+    FPhase& p = a.ph[i];
+    p.K = K; p.KT = (K + 31) / 32; p.NT = paired ? (ntot + 7) / 8 : (ntot + 15) / 16; p.ntot = ntot; p.nseg = i == 0 ? dm : ntot;
+    p.norm = norm; p.paired = paired ? 1 : 0; p.act = act;
+    p.wbytes = (unsigned)((size_t)p.NT * p.KT * 1024);
+    const int nb8 = (p.KT + MG_WAVES - 1) / MG_WAVES, nbt = (nb8 + MG_BATCH - 1) / MG_BATCH;
+    p.inv = (65536 + nbt - 1) / nbt;
+    if ((p.NT + G - 1) / G > tiles) tiles = (p.NT + G - 1) / G;
+    if (p.KT * 128 > xmax) xmax = p.KT * 128;
+    return (size_t)p.NT * p.KT * 1024 <= 0x7fffffffu;
+  };
+  if (!ph(0, dm, 3 * dm, d.norm, false, 0) || !ph(1, dm, dm, -1, false, 0) ||
+      !ph(2, dm, F, d.norm, swiglu, swiglu ? 0 : (d.act == 0 ? 1 : 2)) || !ph(3, F, dm, -1, false, 0)) return false;
+  a.L = c->fl_tab;
+  a.off_res = FU_LDS_G + fu_gain_bytes(dm) * (d.norm == 0 ? 2 : 1);
+  a.off_part = a.off_res + (a.ph[1].NT + G - 1) / G * 64;
+  a.off_x = a.off_part + tiles * MG_WAVES * 64;
+  const int att = fu_att_floats(d.head_dim) * (int)sizeof(float);
+  c->fused_lds = a.off_x + (xmax > att ? xmax : att);
+  a.h = c->h; a.part = c->fl_part; a.ex = c->fl_ex;
+  a.rope = d.pos == 1 ? c->rope : nullptr; a.ds = c->ds;
+  a.H = d.n_heads; a.d_model = dm; a.d_ff = F; a.max_ctx = d.max_ctx; a.nchunk_max = c->nchunk_max;
+  a.kv_bytes = (unsigned)cache_layer_bytes(c);
+  a.scale = 1.0f / sqrtf((float)d.head_dim); a.eps = d.norm_eps;
+  a.spin_ticks = env_int("PPD_SPIN_TICKS", 10 * 1000 * 1000);      // 100 ms
+  return c->fused_lds <= (int)MG_LDS_MAX && (int64_t)d.n_heads * ((c->nchunk_max + 1) / 2) * G < ((int64_t)1 << 31);
+}
+
+// Row 0 (the main token) through layers from .. to - 1: in one launch, or one launch per step of a layer
+int run_main_row(ppd_ctx* c, int from, int to, int pmax) {
+  if (c->fused && c->prof < 2) {
+    FusedArgs a = c->fused_args;
+    a.layer0 = from; a.nsteps = to - from;
+    HIPCHK(c, launch_fused(c->cur, a, c->d.head_dim, c->fused_grid, c->fused_lds));
+    return PPD_OK;
+  }
+  for (int l = from; l < to; ++l) {
+    RowGroup g{l, 1, 0, 0, false};
+    int rc = run_layer(c, 1, &g, pmax);
+    if (rc) return rc;
+  }
+  return PPD_OK;
+}
+
 EmbedArgs embed_args(ppd_ctx* c, const int32_t* ids_dev, int rows, int row0, int pos_off) {
   EmbedArgs a;
   a.tok_emb = c->tok_emb; a.pos_emb = c->d.pos == 0 ? c->pos_emb : nullptr; a.ids = ids_dev; a.ds = c->ds;
@@ -543,17 +610,30 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
 // kind 1: PPD round after a match (layers 1..d-dbar were run by the matching candidate row);
 // kind 2: plain greedy step; kind 3: PPD round after a match whose candidates the previous round's final head
 // already predicted and embedded (speculative early prediction): parallel phase and final head only.  pmax bounds the positions touched (attention grid size only).
-int issue_round(ppd_ctx* c, int kind, int pmax) {
+int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   const int d = c->d.n_layers, dbar = c->dbar, nb = c->nb, k = c->k;
   int rc;
-  hipLaunchKernelGGL(begin_round_kernel, dim3(1), dim3(64), 0, c->cur, c->ds, kind == 3 ? 1 : 0, c->host_result_dev + 2);
-  HIPCHK(c, hipGetLastError());
+  {
+    BeginArgs b; memset(&b, 0, sizeof b);
+    b.ds = c->ds; b.take_next = kind == 3 ? 1 : 0; b.host_cand = c->host_result_dev + 2;
+    const int chain = kind == 2 ? d : dbar - (kind == 0 ? 0 : nb);     // layers the main token goes through alone
+    int grid = 1;
+    if ((c->fused && chain > 0) || restore) {
+      if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
+      b.h = c->h; b.save = c->h_save; b.nsave = (1 + k) * c->d.d_model; b.restore = restore ? 1 : 0;
+      grid = 512;
+    }
+    if (restore) {
+      const ClearKvArgs kv = {(float*)c->Kc, (float*)c->Vc, c->ds, c->d.n_heads, c->d.head_dim, c->d.max_ctx};
+      hipLaunchKernelGGL(clear_kv_kernel, dim3(c->d.n_heads, d), dim3(c->d.head_dim), 0, c->cur, kv);
+      HIPCHK(c, hipGetLastError());
+    }
+    hipLaunchKernelGGL(begin_round_kernel, dim3(grid), dim3(256), 0, c->cur, b);
+    HIPCHK(c, hipGetLastError());
+  }
   if (kind == 2) {
     if ((rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
-    for (int l = 0; l < d; ++l) {
-      RowGroup g{l, 1, 0, 0, false};
-      if ((rc = run_layer(c, 1, &g, pmax))) return rc;
-    }
+    if ((rc = run_main_row(c, 0, d, pmax))) return rc;
     return run_head(c, false, false);
   }
   // main token up to the exit layer
@@ -561,10 +641,7 @@ int issue_round(ppd_ctx* c, int kind, int pmax) {
   if (kind == 0 && (rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
   if (from < dbar) {
     ProfScope phase(c, PPD_KC_PHASE, 1);
-    for (int l = from; l < dbar; ++l) {
-      RowGroup g{l, 1, 0, 0, false};
-      if ((rc = run_layer(c, 1, &g, pmax))) return rc;
-    }
+    if ((rc = run_main_row(c, from, dbar, pmax))) return rc;
   }
   // early prediction; the candidates become rows 1..k at the next position
   if (kind != 3 && (rc = run_head(c, true, false))) return rc;
@@ -582,14 +659,19 @@ int issue_round(ppd_ctx* c, int kind, int pmax) {
 
 // Run one round: set the device state, replay (or capture, or issue eagerly) the launches,
 // wait, read token and match index from pinned memory.
-int run_round(ppd_ctx* c, int kind, int pos) {
+// A one-launch chain needs every compute unit for itself while it runs: rounds of several contexts on one GPU that use it
+// take turns (a round's chain is over when its result is there).
+constexpr int MAX_DEVICES = 64;
+std::mutex g_round_mu[MAX_DEVICES];
+
+int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   int rc;
   // (work the caller queued on its stream before ppd_prefill -- the weights -- was waited for there; a round
   // reads nothing else of the caller's)
   // the device already holds this position as pending when the previous call was a round at pos - 1
   if (c->dev_pos_pending != pos && (rc = set_state(c, pos, -1))) return rc;
   const int pmax = pos + (kind == 2 ? 0 : 1);
-  if (c->use_graphs && !c->prof) {
+  if (c->use_graphs && !c->prof && !again) {
     // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least 4,
     // at most the cache's), so that a sequence re-captures a handful of times instead of every 64 positions;
     // chunks past a row's position return at once.
@@ -614,7 +696,7 @@ int run_round(ppd_ctx* c, int kind, int pos) {
     }
     HIPCHK(c, hipGraphLaunch(c->graph[kind], c->stream));
   } else {
-    if ((rc = issue_round(c, kind, pmax))) return rc;
+    if ((rc = issue_round(c, kind, pmax, again))) return rc;
   }
   c->dev_pos_pending = -1;                       // (unknown until the round is known to have run)
   // The round's last kernel writes token and match index to pinned memory and then the count of finished rounds:
@@ -639,9 +721,23 @@ int run_round(ppd_ctx* c, int kind, int pos) {
     std::atomic_thread_fence(std::memory_order_acquire);
     c->rounds_seen = want;
   }
-  c->dev_pos_pending = pos + 1;                  // left by the round's final selection
+  c->dev_pos_pending = c->host_result[0] < 0 ? pos : pos + 1;   // left by the round's final selection
   if (c->prof) prof_collect(c);
   return PPD_OK;
+}
+
+int run_round(ppd_ctx* c, int kind, int pos) {
+  if (!c->fused) return run_round_once(c, kind, pos, false);
+  std::lock_guard<std::mutex> turn(g_round_mu[c->device]);
+  int rc = run_round_once(c, kind, pos, false);
+  if (rc || c->host_result[0] >= 0) return rc;
+  // A workgroup gave up waiting for the others (something else held compute units): nothing was taken over.  This
+  // context goes back to one launch per step for good, beginning with this round.
+  c->fused = 0;
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  for (int i = 0; i < 4; ++i)
+    if (c->graph[i]) { HIPCHK(c, hipGraphExecDestroy(c->graph[i])); c->graph[i] = nullptr; }
+  return run_round_once(c, kind, pos, true);
 }
 
 void account_round(ppd_ctx* c, int kind, int pos) {
@@ -662,7 +758,8 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 void free_all(ppd_ctx* c) {
   for (int i = 0; i < 4; ++i) if (c->graph[i]) (void)hipGraphExecDestroy(c->graph[i]);
   void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->qkv, c->att, c->ffn, c->part, c->logits,
-                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->xn, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx};
+                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->xn, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
+                 c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
   for (void* p : dev) (void)hipFree(p);
   for (void* p : c->owned) (void)hipFree(p);
   if (c->host_result) (void)hipHostFree(c->host_result);
@@ -744,13 +841,6 @@ int prefill_tiled(ppd_ctx* c, int rows) {
     HIPCHK(c, gemm(c->pf_xf, P.fout, F, dm, 0, 0, false, bias ? w.b_out : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0));
   }
   return PPD_OK;
-}
-
-int env_int(const char* name, int dflt) {
-  const char* v = getenv(name);
-  if (!v || !*v) return dflt;
-  int x = atoi(v);
-  return x > 0 ? x : dflt;
 }
 
 }  // namespace
@@ -934,6 +1024,37 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
       int ob, op, ox;
       const size_t need = (size_t)mg_lds_layout((int)dm, 1 + k, d.norm, (NTh + c->head_grid - 1) / c->head_grid, xrow, ob, op, ox);
       c->spec = 2 * c->dbar == d.n_layers && !c->early_head && need <= MG_LDS_MAX && env_int("PPD_SPEC", 1) != 2;
+    }
+  }
+  // the main token's layers in one launch, one workgroup per compute unit (PPD_FUSED=2: one launch per step; PPD_MGPASSES
+  // asks for the launches whose staging passes it sets)
+  if (e == hipSuccess) e = hipGetDevice(&c->device);
+  if (e == hipSuccess && c->mfma && env_int("PPD_FUSED", 1) != 2 && c->mg_passes_min == 1 && c->device < MAX_DEVICES &&
+      cache_layer_bytes(c) < ((size_t)1 << 32)) {
+    int cus = 0;
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
+    c->fused_grid = cus < FU_MAX_WG ? cus : FU_MAX_WG;
+    std::vector<FLayer> tab(d.n_layers);
+    for (int l = 0; l < d.n_layers; ++l) {
+      FLayer& t = tab[l];
+      memset(&t, 0, sizeof t);
+      const LayerW& x = c->L[l];
+      t.P[0] = c->LP[l].qkv; t.P[1] = c->LP[l].o; t.P[2] = c->LP[l].fin; t.P[3] = c->LP[l].fout;
+      t.ng[0] = x.ln1_g; t.ng[1] = x.ln2_g;
+      if (d.norm == 0) { t.nb[0] = x.ln1_b; t.nb[1] = x.ln2_b; }
+      if (d.has_bias) { t.B[0][0] = x.bq; t.B[0][1] = x.bk; t.B[0][2] = x.bv; t.B[1][0] = x.bo; t.B[2][0] = x.b_in; t.B[3][0] = x.b_out; }
+      t.Kc = (float*)(c->Kc + (size_t)l * cache_layer_bytes(c)); t.Vc = (float*)(c->Vc + (size_t)l * cache_layer_bytes(c));
+    }
+    const size_t nex = (size_t)d.n_layers * fu_ex_row((int)dm, d.d_ff), npart = (size_t)d.n_heads * c->nchunk_max * (d.head_dim + 2);
+    alloc((void**)&c->fl_tab, d.n_layers * sizeof(FLayer));
+    alloc((void**)&c->fl_ex, nex * sizeof(float));
+    alloc((void**)&c->fl_part, npart * sizeof(float));
+    alloc((void**)&c->h_save, R * dm * sizeof(float));
+    if (e == hipSuccess) e = hipMemcpy(c->fl_tab, tab.data(), d.n_layers * sizeof(FLayer), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemsetD32(c->fl_part, (int)FU_EMPTY, npart);
+    if (e == hipSuccess && fused_plan(c)) {
+      e = fused_setup(d.head_dim, c->fused_lds);
+      c->fused = 1;
     }
   }
   // (the fills and copies above went to the null stream, which the context's own stream does not wait for)

@@ -48,6 +48,7 @@ struct DevState {
   int32_t sampled;    // final prediction drawn by the sampling kernel (sampling-based variants)
   int32_t pos_pending; // position of the next round: set explicitly, or left by a round's final selection (pos + 1)
   int32_t seq;         // rounds finished since the context was created (the host waits for the next value)
+  int32_t aborted;     // a workgroup of the round's one-launch chain of layers gave up waiting: the round's results are void
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
@@ -88,7 +89,7 @@ __device__ __forceinline__ u32x4 ld_stream(const void* p) { return __builtin_non
 // for the whole wave and goes through M0).  Written as assembly so that the wait for it stays ours:
 // the request counts in vmcnt like any load, and loads return in order.
 __device__ __forceinline__ void dma16(const void* src, void* lds_dst) {
-  const unsigned la = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_dst;
+  const unsigned la = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_dst);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(la) : "memory", "m0");
 }
 
@@ -148,14 +149,29 @@ __global__ void set_state_kernel(DevState* ds, int pos, int tok) {
 }
 // First launch of every round: the position the previous round (or set_state_kernel) left pending becomes the
 // current one; take_next: the round uses the candidates the previous round predicted for it
-// (host_cand: the candidates' copy in pinned host memory, for the round's record)
-__global__ void begin_round_kernel(DevState* ds, int take_next, int32_t* host_cand) {
-  if (threadIdx.x == 0) ds->pos = ds->pos_pending;
-  if (take_next && threadIdx.x < MAXM) {
-    const int32_t c = ds->cand_next[threadIdx.x];
-    ds->cand[threadIdx.x] = c;
-    host_cand[threadIdx.x] = c;
+// (host_cand: the candidates' copy in pinned host memory, for the round's record).
+// For rounds with a one-launch chain of layers (ex != null): the buffers of its steps' outputs are marked empty, and the
+// activation rows are kept (save) so that the round can be run again if the launch has to give up; restore: this is
+// that second run.
+struct BeginArgs {
+  DevState* ds; int take_next; int32_t* host_cand;
+  u32x4* ex; size_t n16; uint32_t empty;     // 16-byte pieces to fill
+  float* h; float* save; int nsave; int restore;
+};
+__global__ __launch_bounds__(256) void begin_round_kernel(BeginArgs a) {
+  const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+  if (t == 0) {
+    a.ds->pos = a.ds->pos_pending;
+    a.ds->aborted = 0;
   }
+  if (t < MAXM && a.take_next) {
+    const int32_t c = a.ds->cand_next[t];
+    a.ds->cand[t] = c;
+    a.host_cand[t] = c;
+  }
+  const u32x4 e = {a.empty, a.empty, a.empty, a.empty};
+  for (size_t i = t; i < a.n16; i += stride) a.ex[i] = e;
+  for (size_t i = t; i < (size_t)a.nsave; i += stride) { if (a.restore) a.h[i] = a.save[i]; else a.save[i] = a.h[i]; }
 }
 #endif
 
@@ -833,6 +849,18 @@ __global__ void chunk_kv_kernel(ChunkKvArgs a) {
 }
 #endif
 
+// A round that is run again: what its first run left at the pending position of the caches may be no number, and the MFMAs
+// read whole blocks (weight 0 times NaN is NaN), so the position is cleared in every layer.  One workgroup per (head, layer).
+struct ClearKvArgs { float* Kc; float* Vc; const DevState* ds; int H, HD, max_ctx; };
+#ifdef PPD_ENGINE_TU
+__global__ void clear_kv_kernel(ClearKvArgs a) {
+  const int i = threadIdx.x, pos = a.ds->pos_pending;
+  const size_t base = ((size_t)blockIdx.y * a.H + blockIdx.x) * kv_blocks(a.max_ctx) * (KV_BLOCK * a.HD);
+  a.Kc[base + k_index(pos, i, a.HD)] = 0.f;
+  a.Vc[base + v_index(pos, i, a.HD)] = 0.f;
+}
+#endif
+
 // merge of the chunk partials, chunks in index order
 struct MergeArgs {
   const float* part[2]; float* out[2];   // out: [M][d_model]
@@ -1307,6 +1335,16 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
       s_tok = win[pick];
     }
     __syncthreads();
+  }
+  if (a.ds->aborted) {      // the one-launch chain of layers gave up: nothing of this round is taken over, the host runs it again
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
+      a.host_result[0] = -1;
+      const int32_t seq = a.ds->seq + 1;
+      a.ds->seq = seq;
+      __threadfence_system();
+      *(volatile int32_t*)(a.host_result + 2 + MAXM) = seq;
+    }
+    return;
   }
   const int token = id_in_vocab(a.samp_topk > 0 ? s_tok : (a.sampled ? a.ds->sampled : win[0]), a.vocab);
   if (tid == 0) {

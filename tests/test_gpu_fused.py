@@ -1,0 +1,61 @@
+"""The main token's layers in one launch against one launch per step of a layer: the same bits, over layer shapes whose
+tiles, blocks and attention items do not divide evenly among the workgroups and waves; and a launch that has to give up
+waiting (a spin limit of one tick, set from the host) is run again one launch per step."""
+import numpy as np
+import pytest
+
+import ppd_inputs as pi
+from gpu_common import gpu_generate
+from helpers import small_cfg
+from paper_2307_05908_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    "llama": small_cfg("llama"),                                   # head_dim as configured, one attention item per head
+    "opt": small_cfg("opt"),                                       # LayerNorm, biases, learned positions
+    "llama_300": small_cfg("llama", max_ctx=420, n_prompt=300, n_gen=12),     # several items per head, odd number of chunks
+    "opt_250": small_cfg("opt", max_ctx=300, n_prompt=250, n_gen=12),
+    # more 16-row tiles than workgroups in every product, ragged feed-forward width, more attention items than workgroups
+    "wide": small_cfg("llama", d_model=4224, n_heads=33, head_dim=128, d_ff=11000, vocab=700, n_layers=2, exit_layer=1,
+                      max_ctx=1300, n_prompt=1215, n_gen=4),
+    "wide_ln": small_cfg("opt", d_model=2112, n_heads=33, head_dim=64, d_ff=8456, vocab=700, n_layers=2, exit_layer=1,
+                         max_ctx=200, n_prompt=127, n_gen=4),
+}
+
+
+def run(cfg, dev, prompt, monkeypatch, **env):
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    P = binding.PPD(cfg, dev)
+    out = [gpu_generate(P, prompt, cfg.n_gen, mode) for mode in ("plain", "ppd")]
+    P.close()
+    for k in env:
+        monkeypatch.delenv(k)
+    return out
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_one_launch_is_one_launch_per_step_bit_exact(name, monkeypatch):
+    cfg = CASES[name]
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    one = run(cfg, dev, prompt, monkeypatch)
+    steps = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")
+    for a, b in zip(one, steps):
+        np.testing.assert_array_equal(a[0], b[0])
+        np.testing.assert_array_equal(a[1], b[1])
+        assert a[2] == b[2]
+
+
+@pytest.mark.parametrize("name", ["llama_300", "opt"])
+def test_a_launch_that_gives_up_is_run_again(name, monkeypatch):
+    cfg = CASES[name]
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    gave_up = run(cfg, dev, prompt, monkeypatch, PPD_SPIN_TICKS="1")
+    steps = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")
+    for a, b in zip(gave_up, steps):
+        np.testing.assert_array_equal(a[0], b[0])
+        np.testing.assert_array_equal(a[1], b[1])
+        assert a[2] == b[2]
