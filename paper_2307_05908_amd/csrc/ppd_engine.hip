@@ -82,7 +82,7 @@ struct ppd_ctx {
   float* xn;             // [rows][d_model] normalised rows of a prompt chunk (norm_rows_kernel)
   // sampling-based final prediction (Appendix B): 0 arg max, 1 top-k sampling, 2 top-p sampling
   int samp_mode, samp_k; double samp_p; uint64_t samp_seed;
-  double* samp_w; uint32_t* samp_keys; int samp_npad;   // scratch of the sampling kernel
+  double *samp_w, *samp_pm; uint32_t* samp_keys; int *samp_pc, samp_npad;   // scratch of the sampling kernels
   int head_grid;
   float2 *rope;          // [max_ctx][hd/2]
   DevState *ds;
@@ -573,8 +573,10 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
     sa.z = c->logits; sa.n = d.vocab; sa.mode = c->samp_mode; sa.ks = c->samp_k; sa.p = c->samp_p; sa.seed = c->samp_seed;
     sa.ds = c->ds; sa.w = c->samp_w; sa.keys = c->samp_keys; sa.npad = c->samp_npad;
     ProfScope ps(c, PPD_KC_SELECT);
-    if (d.vocab <= SAMP_VPT * SAMP_THREADS) hipLaunchKernelGGL(sample_kernel<true>, dim3(1), dim3(SAMP_THREADS), 0, c->cur, sa);
-    else hipLaunchKernelGGL(sample_kernel<false>, dim3(1), dim3(SAMP_THREADS), 0, c->cur, sa);
+    sa.pk_val = c->pk_val; sa.nblk = c->head_grid; sa.pm = c->samp_pm; sa.pc = c->samp_pc;
+    hipLaunchKernelGGL(sample_weights_kernel, dim3(c->samp_npad / SAMP_THREADS), dim3(SAMP_THREADS), 0, c->cur, sa);
+    HIPCHK(c, hipGetLastError());
+    hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(SAMP_THREADS), 0, c->cur, sa);
     HIPCHK(c, hipGetLastError());
   }
   SelectArgs s; memset(&s, 0, sizeof s);
@@ -758,7 +760,7 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 void free_all(ppd_ctx* c) {
   for (int i = 0; i < 4; ++i) if (c->graph[i]) (void)hipGraphExecDestroy(c->graph[i]);
   void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->qkv, c->att, c->ffn, c->part, c->logits,
-                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->xn, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
+                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->xn, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
                  c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
   for (void* p : dev) (void)hipFree(p);
   for (void* p : c->owned) (void)hipFree(p);
@@ -939,6 +941,8 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   c->samp_npad = (d.vocab + SAMP_THREADS * SAMP_MEMU - 1) / (SAMP_THREADS * SAMP_MEMU) * (SAMP_THREADS * SAMP_MEMU);
   alloc((void**)&c->samp_w, (size_t)c->samp_npad * sizeof(double));
   alloc((void**)&c->samp_keys, (size_t)c->samp_npad * sizeof(uint32_t));
+  alloc((void**)&c->samp_pm, (size_t)c->samp_npad / SAMP_THREADS * (SAMP_NT + 1) * sizeof(double));
+  alloc((void**)&c->samp_pc, (size_t)c->samp_npad / SAMP_THREADS * (SAMP_NT + 1) * sizeof(int));
   alloc((void**)&c->early_logits, (size_t)d.vocab * sizeof(float));
   const size_t pk_slots = (size_t)(c->head_grid > (d.vocab + 255) / 256 ? c->head_grid : (d.vocab + 255) / 256) + 1024;   // room for either head grid
   c->pk_slots = pk_slots;

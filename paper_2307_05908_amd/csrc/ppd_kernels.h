@@ -975,9 +975,8 @@ struct SelectArgs {
 // SC 2011) keyed by the seed, counter = sequence position of the token being chosen: decoding with and
 // without PPD draws the same numbers.
 // No sort: each of the two questions ("where does the kept prefix end", "where does the cumulative mass pass
-// u W") asks for the largest key kappa whose mass-at-or-above G(kappa) meets a bound; G is evaluated in full, in
-// one fixed order of additions, for one trial key per pass (so it is monotone in the key whatever the rounding),
-// and kappa is fixed bit by bit from the top of an order-preserving 32-bit image of the logit.
+// u W") asks for the largest key kappa whose mass-at-or-above G(kappa) meets a bound; kappa is fixed bit by bit
+// from the top of an order-preserving 32-bit image of the logit, G always being added up in one fixed order.
 // ten rounds: two 32x32->64 products, halves crossed over and mixed with counter and key; key steps by the Weyl constants
 __device__ inline uint32_t philox4x32_10_word0(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
   for (int r = 0; r < 10; ++r) {
@@ -992,17 +991,20 @@ __device__ inline uint32_t philox4x32_10_word0(uint32_t c0, uint32_t c1, uint32_
 
 #ifdef PPD_ENGINE_TU
 constexpr int SAMP_THREADS = 1024;
-constexpr int SAMP_MEMU = 8;     // loads in flight per thread when the logits are re-read from memory
-constexpr int SAMP_VPT = 32;     // logits per thread kept on chip (weights in registers, keys in LDS): vocabularies up to 32768;
-                                 // larger ones re-read memory every pass
+constexpr int SAMP_MEMU = 8;     // loads in flight per thread when keys and weights are re-read from memory
+constexpr int SAMP_NT = 64;      // thresholds at which sample_weights_kernel leaves mass and count: 1/8 apart down to 4 below the
+                                 // largest logit, then 1/4 apart to 12 below
+constexpr int SAMP_CAP = 6144;   // tokens between two thresholds that are searched in LDS
 struct SampleArgs {
   const float* z; int n;     // logits [n]
   int mode, ks;              // 1 top-k sampling (ks kept), 2 top-p sampling
   double p;
   uint64_t seed;
   DevState* ds;              // reads pos, writes sampled
-  double* w; uint32_t* keys; // scratch [npad] each (only used when the logits do not fit the chip): weights and keys,
-  int npad;                  // zero beyond n; npad = n rounded up to a multiple of SAMP_THREADS * SAMP_MEMU
+  const float* pk_val; int nblk;   // [nblk][MAXM] block candidates of the head launch: the first of each is the block's largest logit
+  double* w; uint32_t* keys; // scratch [npad] each: weights and keys, zero beyond n; npad = n rounded up to a multiple of
+  int npad;                  // SAMP_THREADS * SAMP_MEMU
+  double* pm; int* pc;       // scratch [npad / SAMP_THREADS][SAMP_NT + 1]: mass and count of a workgroup's tokens at or above a threshold
 };
 
 // larger logit <-> larger key; -0 and +0 are one value; no finite or infinite logit has key 0
@@ -1031,78 +1033,83 @@ __device__ __forceinline__ double wave_sum_f64(double v) {     // same scheme as
   return ((lane_f64(v, 0) + lane_f64(v, 16)) + lane_f64(v, 32)) + lane_f64(v, 48);
 }
 
-template <bool REG>
+
+__device__ inline uint32_t samp_threshold(float zmax, int j) { return samp_key(zmax - (j <= 32 ? 0.125f * (float)j : 4.f + 0.25f * (float)(j - 32))); }
+
+// Keys and weights of all tokens, one per thread, and how much lies at or above each threshold (in one fixed order: wave
+// by wave, then workgroup by workgroup).  In the sampling kernel, one workgroup, the exponentials alone took 30 us at 50272
+// tokens and every look at them another 5.
+__global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs a) {
+  constexpr int NW = SAMP_THREADS / WAVE;
+  __shared__ float s_red[NW];
+  __shared__ double s_m[NW][SAMP_NT + 1];
+  __shared__ int s_c[NW][SAMP_NT + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = blockIdx.x * SAMP_THREADS + tid;
+  const bool in = i < a.n;
+  const float z = in ? a.z[i] : 0.f;
+  float mx = -INFINITY;
+  for (int b = tid; b < a.nblk; b += SAMP_THREADS) mx = fmaxf(mx, a.pk_val[(size_t)b * MAXM]);
+  mx = wave_max(mx);
+  if (lane == 0) s_red[wave] = mx;
+  __syncthreads();
+  mx = s_red[0];
+  for (int v = 1; v < NW; ++v) mx = fmaxf(mx, s_red[v]);
+  const uint32_t key = in ? samp_key(z) : 0u;
+  const double w = in ? exp((double)z - (double)mx) : 0.0;
+  a.keys[i] = key;
+  a.w[i] = w;
+  for (int j = 0; j <= SAMP_NT; ++j) {
+    const bool ge = j < SAMP_NT ? key >= samp_threshold(mx, j) : key != 0u;
+    const unsigned long long b = __ballot(ge);
+    double m = 0.0;
+    if (b) m = wave_sum_f64(ge ? w : 0.0);
+    if (lane == 0) { s_m[wave][j] = m; s_c[wave][j] = __popcll(b); }
+  }
+  __syncthreads();
+  if (tid <= SAMP_NT) {
+    double m = 0.0; int c = 0;
+    for (int v = 0; v < NW; ++v) { m += s_m[v][tid]; c += s_c[v][tid]; }
+    a.pm[(size_t)blockIdx.x * (SAMP_NT + 1) + tid] = m;
+    a.pc[(size_t)blockIdx.x * (SAMP_NT + 1) + tid] = c;
+  }
+}
+
+// The draw.  What bounds it is one workgroup's latency: a search first finds the two thresholds its key lies between, collects
+// the tokens between them in LDS (in a fixed order) and fixes the key's bits on those alone; only if they are more than
+// SAMP_CAP does it look through all tokens for every bit.  Measured (top-p 0.95), both kernels: 50272 tokens 358 -> 65 + 17 us
+// (bit by bit over all tokens, keys and weights re-read from L2), 32000 tokens 112 -> 51 + 19 us (the same with keys and
+// weights on chip).
 __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   constexpr int NW = SAMP_THREADS / WAVE;
-  constexpr int VPT = REG ? SAMP_VPT : 1;
   __shared__ double s_m[2][NW];
   __shared__ int s_c[2][NW];
   __shared__ float s_redf[NW];
   __shared__ int s_bc[NW][16];
   __shared__ int s_cnt[16];
   __shared__ uint32_t s_prefix; __shared__ int s_need, s_min;
-  __shared__ uint32_t s_key[REG ? SAMP_VPT * SAMP_THREADS : 1];     // key of token tid + e * SAMP_THREADS at [e][tid]
+  __shared__ double s_gm[SAMP_NT + 1]; __shared__ int s_gc[SAMP_NT + 1];
+  __shared__ double s_w[SAMP_CAP];
+  __shared__ uint32_t s_key[SAMP_CAP];
+  __shared__ int s_off[NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = a.n;
-  uint32_t* const key = s_key + tid;
-  constexpr int KS = SAMP_THREADS;     // stride between a thread's keys
-
-  // ---- keys, largest logit, weights
-  double wr[VPT];
   float mx = -INFINITY;
-  if (REG) {
-#pragma unroll
-    for (int e = 0; e < VPT; ++e) {
-      const int i = tid + e * SAMP_THREADS;
-      uint32_t k = 0u;
-      if (i < n) { const float z = a.z[i]; k = samp_key(z); mx = fmaxf(mx, z); }
-      key[e * KS] = k;
-    }
-  } else {
-    for (int i = tid; i < n; i += SAMP_THREADS) mx = fmaxf(mx, a.z[i]);
-  }
+  for (int b = tid; b < a.nblk; b += SAMP_THREADS) mx = fmaxf(mx, a.pk_val[(size_t)b * MAXM]);
   mx = wave_max(mx);
   if (lane == 0) s_redf[wave] = mx;
+  if (tid <= SAMP_NT) {
+    double m = 0.0; int c = 0;
+    const int nb = a.npad / SAMP_THREADS;
+    for (int b = 0; b < nb; ++b) { m += a.pm[(size_t)b * (SAMP_NT + 1) + tid]; c += a.pc[(size_t)b * (SAMP_NT + 1) + tid]; }
+    s_gm[tid] = m; s_gc[tid] = c;
+  }
   __syncthreads();
   mx = s_redf[0];
   for (int w = 1; w < NW; ++w) mx = fmaxf(mx, s_redf[w]);
   const double zmax = (double)mx;
-  if (REG) {
-#pragma unroll
-    for (int e = 0; e < VPT; ++e) { const uint32_t k = key[e * KS]; wr[e] = k ? exp((double)samp_unkey(k) - zmax) : 0.0; }
-  } else {
-    for (int i = tid; i < a.npad; i += SAMP_THREADS) {
-      const bool in = i < n;
-      const float z = in ? a.z[i] : 0.f;
-      a.keys[i] = in ? samp_key(z) : 0u;
-      a.w[i] = in ? exp((double)z - zmax) : 0.0;
-    }
-    __syncthreads();
-  }
 
-  // ---- G(kth): mass and number of the tokens whose key is at least kth (kth >= 1); every thread gets both
-  int par = 0;
-  auto G = [&](uint32_t kth, double& mass, int& count) {
-    double m = 0.0; int c = 0;
-    if (REG) {
-#pragma unroll
-      for (int e = 0; e < VPT; ++e) {
-        const bool ge = key[e * KS] >= kth;
-        m += ge ? wr[e] : 0.0;
-        c += __popcll(__ballot(ge));
-      }
-    } else {
-      for (int i0 = tid; i0 < a.npad; i0 += SAMP_THREADS * SAMP_MEMU) {
-        uint32_t k[SAMP_MEMU]; double w[SAMP_MEMU];
-#pragma unroll
-        for (int q = 0; q < SAMP_MEMU; ++q) { k[q] = a.keys[i0 + q * SAMP_THREADS]; w[q] = a.w[i0 + q * SAMP_THREADS]; }
-#pragma unroll
-        for (int q = 0; q < SAMP_MEMU; ++q) {
-          const bool ge = k[q] >= kth;
-          m += ge ? w[q] : 0.0;
-          c += __popcll(__ballot(ge));
-        }
-      }
-    }
+  // ---- mass and number of the tokens whose key is at least kth, every thread gets both: of the nl collected ones, or of all
+  int par = 0, nl = 0;
+  auto sum_up = [&](double m, int c, double& mass, int& count) {
     m = wave_sum_f64(m);
     if (lane == 0) { s_m[par][wave] = m; s_c[par][wave] = c; }
     __syncthreads();
@@ -1110,53 +1117,105 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
     for (int w = 0; w < NW; ++w) { mass += s_m[par][w]; count += s_c[par][w]; }
     par ^= 1;        // the next evaluation writes the other half: no second barrier needed
   };
-  // ---- the largest key kappa with G(kappa) >= T (kind 0), G(kappa) > T (kind 1) or count(kappa) >= K (kind 2);
-  // the bound holds at the smallest key present, so kappa >= 1.  Also the mass and count strictly above kappa
-  // and the number of tokens at kappa.
-  double S; int n_all;
-  G(1u, S, n_all);
-  // The keys still in question after bit b are those that agree with the prefix above b; once a single token
-  // is left (count at the prefix minus count above the bucket), its key is kappa and the remaining bits need
-  // no passes: the mass and count above the bucket are the ones already found.
+  auto G_list = [&](uint32_t kth, double& mass, int& count) {
+    double m = 0.0; int c = 0;
+    for (int e = tid; e < (nl + WAVE - 1) / WAVE * WAVE; e += SAMP_THREADS) {
+      const bool ge = e < nl && s_key[e] >= kth;
+      m += ge ? s_w[e] : 0.0;
+      c += __popcll(__ballot(ge));
+    }
+    sum_up(m, c, mass, count);
+  };
+  auto G_all = [&](uint32_t kth, double& mass, int& count) {
+    double m = 0.0; int c = 0;
+    for (int i0 = tid; i0 < a.npad; i0 += SAMP_THREADS * SAMP_MEMU) {
+      uint32_t k[SAMP_MEMU]; double w[SAMP_MEMU];
+#pragma unroll
+      for (int q = 0; q < SAMP_MEMU; ++q) { k[q] = a.keys[i0 + q * SAMP_THREADS]; w[q] = a.w[i0 + q * SAMP_THREADS]; }
+#pragma unroll
+      for (int q = 0; q < SAMP_MEMU; ++q) {
+        const bool ge = k[q] >= kth;
+        m += ge ? w[q] : 0.0;
+        c += __popcll(__ballot(ge));
+      }
+    }
+    sum_up(m, c, mass, count);
+  };
+  // ---- the largest key kappa with G(kappa) >= T (kind 0), G(kappa) > T (kind 1) or count(kappa) >= K (kind 2).  Also the mass
+  // and count strictly above kappa and the number of tokens at kappa.
+  const double S = s_gm[SAMP_NT];
   auto search = [&](int kind, double T, int K, uint32_t& kappa, double& above, int& nabove, int& ties) {
-    uint32_t pre = 0u;
-    int c_at = n_all, c_hi = 0, bit = 31;
-    double g_hi = 0.0;
+    auto meets = [&](double g, int c) { return kind == 0 ? g >= T : (kind == 1 ? g > T : c >= K); };
+    int j = 0;
+    while (j < SAMP_NT && !meets(s_gm[j], s_gc[j])) ++j;         // (the same for every thread)
+    const uint32_t lo = j < SAMP_NT ? samp_threshold(mx, j) : 1u, top = j > 0 ? samp_threshold(mx, j - 1) - 1u : 0xffffffffu;
+    const double A = j > 0 ? s_gm[j - 1] : 0.0;
+    const int cA = j > 0 ? s_gc[j - 1] : 0, cnt = s_gc[j] - cA;
+    const bool list = cnt <= SAMP_CAP;
+    if (list) {
+      // the tokens with lo <= key <= top, thread by thread
+      int mine = 0;
+      for (int i0 = tid; i0 < a.npad; i0 += SAMP_THREADS * SAMP_MEMU) {
+        uint32_t k[SAMP_MEMU];
+#pragma unroll
+        for (int q = 0; q < SAMP_MEMU; ++q) k[q] = a.keys[i0 + q * SAMP_THREADS];
+#pragma unroll
+        for (int q = 0; q < SAMP_MEMU; ++q) mine += k[q] >= lo && k[q] <= top ? 1 : 0;
+      }
+      int incl = mine;
+#pragma unroll
+      for (int o = 1; o < WAVE; o <<= 1) { const int v = __shfl_up(incl, o, WAVE); if (lane >= o) incl += v; }
+      __syncthreads();                                           // (the list of an earlier search is done with)
+      if (lane == WAVE - 1) s_off[wave] = incl;
+      __syncthreads();
+      int at = incl - mine;
+      for (int w = 0; w < wave; ++w) at += s_off[w];
+      nl = 0;
+      for (int w = 0; w < NW; ++w) nl += s_off[w];
+      if (nl > SAMP_CAP) nl = SAMP_CAP;
+      if (mine)
+        for (int i = tid; i < a.npad; i += SAMP_THREADS) {
+          const uint32_t k = a.keys[i];
+          if (k >= lo && k <= top && at < SAMP_CAP) { s_key[at] = k; s_w[at] = a.w[i]; ++at; }
+        }
+      __syncthreads();
+    }
+    auto G = [&](uint32_t kth, double& mass, int& count) {
+      if (list) { G_list(kth, mass, count); mass += A; count += cA; }
+      else G_all(kth, mass, count);
+    };
+    // bit by bit from the highest one in which lo and top differ; once a single token is left (count at the prefix minus
+    // count above the bucket) its key is kappa
+    int bit = 31;
+    while (bit >= 0 && !((lo ^ top) >> bit)) --bit;
+    uint32_t pre = bit >= 31 ? 0u : lo >> (bit + 1) << (bit + 1);
+    int c_at = s_gc[j], c_hi = cA;
+    double g_hi = A;
     bool single = c_at - c_hi == 1;
     for (; bit >= 0 && !single; --bit) {
       const uint32_t t = pre | (1u << bit);
       double g; int c;
       G(t, g, c);
-      const bool ok = kind == 0 ? g >= T : (kind == 1 ? g > T : c >= K);
-      if (ok) { pre = t; c_at = c; }
+      if (meets(g, c)) { pre = t; c_at = c; }
       else { c_hi = c; g_hi = g; }
       single = c_at - c_hi == 1;
     }
-    if (single) {
-      // bits above `bit` are fixed (the loop has already stepped past the last one it tried)
-      const int sh = bit + 1;
-      __syncthreads();
-      if (REG) {
-#pragma unroll
-        for (int e = 0; e < VPT; ++e) {
-          const uint32_t k = key[e * KS];
-          if (k && (sh >= 32 || (k >> sh) == (pre >> sh))) s_prefix = k;
-        }
-      } else {
-        for (int i = tid; i < a.npad; i += SAMP_THREADS) {
-          const uint32_t k = a.keys[i];
-          if (k && (sh >= 32 || (k >> sh) == (pre >> sh))) s_prefix = k;
-        }
-      }
-      __syncthreads();
-      kappa = s_prefix; above = g_hi; nabove = c_hi; ties = 1;
-      __syncthreads();
-      return;
+    // kappa: the smallest key at or above the prefix (the prefix itself, unless bits are left open)
+    __syncthreads();
+    if (tid == 0) s_prefix = 0xffffffffu;
+    __syncthreads();
+    if (list) { for (int e = tid; e < nl; e += SAMP_THREADS) if (s_key[e] >= pre) atomicMin(&s_prefix, s_key[e]); }
+    else for (int i = tid; i < a.npad; i += SAMP_THREADS) if (a.keys[i] >= pre && a.keys[i]) atomicMin(&s_prefix, a.keys[i]);
+    __syncthreads();
+    kappa = s_prefix;
+    __syncthreads();
+    above = g_hi; nabove = c_hi; ties = 1;
+    if (!single) {
+      above = 0.0; nabove = 0; double g; int c;
+      if (kappa != 0xffffffffu) G(kappa + 1u, above, nabove);
+      G(kappa, g, c);
+      ties = c - nabove > 0 ? c - nabove : 1;
     }
-    kappa = pre;
-    above = 0.0; nabove = 0;
-    if (kappa != 0xffffffffu) G(kappa + 1u, above, nabove);
-    ties = c_at - nabove;
   };
   const int pos_new = a.ds->pos + 1;
   const uint32_t word = philox4x32_10_word0((uint32_t)pos_new, 0u, 0u, 0u, (uint32_t)(a.seed & 0xffffffffu), (uint32_t)(a.seed >> 32));
@@ -1192,12 +1251,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   if (tid == 0) { s_min = 0x7fffffff; s_prefix = 0u; s_need = r; }
   __syncthreads();
   if (r == 1) {
-    if (REG) {
-#pragma unroll
-      for (int e = 0; e < VPT; ++e) if (key[e * KS] == kappa) atomicMin(&s_min, tid + e * SAMP_THREADS);
-    } else {
-      for (int i = tid; i < n; i += SAMP_THREADS) if (samp_key(a.z[i]) == kappa) atomicMin(&s_min, i);
-    }
+    for (int i = tid; i < n; i += SAMP_THREADS) if (a.keys[i] == kappa) atomicMin(&s_min, i);
     __syncthreads();
     if (tid == 0) a.ds->sampled = s_min;
     return;
