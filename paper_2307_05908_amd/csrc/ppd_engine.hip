@@ -79,7 +79,7 @@ struct ppd_ctx {
   uint16_t *pf_xf;       // the feed-forward activations (written by the FFN-in GEMM; zero beyond d_ff)
   uint16_t *pf_qp, *pf_kp, *pf_vp;   // one layer's queries, keys, values as two-term operand blocks of the prompt attention
   int dev_pos_pending;   // host mirror of the device state's pending position (-1: unknown)
-  float* xn;             // [rows][d_model] normalised rows of a prompt chunk (norm_rows_kernel)
+  uint16_t *rp_x, *rp_a, *rp_f;      // packed two-term rows of a prompt chunk: normalised rows, attention outputs, feed-forward activations (zero beyond d_ff)
   // sampling-based final prediction (Appendix B): 0 arg max, 1 top-k sampling, 2 top-p sampling
   int samp_mode, samp_k; double samp_p; uint64_t samp_seed;
   double *samp_w, *samp_pm; uint32_t* samp_keys; int *samp_pc, samp_npad;   // scratch of the sampling kernels
@@ -204,9 +204,9 @@ hipError_t launch_gemm(ppd_ctx* c, GemmArgs& a, int ngroups, bool paired) {
 }
 
 // rows of a prompt chunk (ppd_prefill feeds the prompt through the decode kernels this many positions at a time:
-// one pass over the weights per chunk instead of per token): the 16 columns of an MFMA tile for bf16 models,
+// one pass over the weights per chunk instead of per token): two MFMA tiles' columns for bf16 models (rgemm_kernel),
 // the 8 rows of the fp32 GEMM otherwise
-constexpr int PREFILL_CHUNK = 16;
+constexpr int PREFILL_CHUNK = 32;
 constexpr int PREFILL_CHUNK_FP32 = 8;
 
 // ---- bf16 models: MFMA GEMM on repacked weights
@@ -292,7 +292,11 @@ hipError_t launch_attn(ppd_ctx* c, const AttnArgs& a, int ngroups, int pmax) {
   int mmax = a.g[0].M;
   if (ngroups == 2 && a.g[1].M > mmax) mmax = a.g[1].M;
   const bool causal = a.g[0].causal != 0;
-  if (causal && ngroups != 1) return hipErrorInvalidValue;
+  if (causal && (ngroups != 1 || mmax > PREFILL_CHUNK)) return hipErrorInvalidValue;
+  if (causal) {
+    grid.z = (mmax + ATT_CAUSAL_ROWS - 1) / ATT_CAUSAL_ROWS;
+    if (mmax > ATT_CAUSAL_ROWS) mmax = ATT_CAUSAL_ROWS;
+  }
   if (c->d.head_dim == 64) return launch_attn_t<64>(c->cur, a, mmax, grid, causal);
   return launch_attn_t<128>(c->cur, a, mmax, grid, causal);
 }
@@ -324,17 +328,6 @@ struct RowGroup {
   bool chunk = false;   // prompt chunk: row m sits m positions further on and sees the rows before it
 };
 
-// Prompt chunk: the rows of group 0 are normalised by a kernel of their own (same arithmetic as the fused norm)
-// and the GEMM runs without a fused norm on the result, so that it can stage its rows in passes.
-int norm_chunk(ppd_ctx* c, GemmArgs& a, const void* gain, const void* bias) {
-  NormRowsArgs n; memset(&n, 0, sizeof n);
-  n.X = a.g[0].X; n.Y = c->xn; n.g = gain; n.b = bias; n.K = a.K; n.ld = a.ldx; n.norm = a.norm; n.eps = a.eps;
-  hipLaunchKernelGGL(norm_rows_kernel, dim3(a.g[0].M), dim3(MG_THREADS), 0, c->cur, n);
-  HIPCHK(c, hipGetLastError());
-  a.g[0].X = c->xn; a.g[0].ng = nullptr; a.g[0].nb = nullptr; a.norm = -1;
-  return PPD_OK;
-}
-
 // One transformer layer for one or two row groups (a pipelined step when two).
 // pmax: host-side upper bound of the rows' positions (sizes the attention grid only).
 int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages = 15) {
@@ -355,7 +348,6 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     }
     a.K = dm; a.N[0] = a.N[1] = a.N[2] = dm; a.ntot = 3 * dm; a.ldx = dm; a.ldy = 3 * dm;
     a.norm = d.norm; a.eps = d.norm_eps; a.act = 0;
-    if (rg[0].chunk && c->mfma) { int rc = norm_chunk(c, a, c->L[rg[0].layer].ln1_g, d.norm == 0 ? c->L[rg[0].layer].ln1_b : nullptr); if (rc) return rc; }
     ProfScope ps(c, PPD_KC_GEMM_QKV, ngroups);
     if (c->mfma) {
       void* P[2] = {c->LP[rg[0].layer].qkv, ngroups == 2 ? c->LP[rg[1].layer].qkv : nullptr};
@@ -433,7 +425,6 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     }
     a.K = dm; a.N[0] = F; a.N[1] = swiglu ? F : 0; a.ntot = F; a.ldx = dm; a.ldy = F;
     a.norm = d.norm; a.eps = d.norm_eps; a.act = swiglu ? 3 : (d.act == 0 ? 1 : 2);
-    if (rg[0].chunk && c->mfma) { int rc = norm_chunk(c, a, c->L[rg[0].layer].ln2_g, d.norm == 0 ? c->L[rg[0].layer].ln2_b : nullptr); if (rc) return rc; }
     ProfScope ps(c, PPD_KC_GEMM_FFN_IN, ngroups);
     if (c->mfma) {
       void* P[2] = {c->LP[rg[0].layer].fin, ngroups == 2 ? c->LP[rg[1].layer].fin : nullptr};
@@ -458,6 +449,61 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     } else
     HIPCHK(c, launch_gemm(c, a, ngroups, false));
   }
+  return PPD_OK;
+}
+
+// One transformer layer for the M <= PREFILL_CHUNK rows of a prompt chunk of a bf16 model (M > 1), the first of them at the
+// device state's position.  Row for row the arithmetic of run_layer.
+int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
+  const ppd_model_dims& d = c->d;
+  const int dm = d.d_model, F = d.d_ff;
+  const bool bias = d.has_bias != 0, swiglu = d.act == 2;
+  const LayerW& w = c->L[l];
+  const ppd_ctx::LayerP& P = c->LP[l];
+  auto pack = [&](const void* g, const void* b) -> hipError_t {
+    PackArgs p; memset(&p, 0, sizeof p);
+    p.X = c->h; p.ld = dm; p.M = M; p.K = dm; p.KT = (dm + 31) / 32; p.MT = 2; p.g = g; p.b = d.norm == 0 ? b : nullptr;
+    p.norm = d.norm; p.eps = d.norm_eps; p.out = c->rp_x;
+    return launch_pack_rows(c->cur, p);
+  };
+  auto gemm = [&](const uint16_t* Xp, const void* W, int K, int n0, int n12, bool paired, const void* b0, const void* b1, const void* b2,
+                  const float* rsd, float* Y, int ldy, int act, uint16_t* Yp = nullptr) -> hipError_t {
+    RGemmArgs g; memset(&g, 0, sizeof g);
+    g.Xp = Xp; g.P = W; g.B[0] = bias ? b0 : nullptr; g.B[1] = bias ? b1 : nullptr; g.B[2] = bias ? b2 : nullptr;
+    g.Rsd = rsd; g.Y = Y; g.Yp = Yp; g.KTp = (n0 + 31) / 32; g.M = M; g.KT = (K + 31) / 32;
+    g.N[0] = n0; g.N[1] = g.N[2] = n12; g.ntot = n0 + 2 * n12;
+    g.NT = paired ? (n0 + 7) / 8 : (g.ntot + 15) / 16;
+    g.ldy = ldy; g.act = act;
+    return launch_rgemm(c->cur, g, paired);
+  };
+  HIPCHK(c, pack(w.ln1_g, w.ln1_b));
+  HIPCHK(c, gemm(c->rp_x, P.qkv, dm, dm, dm, false, w.bq, w.bk, w.bv, nullptr, c->qkv, 3 * dm, 0));
+  // keys and values of all rows of the chunk go into the cache first; then the rows attend, each to the rows before it
+  float* const Kc = (float*)(c->Kc + (size_t)l * cache_layer_bytes(c));
+  float* const Vc = (float*)(c->Vc + (size_t)l * cache_layer_bytes(c));
+  ChunkKvArgs kv; memset(&kv, 0, sizeof kv);
+  kv.qkv = c->qkv; kv.Kc = Kc; kv.Vc = Vc; kv.rope = d.pos == 1 ? c->rope : nullptr; kv.ds = c->ds;
+  kv.HD = d.head_dim; kv.d_model = dm; kv.max_ctx = d.max_ctx;
+  hipLaunchKernelGGL(chunk_kv_kernel, dim3(M, d.n_heads), dim3(d.head_dim), 0, c->cur, kv);
+  HIPCHK(c, hipGetLastError());
+  AttnArgs a; memset(&a, 0, sizeof a);
+  AttnGroup& G = a.g[0];
+  G.qkv = c->qkv; G.Kc = Kc; G.Vc = Vc; G.own_cache = 1; G.part = c->part; G.M = M; G.causal = 1;
+  a.ds = c->ds; a.rope = kv.rope; a.H = d.n_heads; a.d_model = dm; a.max_ctx = d.max_ctx; a.nchunk_max = c->nchunk_max;
+  a.scale = 1.0f / sqrtf((float)d.head_dim);
+  if (pmax < ATT_CHUNK) a.outp = c->rp_a;
+  HIPCHK(c, launch_attn(c, a, 1, pmax));
+  if (pmax >= ATT_CHUNK) {
+    MergeArgs mg; memset(&mg, 0, sizeof mg);
+    mg.part[0] = c->part; mg.outp = c->rp_a; mg.M[0] = M; mg.causal[0] = 1; mg.ds = c->ds;
+    mg.H = d.n_heads; mg.HD = d.head_dim; mg.d_model = dm; mg.nchunk_max = c->nchunk_max;
+    hipLaunchKernelGGL(attn_merge_kernel, dim3(M, d.n_heads, 1), dim3(MERGE_THREADS), 0, c->cur, mg);
+    HIPCHK(c, hipGetLastError());
+  }
+  HIPCHK(c, gemm(c->rp_a, P.o, dm, dm, 0, false, w.bo, nullptr, nullptr, c->h, c->h, dm, 0));
+  HIPCHK(c, pack(w.ln2_g, w.ln2_b));
+  HIPCHK(c, gemm(c->rp_x, P.fin, dm, F, 0, swiglu, w.b_in, nullptr, nullptr, nullptr, nullptr, F, swiglu ? 0 : (d.act == 0 ? 1 : 2), c->rp_f));
+  HIPCHK(c, gemm(c->rp_f, P.fout, F, dm, 0, false, w.b_out, nullptr, nullptr, c->h, c->h, dm, 0));
   return PPD_OK;
 }
 
@@ -760,7 +806,7 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 void free_all(ppd_ctx* c) {
   for (int i = 0; i < 4; ++i) if (c->graph[i]) (void)hipGraphExecDestroy(c->graph[i]);
   void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->qkv, c->att, c->ffn, c->part, c->logits,
-                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->xn, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
+                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
                  c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
   for (void* p : dev) (void)hipFree(p);
   for (void* p : c->owned) (void)hipFree(p);
@@ -923,7 +969,8 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     c->head_grid = head_grid_valu(d.vocab, c->gmax1);
   }
   const size_t dm = d.d_model, R = 1 + k;
-  const size_t RB = R > PREFILL_CHUNK ? R : PREFILL_CHUNK;   // activation rows: a round's 1 + k, or a prompt chunk
+  const size_t RC = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
+  const size_t RB = R > RC ? R : RC;   // activation rows: a round's 1 + k, or a prompt chunk
   hipError_t e = hipSuccess;
   auto alloc = [&](void** p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
   alloc((void**)&c->Kc, (size_t)d.n_layers * cache_layer_bytes(c));
@@ -933,7 +980,12 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   alloc((void**)&c->h, RB * dm * sizeof(float));
   alloc((void**)&c->qkv, RB * 3 * dm * sizeof(float));
   alloc((void**)&c->att, RB * dm * sizeof(float));
-  alloc((void**)&c->xn, RB * dm * sizeof(float));
+  if (d.wdtype == 1) {
+    alloc((void**)&c->rp_x, packed_bytes(PREFILL_CHUNK, (int)dm));
+    alloc((void**)&c->rp_a, packed_bytes(PREFILL_CHUNK, (int)dm));
+    alloc((void**)&c->rp_f, packed_bytes(PREFILL_CHUNK, d.d_ff));
+    if (e == hipSuccess) e = hipMemset(c->rp_f, 0, packed_bytes(PREFILL_CHUNK, d.d_ff));
+  }
   alloc((void**)&c->ffn, RB * (size_t)d.d_ff * sizeof(float));
   alloc((void**)&c->part, RB * d.n_heads * (size_t)c->nchunk_max * (d.head_dim + 2) * sizeof(float));
   alloc((void**)&c->logits, R * d.vocab * sizeof(float));
@@ -1010,6 +1062,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
+    if (e == hipSuccess) e = rgemm_setup();
     // head launches: the same balanced grid as any other GEMM; a workgroup keeps at most
     // HEAD_MAX_ROWS logits = 16 tiles
     c->mg_passes_min = env_int("PPD_MGPASSES", 1);
@@ -1114,7 +1167,7 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
     for (int l = 0; l < c->d.n_layers && !rc; ++l) {
       RowGroup g{l, m, 0, 0, false};
       g.chunk = m > 1;
-      rc = run_layer(c, 1, &g, i + m - 1);
+      rc = c->mfma && g.chunk ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1);
     }
   }
   c->prof = prof;

@@ -22,6 +22,8 @@ namespace ppd {
 
 struct bf16_t { uint16_t v; };
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int WAVE = 64;
@@ -638,6 +640,15 @@ __host__ __device__ inline size_t v_index(int pos, int comp, int HD) {
   return (((size_t)(pos >> 4) * (HD / 16) + (comp >> 4)) * 64 + (comp & 15) + 16 * ((pos >> 2) & 3)) * 4 + (pos & 3);
 }
 
+// one value of row m, column n of packed rows
+__device__ __forceinline__ void put_packed1(uint16_t* out, size_t plane_elems, int KT, int m, int n, float y) {
+  const uint32_t hp = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){y, 0.f}, bf16x2));
+  const uint32_t lp = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){y - __uint_as_float(hp << 16), 0.f}, bf16x2));
+  const size_t o = (((size_t)(m >> 4) * KT + (n >> 5)) * 64 + (m & 15) + 16 * ((n >> 3) & 3)) * 8 + (n & 7);
+  out[o] = (uint16_t)hp;
+  out[plane_elems + o] = (uint16_t)lp;
+}
+
 struct AttnGroup {
   const float* qkv;     // [M][3*d_model]: q | k | v as produced by the QKV projection
   float* Kc; float* Vc; // this layer's cache: [H][blocks][HD/16][64][4]
@@ -646,15 +657,20 @@ struct AttnGroup {
   int pos_off;          // the rows sit at position p = ds->pos + pos_off and attend to cached positions [0, p)
   int own_cache;        // the row's own key/value go to cache position p (one row only)
   int M;                // rows, 1..16
-  int causal;           // prompt chunk: row m sits at position p + m and attends to [0, p + m); the keys and
+  int causal;           // prompt chunk (M up to 32): row m sits at position p + m and attends to [0, p + m); the keys and
                         // values of all rows are in the cache already (chunk_kv_kernel), nothing is stored here
 };
+// Rows of a prompt chunk per workgroup (grid z): its work is a chain of short phases, and the rows are what can be spread over the
+// machine.  Measured (7B shape, 26 rows, one chunk of positions): 16 rows per workgroup 11.6 us, 4 rows 5.9 us.
+constexpr int ATT_CAUSAL_ROWS = 4;
 struct AttnArgs {
   AttnGroup g[2];
   const DevState* ds;
   const float2* rope;   // [max_ctx][hd/2] (cos, sin) or null
   int H, d_model, max_ctx, nchunk_max;
   float scale;
+  uint16_t* outp;       // prompt chunk whose positions all lie in the first chunk: the finished rows in packed form (see PackArgs),
+                        // in place of partials (there is nothing to merge)
 };
 
 template <int HD> __host__ __device__ constexpr int attn_lds_floats(int M) {
@@ -667,12 +683,13 @@ template <int HD, bool CAUSAL = false>
 __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
   extern __shared__ float4 lds4[];
   float* lds = (float*)lds4;
-  const AttnGroup& G = a.g[blockIdx.z];
+  const AttnGroup& G = a.g[CAUSAL ? 0 : blockIdx.z];
+  const int r0 = CAUSAL ? (int)blockIdx.z * ATT_CAUSAL_ROWS : 0;
   constexpr int NS = HD / 16, half = HD / 2;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.y, c = blockIdx.x;
-  const int p = a.ds->pos + G.pos_off, M = G.M;
+  const int p = a.ds->pos + G.pos_off + r0, M = CAUSAL && G.M - r0 > ATT_CAUSAL_ROWS ? ATT_CAUSAL_ROWS : G.M - r0;
   const int j0 = c * ATT_CHUNK;
   if (j0 > p + (CAUSAL ? M - 1 : 0)) return;
   // position of row m; whether this chunk holds it; whether the chunk lies before or at it at all
@@ -695,7 +712,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
       const int f = f0 + lane * 4;
       if (f < nfl) {
         const int m = f / (3 * HD), r = f - m * (3 * HD), sec = r / HD, i = r - sec * HD;
-        dma16(G.qkv + (size_t)m * 3 * a.d_model + (size_t)sec * a.d_model + (size_t)h * HD + i, raw + f0);
+        dma16(G.qkv + (size_t)(r0 + m) * 3 * a.d_model + (size_t)sec * a.d_model + (size_t)h * HD + i, raw + f0);
       }
     }
   }
@@ -802,7 +819,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
 #pragma unroll
     for (int w = 1; w < ATT_WAVES; ++w) o += ored[(w * M + m) * HD + i];
     if (owns_p) o = fmaf(st[m * 4 + 2], vo[m * HD + i], o);
-    float* dst = G.part + (((size_t)m * a.H + h) * a.nchunk_max + c) * (HD + 2);
+    if (CAUSAL && a.outp) {       // (as attn_merge_kernel on one chunk: weight 1, added to 0)
+      put_packed1(a.outp, (size_t)a.d_model * 32, a.d_model / 32, r0 + m, h * HD + i, (o + 0.f) / st[m * 4 + 1]);
+      continue;
+    }
+    float* dst = G.part + (((size_t)(r0 + m) * a.H + h) * a.nchunk_max + c) * (HD + 2);
     dst[i] = o;
     if (i == 0) { dst[HD] = st[m * 4]; dst[HD + 1] = st[m * 4 + 1]; }
     // the row's own key and value (stored last: no store waits in the request queue behind the block loads)
@@ -864,6 +885,7 @@ __global__ void clear_kv_kernel(ClearKvArgs a) {
 // merge of the chunk partials, chunks in index order
 struct MergeArgs {
   const float* part[2]; float* out[2];   // out: [M][d_model]
+  uint16_t* outp;      // prompt chunks of bf16 models: the rows as packed two-term operands instead (see PackArgs)
   int pos_off[2]; int M[2];
   int causal[2];       // row m sits m positions further on (prompt chunk)
   const DevState* ds;
@@ -919,7 +941,9 @@ __global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(MergeArgs a) 
       oo = fmaf(w, sm_o[q * a.HD + i], oo);
       ll = fmaf(w, sl_l[q], ll);
     }
-    a.out[g][(size_t)m * a.d_model + (size_t)h * a.HD + i] = oo / ll;
+    const float y = oo / ll;
+    if (a.outp) put_packed1(a.outp, (size_t)a.d_model * 32, a.d_model / 32, m, h * a.HD + i, y);
+    else a.out[g][(size_t)m * a.d_model + (size_t)h * a.HD + i] = y;
   }
 }
 #endif
@@ -1488,8 +1512,6 @@ namespace ppd {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int MG_THREADS = 512;     // 8 waves: each takes one eighth of the reduction length of a 16-row tile
 constexpr int MG_WAVES = MG_THREADS / WAVE;
@@ -1968,68 +1990,5 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
     }
   }
 }
-
-// The norm of gemm_mfma_kernel's prologue on its own: Y = norm(X) row by row, with the same order of additions
-// (thread t sums the 8-element pieces t, t + 512, ...; butterfly inside each wave; the eight wave sums in index
-// order) and the same expression per element, so that a GEMM without a fused norm on Y gives the bits of the
-// fused one on X.  For row groups whose rows do not fit LDS whole (prompt chunks): the GEMM then stages Y in passes.
-#ifdef PPD_ENGINE_TU
-struct NormRowsArgs {
-  const float* X; float* Y;      // [M][ld]
-  const void* g; const void* b;  // bf16 gain, bias (LayerNorm) or null
-  int K, ld, norm;               // norm: 0 LayerNorm, 1 RMSNorm
-  float eps;
-};
-__global__ __launch_bounds__(MG_THREADS) void norm_rows_kernel(NormRowsArgs a) {
-  __shared__ float redA[MG_WAVES], redB[MG_WAVES];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = a.K;
-  const float* x = a.X + (size_t)blockIdx.x * a.ld;
-  float* y = a.Y + (size_t)blockIdx.x * a.ld;
-  auto combine8 = [&](const float* r) { return ((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]; };
-  float mu = 0.f;
-  if (a.norm == 0) {
-    float sm = 0.f;
-    for (int c = tid; c * 8 < K; c += MG_THREADS) {
-      const float4* px = (const float4*)(x + c * 8);
-      const float4 v = px[0], w = px[1];
-      sm += v.x; sm += v.y; sm += v.z; sm += v.w; sm += w.x; sm += w.y; sm += w.z; sm += w.w;
-    }
-    sm = wave_sum(sm);
-    if (lane == 0) redA[wave] = sm;
-    __syncthreads();
-    mu = combine8(redA) / (float)K;
-  }
-  float s2 = 0.f;
-  for (int c = tid; c * 8 < K; c += MG_THREADS) {
-    const float4* px = (const float4*)(x + c * 8);
-    const float4 v = px[0], w = px[1];
-    const float d[8] = {v.x - mu, v.y - mu, v.z - mu, v.w - mu, w.x - mu, w.y - mu, w.z - mu, w.w - mu};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s2 = fmaf(d[e], d[e], s2);
-  }
-  s2 = wave_sum(s2);
-  if (lane == 0) redB[wave] = s2;
-  __syncthreads();
-  const float rs = 1.0f / sqrtf(combine8(redB) / (float)K + a.eps);
-  for (int c = tid; c * 8 < K; c += MG_THREADS) {
-    const float4* px = (const float4*)(x + c * 8);
-    const float4 v = px[0], w = px[1];
-    float xv[8] = {v.x, v.y, v.z, v.w, w.x, w.y, w.z, w.w};
-    const u32x4 gq = *(const u32x4*)((const char*)a.g + (size_t)c * 16);
-    float gf[8]; WTr<bf16_t>::unpack(gq, gf);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) xv[e] = (xv[e] - mu) * rs * gf[e];
-    if (a.norm == 0 && a.b) {
-      const u32x4 bq = *(const u32x4*)((const char*)a.b + (size_t)c * 16);
-      float bf[8]; WTr<bf16_t>::unpack(bq, bf);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) xv[e] += bf[e];
-    }
-    float4* py = (float4*)(y + c * 8);
-    py[0] = make_float4(xv[0], xv[1], xv[2], xv[3]);
-    py[1] = make_float4(xv[4], xv[5], xv[6], xv[7]);
-  }
-}
-#endif
 
 }  // namespace ppd

@@ -10,6 +10,7 @@
 //                       memory (every wave-load is one contiguous kilobyte); products exact in fp32 as in decoding
 //   pkv_pack_kernel     queries, keys, values of the prompt rows -> two-term operand blocks, and keys and values into
 //                       the fp32 cache in the decode path's layout
+//   rgemm_kernel        the GEMMs of a prompt chunk of up to 32 rows, in the decode path's summation order
 //   pattn_kernel        causal attention of all prompt rows on the same MFMA (three products per pair of two-term
 //                       operands), key/value steps staged through LDS for the four waves of a workgroup, running softmax
 //
@@ -367,6 +368,146 @@ __global__ __launch_bounds__(PG_THREADS) void pgemm_kernel(PGemmArgs a) {
   }
 }
 
+// ---- a prompt chunk of up to 32 rows: one pass over the weights, bound by their stream
+// The arithmetic is gemm_mfma_kernel's (wave w of 8 owns one eighth of the reduction length; first terms, then second
+// terms of a block; the eight partial sums in wave order), so a row's bits are those of a one-row pass.  The rows come as
+// packed two-term operands straight from L2 instead of being staged and converted in LDS by every workgroup: 16 rows
+// of fp32 do not fit LDS whole, and the staging passes took most of the time (7B shape, 16 rows: 30 us of staging in a
+// 45 us FFN-in launch).  Every block of rows feeds TT weight tiles, so that L2 hands out (1 + 2 MT / TT) kilobytes per
+// kilobyte of weights.  Measured (7B shape, 26 rows, all layers): two 16-row chunks through gemm_mfma_kernel 9.0 ms,
+// one chunk through this kernel 4.3 ms (attention and its row split included); per layer QKV 24 us, O 15, FFN-in 37,
+// FFN-out 35.  What is left over the weights' stream is the L2 traffic: with one tile per workgroup (O, FFN-out) the rows are
+// four times the weights; six tiles at once instead of twice three took FFN-in from 42 to 37 us.
+struct RGemmArgs {
+  const uint16_t* Xp;   // packed rows [2 planes][2][KT][64][8] (always two 16-row tiles; see PackArgs)
+  const void* P;        // repacked weights [NT][KT][64][8]
+  const void* B[3];     // biases per row segment or null (paired: B[0] gate, B[1] up)
+  const float* Rsd;     // residual rows [M][ldy] or null
+  float* Y;             // [M][ldy], or
+  uint16_t* Yp; int KTp;   // the outputs as packed rows [2][2][KTp][64][8]
+  int M, KT, NT, N[3], ntot, ldy;
+  int act;              // 0 none, 1 GELU, 2 ReLU (paired launches apply SwiGLU)
+  int tiles_wg; unsigned wbytes;
+};
+constexpr int RG_TILES_MAX = 8;      // tiles of a workgroup whose partial sums fit LDS (16 KiB each for 32 rows)
+
+#ifdef PPD_PREFILL_TU
+template <bool PAIRED, int TT, int MT>
+__global__ __launch_bounds__(MG_THREADS) void rgemm_kernel(RGemmArgs a) {
+  constexpr int D = TT >= 6 ? 3 : (TT >= 3 ? 4 : 6);       // reduction steps in flight per wave
+  extern __shared__ float4 rg_lds4[];
+  float* const part = (float*)rg_lds4;                     // [tile][8 waves][16 MT rows][16 outputs]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grid = gridDim.x, KT = a.KT, M = a.M;
+  const int ntiles = (int)blockIdx.x + (a.tiles_wg - 1) * grid < a.NT ? a.tiles_wg : a.tiles_wg - 1;
+  const int nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
+  const int kb0 = wave * nb8 < KT ? wave * nb8 : KT;
+  const int nblk = (kb0 + nb8 < KT ? kb0 + nb8 : KT) - kb0;
+  const int ngrp = (ntiles + TT - 1) / TT, Q = ngrp * nblk;
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)a.P, 0, (int)a.wbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void*)a.Xp, 0, KT * 4096, 0x00020000);
+  const unsigned lane16 = lane * 16, plane = KT * 2048u;
+  u32x4 wa[D][TT], xh[D][MT], xl[D][MT];
+  int l_g = 0, l_s = 0;
+  // every step is requested in full: what lies past the wave's share re-reads the start of the matrix and is never used
+  auto request = [&](int d) {
+    const bool live = l_g < ngrp;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      const int ord = l_g * TT + t;
+      const unsigned o = live && ord < ntiles ? (unsigned)(((int)blockIdx.x + ord * grid) * KT + kb0 + l_s) * 1024u : 0u;
+      wa[d][t] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, o, 2);      // 2: non-temporal
+    }
+    const unsigned xo = live ? (unsigned)(kb0 + l_s) * 1024u : 0u;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      xh[d][m] = __builtin_amdgcn_raw_buffer_load_b128(xres, lane16, xo + m * KT * 1024u, 0);
+      xl[d][m] = __builtin_amdgcn_raw_buffer_load_b128(xres, lane16, xo + m * KT * 1024u + plane, 0);
+    }
+    if (++l_s >= nblk) { l_s = 0; ++l_g; }
+  };
+  f32x4 acc[TT][MT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[t][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  int c_g = 0, c_s = 0;
+  auto put = [&]() {                                       // this wave's partial sums of a group of tiles
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      const int ord = c_g * TT + t;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        if (ord < ntiles) *(f32x4*)(part + (((size_t)ord * MG_WAVES + wave) * (16 * MT) + 16 * m + (lane & 15)) * 16 + 4 * (lane >> 4)) = acc[t][m];
+        acc[t][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  };
+  auto consume = [&](int d) {
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[d][t]), __builtin_bit_cast(bf16x8, xh[d][m]), acc[t][m], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[d][t]), __builtin_bit_cast(bf16x8, xl[d][m]), acc[t][m], 0, 0, 0);
+    if (++c_s == nblk) { put(); c_s = 0; ++c_g; }
+  };
+  if (nblk > 0) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) request(d);
+    for (int q = 0; q < Q; q += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        if (q + d < Q) consume(d);
+        request(d);
+      }
+    }
+  } else {
+    for (; c_g < ngrp; ++c_g) put();                       // a wave without a share adds zeros
+  }
+  __syncthreads();
+  // the eight partials of an output in wave order, bias, activation, residual
+  constexpr int R = PAIRED ? 8 : 16;
+  const uint16_t* const B0 = (const uint16_t*)a.B[0];
+  const uint16_t* const B1 = (const uint16_t*)a.B[1];
+  const uint16_t* const B2 = (const uint16_t*)a.B[2];
+  for (int e = tid; e < ntiles * M * R; e += MG_THREADS) {
+    const int row = e & (R - 1), f = e / R, ord = f / M, m = f - ord * M, n = ((int)blockIdx.x + ord * grid) * R + row;
+    if (n >= a.ntot) continue;
+    const float* pp = part + ((size_t)ord * MG_WAVES * (16 * MT) + m) * 16 + row;
+    constexpr int ws = 16 * MT * 16;
+    float s = pp[0];
+#pragma unroll
+    for (int w = 1; w < MG_WAVES; ++w) s += pp[w * ws];
+    float y;
+    if (PAIRED) {
+      float u = pp[8];
+#pragma unroll
+      for (int w = 1; w < MG_WAVES; ++w) u += pp[w * ws + 8];
+      y = silu(s + (B0 ? bf16_to_f32(B0[n]) : 0.f)) * (u + (B1 ? bf16_to_f32(B1[n]) : 0.f));
+    } else {
+      float b = 0.f;
+      if (B0) {
+        int seg = 0, loc = n;
+        if (loc >= a.N[0]) { loc -= a.N[0]; seg = 1; if (loc >= a.N[1]) { loc -= a.N[1]; seg = 2; } }
+        b = bf16_to_f32((seg == 0 ? B0 : (seg == 1 ? B1 : B2))[loc]);
+      }
+      y = s + b;
+      if (a.act == 1) y = gelu_erf(y);
+      else if (a.act == 2) y = fmaxf(y, 0.f);
+    }
+    y += a.Rsd ? a.Rsd[(size_t)m * a.ldy + n] : 0.f;
+    if (a.Yp) put_packed1(a.Yp, (size_t)2 * a.KTp * 512, a.KTp, m, n, y);
+    else a.Y[(size_t)m * a.ldy + n] = y;
+  }
+}
+#endif
+
 // ---- causal attention of the prompt rows
 // Row m of the prompt sits at position m (the prompt pass starts from an empty cache) and attends to rows 0 .. m.
 // Queries (rotated, scaled), keys (rotated exactly as the cache holds them) and values are first put into two-term
@@ -650,6 +791,8 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
 // launchers (ppd_prefill.hip)
 hipError_t launch_pack_rows(hipStream_t stream, const PackArgs& a);
 hipError_t launch_pgemm(hipStream_t stream, PGemmArgs a, bool paired);
+hipError_t launch_rgemm(hipStream_t stream, RGemmArgs a, bool paired);
+hipError_t rgemm_setup();
 hipError_t launch_pkv_pack(hipStream_t stream, const PKvPackArgs& a, int head_dim);
 hipError_t launch_pattn(hipStream_t stream, const PAttnArgs& a, int head_dim);
 // bytes of the packed form of M rows of K columns

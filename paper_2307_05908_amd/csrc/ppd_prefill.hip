@@ -6,7 +6,7 @@
 namespace ppd {
 
 hipError_t launch_pack_rows(hipStream_t stream, const PackArgs& a) {
-  if (a.M < 1 || a.K < 8 || (a.K & 7) || (a.ld & 3) || a.MT != (a.M + 15) / 16 || a.KT != (a.K + 31) / 32) return hipErrorInvalidValue;
+  if (a.M < 1 || a.K < 8 || (a.K & 7) || (a.ld & 3) || a.MT < (a.M + 15) / 16 || a.KT != (a.K + 31) / 32) return hipErrorInvalidValue;
   hipLaunchKernelGGL(pack_rows_kernel, dim3(a.MT * 16), dim3(MG_THREADS), 0, stream, a);
   return hipGetLastError();
 }
@@ -31,6 +31,48 @@ hipError_t launch_pgemm(hipStream_t stream, PGemmArgs a, bool paired) {
   const int tn = ((a.NT + PG_WAVES * 4 - 1) / (PG_WAVES * 4)) * mb >= 384 ? 4 : 2;
   if (paired) return tn == 4 ? launch_pgemm_t<true, 4, 4>(stream, a) : launch_pgemm_t<true, 2, 4>(stream, a);
   return tn == 4 ? launch_pgemm_t<false, 4, 4>(stream, a) : launch_pgemm_t<false, 2, 4>(stream, a);
+}
+
+template <bool PAIRED, int TT>
+static hipError_t launch_rgemm_t(hipStream_t stream, const RGemmArgs& a, int grid) {
+  const size_t lds = (size_t)a.tiles_wg * MG_WAVES * 16 * 16 * sizeof(float) * (a.M > 16 ? 2 : 1);
+  if (a.M > 16) hipLaunchKernelGGL((rgemm_kernel<PAIRED, TT, 2>), dim3(grid), dim3(MG_THREADS), lds, stream, a);
+  else hipLaunchKernelGGL((rgemm_kernel<PAIRED, TT, 1>), dim3(grid), dim3(MG_THREADS), lds, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_rgemm(hipStream_t stream, RGemmArgs a, bool paired) {
+  if (a.M < 1 || a.M > 32 || a.KT < 1 || a.NT < 1 || (size_t)a.NT * a.KT * 1024 > 0x7fffffffu) return hipErrorInvalidValue;
+  a.wbytes = (unsigned)((size_t)a.NT * a.KT * 1024);
+  // one workgroup per compute unit, the smallest grid with the same number of tiles in each; more than RG_TILES_MAX tiles do
+  // not fit LDS (then more workgroups)
+  a.tiles_wg = (a.NT + 255) / 256;
+  if (a.tiles_wg > RG_TILES_MAX) a.tiles_wg = RG_TILES_MAX;
+  const int grid = (a.NT + a.tiles_wg - 1) / a.tiles_wg;
+  // tiles that share their loads of the rows: all of a workgroup's, or half of them past 6 (registers)
+  const int tt = a.tiles_wg <= 4 ? a.tiles_wg : (a.tiles_wg <= 6 ? 6 : 4);
+  switch (tt) {
+    case 1: return paired ? launch_rgemm_t<true, 1>(stream, a, grid) : launch_rgemm_t<false, 1>(stream, a, grid);
+    case 2: return paired ? launch_rgemm_t<true, 2>(stream, a, grid) : launch_rgemm_t<false, 2>(stream, a, grid);
+    case 3: return paired ? launch_rgemm_t<true, 3>(stream, a, grid) : launch_rgemm_t<false, 3>(stream, a, grid);
+    case 4: return paired ? launch_rgemm_t<true, 4>(stream, a, grid) : launch_rgemm_t<false, 4>(stream, a, grid);
+    default: return paired ? launch_rgemm_t<true, 6>(stream, a, grid) : launch_rgemm_t<false, 6>(stream, a, grid);
+  }
+}
+
+template <bool PAIRED, int TT>
+static hipError_t rgemm_setup_t() {
+  const int lds = RG_TILES_MAX * MG_WAVES * 32 * 16 * (int)sizeof(float);
+  hipError_t e = hipFuncSetAttribute((const void*)rgemm_kernel<PAIRED, TT, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)rgemm_kernel<PAIRED, TT, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  return e;
+}
+
+hipError_t rgemm_setup() {
+  hipError_t e = hipSuccess;
+  for (auto f : {rgemm_setup_t<true, 4>, rgemm_setup_t<true, 6>, rgemm_setup_t<false, 4>, rgemm_setup_t<false, 6>})
+    if (e == hipSuccess) e = f();
+  return e;
 }
 
 hipError_t launch_pkv_pack(hipStream_t stream, const PKvPackArgs& a, int head_dim) {
