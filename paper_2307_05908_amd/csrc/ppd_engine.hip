@@ -486,6 +486,7 @@ int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
   kv.HD = d.head_dim; kv.d_model = dm; kv.max_ctx = d.max_ctx;
   hipLaunchKernelGGL(chunk_kv_kernel, dim3(M, d.n_heads), dim3(d.head_dim), 0, c->cur, kv);
   HIPCHK(c, hipGetLastError());
+  if (l == d.n_layers - 1) return PPD_OK;    // a prompt leaves its keys and values; no one reads the last layer's rows
   AttnArgs a; memset(&a, 0, sizeof a);
   AttnGroup& G = a.g[0];
   G.qkv = c->qkv; G.Kc = Kc; G.Vc = Vc; G.own_cache = 1; G.part = c->part; G.M = M; G.causal = 1;
@@ -877,6 +878,7 @@ int prefill_tiled(ppd_ctx* c, int rows) {
       pk.Kc = (float*)(c->Kc + (size_t)l * cache_layer_bytes(c)); pk.Vc = (float*)(c->Vc + (size_t)l * cache_layer_bytes(c));
       pk.max_ctx = d.max_ctx; pk.M = rows; pk.H = d.n_heads; pk.d_model = dm; pk.JP = (rows + 31) / 32; pk.scale = 1.44269504088896340736f / sqrtf((float)d.head_dim);
       HIPCHK(c, launch_pkv_pack(c->cur, pk, d.head_dim));
+      if (l == d.n_layers - 1) break;        // a prompt leaves its keys and values; no one reads the last layer's rows
       PAttnArgs pa; memset(&pa, 0, sizeof pa);
       pa.Qp = c->pf_qp; pa.Kp = c->pf_kp; pa.Vp = c->pf_vp; pa.outp = c->pf_xa;
       pa.M = rows; pa.H = d.n_heads; pa.d_model = dm; pa.JP = pk.JP;
@@ -1167,7 +1169,8 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
     for (int l = 0; l < c->d.n_layers && !rc; ++l) {
       RowGroup g{l, m, 0, 0, false};
       g.chunk = m > 1;
-      rc = c->mfma && g.chunk ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1);
+      // (the last layer's rows are read by no one: its keys and values are all that a prompt leaves there)
+      rc = c->mfma && g.chunk ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
     }
   }
   c->prof = prof;
