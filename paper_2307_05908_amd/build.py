@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libppd.so")
 PROBE_PATH = os.path.join(HERE, "ppd_pmc_probe")
-N_INST = 7
+N_INST = 8
 DEPS = [os.path.join(CSRC, f) for f in ("ppd_engine.hip", "ppd_ops.hip", "ppd_pmc_probe.cpp", "ppd_prefill.hip", "ppd_prefill.h", "ppd_fused.hip", "ppd_fused.h", "ppd_inst.hip", "ppd_kernels.h", "ppd_launch.h")] + \
        [os.path.join(os.path.dirname(HERE), "include", f) for f in ("ppd.h", "ppd_measure.h")]
 # -ffp-contract=off: every fused multiply-add in the kernels is an explicit fmaf, so a row's arithmetic

@@ -171,6 +171,7 @@ void prof_collect(ppd_ctx* c) {   // stream must be idle
 // ------------------------------------------------------------ launch helpers
 // one skinny GEMM launch; group 0 is always one row, group 1 (optional) has MB rows
 hipError_t launch_gemm(ppd_ctx* c, GemmArgs& a, int ngroups, bool paired) {
+  if (c->wbytes == 4 && gemm_small_fits(a, c->head_grid)) return launch_gemm_small(c->cur, a, ngroups, paired, c->head_grid);
   const int vec = 16 / c->wbytes;
   const int gmax = ngroups == 2 ? c->gmax2 : c->gmax1;
   const int mmax = ngroups == 2 ? (a.g[1].M > a.g[0].M ? a.g[1].M : a.g[0].M) : a.g[0].M;

@@ -3,7 +3,30 @@
 
 namespace ppd {
 
-#if PPD_INST < 4 || PPD_INST == 6
+#if PPD_INST == 7
+template <int NB>
+static hipError_t launch_gemm_small_t(hipStream_t stream, const GemmArgs& a, int mmax, bool paired, dim3 grid) {
+#define GO(mt, lr) do { if (paired) hipLaunchKernelGGL((gemm_small_kernel<mt, NB, true, 1>), grid, dim3(GEMM_THREADS), 0, stream, a); \
+    else hipLaunchKernelGGL((gemm_small_kernel<mt, NB, false, lr>), grid, dim3(GEMM_THREADS), 0, stream, a); } while (0)
+  if (a.topk > 0) GO(1, 4);
+  else if (mmax == 1) GO(1, 1);
+  else if (mmax <= 4) GO(4, 1);
+  else GO(8, 1);
+#undef GO
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups, bool paired, int head_grid) {
+  int mmax = a.g[0].M;
+  if (ngroups == 2 && a.g[1].M > mmax) mmax = a.g[1].M;
+  if (!gemm_small_fits(a, head_grid) || mmax < 1 || mmax > MAXM || ngroups < 1 || ngroups > 2) return hipErrorInvalidValue;
+  if (a.topk > 0 && (ngroups != 1 || mmax != 1 || paired || head_grid > a.ntot)) return hipErrorInvalidValue;
+  const dim3 grid(a.topk > 0 ? head_grid : (a.ntot + GEMM_WAVES - 1) / GEMM_WAVES, ngroups);
+  if (a.K <= 256) return launch_gemm_small_t<1>(stream, a, mmax, paired, grid);
+  if (a.K <= 512) return launch_gemm_small_t<2>(stream, a, mmax, paired, grid);
+  return launch_gemm_small_t<4>(stream, a, mmax, paired, grid);
+}
+#elif PPD_INST < 4 || PPD_INST == 6
 // MA rows in group 0; MB rows in group 1 (0: single-group launch).  Launch shapes in use:
 // (1, 0) main token alone, (k, 0) the candidates alone, (1, k) both in one launch.
 template <typename WT, bool PAIRED, int WR>

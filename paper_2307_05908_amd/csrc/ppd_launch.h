@@ -8,6 +8,13 @@ namespace ppd {
 template <typename WT, bool PAIRED, int WR>
 hipError_t launch_gemm_t(hipStream_t stream, const GemmArgs& a, int MA, int MB, dim3 grid, size_t lds);
 
+// gemm_small_kernel, where it applies: fp32 weights, K <= GEMM_SMALL_K, and every output has a wave's turn of its own (up to
+// GEMM_SMALL_ROWS outputs; of a head launch, one set per wave of its grid).
+inline bool gemm_small_fits(const GemmArgs& a, int head_grid) {
+  return a.K <= GEMM_SMALL_K && (a.topk > 0 ? (int64_t)a.ntot <= (int64_t)head_grid * GEMM_WAVES * 4 : a.ntot <= GEMM_SMALL_ROWS);
+}
+hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups, bool paired, int head_grid);
+
 template <int HD>
 hipError_t launch_attn_t(hipStream_t stream, const AttnArgs& a, int mmax, dim3 grid, bool causal);
 
