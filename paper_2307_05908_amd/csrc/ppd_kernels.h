@@ -341,6 +341,20 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
       const int m = i / spr, kk = (i - m * spr) * 1024 + tid * 4;
       if (m < M && kk < K) xr[i] = *(const float4*)(G.X + (size_t)m * a.ldx + kk);
     }
+    // one row: its gains come with it (later they would wait behind the weights)
+    constexpr int GR = MT == 1 ? 4 : 0;
+    float gr[GR + 1][4], br[GR + 1][4];
+    if (MT == 1 && a.norm >= 0) {
+#pragma unroll
+      for (int i = 0; i < GR; ++i) {
+        const int kk = i * 1024 + tid * 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          gr[i][e] = kk < K ? WTr<WT>::load1(G.ng, kk + e) : 0.f;
+          br[i][e] = kk < K && G.nb ? WTr<WT>::load1(G.nb, kk + e) : 0.f;
+        }
+      }
+    }
     issue_next(b0);
     issue_next(b1);
     issue_next(b2);
@@ -384,8 +398,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
         float xv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float t = (xv[e] - mu) * rs * WTr<WT>::load1(G.ng, kk + e);
-          if (G.nb) t += WTr<WT>::load1(G.nb, kk + e);
+          float t = (xv[e] - mu) * rs * (i < GR ? gr[i < GR ? i : 0][e] : WTr<WT>::load1(G.ng, kk + e));
+          if (G.nb) t += i < GR ? br[i < GR ? i : 0][e] : WTr<WT>::load1(G.nb, kk + e);
           xv[e] = t;
         }
         v = make_float4(xv[0], xv[1], xv[2], xv[3]);
