@@ -7,7 +7,7 @@ namespace ppd {
 
 hipError_t launch_pack_rows(hipStream_t stream, const PackArgs& a) {
   if (a.M < 1 || a.K < 8 || (a.K & 7) || (a.ld & 3) || a.MT < (a.M + 15) / 16 || a.KT != (a.K + 31) / 32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pack_rows_kernel, dim3(a.MT * 16), dim3(MG_THREADS), 0, stream, a);
+  hipLaunchKernelGGL(pack_rows_kernel, dim3((a.MT + 7) / 8 * 128), dim3(MG_THREADS), 0, stream, a);
   return hipGetLastError();
 }
 
