@@ -32,6 +32,14 @@ enum {
 int ppd_get_logits(ppd_ctx *ctx, float *host_logits);
 int ppd_get_early_logits(ppd_ctx *ctx, float *host_logits);
 
+/* The one-launch chain of layers of bf16 models.  ppd_get_chain_rounds (HOST outputs): the context's rounds since
+ * ppd_create in which the main token went through its layers in one launch, and those that were run again, one
+ * launch per step of a layer, because that launch gave up waiting for compute units (the results are the same).
+ * ppd_set_chain_wait: how long such a wait lasts, in ticks of 10 ns; 0: as at ppd_create (100 ms, or PPD_SPIN_TICKS
+ * of the environment).  A test hook: with 1 tick a launch gives up at its first wait. */
+int ppd_get_chain_rounds(const ppd_ctx *ctx, uint64_t *rounds, uint64_t *again);
+int ppd_set_chain_wait(ppd_ctx *ctx, int ticks);
+
 /* Timing with HIP events on the context's streams.  level 2: every launch is bracketed by two
  * events; level 1: only the phases of a round are (class PPD_KC_PHASE), so the kernels run
  * back to back as in normal operation; level 0: off.  While on, rounds are issued eagerly

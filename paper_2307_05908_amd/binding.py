@@ -51,7 +51,7 @@ class Stats(ctypes.Structure):
 
 EXPORTS = ("ppd_create", "ppd_reset", "ppd_prefill", "ppd_step", "plain_greedy_step", "ppd_get_logits",
            "ppd_get_early_logits", "ppd_get_stats", "ppd_set_profiling", "ppd_set_graphs", "ppd_set_sampling", "ppd_get_kernel_time",
-           "ppd_time_ffn_in", "ppd_stream_read_probe", "ppd_early_topk", "ppd_early_topk_noalloc", "ppd_destroy",
+           "ppd_time_ffn_in", "ppd_get_chain_rounds", "ppd_set_chain_wait", "ppd_stream_read_probe", "ppd_early_topk", "ppd_early_topk_noalloc", "ppd_destroy",
            "ppd_strerror", "ppd_last_hip_error")
 
 _lib = None
@@ -83,6 +83,8 @@ def load_library() -> ctypes.CDLL:
     lib.ppd_set_sampling.argtypes = [vp, ci, ci, ctypes.c_double, ctypes.c_uint64]
     lib.ppd_get_kernel_time.argtypes = [vp, ci, ci, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_uint64)]
     lib.ppd_time_ffn_in.argtypes = [vp, ci, ci, ctypes.POINTER(ctypes.c_double)]
+    lib.ppd_get_chain_rounds.argtypes = [vp, ctypes.POINTER(ctypes.c_uint64), ctypes.POINTER(ctypes.c_uint64)]
+    lib.ppd_set_chain_wait.argtypes = [vp, ci]
     lib.ppd_stream_read_probe.argtypes = [vp, ctypes.c_uint64, ci, ctypes.POINTER(ctypes.c_double)]
     lib.ppd_early_topk.argtypes = [ci, ci, ci, ctypes.c_float, ci, vp, vp, vp, vp, ci, vp, vp, vp, vp]
     lib.ppd_early_topk_noalloc.argtypes = lib.ppd_early_topk.argtypes
@@ -265,6 +267,15 @@ class PPD:
         out = ctypes.c_double(0.0)
         self._chk(load_library().ppd_time_ffn_in(self._h, reps, groups, ctypes.byref(out)), "ppd_time_ffn_in")
         return float(out.value)
+
+    def ppd_get_chain_rounds(self):
+        """(rounds whose main token went through its layers in one launch, rounds that were run again)."""
+        n, again = ctypes.c_uint64(), ctypes.c_uint64()
+        self._chk(load_library().ppd_get_chain_rounds(self._h, ctypes.byref(n), ctypes.byref(again)), "ppd_get_chain_rounds")
+        return int(n.value), int(again.value)
+
+    def ppd_set_chain_wait(self, ticks: int = 0):
+        self._chk(load_library().ppd_set_chain_wait(self._h, int(ticks)), "ppd_set_chain_wait")
 
     def ppd_get_kernel_time(self) -> Dict[str, Dict[str, float]]:
         out = {}

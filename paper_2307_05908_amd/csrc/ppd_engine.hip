@@ -102,6 +102,8 @@ struct ppd_ctx {
   FusedArgs fused_args;
   FLayer* fl_tab;        // [n_layers] in device memory
   float *fl_ex, *fl_part, *h_save;   // outputs of the steps [n_layers], attention partials, the rows as the round found them
+  int chain_wait;        // ticks a wait in the chain lasts by default
+  uint64_t chain_rounds, chain_again;   // rounds with a chain, rounds run again because it gave up
   // round state
   int n_ctx;      // absolute position of the pending token x_t (-1: no prefill yet)
   int matched;    // the pending token already went through layers 1..nb (its h is row 0)
@@ -542,7 +544,7 @@ bool fused_plan(ppd_ctx* c) {
   a.H = d.n_heads; a.d_model = dm; a.d_ff = F; a.max_ctx = d.max_ctx; a.nchunk_max = c->nchunk_max;
   a.kv_bytes = (unsigned)cache_layer_bytes(c);
   a.scale = 1.0f / sqrtf((float)d.head_dim); a.eps = d.norm_eps;
-  a.spin_ticks = env_int("PPD_SPIN_TICKS", 10 * 1000 * 1000);      // 100 ms
+  a.spin_ticks = c->chain_wait = env_int("PPD_SPIN_TICKS", 10 * 1000 * 1000);      // 100 ms
   return c->fused_lds <= (int)MG_LDS_MAX && (int64_t)d.n_heads * ((c->nchunk_max + 1) / 2) * G < ((int64_t)1 << 31);
 }
 
@@ -662,11 +664,12 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
 // already predicted and embedded (speculative early prediction): parallel phase and final head only.  pmax bounds the positions touched (attention grid size only).
 int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   const int d = c->d.n_layers, dbar = c->dbar, nb = c->nb, k = c->k;
+  const int from = (kind == 1 || kind == 3) ? nb : 0;        // first layer the round takes the main token through
   int rc;
   {
     BeginArgs b; memset(&b, 0, sizeof b);
     b.ds = c->ds; b.take_next = kind == 3 ? 1 : 0; b.host_cand = c->host_result_dev + 2;
-    const int chain = kind == 2 ? d : dbar - (kind == 0 ? 0 : nb);     // layers the main token goes through alone
+    const int chain = (kind == 2 ? d : dbar) - from;     // layers the main token goes through alone
     int grid = 1;
     if ((c->fused && chain > 0) || restore) {
       if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
@@ -674,8 +677,8 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
       grid = 512;
     }
     if (restore) {
-      const ClearKvArgs kv = {(float*)c->Kc, (float*)c->Vc, c->ds, c->d.n_heads, c->d.head_dim, c->d.max_ctx};
-      hipLaunchKernelGGL(clear_kv_kernel, dim3(c->d.n_heads, d), dim3(c->d.head_dim), 0, c->cur, kv);
+      const ClearKvArgs kv = {(float*)c->Kc, (float*)c->Vc, c->ds, c->d.n_heads, c->d.head_dim, c->d.max_ctx, from};
+      hipLaunchKernelGGL(clear_kv_kernel, dim3(c->d.n_heads, d - from), dim3(c->d.head_dim), 0, c->cur, kv);
       HIPCHK(c, hipGetLastError());
     }
     hipLaunchKernelGGL(begin_round_kernel, dim3(grid), dim3(256), 0, c->cur, b);
@@ -687,7 +690,6 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
     return run_head(c, false, false);
   }
   // main token up to the exit layer
-  int from = (kind == 1 || kind == 3) ? nb : 0;
   if (kind == 0 && (rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
   if (from < dbar) {
     ProfScope phase(c, PPD_KC_PHASE, 1);
@@ -705,6 +707,18 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   }
   // final prediction, verification, adoption
   return run_head(c, false, true);
+}
+
+// the captured rounds are captured anew
+hipError_t drop_graphs(ppd_ctx* c) {
+  hipError_t e = hipSuccess;
+  for (hipGraphExec_t& g : c->graph)
+    if (g) {
+      const hipError_t e1 = hipGraphExecDestroy(g);
+      if (e == hipSuccess) e = e1;
+      g = nullptr;
+    }
+  return e;
 }
 
 // Run one round: set the device state, replay (or capture, or issue eagerly) the launches,
@@ -780,13 +794,14 @@ int run_round(ppd_ctx* c, int kind, int pos) {
   if (!c->fused) return run_round_once(c, kind, pos, false);
   std::lock_guard<std::mutex> turn(g_round_mu[c->device]);
   int rc = run_round_once(c, kind, pos, false);
+  if (!rc && c->prof < 2 && (kind == 2 || c->dbar > (kind == 0 ? 0 : c->nb))) c->chain_rounds += 1;
   if (rc || c->host_result[0] >= 0) return rc;
   // A workgroup gave up waiting for the others (something else held compute units): nothing was taken over.  This
   // context goes back to one launch per step for good, beginning with this round.
   c->fused = 0;
+  c->chain_again += 1;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  for (int i = 0; i < 4; ++i)
-    if (c->graph[i]) { HIPCHK(c, hipGraphExecDestroy(c->graph[i])); c->graph[i] = nullptr; }
+  HIPCHK(c, drop_graphs(c));
   return run_round_once(c, kind, pos, true);
 }
 
@@ -806,7 +821,7 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 }
 
 void free_all(ppd_ctx* c) {
-  for (int i = 0; i < 4; ++i) if (c->graph[i]) (void)hipGraphExecDestroy(c->graph[i]);
+  (void)drop_graphs(c);
   void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->qkv, c->att, c->ffn, c->part, c->logits,
                  c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
                  c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
@@ -1269,9 +1284,21 @@ int ppd_set_sampling(ppd_ctx* c, int mode, int top_k, double top_p, uint64_t see
   if (mode == 2 && !(top_p > 0.0 && top_p <= 1.0)) return PPD_EINVAL;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->samp_mode = mode; c->samp_k = top_k; c->samp_p = top_p; c->samp_seed = seed;
-  // the captured rounds hold the old rule
-  for (int i = 0; i < 4; ++i)
-    if (c->graph[i]) { HIPCHK(c, hipGraphExecDestroy(c->graph[i])); c->graph[i] = nullptr; }
+  HIPCHK(c, drop_graphs(c));     // the captured rounds hold the old rule
+  return PPD_OK;
+}
+
+int ppd_set_chain_wait(ppd_ctx* c, int ticks) {
+  if (!c || ticks < 0) return PPD_EINVAL;
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  c->fused_args.spin_ticks = ticks ? ticks : c->chain_wait;
+  HIPCHK(c, drop_graphs(c));     // the captured rounds hold the old limit
+  return PPD_OK;
+}
+
+int ppd_get_chain_rounds(const ppd_ctx* c, uint64_t* rounds, uint64_t* again) {
+  if (!c || !rounds || !again) return PPD_EINVAL;
+  *rounds = c->chain_rounds; *again = c->chain_again;
   return PPD_OK;
 }
 

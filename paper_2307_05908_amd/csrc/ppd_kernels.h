@@ -1028,12 +1028,14 @@ __global__ void chunk_kv_kernel(ChunkKvArgs a) {
 #endif
 
 // A round that is run again: what its first run left at the pending position of the caches may be no number, and the MFMAs
-// read whole blocks (weight 0 times NaN is NaN), so the position is cleared in every layer.  One workgroup per (head, layer).
-struct ClearKvArgs { float* Kc; float* Vc; const DevState* ds; int H, HD, max_ctx; };
+// read whole blocks (weight 0 times NaN is NaN), so the position is cleared in the layers that the round goes through, from
+// layer0 on.  (After a match the layers below hold the matching candidate's keys and values there: the round does not
+// compute them again.)  One workgroup per (head, layer).
+struct ClearKvArgs { float* Kc; float* Vc; const DevState* ds; int H, HD, max_ctx, layer0; };
 #ifdef PPD_ENGINE_TU
 __global__ void clear_kv_kernel(ClearKvArgs a) {
   const int i = threadIdx.x, pos = a.ds->pos_pending;
-  const size_t base = ((size_t)blockIdx.y * a.H + blockIdx.x) * kv_blocks(a.max_ctx) * (KV_BLOCK * a.HD);
+  const size_t base = ((size_t)(a.layer0 + blockIdx.y) * a.H + blockIdx.x) * kv_blocks(a.max_ctx) * (KV_BLOCK * a.HD);
   a.Kc[base + k_index(pos, i, a.HD)] = 0.f;
   a.Vc[base + v_index(pos, i, a.HD)] = 0.f;
 }

@@ -59,3 +59,30 @@ def test_a_launch_that_gives_up_is_run_again(name, monkeypatch):
         np.testing.assert_array_equal(a[0], b[0])
         np.testing.assert_array_equal(a[1], b[1])
         assert a[2] == b[2]
+
+
+@pytest.mark.parametrize("family", ["llama", "opt"])
+def test_a_round_behind_a_match_is_run_again(family, monkeypatch):
+    """The chain of such a round begins behind the layers that the matching candidate has been through: their keys and
+    values at the round's position stay, and every later token attends to them."""
+    n = {"llama": 6, "opt": 4}[family]
+    cfg = small_cfg(family, n_layers=n, exit_layer=n - 1, alpha=0.02, max_ctx=160, n_prompt=40, n_gen=30)
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    ref = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")[1]
+    match = [m for m, _, _ in ref[2]]
+    first = match.index(1)
+    assert first < cfg.n_gen // 2
+    P = binding.PPD(cfg, dev)
+    P.ppd_prefill(prompt)
+    for t in range(cfg.n_gen):
+        if t == first + 1:
+            assert P.ppd_get_chain_rounds() == (first + 1, 0)
+            P.ppd_set_chain_wait(1)
+        tok, info = P.ppd_step()
+        if t == first + 1:
+            assert P.ppd_get_chain_rounds() == (first + 2, 1)
+        assert tok == ref[0][t], t
+        assert (info.matched, info.match_idx, list(info.cand)) == ref[2][t], t
+        np.testing.assert_array_equal(P.ppd_get_logits(), ref[1][t])
+    P.close()
