@@ -118,7 +118,15 @@ typedef struct {
  * again at every step and must not change.  Every call is synchronous: the
  * context's stream is idle on return.  The KV cache, the candidates' KV
  * tails and all scratch are allocated here (device memory, freed by
- * ppd_destroy).  *out receives the context (HOST).  PPD_ELIMIT for a model
+ * ppd_destroy).  *out receives the context (HOST).
+ * Several contexts may be used from several threads (one thread per context
+ * at a time).  bf16 models: a round whose context is the only one at work on
+ * the GPU takes the main token through its layers in one launch that holds
+ * every compute unit until it is done; contexts whose rounds and prompt
+ * passes overlap go launch by launch (same results).  Work that the caller
+ * itself runs on the GPU at the same time waits for such a launch (up to a
+ * few milliseconds); PPD_FUSED=2 in the environment at ppd_create keeps a
+ * context to one launch per step.  PPD_ELIMIT for a model
  * one of whose matrices, as launched (Q|K|V together, gate|up together, the
  * LM head), reaches 4 GiB (rows padded to 16, columns to 32): the kernels
  * address a matrix with 32-bit byte offsets. */

@@ -90,15 +90,16 @@ struct ppd_ctx {
   int32_t *host_result;  // pinned: token, match index, the round's candidates, number of finished rounds
   int32_t rounds_seen;   // value of that counter after the last round the host waited for
   int32_t *host_result_dev; // the same memory as the GPU sees it
-  // captured rounds: 0 ppd round from layer 1, 1 ppd round after a match, 2 plain step, 3 ppd round after a
-  // match whose candidates were predicted by the round before
+  // captured rounds, with one launch per step of a layer and with the one-launch chain: 0 ppd round from layer 1,
+  // 1 ppd round after a match, 2 plain step, 3 ppd round after a match whose candidates were predicted by the round before
   int use_graphs;
-  hipGraphExec_t graph[4];
-  int graph_chunks[4];   // attention grid (64-position chunks) each graph was captured with
+  hipGraphExec_t graph[2][4];
+  int graph_chunks[2][4];   // attention grid (64-position chunks) each graph was captured with
   int gmax1, gmax2;      // workgroup budget of an fp32 GEMM launch: one group / per group of a two-group launch
   int nchunk_max;
   // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
   int fused, fused_grid, fused_lds, device;
+  int chain;             // the round under way uses it
   FusedArgs fused_args;
   FLayer* fl_tab;        // [n_layers] in device memory
   float *fl_ex, *fl_part, *h_save;   // outputs of the steps [n_layers], attention partials, the rows as the round found them
@@ -550,7 +551,7 @@ bool fused_plan(ppd_ctx* c) {
 
 // Row 0 (the main token) through layers from .. to - 1: in one launch, or one launch per step of a layer
 int run_main_row(ppd_ctx* c, int from, int to, int pmax) {
-  if (c->fused && c->prof < 2) {
+  if (c->chain) {
     FusedArgs a = c->fused_args;
     a.layer0 = from; a.nsteps = to - from;
     HIPCHK(c, launch_fused(c->cur, a, c->d.head_dim, c->fused_grid, c->fused_lds));
@@ -658,21 +659,24 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
   return PPD_OK;
 }
 
+// layers the main token goes through alone in a round, from the round's first one on
+int chain_from(const ppd_ctx* c, int kind) { return kind == 1 || kind == 3 ? c->nb : 0; }
+int chain_layers(const ppd_ctx* c, int kind) { return (kind == 2 ? c->d.n_layers : c->dbar) - chain_from(c, kind); }
+
 // The launches of one round.  kind 0: PPD round from layer 1 (after a miss or a prefill);
 // kind 1: PPD round after a match (layers 1..d-dbar were run by the matching candidate row);
 // kind 2: plain greedy step; kind 3: PPD round after a match whose candidates the previous round's final head
 // already predicted and embedded (speculative early prediction): parallel phase and final head only.  pmax bounds the positions touched (attention grid size only).
 int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   const int d = c->d.n_layers, dbar = c->dbar, nb = c->nb, k = c->k;
-  const int from = (kind == 1 || kind == 3) ? nb : 0;        // first layer the round takes the main token through
+  const int from = chain_from(c, kind);
   int rc;
   {
     BeginArgs b; memset(&b, 0, sizeof b);
     b.ds = c->ds; b.take_next = kind == 3 ? 1 : 0; b.host_cand = c->host_result_dev + 2;
-    const int chain = (kind == 2 ? d : dbar) - from;     // layers the main token goes through alone
     int grid = 1;
-    if ((c->fused && chain > 0) || restore) {
-      if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
+    if (c->chain || restore) {
+      if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain_layers(c, kind) * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
       b.h = c->h; b.save = c->h_save; b.nsave = (1 + k) * c->d.d_model; b.restore = restore ? 1 : 0;
       grid = 512;
     }
@@ -712,8 +716,8 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
 // the captured rounds are captured anew
 hipError_t drop_graphs(ppd_ctx* c) {
   hipError_t e = hipSuccess;
-  for (hipGraphExec_t& g : c->graph)
-    if (g) {
+  for (auto& set : c->graph)
+    for (hipGraphExec_t& g : set) if (g) {
       const hipError_t e1 = hipGraphExecDestroy(g);
       if (e == hipSuccess) e = e1;
       g = nullptr;
@@ -721,13 +725,33 @@ hipError_t drop_graphs(ppd_ctx* c) {
   return e;
 }
 
+// Rounds and prompt passes in flight on each GPU, those of all contexts.  A one-launch chain of layers needs every compute unit
+// for itself while it runs, so a round takes it only if nothing else is in flight: contexts that decode at the same time
+// (threads of a server) overlap launch by launch, each filling the other's gaps, which is faster than taking turns with chains
+// (two contexts, per token of both: OPT-125m shape 0.287 ms against 0.360, 7B shape 2.33 against 2.52).  They meet anew
+// every round, with some host work in between: a meeting counts for ALONE_AFTER.
+constexpr int MAX_DEVICES = 64;
+constexpr std::chrono::milliseconds ALONE_AFTER(50);
+struct DeviceWork { std::mutex mu; int in_flight = 0; std::chrono::steady_clock::time_point met; };
+DeviceWork g_work[MAX_DEVICES];
+struct WorkScope {
+  DeviceWork* w; bool alone = false;
+  explicit WorkScope(const ppd_ctx* c) : w(c->device < MAX_DEVICES ? &g_work[c->device] : nullptr) {
+    if (!w) return;
+    const auto now = std::chrono::steady_clock::now();
+    std::lock_guard<std::mutex> lock(w->mu);
+    if (w->in_flight++) w->met = now;
+    else alone = now - w->met > ALONE_AFTER;
+  }
+  ~WorkScope() {
+    if (!w) return;
+    std::lock_guard<std::mutex> lock(w->mu);
+    --w->in_flight;
+  }
+};
+
 // Run one round: set the device state, replay (or capture, or issue eagerly) the launches,
 // wait, read token and match index from pinned memory.
-// A one-launch chain needs every compute unit for itself while it runs: rounds of several contexts on one GPU that use it
-// take turns (a round's chain is over when its result is there).
-constexpr int MAX_DEVICES = 64;
-std::mutex g_round_mu[MAX_DEVICES];
-
 int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   int rc;
   // (work the caller queued on its stream before ppd_prefill -- the weights -- was waited for there; a round
@@ -742,23 +766,25 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
     int nchunks = 4;
     while (nchunks < pmax / ATT_CHUNK + 1) nchunks *= 2;
     if (nchunks > c->nchunk_max) nchunks = c->nchunk_max;
-    if (c->graph[kind] && c->graph_chunks[kind] < nchunks) {
-      HIPCHK(c, hipGraphExecDestroy(c->graph[kind]));
-      c->graph[kind] = nullptr;
+    hipGraphExec_t& graph = c->graph[c->chain][kind];
+    int& graph_chunks = c->graph_chunks[c->chain][kind];
+    if (graph && graph_chunks < nchunks) {
+      HIPCHK(c, hipGraphExecDestroy(graph));
+      graph = nullptr;
     }
-    if (!c->graph[kind]) {
+    if (!graph) {
       hipGraph_t g = nullptr;
       HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
       rc = issue_round(c, kind, nchunks * ATT_CHUNK - 1);
       hipError_t e = hipStreamEndCapture(c->stream, &g);
       if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
       HIPCHK(c, e);
-      e = hipGraphInstantiate(&c->graph[kind], g, nullptr, nullptr, 0);
+      e = hipGraphInstantiate(&graph, g, nullptr, nullptr, 0);
       (void)hipGraphDestroy(g);
       HIPCHK(c, e);
-      c->graph_chunks[kind] = nchunks;
+      graph_chunks = nchunks;
     }
-    HIPCHK(c, hipGraphLaunch(c->graph[kind], c->stream));
+    HIPCHK(c, hipGraphLaunch(graph, c->stream));
   } else {
     if ((rc = issue_round(c, kind, pmax, again))) return rc;
   }
@@ -791,14 +817,15 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
 }
 
 int run_round(ppd_ctx* c, int kind, int pos) {
-  if (!c->fused) return run_round_once(c, kind, pos, false);
-  std::lock_guard<std::mutex> turn(g_round_mu[c->device]);
+  const WorkScope work(c);
+  c->chain = c->fused && work.alone && c->prof < 2 && chain_layers(c, kind) > 0;
   int rc = run_round_once(c, kind, pos, false);
-  if (!rc && c->prof < 2 && (kind == 2 || c->dbar > (kind == 0 ? 0 : c->nb))) c->chain_rounds += 1;
-  if (rc || c->host_result[0] >= 0) return rc;
+  if (rc || !c->chain) return rc;
+  c->chain_rounds += 1;
+  if (c->host_result[0] >= 0) return rc;
   // A workgroup gave up waiting for the others (something else held compute units): nothing was taken over.  This
   // context goes back to one launch per step for good, beginning with this round.
-  c->fused = 0;
+  c->fused = c->chain = 0;
   c->chain_again += 1;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   HIPCHK(c, drop_graphs(c));
@@ -1165,7 +1192,9 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
   HIPCHK(c, hipStreamWaitEvent(c->stream, c->join_ev, 0));
   HIPCHK(c, hipMemcpyAsync(c->prompt_dev, prompt, (size_t)n_prompt * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));   // prompt is pageable host memory of the caller
+  const WorkScope work(c);
   int prof = c->prof; c->prof = 0;
+  c->chain = 0;
   // positions 0 .. n_prompt-2 in chunks of consecutive positions: every row's arithmetic is that of a
   // token-by-token pass (PPD_PREFILL_CHUNK=1 runs exactly that), the weights are streamed once per chunk
   const int chunk = c->prefill_chunk;

@@ -1,6 +1,9 @@
 """The main token's layers in one launch against one launch per step of a layer: the same bits, over layer shapes whose
 tiles, blocks and attention items do not divide evenly among the workgroups and waves; and a launch that has to give up
 waiting (a spin limit of one tick, set from the host) is run again one launch per step."""
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -86,3 +89,39 @@ def test_a_round_behind_a_match_is_run_again(family, monkeypatch):
         assert (info.matched, info.match_idx, list(info.cand)) == ref[2][t], t
         np.testing.assert_array_equal(P.ppd_get_logits(), ref[1][t])
     P.close()
+
+
+def test_contexts_at_work_together_go_launch_by_launch():
+    """Two contexts that one thread uses in turn take the one-launch chain every round; from two threads they meet, and go
+    launch by launch then.  The tokens and logits stay the same."""
+    cfg = small_cfg("llama", max_ctx=260, n_prompt=40, n_gen=200)
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    P = [binding.PPD(cfg, dev) for _ in range(2)]
+    time.sleep(0.1)                                   # (a meeting with an earlier test's contexts is over)
+    ref = gpu_generate(P[0], prompt, cfg.n_gen, "plain")
+    assert P[0].ppd_get_chain_rounds() == (cfg.n_gen, 0)
+    for p in P:
+        p.ppd_prefill(prompt)
+    for t in range(20):
+        for p in P:
+            assert p.plain_greedy_step() == ref[0][t]
+    assert [p.ppd_get_chain_rounds() for p in P] == [(cfg.n_gen + 20, 0), (20, 0)]
+    got, gate = [None, None], threading.Barrier(2)
+
+    def work(i):
+        gate.wait()
+        got[i] = gpu_generate(P[i], prompt, cfg.n_gen, "plain")
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for g in got:
+        np.testing.assert_array_equal(g[0], ref[0])
+        np.testing.assert_array_equal(g[1], ref[1])
+    rounds = [p.ppd_get_chain_rounds() for p in P]
+    assert rounds[0][0] + rounds[1][0] < 3 * cfg.n_gen + 40 and rounds[0][1] + rounds[1][1] == 0
+    for p in P:
+        p.close()
