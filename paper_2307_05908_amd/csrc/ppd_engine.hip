@@ -100,6 +100,7 @@ struct ppd_ctx {
   // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
   int fused, fused_grid, fused_lds, device;
   int chain;             // the round under way uses it
+  int chain_pause;       // rounds that go without it after a launch gave up
   FusedArgs fused_args;
   FLayer* fl_tab;        // [n_layers] in device memory
   float *fl_ex, *fl_part, *h_save;   // outputs of the steps [n_layers], attention partials, the rows as the round found them
@@ -659,6 +660,9 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
   return PPD_OK;
 }
 
+// floats of the chain's attention partials (rounded up to whole 16-byte pieces)
+size_t fl_part_floats(const ppd_ctx* c) { return ((size_t)c->d.n_heads * c->nchunk_max * (c->d.head_dim + 2) + 3) & ~(size_t)3; }
+
 // layers the main token goes through alone in a round, from the round's first one on
 int chain_from(const ppd_ctx* c, int kind) { return kind == 1 || kind == 3 ? c->nb : 0; }
 int chain_layers(const ppd_ctx* c, int kind) { return (kind == 2 ? c->d.n_layers : c->dbar) - chain_from(c, kind); }
@@ -677,6 +681,8 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
     int grid = 1;
     if (c->chain || restore) {
       if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain_layers(c, kind) * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
+      // (what the launch that gave up left of the attention partials goes, too: see FusedArgs::part)
+      else { b.ex = (u32x4*)c->fl_part; b.n16 = fl_part_floats(c) / 4; b.empty = FU_EMPTY; }
       b.h = c->h; b.save = c->h_save; b.nsave = (1 + k) * c->d.d_model; b.restore = restore ? 1 : 0;
       grid = 512;
     }
@@ -816,19 +822,23 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   return PPD_OK;
 }
 
+// A launch that gave up has cost its limit, some hundred rounds' time: the context goes without the chain for as many rounds
+// (twice as many each time it happens again, up to 2^8 times), then tries it once more.
+constexpr int CHAIN_PAUSE = 64;
+
 int run_round(ppd_ctx* c, int kind, int pos) {
   const WorkScope work(c);
-  c->chain = c->fused && work.alone && c->prof < 2 && chain_layers(c, kind) > 0;
+  c->chain = c->fused && work.alone && c->prof < 2 && c->chain_pause == 0 && chain_layers(c, kind) > 0;
+  if (c->chain_pause > 0) --c->chain_pause;
   int rc = run_round_once(c, kind, pos, false);
   if (rc || !c->chain) return rc;
   c->chain_rounds += 1;
   if (c->host_result[0] >= 0) return rc;
-  // A workgroup gave up waiting for the others (something else held compute units): nothing was taken over.  This
-  // context goes back to one launch per step for good, beginning with this round.
-  c->fused = c->chain = 0;
+  // A workgroup gave up waiting for the others (something else held compute units): nothing was taken over.  The round is
+  // run again, one launch per step.
+  c->chain = 0;
+  c->chain_pause = CHAIN_PAUSE << (c->chain_again < 8 ? c->chain_again : 8);
   c->chain_again += 1;
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, drop_graphs(c));
   return run_round_once(c, kind, pos, true);
 }
 
@@ -1147,7 +1157,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
       if (d.has_bias) { t.B[0][0] = x.bq; t.B[0][1] = x.bk; t.B[0][2] = x.bv; t.B[1][0] = x.bo; t.B[2][0] = x.b_in; t.B[3][0] = x.b_out; }
       t.Kc = (float*)(c->Kc + (size_t)l * cache_layer_bytes(c)); t.Vc = (float*)(c->Vc + (size_t)l * cache_layer_bytes(c));
     }
-    const size_t nex = (size_t)d.n_layers * fu_ex_row((int)dm, d.d_ff), npart = (size_t)d.n_heads * c->nchunk_max * (d.head_dim + 2);
+    const size_t nex = (size_t)d.n_layers * fu_ex_row((int)dm, d.d_ff), npart = fl_part_floats(c);
     alloc((void**)&c->fl_tab, d.n_layers * sizeof(FLayer));
     alloc((void**)&c->fl_ex, nex * sizeof(float));
     alloc((void**)&c->fl_part, npart * sizeof(float));

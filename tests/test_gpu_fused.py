@@ -125,3 +125,26 @@ def test_contexts_at_work_together_go_launch_by_launch():
     assert rounds[0][0] + rounds[1][0] < 3 * cfg.n_gen + 40 and rounds[0][1] + rounds[1][1] == 0
     for p in P:
         p.close()
+
+
+def test_the_chain_comes_back_after_a_launch_gave_up(monkeypatch):
+    """64 rounds go without the chain then, 128 after the second time; its attention partials (several per head here) are
+    in order again."""
+    cfg = small_cfg("llama", max_ctx=560, n_prompt=300, n_gen=230)
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    ref = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")[0]
+    P = binding.PPD(cfg, dev)
+    P.ppd_prefill(prompt)
+    count = []
+    for t in range(cfg.n_gen):
+        if t in (5, 80):
+            P.ppd_set_chain_wait(1)
+        assert P.plain_greedy_step() == ref[0][t], t
+        np.testing.assert_array_equal(P.ppd_get_logits(), ref[1][t])
+        if t in (5, 80):
+            P.ppd_set_chain_wait(0)
+        count.append(P.ppd_get_chain_rounds())
+    P.close()
+    assert count[5] == (6, 1) and count[69] == (6, 1) and count[70] == (7, 1)
+    assert count[80] == (17, 2) and count[208] == (17, 2) and count[229] == (38, 2)
