@@ -822,13 +822,26 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   return PPD_OK;
 }
 
+// Whether the chain is the faster way at this position.  It saves the launches' ramps, 5 - 17 us a layer, but its workgroups go
+// through the items of the attention (a head's pair of chunks) one after the other and one workgroup merges all chunks of a
+// head, where the launches spread both.  Measured, a plain token with chain and with launches (MI355X, us saved per layer at
+// positions 1000 / 4000 / 8000 / 12000): 4 heads 7 / 7 / 0 / -6, 8 heads 9 / 9 / 4 / -1, 12 heads of 64 11 / 10 / 6 / 1, 32 heads
+// 14 / 12 / 7 / 5 (16384: -7); 36 heads 6 / 2 / -3 / -6, 40 heads 7 / 5 / -3 / -4, 48 heads 9 / 2 / -5, 64 heads 10 / 8 / 4; 40 heads of 64
+// 17 / 15 / 7 / 5.  So: up to 192 chunks, with few heads fewer; and where more than 32 heads of 128 do not divide among the
+// workgroups, up to 6 items for each of them.
+bool chain_pays(const ppd_ctx* c, int pos) {
+  const int H = c->d.n_heads, G = c->fused_grid, chunks = pos / ATT_CHUNK + 1;
+  if (chunks > 192 || chunks > 24 * H) return false;
+  return c->d.head_dim == 64 || H <= 32 || G % H == 0 || H * ((chunks + 1) / 2) <= 6 * G;
+}
+
 // A launch that gave up has cost its limit, some hundred rounds' time: the context goes without the chain for as many rounds
 // (twice as many each time it happens again, up to 2^8 times), then tries it once more.
 constexpr int CHAIN_PAUSE = 64;
 
 int run_round(ppd_ctx* c, int kind, int pos) {
   const WorkScope work(c);
-  c->chain = c->fused && work.alone && c->prof < 2 && c->chain_pause == 0 && chain_layers(c, kind) > 0;
+  c->chain = c->fused && work.alone && c->prof < 2 && c->chain_pause == 0 && chain_layers(c, kind) > 0 && chain_pays(c, pos);
   if (c->chain_pause > 0) --c->chain_pause;
   int rc = run_round_once(c, kind, pos, false);
   if (rc || !c->chain) return rc;

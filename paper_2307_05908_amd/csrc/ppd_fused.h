@@ -13,8 +13,9 @@
 // before it waits for anything: 256 workgroups hold 48 MiB that way, about seven microseconds of the stream.
 // Meanwhile the helpers add up the step's outputs, publish them, and bring the next step's row into LDS; they have no
 // weight requests in flight, so nothing of this queues behind the ring (a wave's loads return in order).
-// Measured (MI355X, context 512, one token): 7B shape 3.09 -> 2.60 ms, OPT-125m shape 0.55 -> 0.47 ms.  At 4096 positions
-// (13B shape) the two are even: the attention's items pay for their barriers.
+// Measured (MI355X, context 512, one token): 7B shape 3.09 -> 2.60 ms, OPT-125m shape 0.55 -> 0.47 ms.  Every 1000 positions
+// take about 1 us a layer from that: the attention's items pay for their barriers, and the launches are the faster way
+// from some 4000 - 12000 positions on (the rule and its figures: chain_pays, ppd_engine.hip).
 //
 // Exchange between workgroups.  Every step of every layer has an output buffer of its own, filled with FU_EMPTY before the
 // round.  FU_EMPTY is a signalling NaN, which no arithmetic returns, so a value says by itself that it is there: the

@@ -148,3 +148,18 @@ def test_the_chain_comes_back_after_a_launch_gave_up(monkeypatch):
     P.close()
     assert count[5] == (6, 1) and count[69] == (6, 1) and count[70] == (7, 1)
     assert count[80] == (17, 2) and count[208] == (17, 2) and count[229] == (38, 2)
+
+
+@pytest.mark.parametrize("heads,head_dim,limit", [(2, 128, 48 * 64), (3, 64, 72 * 64)])
+def test_long_sequences_leave_the_chain(heads, head_dim, limit, monkeypatch):
+    """Past 24 chunks of positions per head the rounds go launch by launch: the same tokens and logits across the line."""
+    cfg = small_cfg("llama", n_layers=2, exit_layer=1, n_heads=heads, head_dim=head_dim, d_model=heads * head_dim, max_ctx=limit + 64, n_prompt=limit - 3, n_gen=8)
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    ref = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")[0]
+    P = binding.PPD(cfg, dev)
+    got = gpu_generate(P, prompt, cfg.n_gen, "plain")
+    np.testing.assert_array_equal(got[0], ref[0])
+    np.testing.assert_array_equal(got[1], ref[1])
+    assert P.ppd_get_chain_rounds() == (4, 0)        # positions limit - 4 .. limit - 1
+    P.close()
