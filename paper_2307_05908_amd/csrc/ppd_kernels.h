@@ -1258,10 +1258,12 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs
 }
 
 // The draw.  What bounds it is one workgroup's latency: a search first finds the two thresholds its key lies between, collects
-// the tokens between them in LDS (in a fixed order) and fixes the key's bits on those alone; only if they are more than
-// SAMP_CAP does it look through all tokens for every bit.  Measured (top-p 0.95), both kernels: 50272 tokens 358 -> 65 + 17 us
-// (bit by bit over all tokens, keys and weights re-read from L2), 32000 tokens 112 -> 51 + 19 us (the same with keys and
-// weights on chip).
+// the tokens between them in LDS (in a fixed order) and fixes the key's bits on those alone; while they are more than
+// SAMP_CAP (a flat softmax, the tail below the last threshold) it looks through all tokens for a bit, until they are fewer.
+// Measured (top-p 0.95), both kernels: 50272 tokens 358 -> 65 + 17 us (bit by bit over all tokens, keys and weights re-read
+// from L2), 32000 tokens 112 -> 51 + 19 us (the same with keys and weights on chip).
+// In the far tail (p = 0.999, logits of standard deviation 4), 50272 / 32000 / 16000 tokens: every bit over all tokens 306 / 191 /
+// 113 us, until few are left 151 / 106 / 76.
 __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   constexpr int NW = SAMP_THREADS / WAVE;
   __shared__ double s_m[2][NW];
@@ -1331,19 +1333,50 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
     auto meets = [&](double g, int c) { return kind == 0 ? g >= T : (kind == 1 ? g > T : c >= K); };
     int j = 0;
     while (j < SAMP_NT && !meets(s_gm[j], s_gc[j])) ++j;         // (the same for every thread)
-    const uint32_t lo = j < SAMP_NT ? samp_threshold(mx, j) : 1u, top = j > 0 ? samp_threshold(mx, j - 1) - 1u : 0xffffffffu;
-    const double A = j > 0 ? s_gm[j - 1] : 0.0;
-    const int cA = j > 0 ? s_gc[j - 1] : 0, cnt = s_gc[j] - cA;
-    const bool list = cnt <= SAMP_CAP;
+    uint32_t lo = j < SAMP_NT ? samp_threshold(mx, j) : 1u;
+    const uint32_t top = j > 0 ? samp_threshold(mx, j - 1) - 1u : samp_key(mx);
+    int c_at = s_gc[j], c_hi = j > 0 ? s_gc[j - 1] : 0;          // tokens at or above the prefix, above the range in question
+    double g_hi = j > 0 ? s_gm[j - 1] : 0.0;                     // mass above that range
+    if (c_at - c_hi > SAMP_CAP && j == SAMP_NT) {                // nothing bounds these from below yet
+      uint32_t least = 0xffffffffu;
+      for (int i = tid; i < n; i += SAMP_THREADS) least = min(least, a.keys[i]);
+#pragma unroll
+      for (int o = WAVE / 2; o >= 1; o >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, o));
+      if (tid == 0) s_prefix = 0xffffffffu;
+      __syncthreads();
+      if (lane == 0) atomicMin(&s_prefix, least);
+      __syncthreads();
+      lo = s_prefix;
+    }
+    // bit by bit from the highest one in which lo and top differ; once a single token is left its key is kappa
+    int bit = 31;
+    while (bit >= 0 && !((lo ^ top) >> bit)) --bit;
+    uint32_t pre = bit >= 31 ? 0u : lo >> (bit + 1) << (bit + 1);
+    auto fix_bit = [&](auto&& G) {
+      const uint32_t t = pre | (1u << bit--);
+      if (t <= lo) { pre = t; return; }
+      if (t > top) return;
+      double g; int c;
+      G(t, g, c);
+      // (no token between the prefix and t: the bound holds at the prefix, and so here, whatever the sums' last bits say)
+      if (meets(g, c) || c == c_at) { pre = t; c_at = c; }
+      else { c_hi = c; g_hi = g; }
+    };
+    // over all tokens until few enough are left, then on those, collected in LDS
+    while (bit >= 0 && c_at - c_hi > SAMP_CAP) fix_bit(G_all);
+    const bool list = c_at - c_hi <= SAMP_CAP;
+    const double A = g_hi;
+    const int cA = c_hi;
     if (list) {
-      // the tokens with lo <= key <= top, thread by thread
+      // the tokens in question, first <= key <= last, thread by thread
+      const uint32_t first = pre > lo ? pre : lo, rest = pre | (bit < 0 ? 0u : (2u << bit) - 1u), last = rest < top ? rest : top;
       int mine = 0;
       for (int i0 = tid; i0 < a.npad; i0 += SAMP_THREADS * SAMP_MEMU) {
         uint32_t k[SAMP_MEMU];
 #pragma unroll
         for (int q = 0; q < SAMP_MEMU; ++q) k[q] = a.keys[i0 + q * SAMP_THREADS];
 #pragma unroll
-        for (int q = 0; q < SAMP_MEMU; ++q) mine += k[q] >= lo && k[q] <= top ? 1 : 0;
+        for (int q = 0; q < SAMP_MEMU; ++q) mine += k[q] >= first && k[q] <= last ? 1 : 0;
       }
       int incl = mine;
 #pragma unroll
@@ -1359,7 +1392,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       if (mine)
         for (int i = tid; i < a.npad; i += SAMP_THREADS) {
           const uint32_t k = a.keys[i];
-          if (k >= lo && k <= top && at < SAMP_CAP) { s_key[at] = k; s_w[at] = a.w[i]; ++at; }
+          if (k >= first && k <= last && at < SAMP_CAP) { s_key[at] = k; s_w[at] = a.w[i]; ++at; }
         }
       __syncthreads();
     }
@@ -1367,22 +1400,8 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       if (list) { G_list(kth, mass, count); mass += A; count += cA; }
       else G_all(kth, mass, count);
     };
-    // bit by bit from the highest one in which lo and top differ; once a single token is left (count at the prefix minus
-    // count above the bucket) its key is kappa
-    int bit = 31;
-    while (bit >= 0 && !((lo ^ top) >> bit)) --bit;
-    uint32_t pre = bit >= 31 ? 0u : lo >> (bit + 1) << (bit + 1);
-    int c_at = s_gc[j], c_hi = cA;
-    double g_hi = A;
-    bool single = c_at - c_hi == 1;
-    for (; bit >= 0 && !single; --bit) {
-      const uint32_t t = pre | (1u << bit);
-      double g; int c;
-      G(t, g, c);
-      if (meets(g, c)) { pre = t; c_at = c; }
-      else { c_hi = c; g_hi = g; }
-      single = c_at - c_hi == 1;
-    }
+    while (bit >= 0 && c_at - c_hi != 1) fix_bit(G);
+    const bool single = c_at - c_hi == 1;
     // kappa: the smallest key at or above the prefix (the prefix itself, unless bits are left open)
     __syncthreads();
     if (tid == 0) s_prefix = 0xffffffffu;
@@ -1414,7 +1433,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       W = above;
       for (int r = nabove; r < ks; ++r) W += wk;
     }
-  } else {
+  } else if (a.p < 1.0) {       // (all are kept otherwise)
     const double T = a.p * S;
     search(0, T, 0, kappa, above, nabove, ties);
     const double wk = exp((double)samp_unkey(kappa) - zmax);

@@ -37,3 +37,10 @@ def test_draw_is_the_oracles(vocab, factor, mode, ks, p):
         u = oracle.uniform(SEED, len(prompt) + t)
         assert tok == oracle.sample(z, mode, ks, p, u), (t, u)
     P.close()
+
+
+@pytest.mark.parametrize("vocab,factor", [(6145, 0.0), (50272, 0.0), (9000, 0.02), (16000, 20.0), (32000, 1.0), (128256, 0.3), (128256, 14.0), (128256, 40.0)])
+@pytest.mark.parametrize("mode,ks,p", [(oracle.TOP_P, 0, 1.0), (oracle.TOP_P, 0, 0.999), (oracle.TOP_P, 0, 0.3), (oracle.TOP_K, 7000, 1.0)])
+def test_draw_among_more_tokens_than_are_collected(vocab, factor, mode, ks, p):
+    """Equal logits, flat softmaxes and long tails: the range in question holds more tokens than LDS does."""
+    test_draw_is_the_oracles(vocab, factor, mode, min(ks, vocab - 1), p)
