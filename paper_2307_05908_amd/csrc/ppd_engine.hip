@@ -69,6 +69,7 @@ struct ppd_ctx {
   int spec;
   int last_kind;         // kind of the last round (which buffer holds its early logits)
   int prefill_chunk;     // prompt positions per chunk
+  int few_rows;          // chunks of up to so many rows of a bf16 model go through the decode step's launches
   // compute-bound prompt pass (bf16 models, prompts of at least PREFILL_TILED_MIN rows): all rows at once through
   // tiled MFMA GEMMs and causal attention over two-term operand blocks; its buffers are made at the first such prompt
   int prefill_tiled;
@@ -208,9 +209,8 @@ hipError_t launch_gemm(ppd_ctx* c, GemmArgs& a, int ngroups, bool paired) {
   return hipErrorInvalidValue;   // bf16 weights never come here: they take the MFMA kernel
 }
 
-// rows of a prompt chunk (ppd_prefill feeds the prompt through the decode kernels this many positions at a time:
-// one pass over the weights per chunk instead of per token): two MFMA tiles' columns for bf16 models (rgemm_kernel),
-// the 8 rows of the fp32 GEMM otherwise
+// rows of a prompt chunk (ppd_prefill takes this many positions at a time through a layer: one pass over the weights per
+// chunk instead of per token): two MFMA tiles' columns for bf16 models (rgemm_kernel), the 8 rows of the fp32 GEMM otherwise
 constexpr int PREFILL_CHUNK = 32;
 constexpr int PREFILL_CHUNK_FP32 = 8;
 
@@ -457,7 +457,26 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
   return PPD_OK;
 }
 
-// One transformer layer for the M <= PREFILL_CHUNK rows of a prompt chunk of a bf16 model (M > 1), the first of them at the
+// Rows of a prompt chunk of a bf16 model up to which the decode step's own launches (run_layer) are the faster way: they stage
+// and normalise the rows in every workgroup, which takes longer with every row, where run_chunk_layer has packing launches and
+// reads two tiles of rows from L2 whatever their number.  Measured (whole prompt, run_chunk_layer / run_layer, ms): 4096
+// columns 2 rows 3.51 / 3.07, 4 rows 3.35 / 3.28, 6 rows 3.38 / 3.47; 5120 columns 6.46 / 5.37, 6.51 / 5.74, 5 rows 6.53 / 5.90;
+// 2048 columns 0.97 / 0.88, 0.97 / 0.96; 1024 columns 2 rows 0.68 / 0.73.  Rows that do not fit LDS whole would read the
+// weights twice.
+constexpr int FEW_ROWS_MAX = 5;
+int few_rows(const ppd_model_dims& d) {
+  const int dm = d.d_model;
+  if (dm < 2048) return 1;
+  const int nt = d.act == 2 ? (d.d_ff + 7) / 8 : (d.d_ff + 15) / 16, tiles = ((nt > 3 * dm / 16 ? nt : 3 * dm / 16) + 255) / 256;
+  int m = dm > 4096 ? FEW_ROWS_MAX : 4;
+  for (; m > 1; --m) {
+    int b, p, x;
+    if ((size_t)mg_lds_layout(dm, m, d.norm, tiles, mg_xrow((dm + 31) / 32), b, p, x) <= MG_LDS_MAX) break;
+  }
+  return m;
+}
+
+// One transformer layer for the M <= PREFILL_CHUNK rows of a prompt chunk of a bf16 model (M > few_rows), the first of them at the
 // device state's position.  Row for row the arithmetic of run_layer.
 int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
   const ppd_model_dims& d = c->d;
@@ -1025,6 +1044,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     const int cap = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
     c->prefill_chunk = env_int("PPD_PREFILL_CHUNK", cap);
     if (c->prefill_chunk > cap) c->prefill_chunk = cap;
+    c->few_rows = few_rows(d);
     // the compute-bound pass takes prompts of bf16 models unless the row-chunk path is asked for (PPD_PREFILL_CHUNK
     // set, or PPD_PREFILL_TILED=2)
     c->prefill_tiled = d.wdtype == 1 && !getenv("PPD_PREFILL_CHUNK") && env_int("PPD_PREFILL_TILED", 1) != 2;
@@ -1238,7 +1258,7 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
       RowGroup g{l, m, 0, 0, false};
       g.chunk = m > 1;
       // (the last layer's rows are read by no one: its keys and values are all that a prompt leaves there)
-      rc = c->mfma && g.chunk ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
+      rc = c->mfma && m > c->few_rows ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
     }
   }
   c->prof = prof;

@@ -23,6 +23,27 @@ CASES = {
 }
 
 
+# where a few rows go through the decode step's launches: up to 4, 5 and (the rows have to fit LDS whole) 3 of them
+WIDE = {"4_rows": (2048, 16), "5_rows": (4224, 33), "3_rows": (8192, 64)}
+
+
+@pytest.mark.parametrize("name", list(WIDE))
+def test_few_prompt_rows_are_the_token_by_token_pass_bit_exact(name, monkeypatch):
+    d_model, heads = WIDE[name]
+    cfg = small_cfg("llama", d_model=d_model, n_heads=heads, head_dim=128, d_ff=1096, n_layers=2, exit_layer=1, max_ctx=80, n_gen=3)
+    dev = binding.upload_model(pi.make_model(cfg))
+    runs = []
+    for env in (("PPD_PREFILL_TILED", "2"), ("PPD_PREFILL_CHUNK", "1")):
+        monkeypatch.setenv(*env)
+        P = binding.PPD(cfg, dev, k=1)
+        runs.append([gpu_generate(P, pi.make_prompt(cfg, n), cfg.n_gen, "plain")[:2] for n in (3, 4, 5, 6, 7, 36, 37, 69)])
+        P.close()
+        monkeypatch.delenv(env[0])
+    for (tok, z), (rtok, rz) in zip(*runs):
+        np.testing.assert_array_equal(tok, rtok)
+        np.testing.assert_array_equal(np.asarray(z).view(np.uint32), np.asarray(rz).view(np.uint32))
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_prompt_rows_are_the_token_by_token_pass_bit_exact(name, monkeypatch):
     cfg = CASES[name]
