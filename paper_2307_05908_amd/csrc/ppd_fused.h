@@ -94,9 +94,15 @@ extern __shared__ float4 fu_lds4[];
 __device__ __forceinline__ int fu_here(int v) { asm volatile("" : "+v"(v)); return v; }
 __device__ __forceinline__ void fu_bar() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ void fu_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// dma16 at agent scope: not from this XCD's L2
+// dma16 where the compiler cannot see that all lanes have the same destination
+__device__ __forceinline__ unsigned fu_lds_addr(const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p); }
+__device__ __forceinline__ void fu_dma16(const void* src, void* lds_dst) {
+  const unsigned la = fu_lds_addr(lds_dst);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(la) : "memory", "m0");
+}
+// ... at agent scope: not from this XCD's L2
 __device__ __forceinline__ void dma16_agent(const void* src, void* lds_dst) {
-  const unsigned la = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds_dst);
+  const unsigned la = fu_lds_addr(lds_dst);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc1" ::"v"(src), "s"(la) : "memory", "m0");
 }
 template <typename T> __device__ __forceinline__ T ld_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -198,8 +204,8 @@ __device__ __forceinline__ void fu_gain(const FWg& w, const FHelper& hp, int i, 
   for (int u = hp.wave; u * 512 < K; u += FU_HELPERS) {
     const int kk = u * 512 + w.lane * 8;
     if (kk < K) {
-      dma16(ng + kk, dst + u * 1024);
-      if (norm == 0) dma16(nb + kk, dst + fu_gain_bytes(w.a->d_model) + u * 1024);
+      fu_dma16(ng + kk, dst + u * 1024);
+      if (norm == 0) fu_dma16(nb + kk, dst + fu_gain_bytes(w.a->d_model) + u * 1024);
     }
   }
 }
@@ -340,7 +346,7 @@ __device__ __forceinline__ void fu_help_attention(const FWg& w, FHelper& hp, int
   for (int it = w.it0; it < w.it1; ++it) {
     if (it == w.it0 || it % ncp == 0) {  // another head: its query, key and value
       const int hh = it / ncp;
-      if (it == w.it0 && hp.wave == FU_HELPERS - 1 && rope && lane * 4 < HD) dma16((const float*)(rope + (size_t)w.pos * (HD / 2)) + lane * 4, s.rope);
+      if (it == w.it0 && hp.wave == FU_HELPERS - 1 && rope && lane * 4 < HD) fu_dma16((const float*)(rope + (size_t)w.pos * (HD / 2)) + lane * 4, s.rope);
       const int q0 = hp.wave;
       fu_stage(w, hp, q0 < (3 * HD + 255) / 256 ? 1 : 0, [&](int, const float*& src, char*& dst) {
         const int f = q0 * 256 + lane * 4, sec = f / HD, i = f - sec * HD;
