@@ -656,10 +656,11 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
   s.pk_stride = (int)c->pk_slots;
   s.k = adopt || early ? c->k : 0; s.mode = early ? 0 : 1; s.ds = c->ds; s.host_result = c->host_result_dev;
   s.vocab = d.vocab;
+  const int T = select_threads(s.nblk * s.kk);
   dim3 grid(1, 1);
   if (early) {
     s.emb = embed_args(c, nullptr, c->k, 1, 1);
-    grid = dim3((d.d_model + SEL_THREADS - 1) / SEL_THREADS, c->k);
+    grid = dim3((d.d_model + T - 1) / T, c->k);
   } else if (adopt) {
     s.h = c->h; s.tailK = (const float*)c->tailK; s.tailV = (const float*)c->tailV; s.Kc = (float*)c->Kc; s.Vc = (float*)c->Vc;
     s.head_floats = cache_head_floats(c);
@@ -669,12 +670,14 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
       s.emb = embed_args(c, nullptr, c->k, 1, 2);
     }
     // tail blocks, then (spec) blocks that copy the logits row / embed the next candidates, a column per thread
-    const int extra = spec ? (d.d_model + SEL_THREADS - 1) / SEL_THREADS : 0;
+    const int extra = spec ? (d.d_model + T - 1) / T : 0;
     grid = dim3(c->nb + (extra > 16 ? 16 : extra), 2);
   }
   ProfScope ps(c, PPD_KC_SELECT);
-  if (c->wbytes == 4) hipLaunchKernelGGL(select_kernel<float>, grid, dim3(SEL_THREADS), 0, c->cur, s);
-  else hipLaunchKernelGGL(select_kernel<bf16_t>, grid, dim3(SEL_THREADS), 0, c->cur, s);
+  if (c->wbytes == 4 && T == 256) hipLaunchKernelGGL((select_kernel<float, 256>), grid, dim3(T), 0, c->cur, s);
+  else if (c->wbytes == 4) hipLaunchKernelGGL((select_kernel<float, 512>), grid, dim3(T), 0, c->cur, s);
+  else if (T == 256) hipLaunchKernelGGL((select_kernel<bf16_t, 256>), grid, dim3(T), 0, c->cur, s);
+  else hipLaunchKernelGGL((select_kernel<bf16_t, 512>), grid, dim3(T), 0, c->cur, s);
   HIPCHK(c, hipGetLastError());
   return PPD_OK;
 }

@@ -1496,13 +1496,18 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
 }
 #endif
 
-// (a thread reads its share of the lists one entry after the other: 512 threads rather than 256 took the merge of 500 lists of 3
-// from 8.6 to 7.7 us and a selection over 242 lists, 12 heads of 64, from 9.9 to 6.9 us; few lists take the same time)
-constexpr int SEL_THREADS = 512;
+// Threads of a merge of the heads' lists.  A thread reads its share of the entries one after the other, which 512 threads shorten;
+// every wave more is one more to compare in each of the k steps that follow, which 256 shorten.  Measured, 256 / 512 threads:
+// merge of 63 lists of 3 and the head before it 14.2 / 15.7 us, 250 lists of 8 26.7 / 27.9, 338 lists the same, 500 lists of 3
+// 20.7 / 20.2, of 8 35.5 / 33.6; selection (it embeds or copies rows, too) over 64 lists of 3 7.4 / 8.5 us, 250 lists of 3 8.95 /
+// 9.2, of 8 15.2 / 14.6, 500 lists of 3 9.75 / 9.65.
+inline int merge_threads(int lists) { return lists <= 320 ? 256 : 512; }
+inline int select_threads(int entries) { return entries <= 1024 ? 256 : 512; }
 
 // Merge of the head GEMM's block lists (nblk lists, the first kk entries of each valid, MAXM apart): the best nk
 // by (value descending, id ascending) land in win[] / winv[] (shared memory, MAXM entries each; wv / wi: shared
-// scratch of one entry per wave).  Called by all SEL_THREADS threads of a workgroup; ends with a barrier.
+// scratch of one entry per wave).  Called by all T threads of a workgroup; ends with a barrier.
+template <int T>
 __device__ __forceinline__ void merge_block_lists(const float* pkv, const int32_t* pki, int nblk, int kk, int nk,
                                                   float* wv, int* wi, int* win, float* winv) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1511,7 +1516,7 @@ __device__ __forceinline__ void merge_block_lists(const float* pkv, const int32_
   float lv[MAXM]; int li[MAXM];
 #pragma unroll
   for (int q = 0; q < MAXM; ++q) { lv[q] = -INFINITY; li[q] = 0x7fffffff; }
-  for (int e = tid; e < total; e += SEL_THREADS) {
+  for (int e = tid; e < total; e += T) {
     int b = e / kk, r = e - b * kk;
     float v = pkv[b * MAXM + r]; int i = pki[b * MAXM + r];
     if (better(v, i, lv[MAXM - 1], li[MAXM - 1])) {
@@ -1535,7 +1540,7 @@ __device__ __forceinline__ void merge_block_lists(const float* pkv, const int32_
     __syncthreads();
     int bw = 0;
 #pragma unroll
-    for (int w = 1; w < SEL_THREADS / WAVE; ++w) if (better(wv[w], wi[w], wv[bw], wi[bw])) bw = w;
+    for (int w = 1; w < T / WAVE; ++w) if (better(wv[w], wi[w], wv[bw], wi[bw])) bw = w;
     const int wid = wi[bw];
     if (tid == 0) { win[r] = wid; winv[r] = wv[bw]; }
     int cur = 0x7fffffff;
@@ -1554,17 +1559,17 @@ struct TopkMergeArgs {
 };
 
 // every workgroup merges the block candidates redundantly (they are few); winners land in win[]
-template <typename WT>
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
-  __shared__ float wv[SEL_THREADS / WAVE];
-  __shared__ int wi[SEL_THREADS / WAVE];
+template <typename WT, int T>
+__global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
+  __shared__ float wv[T / WAVE];
+  __shared__ int wi[T / WAVE];
   __shared__ int win[MAXM];
   __shared__ float winv[MAXM];
   __shared__ int s_midx, s_tok;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // merge of one row's block lists: the best nk by (value descending, id ascending) land in win[]
   auto merge_row = [&](int prow, int nk) {
-    merge_block_lists(a.pk_val + (size_t)prow * a.pk_stride * MAXM, a.pk_idx + (size_t)prow * a.pk_stride * MAXM,
+    merge_block_lists<T>(a.pk_val + (size_t)prow * a.pk_stride * MAXM, a.pk_idx + (size_t)prow * a.pk_stride * MAXM,
                       a.nblk, a.kk, nk, wv, wi, win, winv);
   };
   merge_row(0, a.mode == 0 ? a.k : (a.samp_topk > 0 ? a.samp_topk : 1));
@@ -1575,7 +1580,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
     EmbedArgs e = a.emb;
     const int tok = id_in_vocab(win[r], a.vocab);
     int pos = a.ds->pos + e.pos_off;
-    for (int i = blockIdx.x * SEL_THREADS + tid; i < e.d_model; i += gridDim.x * SEL_THREADS) {
+    for (int i = blockIdx.x * T + tid; i < e.d_model; i += gridDim.x * T) {
       float v = WTr<WT>::load1(e.tok_emb, (size_t)tok * e.d_model + i);
       if (e.pos_emb) v += WTr<WT>::load1(e.pos_emb, (size_t)pos * e.d_model + i);
       e.h[(size_t)r * e.d_model + i] = v;
@@ -1636,7 +1641,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
       // the matching row's logits are the next round's early logits
       const float* src = a.spec_logits + (size_t)midx * a.vocab;
       float* dst = a.early_spec + (size_t)(pos_next & 1) * a.vocab;
-      for (int i = b * SEL_THREADS + tid; i < a.vocab; i += nblocks * SEL_THREADS) dst[i] = src[i];
+      for (int i = b * T + tid; i < a.vocab; i += nblocks * T) dst[i] = src[i];
       return;
     }
     // the next round's candidates: top-k of the matching row's logits; then, column by column (each thread
@@ -1646,7 +1651,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
     if (b == 0 && tid < a.k) a.ds->cand_next[tid] = win[tid];
     const EmbedArgs e = a.emb;
     const int pos2 = pos_next + 1;
-    for (int i = b * SEL_THREADS + tid; i < a.d_model; i += nblocks * SEL_THREADS) {
+    for (int i = b * T + tid; i < a.d_model; i += nblocks * T) {
       a.h[i] = a.h[(size_t)(1 + midx) * a.d_model + i];
       if (pos2 < a.max_ctx)
         for (int r = 0; r < a.k; ++r) {
@@ -1658,11 +1663,11 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(SelectArgs a) {
     return;
   }
   if (!a.spec && l == 0 && blockIdx.y == 0)
-    for (int i = tid; i < a.d_model; i += SEL_THREADS) a.h[i] = a.h[(size_t)(1 + midx) * a.d_model + i];
+    for (int i = tid; i < a.d_model; i += T) a.h[i] = a.h[(size_t)(1 + midx) * a.d_model + i];
   // tails are [nb][k][H][hd] rows; the cache is blocked (k_index / v_index)
   const float* src = (blockIdx.y == 0 ? a.tailK : a.tailV) + ((size_t)l * a.k + midx) * a.d_model;
   float* dst = (blockIdx.y == 0 ? a.Kc : a.Vc) + (size_t)l * a.H * a.head_floats;
-  for (int idx = tid; idx < a.H * a.hd; idx += SEL_THREADS) {
+  for (int idx = tid; idx < a.H * a.hd; idx += T) {
     const int hh = idx / a.hd, i = idx - hh * a.hd;
     const size_t o = (size_t)hh * a.head_floats + (blockIdx.y == 0 ? k_index(pos_next, i, a.hd) : v_index(pos_next, i, a.hd));
     dst[o] = src[idx];

@@ -14,12 +14,13 @@ using namespace ppd;
 
 namespace ppd {
 
-__global__ __launch_bounds__(SEL_THREADS) void topk_merge_kernel(TopkMergeArgs a) {
-  __shared__ float wv[SEL_THREADS / WAVE];
-  __shared__ int wi[SEL_THREADS / WAVE];
+template <int T>
+__global__ __launch_bounds__(T) void topk_merge_kernel(TopkMergeArgs a) {
+  __shared__ float wv[T / WAVE];
+  __shared__ int wi[T / WAVE];
   __shared__ int win[MAXM];
   __shared__ float winv[MAXM];
-  merge_block_lists(a.pk_val, a.pk_idx, a.nblk, a.kk, a.k, wv, wi, win, winv);
+  merge_block_lists<T>(a.pk_val, a.pk_idx, a.nblk, a.kk, a.k, wv, wi, win, winv);
   if ((int)threadIdx.x < a.k) {
     a.ids[threadIdx.x] = win[threadIdx.x];
     if (a.vals) a.vals[threadIdx.x] = winv[threadIdx.x];
@@ -75,7 +76,8 @@ hipError_t early_topk_launch(const EarlyTopkPlan& p, int d_model, int vocab, int
   if (e != hipSuccess) return e;
   TopkMergeArgs t;
   t.pk_val = pk_val; t.pk_idx = pk_idx; t.nblk = p.grid; t.kk = k; t.k = k; t.ids = ids_out; t.vals = vals_out;
-  hipLaunchKernelGGL(topk_merge_kernel, dim3(1), dim3(SEL_THREADS), 0, stream, t);
+  if (merge_threads(t.nblk) == 256) hipLaunchKernelGGL(topk_merge_kernel<256>, dim3(1), dim3(256), 0, stream, t);
+  else hipLaunchKernelGGL(topk_merge_kernel<512>, dim3(1), dim3(512), 0, stream, t);
   return hipGetLastError();
 }
 

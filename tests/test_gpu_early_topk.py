@@ -81,3 +81,18 @@ def test_early_topk_ties_go_to_the_lowest_id():
     np.testing.assert_array_equal(z[0::2], z[1::2])
     np.testing.assert_array_equal(ids, np.lexsort((np.arange(cfg.vocab), -z.astype(np.float64)))[:6])
     assert (ids[0::2] % 2 == 0).all() and (ids[1::2] == ids[0::2] + 1).all()
+
+
+@pytest.mark.parametrize("vocab", [5104, 5120, 5121, 8191])
+@pytest.mark.parametrize("k", [1, 8])
+def test_early_topk_on_both_sides_of_the_merge_rule(vocab, k):
+    """319, 320, 321 and 512 lists: 256 or 512 threads merge them.  Equal logits among them: the lower id comes first."""
+    gen = torch.Generator().manual_seed(vocab)
+    head = torch.randn(vocab, 64, generator=gen)
+    head = torch.cat([head[:vocab // 2], head])[:vocab]           # every logit of the first half twice
+    head, h, g = head.bfloat16().cuda(), torch.randn(64, generator=gen).cuda(), torch.ones(64).bfloat16().cuda()
+    ids, vals, z = binding.ppd_early_topk(h, g, None, head, k, 1, 1e-5, want_logits=True)
+    z = z.cpu().numpy()
+    order = np.argsort(-z, kind="stable")[:k]
+    np.testing.assert_array_equal(ids.cpu().numpy(), order)
+    np.testing.assert_array_equal(vals.cpu().numpy(), z[order])
