@@ -27,11 +27,14 @@ CASES = {
 }
 
 
-def run(cfg, dev, prompt, monkeypatch, **env):
+def run(cfg, dev, prompt, monkeypatch, rounds=None, **env):
+    """Tokens, logits and rounds of both modes; rounds: receives the chain's counters."""
     for k, v in env.items():
         monkeypatch.setenv(k, v)
     P = binding.PPD(cfg, dev)
     out = [gpu_generate(P, prompt, cfg.n_gen, mode) for mode in ("plain", "ppd")]
+    if rounds is not None:
+        rounds.append(P.ppd_get_chain_rounds())
     P.close()
     for k in env:
         monkeypatch.delenv(k)
@@ -43,8 +46,30 @@ def test_one_launch_is_one_launch_per_step_bit_exact(name, monkeypatch):
     cfg = CASES[name]
     dev = binding.upload_model(pi.make_model(cfg))
     prompt = pi.make_prompt(cfg)
-    one = run(cfg, dev, prompt, monkeypatch)
+    rounds = []
+    one = run(cfg, dev, prompt, monkeypatch, rounds)
+    steps = run(cfg, dev, prompt, monkeypatch, rounds, PPD_FUSED="2")
+    # every plain step, and the PPD rounds that do not begin at the exit layer (here: those behind no match)
+    behind = [m for m, _, _ in one[1][2]][:-1]
+    assert rounds == [(2 * cfg.n_gen - sum(behind), 0), (0, 0)]
+    for a, b in zip(one, steps):
+        np.testing.assert_array_equal(a[0], b[0])
+        np.testing.assert_array_equal(a[1], b[1])
+        assert a[2] == b[2]
+
+
+@pytest.mark.parametrize("family", ["llama", "opt"])
+def test_a_chain_that_begins_behind_a_match_bit_exact(family, monkeypatch):
+    """An exit layer above the middle and a late part that changes little: rounds behind a match go through the layers
+    between in one launch, too."""
+    n = {"llama": 6, "opt": 4}[family]
+    cfg = small_cfg(family, n_layers=n, exit_layer=n - 1, alpha=0.02, max_ctx=160, n_prompt=70, n_gen=30)
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    rounds = []
+    one = run(cfg, dev, prompt, monkeypatch, rounds)
     steps = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")
+    assert sum(m for m, _, _ in one[1][2][:-1]) > 0 and rounds == [(2 * cfg.n_gen, 0)]
     for a, b in zip(one, steps):
         np.testing.assert_array_equal(a[0], b[0])
         np.testing.assert_array_equal(a[1], b[1])
@@ -56,8 +81,10 @@ def test_a_launch_that_gives_up_is_run_again(name, monkeypatch):
     cfg = CASES[name]
     dev = binding.upload_model(pi.make_model(cfg))
     prompt = pi.make_prompt(cfg)
-    gave_up = run(cfg, dev, prompt, monkeypatch, PPD_SPIN_TICKS="1")
+    rounds = []
+    gave_up = run(cfg, dev, prompt, monkeypatch, rounds, PPD_SPIN_TICKS="1")
     steps = run(cfg, dev, prompt, monkeypatch, PPD_FUSED="2")
+    assert rounds == [(1, 1)]          # the first round; those after it go without
     for a, b in zip(gave_up, steps):
         np.testing.assert_array_equal(a[0], b[0])
         np.testing.assert_array_equal(a[1], b[1])
