@@ -52,7 +52,8 @@ struct ppd_ctx {
   // device memory owned by the context
   char *Kc, *Vc;         // [L][H][16-position blocks][hd/16][64][4] fp32 (see k_index / v_index)
   char *tailK, *tailV;   // [nb][k][H][hd]
-  // activation rows: max(1 + k, rows of a prompt chunk); row 0: main token, rows 1..k: candidates
+  // activation rows: max(1 + k, rows of a prompt chunk; in att and ffn those of the chunks that run_layer takes); row 0: main
+  // token, rows 1..k: candidates
   float *h;              // [rows][d_model]
   float *qkv;            // [rows][3*d_model]
   float *att;            // [rows][d_model]
@@ -1062,6 +1063,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   const size_t dm = d.d_model, R = 1 + k;
   const size_t RC = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
   const size_t RB = R > RC ? R : RC;   // activation rows: a round's 1 + k, or a prompt chunk
+  const size_t RL = d.wdtype == 1 ? c->few_rows : PREFILL_CHUNK_FP32, RS = R > RL ? R : RL;   // those that go through run_layer
   hipError_t e = hipSuccess;
   auto alloc = [&](void** p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
   alloc((void**)&c->Kc, (size_t)d.n_layers * cache_layer_bytes(c));
@@ -1070,14 +1072,14 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   alloc((void**)&c->tailV, (size_t)c->nb * k * dm * c->kvbytes);
   alloc((void**)&c->h, RB * dm * sizeof(float));
   alloc((void**)&c->qkv, RB * 3 * dm * sizeof(float));
-  alloc((void**)&c->att, RB * dm * sizeof(float));
+  alloc((void**)&c->att, RS * dm * sizeof(float));
   if (d.wdtype == 1) {
     alloc((void**)&c->rp_x, packed_bytes(PREFILL_CHUNK, (int)dm));
     alloc((void**)&c->rp_a, packed_bytes(PREFILL_CHUNK, (int)dm));
     alloc((void**)&c->rp_f, packed_bytes(PREFILL_CHUNK, d.d_ff));
     if (e == hipSuccess) e = hipMemset(c->rp_f, 0, packed_bytes(PREFILL_CHUNK, d.d_ff));
   }
-  alloc((void**)&c->ffn, RB * (size_t)d.d_ff * sizeof(float));
+  alloc((void**)&c->ffn, RS * (size_t)d.d_ff * sizeof(float));
   alloc((void**)&c->part, RB * d.n_heads * (size_t)c->nchunk_max * (d.head_dim + 2) * sizeof(float));
   alloc((void**)&c->logits, R * d.vocab * sizeof(float));
   alloc((void**)&c->early_spec, (size_t)2 * d.vocab * sizeof(float));
