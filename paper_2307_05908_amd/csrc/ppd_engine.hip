@@ -906,7 +906,7 @@ void free_all(ppd_ctx* c) {
   if (c->stream) (void)hipStreamDestroy(c->stream);
 }
 
-constexpr int PREFILL_TILED_MIN = 32;
+constexpr int PREFILL_TILED_MIN = 32;      // rows: prompts of at least 33 tokens
 
 // The whole prompt (rows 0 .. rows-1 at positions 0 .. rows-1) through all layers: fills the cache.
 int prefill_tiled(ppd_ctx* c, int rows) {
@@ -1262,7 +1262,8 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
     for (int l = 0; l < c->d.n_layers && !rc; ++l) {
       RowGroup g{l, m, 0, 0, false};
       g.chunk = m > 1;
-      // (the last layer's rows are read by no one: its keys and values are all that a prompt leaves there)
+      // (the last layer's rows are read by no one: its keys and values are all that a prompt leaves there; run_layer's first
+      // stage runs its attention, too, whose kernel writes them where there is one row)
       rc = c->mfma && m > c->few_rows ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
     }
   }

@@ -23,11 +23,11 @@
 // store on its way to memory and one load.  (With flags: 2.82 instead of 3.16 ms per token.)  Stores and loads are
 // relaxed atomic accesses of agent scope (sc1: past the XCD's L2, which is not coherent with the other seven).
 //
-// All workgroups of the launch have to be on the machine at once.  The host launches one per compute unit and keeps
-// launches of several contexts apart; should another program hold compute units all the same, every wait ends after
+// All workgroups of the launch have to be on the machine at once.  The host launches one per compute unit, and only while no
+// other context has work in flight; should another program hold compute units all the same, every wait ends after
 // spin_ticks of the 100 MHz clock: the workgroup then sets DevState::aborted, waits for nothing any more, and runs to
 // the end on whatever is there; the selection kernel sees the mark and leaves the round's state alone, and the host
-// runs the round again one launch per step.
+// runs the round again one launch per step (and keeps to that for a while).
 //
 // Two row groups (the pipelined steps) stay with one launch per step: k rows that every compute unit reads from memory
 // instead of from its XCD's L2 cost more than the boundaries do (7B shape, k = 5: 189 us a step against 162).

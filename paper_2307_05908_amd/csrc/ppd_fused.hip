@@ -1,4 +1,4 @@
-// Instances and launcher of the one-launch-per-phase decode kernel (ppd_fused.h).
+// Instances and launcher of the kernel that takes one row through all layers in one launch (ppd_fused.h).
 #define PPD_FUSED_TU 1
 #include "ppd_fused.h"
 
