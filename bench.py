@@ -9,9 +9,10 @@ one token.  Inputs (synthetic weights and prompt) are resident in HBM before the
 Prints one JSON line: PPD tokens/s as `value`, plain greedy on the same kernels next to it;
 `roofline`: the dominant kernel of a pipelined step, the two-group FFN-in GEMM (main row on one
 layer's gate/up matrices, the k candidate rows on another's), timed live with HIP events, with the
-one-row launch of the solo phase / plain steps beside it; `pipelined_step`: the unit the 70 % target
-is stated on, against both byte counts (bf16 KV as the hot-path table counts it, fp32 KV as built);
-per-kernel bytes / time / fraction for both launch shapes; a two-term time model (bytes / rate +
+one-row launch beside it; `pipelined_step`: the unit the 70 % target is stated on, against both byte
+counts (bf16 KV as the hot-path table counts it, fp32 KV as built); `solo_phase`: a layer of the main
+token alone, in the one-launch chain (bf16 models); per-kernel bytes / time / fraction for both launch
+shapes, one launch per step of a layer; a time model (the chain's layers as measured; bytes / rate +
 launches x fixed cost) for plain tokens and for rounds after a miss and after a hit; the measured
 match rate and layer-row counts against Theorem 4.1; the CPU oracle timed on the host cores.
 
@@ -246,10 +247,12 @@ def main():
     wall_plain = timed(P, P.plain_greedy_step, W, K)
 
     # ---- timing with HIP events on the library's own stream, separate short passes
-    # (a) every kernel bracketed, plain greedy steps and PPD rounds: per-kernel durations of both launch shapes
-    # (b) only the phases bracketed, PPD rounds: the parallel phase as it runs in normal operation
+    # (a) every kernel bracketed, plain greedy steps and PPD rounds: per-kernel durations of both launch shapes (one launch
+    #     per step of a layer: the one-launch chain is not used under this profiling)
+    # (b) only the phases bracketed, PPD rounds: the parallel phase and the main token's layers as they run in normal operation
     # (c) the roofline kernel alone: bursts of FFN-in GEMMs (other layers' weights in every launch) between two events
     kt, ph = {}, {}
+    solo_layers, solo_chain = 0, False
     burst1_ms = burst2_ms = None
     R = args.profile_rounds
     if R > 0:
@@ -276,9 +279,13 @@ def main():
         for _ in range(W):
             P.ppd_step(want_info=False)
         P.ppd_set_profiling(1)
+        s0, c0 = P.ppd_get_stats(), P.ppd_get_chain_rounds()
         for _ in range(R):
             P.ppd_step(want_info=False)
         ph = P.ppd_get_kernel_time()
+        s1, c1 = P.ppd_get_stats(), P.ppd_get_chain_rounds()
+        solo_layers = s1["main_layer_rows"] - s0["main_layer_rows"] - (cfg.n_layers - e) * R
+        solo_chain = c1[0] > c0[0]
         P.ppd_set_profiling(0)
         P.ppd_prefill(prompt)
         burst1_ms = P.ppd_time_ffn_in(4 * cfg.n_layers, groups=1)
@@ -313,7 +320,7 @@ def main():
                 "bytes_per_launch": 2 * ffn_in_bytes, "avg_launch_us": round(burst2_ms * 1e3, 2),
                 "timing": "HIP events around a burst of %d back-to-back launches on the library's stream, other layers' weights in every launch" % (2 * cfg.n_layers),
                 "stream_read_GBps": round(stream_gbs, 1), "frac_of_stream_read": round(ach2 / stream_gbs, 4),
-                "one_row_launch": {"what": "the same kernel with the main row alone (solo phase, plain steps)",
+                "one_row_launch": {"what": "the same kernel with the main row alone (where the one-launch chain does not take its layers: long contexts, contexts at work together)",
                                    "bytes_per_launch": ffn_in_bytes, "avg_launch_us": round(burst1_ms * 1e3, 2),
                                    "achieved": round(ach1, 1), "frac": round(ach1 / HBM_PEAK_GBS, 4)}}
     pp = ph.get("phase.g2")
@@ -332,7 +339,19 @@ def main():
                 "frac_of_stream_read": round(b_table / step_s / 1e9 / stream_gbs, 4), "context": ctx_mid,
                 "target_hbm_frac": 0.70}
 
-    # ---- two-term time model: t = bytes / rate + launches * t_fixed, fitted on the bracketed GEMM launches of both shapes
+    # ---- the main token alone: a layer's weights, keys and values at the rate of the chain that takes them through
+    solo = None
+    chain_us = 0.0
+    if "phase.g1" in ph and solo_layers > 0:
+        us = ph["phase.g1"]["ms"] * 1e3 / solo_layers
+        b = wl + ctx_mid * cfg.kv_bytes_per_pos_layer()
+        solo = {"kernel": "decode_layers_kernel<%d> (all layers of the phase in one launch)" % cfg.head_dim if solo_chain else "one launch per step of a layer",
+                "us_per_layer": round(us, 2), "layers_timed": solo_layers, "bytes_per_layer": b, "GBps": round(b / us / 1e3, 1),
+                "hbm_frac": round(b / us / 1e3 / HBM_PEAK_GBS, 4), "frac_of_stream_read": round(b / us / 1e3 / stream_gbs, 4), "context": ctx_mid}
+        if solo_chain:
+            chain_us = us
+
+    # ---- time model: t = bytes / rate + launches * t_fixed, fitted on the bracketed GEMM launches of both shapes
     model_fit = None
     gemms = [n for n in kernels if n.startswith("gemm_") or n.startswith("head")]
     if len(gemms) >= 4:
@@ -348,11 +367,13 @@ def main():
         small = us("select.g1")
 
         def est(layers1, layers2, heads, embeds):
-            bytes_ = (layers1 + 2 * layers2) * wl + heads * head_b
-            launches = 4 * (layers1 + layers2) + heads
+            # (the layers of a chain as measured; all others by the fit)
+            l1 = 0 if chain_us else layers1
+            bytes_ = (l1 + 2 * layers2) * wl + heads * head_b
+            launches = 4 * (l1 + layers2) + heads
             stream_ms = bytes_ / (rate * 1e9) * 1e3
-            fixed_ms = (launches * t_fixed + layers1 * lat1 + layers2 * lat2 + heads * small + embeds * us("embed.g1")) / 1e3
-            return bytes_, launches, stream_ms, fixed_ms
+            fixed_ms = (launches * t_fixed + l1 * lat1 + layers2 * lat2 + heads * small + embeds * us("embed.g1")) / 1e3
+            return bytes_, launches, stream_ms, fixed_ms, layers1 * chain_us / 1e3
 
         solo_after_hit = e - nb
         spec = 2 * e == d and cfg.wdtype == pi.WD_BF16
@@ -365,16 +386,17 @@ def main():
         bracket_us = 0.0
         if burst1_ms and "gemm_ffn_in.g1" in kernels:
             bracket_us = max(0.0, kernels["gemm_ffn_in.g1"]["avg_us"] - burst1_ms * 1e3)
-        n_launch = {"plain_token": 6 * d + 3, "ppd_round_after_miss": 6 * (e + nb) + 5,
-                    "ppd_round_after_hit": 6 * (solo_after_hit + nb) + (2 if spec else 4)}
-        cases = {n: ((m[0], m[1], m[2], m[3] - n_launch[n] * bracket_us / 1e3), meas) for n, (m, meas) in cases.items()}
-        model_fit = {"form": "t = bytes / rate + launches * t_fixed (GEMM launches) + latency-bound kernels (attention, merge, selection) as measured",
+        by_launch = 0 if chain_us else 1
+        n_launch = {"plain_token": 6 * d * by_launch + 3, "ppd_round_after_miss": 6 * (e * by_launch + nb) + 5,
+                    "ppd_round_after_hit": 6 * (solo_after_hit * by_launch + nb) + (2 if spec else 4)}
+        cases = {n: ((m[0], m[1], m[2], m[3] - n_launch[n] * bracket_us / 1e3, m[4]), meas) for n, (m, meas) in cases.items()}
+        model_fit = {"form": "t = the main token's layers in the one-launch chain, as measured (chain_ms) + bytes / rate + launches * t_fixed (GEMM launches) + latency-bound kernels (attention, merge, selection) as measured",
                      "rate_GBps": round(rate, 1), "t_fixed_us_per_gemm_launch": round(t_fixed, 2),
                      "fitted_on": "bracketed durations (an event pair around every launch) of %d GEMM launch shapes" % len(gemms),
                      "bracket_overhead_us_per_launch": round(bracket_us, 2),
-                     "note": "fixed_ms is net of the bracketing; measured_ms minus model_ms is what a round costs outside its kernels (graph launch, host wait)",
-                     "cases": {n: {"weight_bytes": m[0], "gemm_launches": m[1], "stream_ms": round(m[2], 4), "fixed_ms": round(m[3], 4),
-                                   "model_ms": round(m[2] + m[3], 4), "measured_ms": None if meas is None else round(meas, 4)}
+                     "note": "weight_bytes, gemm_launches, stream_ms and fixed_ms leave out a chain's layers; fixed_ms is net of the bracketing; measured_ms minus model_ms is what a round costs outside its kernels (graph launch, host wait)",
+                     "cases": {n: {"weight_bytes": m[0], "gemm_launches": m[1], "chain_ms": round(m[4], 4), "stream_ms": round(m[2], 4), "fixed_ms": round(m[3], 4),
+                                   "model_ms": round(m[2] + m[3] + m[4], 4), "measured_ms": None if meas is None else round(meas, 4)}
                                for n, (m, meas) in cases.items()}}
 
     # ---- CPU oracle on the host cores (bounded sample)
@@ -418,7 +440,7 @@ def main():
                                  "theorem_latency": tradeoff.expected_latency(d, e, ell, p_hat) / ell,
                                  "theorem_compute": tradeoff.expected_compute(d, e, ell, k, p_hat) / ell},
         "prefill": prefill_report(cfg, pi, n_prompt - 1, prefill_s, prefill_first_s),
-        "roofline": roof, "pipelined_step": pipe, "kernels": kernels, "time_model": model_fit, "cpu_baseline": cpu,
+        "roofline": roof, "pipelined_step": pipe, "solo_phase": solo, "kernels": kernels, "time_model": model_fit, "cpu_baseline": cpu,
         "setup_s": {"generate_weights": round(t_gen, 1)},
     }
     print(json.dumps(out))
