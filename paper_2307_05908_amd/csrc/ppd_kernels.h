@@ -246,7 +246,8 @@ __device__ __forceinline__ float silu(float u) { return u / (1.0f + expf(-u)); }
 
 // WR: weight rows a wave streams together (4, or 2 when the matrix has few rows per wave);
 // a register batch is always 8 loads per lane: WR rows x (8 / WR) k-blocks.
-template <typename WT, int MT, bool PAIRED, int WR>
+// GF: one row's gains are requested with the row (see gains_first).
+template <typename WT, int MT, bool PAIRED, int WR, bool GF>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G, float* lds) {
   constexpr int VEC = WTr<WT>::VEC;
   constexpr int BK = WAVE * VEC;                 // k elements per block
@@ -343,11 +344,10 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
       const int m = i / spr, kk = (i - m * spr) * 1024 + tid * 4;
       if (m < M && kk < K) xr[i] = *(const float4*)(G.X + (size_t)m * a.ldx + kk);
     }
-    // One row: its gains come with it (later they would wait behind the weights).  GR float4 slots of a thread, 4096 elements, are
-    // what the registers take; the rest of a longer row's gains is read behind the weights.  Measured (early prediction, bf16, 4096
-    // elements, 8000 / 32000 logits): no slot 31.4 / 60.6 us, 4 slots 29.8 / 58.9, 8 slots 38.5 / 70.3 (one workgroup fewer on a
-    // compute unit); 8192 elements 41.8 / 106.6, 41.5 / 106.1, 52.4 / 117.9.
-    constexpr int GR = MT == 1 ? 4 : 0;
+    // One row, GF: its gains come with it (later they would wait behind the weights).  GR float4 slots of a thread, 4096 elements,
+    // are what the registers take: with 8 of them a workgroup fewer fits a compute unit; the rest of a longer row's gains is
+    // read behind the weights.
+    constexpr int GR = MT == 1 && GF ? 4 : 0;
     float gr[GR + 1][4], br[GR + 1][4];
     if (MT == 1 && a.norm >= 0) {
 #pragma unroll
@@ -619,12 +619,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
 }
 
 // MA rows in group 0, MB rows in group 1 (MB == 0: single-group launch)
-template <typename WT, int MA, int MB, bool PAIRED, int WR>
+template <typename WT, int MA, int MB, bool PAIRED, int WR, bool GF = true>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs a) {
   extern __shared__ float4 lds4[];
   float* lds = (float*)lds4;
-  if (MB == 0 || blockIdx.y == 0) gemm_body<WT, MA, PAIRED, WR>(a, a.g[0], lds);
-  else gemm_body<WT, (MB < 1 ? 1 : MB), PAIRED, WR>(a, a.g[1], lds);
+  if (MB == 0 || blockIdx.y == 0) gemm_body<WT, MA, PAIRED, WR, GF>(a, a.g[0], lds);
+  else gemm_body<WT, (MB < 1 ? 1 : MB), PAIRED, WR, GF>(a, a.g[1], lds);
 }
 
 // Reduction lengths of at most 1024, fp32 weights: a launch is a chain of latencies, not a stream.  Every operand of an output

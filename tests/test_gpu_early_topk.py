@@ -96,3 +96,22 @@ def test_early_topk_on_both_sides_of_the_merge_rule(vocab, k):
     order = np.argsort(-z, kind="stable")[:k]
     np.testing.assert_array_equal(ids.cpu().numpy(), order)
     np.testing.assert_array_equal(vals.cpu().numpy(), z[order])
+
+
+@pytest.mark.parametrize("K", [2048, 2056, 4096, 4104, 5120])
+@pytest.mark.parametrize("norm", [0, 1])
+def test_gains_with_the_row_or_behind_the_weights_bit_exact(K, norm):
+    """bf16 classifiers of at least 2048 columns whose waves take three sets of rows or more have an instance of their own:
+    its logits against those of fewer rows, which the other one takes."""
+    gen = torch.Generator().manual_seed(K)
+    head = torch.randn(17001, K, generator=gen).bfloat16().cuda()
+    h = (3 * torch.randn(K, generator=gen) + 1).cuda()
+    g = (1 + 0.1 * torch.randn(K, generator=gen)).bfloat16().cuda()
+    b = (0.1 * torch.randn(K, generator=gen)).bfloat16().cuda() if norm == 0 else None
+    ids, vals, z = binding.ppd_early_topk(h, g, b, head, 8, norm, 1e-5, want_logits=True)
+    z = z.cpu().numpy()
+    _, _, few = binding.ppd_early_topk(h, g, b, head[:8000].contiguous(), 8, norm, 1e-5, want_logits=True)
+    np.testing.assert_array_equal(z[:8000].view(np.uint32), few.cpu().numpy().view(np.uint32))
+    order = np.argsort(-z, kind="stable")[:8]
+    np.testing.assert_array_equal(ids.cpu().numpy(), order)
+    np.testing.assert_array_equal(vals.cpu().numpy(), z[order])
