@@ -48,7 +48,7 @@ struct ppd_ctx {
   struct LayerP { void *qkv, *o, *fin, *fout; };
   std::vector<LayerP> LP;
   void *head_p, *early_p;
-  std::vector<void*> owned;   // every repacked buffer, for ppd_destroy
+  std::vector<void*> owned;   // every repacked buffer (and pf_ws), for ppd_destroy
   // device memory owned by the context
   char *Kc, *Vc;         // [L][H][16-position blocks][hd/16][64][4] fp32 (see k_index / v_index)
   char *tailK, *tailV;   // [nb][k][H][hd]
@@ -80,6 +80,9 @@ struct ppd_ctx {
   uint16_t *pf_xa;       // the attention outputs (written by the attention kernel),
   uint16_t *pf_xf;       // the feed-forward activations (written by the FFN-in GEMM; zero beyond d_ff)
   uint16_t *pf_qp, *pf_kp, *pf_vp;   // one layer's queries, keys, values as two-term operand blocks of the prompt attention
+  float *pf_ws; int *pf_cnt;         // partial sums of products whose reduction length is cut, parts done per tile (made when first needed)
+  unsigned pg_ready;                 // bit 2 t + paired: that kernel's LDS is set up
+  int pg_tile, pg_parts;             // >= 0, > 0: the tile and the cut of every product of the pass (tests)
   int dev_pos_pending;   // host mirror of the device state's pending position (-1: unknown)
   uint16_t *rp_x, *rp_a, *rp_f;      // packed two-term rows of a prompt chunk: normalised rows, attention outputs, feed-forward activations (zero beyond d_ff)
   // sampling-based final prediction (Appendix B): 0 arg max, 1 top-k sampling, 2 top-p sampling
@@ -939,6 +942,28 @@ int prefill_tiled(ppd_ctx* c, int rows) {
     HIPCHK(c, hipGetLastError());
   }
   const int MT = (rows + 15) / 16;
+  // QKV, O, FFN in, FFN out
+  PGemmPlan plan[4];
+  const int nk[4][2] = {{(3 * dm + 15) / 16, dm}, {(dm + 15) / 16, dm}, {swiglu ? (F + 7) / 8 : (F + 15) / 16, dm}, {(dm + 15) / 16, F}};
+  for (int i = 0; i < 4; ++i) {
+    const int KT = (nk[i][1] + 31) / 32;
+    plan[i] = plan_pgemm(rows, KT, nk[i][0]);
+    if (c->pg_tile >= 0) plan[i].tile = c->pg_tile < PG_TILES ? c->pg_tile : PG_TILES - 1;
+    if (c->pg_parts > 0) plan[i].S = c->pg_parts < KT ? c->pg_parts : KT;
+    const int paired = i == 2 && swiglu ? 1 : 0;
+    const unsigned bit = 1u << (2 * plan[i].tile + paired);
+    if (!(c->pg_ready & bit)) {
+      HIPCHK(c, pgemm_setup(plan[i], paired != 0));
+      c->pg_ready |= bit;
+    }
+    if (plan[i].S > 1 && !c->pf_ws) {
+      void* ws = nullptr;
+      HIPCHK(c, hipMalloc(&ws, PG_WS_BYTES + PG_MAX_TILES * sizeof(int)));
+      c->owned.push_back(ws);
+      HIPCHK(c, hipMemsetAsync((char*)ws + PG_WS_BYTES, 0, PG_MAX_TILES * sizeof(int), c->cur));
+      c->pf_ws = (float*)ws; c->pf_cnt = (int*)((char*)ws + PG_WS_BYTES);
+    }
+  }
   auto pack = [&](const float* X, int ld, int K, const void* g, const void* b, int norm) -> hipError_t {
     PackArgs p; memset(&p, 0, sizeof p);
     p.X = X; p.ld = ld; p.M = rows; p.K = K; p.KT = (K + 31) / 32; p.MT = MT; p.g = g; p.b = b; p.norm = norm; p.eps = d.norm_eps;
@@ -946,21 +971,22 @@ int prefill_tiled(ppd_ctx* c, int rows) {
     return launch_pack_rows(c->cur, p);
   };
   auto gemm = [&](const uint16_t* Xp, const void* P, int K, int n0, int n1, int n2, bool paired, const void* b0, const void* b1, const void* b2,
-                  const float* rsd, float* Y, int ldy, int act, uint16_t* Yp = nullptr) -> hipError_t {
+                  const float* rsd, float* Y, int ldy, int act, PGemmPlan plan, uint16_t* Yp = nullptr) -> hipError_t {
     PGemmArgs g; memset(&g, 0, sizeof g);
+    g.ws = c->pf_ws; g.cnt = c->pf_cnt;
     g.Xp = Xp; g.P = P; g.Yp = Yp; g.KTp = (n0 + 31) / 32; g.B[0] = b0; g.B[1] = b1; g.B[2] = b2; g.Rsd = rsd; g.Y = Y;
     g.M = rows; g.MT = MT; g.KT = (K + 31) / 32;
     g.N[0] = n0; g.N[1] = n1; g.N[2] = n2; g.ntot = paired ? n0 : n0 + n1 + n2;
     g.NT = paired ? (n0 + 7) / 8 : (g.ntot + 15) / 16;
     g.ldy = ldy; g.act = act;
-    return launch_pgemm(c->cur, g, paired);
+    return launch_pgemm(c->cur, g, paired, plan);
   };
   for (int l = 0; l < d.n_layers; ++l) {
     const LayerW& w = c->L[l];
     const ppd_ctx::LayerP& P = c->LP[l];
     HIPCHK(c, pack(c->pf_h, dm, dm, w.ln1_g, d.norm == 0 ? w.ln1_b : nullptr, d.norm));
     HIPCHK(c, gemm(c->pf_xp, P.qkv, dm, dm, dm, dm, false, bias ? w.bq : nullptr, bias ? w.bk : nullptr, bias ? w.bv : nullptr,
-                   nullptr, c->pf_qkv, 3 * dm, 0));
+                   nullptr, c->pf_qkv, 3 * dm, 0, plan[0]));
     {
       PKvPackArgs pk; memset(&pk, 0, sizeof pk);
       pk.qkv = c->pf_qkv; pk.rope = d.pos == 1 ? c->rope : nullptr; pk.Qp = c->pf_qp; pk.Kp = c->pf_kp; pk.Vp = c->pf_vp;
@@ -973,11 +999,11 @@ int prefill_tiled(ppd_ctx* c, int rows) {
       pa.M = rows; pa.H = d.n_heads; pa.d_model = dm; pa.JP = pk.JP;
       HIPCHK(c, launch_pattn(c->cur, pa, d.head_dim));
     }
-    HIPCHK(c, gemm(c->pf_xa, P.o, dm, dm, 0, 0, false, bias ? w.bo : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0));
+    HIPCHK(c, gemm(c->pf_xa, P.o, dm, dm, 0, 0, false, bias ? w.bo : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0, plan[1]));
     HIPCHK(c, pack(c->pf_h, dm, dm, w.ln2_g, d.norm == 0 ? w.ln2_b : nullptr, d.norm));
-    if (swiglu) HIPCHK(c, gemm(c->pf_xp, P.fin, dm, F, F, 0, true, bias ? w.b_in : nullptr, nullptr, nullptr, nullptr, nullptr, F, 0, c->pf_xf));
-    else HIPCHK(c, gemm(c->pf_xp, P.fin, dm, F, 0, 0, false, bias ? w.b_in : nullptr, nullptr, nullptr, nullptr, nullptr, F, d.act == 0 ? 1 : 2, c->pf_xf));
-    HIPCHK(c, gemm(c->pf_xf, P.fout, F, dm, 0, 0, false, bias ? w.b_out : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0));
+    if (swiglu) HIPCHK(c, gemm(c->pf_xp, P.fin, dm, F, F, 0, true, bias ? w.b_in : nullptr, nullptr, nullptr, nullptr, nullptr, F, 0, plan[2], c->pf_xf));
+    else HIPCHK(c, gemm(c->pf_xp, P.fin, dm, F, 0, 0, false, bias ? w.b_in : nullptr, nullptr, nullptr, nullptr, nullptr, F, d.act == 0 ? 1 : 2, plan[2], c->pf_xf));
+    HIPCHK(c, gemm(c->pf_xf, P.fout, F, dm, 0, 0, false, bias ? w.b_out : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0, plan[3]));
   }
   return PPD_OK;
 }
@@ -1156,6 +1182,9 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = rgemm_setup();
+    // the prompt pass's products with one tile shape (1 ..) and one cut of the reduction length (tests)
+    c->pg_tile = env_int("PPD_PG_TILE", 0) - 1;
+    c->pg_parts = env_int("PPD_PG_PARTS", 0);
     // head launches: the same balanced grid as any other GEMM; a workgroup keeps at most
     // HEAD_MAX_ROWS logits = 16 tiles
     c->mg_passes_min = env_int("PPD_MGPASSES", 1);

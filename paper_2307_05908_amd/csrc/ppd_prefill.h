@@ -5,9 +5,9 @@
 // handful of rows and the wrong one for a prompt: here the prompt's rows are a real matrix operand.
 //
 //   pack_rows_kernel    rows (after an optional norm) -> two bf16 terms x = hi + lo in MFMA operand blocks
-//   pgemm_kernel        Y = epilogue(X W^T): register-tiled v_mfma_f32_32x32x16_bf16, weights in the repacked
-//                       1 KiB blocks of the decode path (A operand), packed rows as B operand, both straight from
-//                       memory (every wave-load is one contiguous kilobyte); products exact in fp32 as in decoding
+//   pgemm_kernel        Y = epilogue(X W^T): tiled v_mfma_f32_32x32x16_bf16, weights in the repacked 1 KiB blocks of the
+//                       decode path (A operand), packed rows as B operand, both through LDS (every request is one
+//                       contiguous kilobyte); products exact in fp32 as in decoding
 //   pkv_pack_kernel     queries, keys, values of the prompt rows -> two-term operand blocks, and keys and values into
 //                       the fp32 cache in the decode path's layout
 //   rgemm_kernel        the GEMMs of a prompt chunk of up to 32 rows, in the decode path's summation order
@@ -23,22 +23,6 @@
 namespace ppd {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int PG_WAVES = 4;                        // waves that multiply: each its own outputs against the workgroup's prompt rows
-constexpr int PG_THREADS = (PG_WAVES + 1) * WAVE;  // and one wave that stages the rows in LDS for them
-constexpr int PG_D = 2, PG_R = PG_D + 2;           // stages of rows in flight ahead of their use; ring slots in LDS
-constexpr int PG_STAGE_BLKS = 16;                  // 1 KiB blocks per stage: KB 32-column blocks x 2 planes x TMB 16-row blocks
-#ifndef PPD_PG_NBUF
-#define PPD_PG_NBUF 6
-#endif
-constexpr int PG_NBUF = PPD_PG_NBUF;   // register buffers of operand blocks per wave
-#ifndef PPD_PG_GROUP_M
-#define PPD_PG_GROUP_M 8
-#endif
-#ifndef PPD_PG_GROUP_Q
-#define PPD_PG_GROUP_Q 8
-#endif
-constexpr int PG_GROUP_M = PPD_PG_GROUP_M, PG_GROUP_Q = PPD_PG_GROUP_Q;   // launch-order groups on one XCD (row blocks x output blocks)
 
 // ---- rows -> packed two-term operand blocks
 // Block (mt, kt) holds rows 16 mt .. +15, columns 32 kt .. +31 as 64 lanes x 8 bf16: lane i + 16 c = row i, columns
@@ -136,6 +120,9 @@ __global__ __launch_bounds__(MG_THREADS) void pack_rows_kernel(PackArgs a) {
 #endif
 
 // ---- tiled GEMM
+// How a product is cut: tile shape (index into pg_tiles) and number of parts of the reduction length
+struct PGemmPlan { int tile, S; };
+constexpr int PG_TILES = 7;
 struct PGemmArgs {
   const uint16_t* Xp;   // packed rows [2][MT][KT][64][8]
   const void* P;        // repacked weights [NT][KT][64][8]
@@ -146,12 +133,15 @@ struct PGemmArgs {
   int N[3], ntot;       // rows per segment (bias lookup); logical output rows
   int ldy;
   int act;              // 0 none, 1 GELU, 2 ReLU (paired launches apply SwiGLU)
-  int NB, MB;           // workgroup grid: NB blocks of 4 * TN 16-row blocks along the outputs, MB blocks of TMB 16-row blocks along the rows
-  int GQ, GM, MBG;      // launch order on one XCD: groups of GQ output blocks x GM row blocks, MBG = ceil(MB / GM) groups per output-block row
+  int NB, MB;           // tiles along the outputs and along the rows (launch_pgemm fills these and S)
+  int S;                // parts of the reduction length, each a workgroup's
+  float* ws; int* cnt;  // S > 1: partial sums [tile][part], parts that are done per tile (zero between launches)
   // the outputs in packed two-term form instead of Y (they are the next GEMM's rows: the feed-forward activations):
   // [2][MT][KTp][64][8]; only outputs below ntot are written, the padding columns of the buffer stay as they are (zero)
   uint16_t* Yp; int KTp;
 };
+constexpr size_t PG_WS_BYTES = (size_t)32 << 20;     // of partial sums at most
+constexpr int PG_MAX_TILES = 1024;                   // tiles of a product whose reduction length is cut
 
 // four consecutive outputs n0 .. n0 + 3 (n0 a multiple of 4) of row m into the packed form: half of an 8-column piece
 __device__ __forceinline__ void put_packed4(uint16_t* out, size_t plane_elems, int KT, int m, int n0, const float (&y)[4]) {
@@ -169,84 +159,77 @@ __device__ __forceinline__ void put_packed4(uint16_t* out, size_t plane_elems, i
 }
 
 
-// Workgroup b of the launch runs on XCD b % 8 (workgroups go round the XCDs in launch order), which owns every
-// eighth output block.  Its workgroups come in groups of GQ output blocks x GM row blocks, about what the XCD's
-// compute units work on at a time: the group reads GQ weight panels and GM row panels from memory once and serves
-// the other uses from that XCD's L2 (one output block against all row blocks would re-read every row panel for
-// every output block).  Measured on the 13B shape with 4095 rows: QKV projection 1.23 -> 1.06 ms.
-// The MFMA is v_mfma_f32_32x32x16_bf16 (a 16x16x32 one issues at half its rate on this part).  Its operands
-// come out of the 16-row blocks as they lie in memory: lane r + 32 h of a 32-row tile reads 16 bytes of the
-// 16-row block r / 16 at lane position (r % 16) + 16 (2 w + h), w = 0, 1 being the two 16-column halves of the
-// 32-column block, so one block pair feeds two MFMAs per operand pair, and weights and rows pair up column by
-// column whatever order the hardware takes the 16 columns in.
-// A workgroup is four multiplying waves and one staging wave.  Multiplying wave w holds TN / 2 x TMB / 2
-// accumulator tiles of 32 x 32: its own TN 16-row weight blocks, straight from memory into PG_NBUF register
-// buffers, against the workgroup's 16 TMB prompt rows, which the staging wave brings into LDS by direct loads (a
-// ring of PG_R stages, PG_D in flight; one barrier per stage hands a stage over): a row block is fetched once per
-// workgroup instead of once per wave, and the waits on the two kinds of loads do not mix in one wave's counter.
-template <bool PAIRED, int TN, int TMB>
-__global__ __launch_bounds__(PG_THREADS) void pgemm_kernel(PGemmArgs a) {
-  constexpr int TW = TN / 2, TX = TMB / 2;                 // 32-row tiles per wave: weights, prompt rows
-  constexpr int KB = PG_STAGE_BLKS / (2 * TMB);            // 32-column blocks per stage
-  static_assert(TN % 2 == 0 && TMB % 2 == 0 && KB >= 1 && KB * 2 * TMB == PG_STAGE_BLKS && PG_NBUF % KB == 0, "tile shapes");
-  static_assert(PG_D * PG_STAGE_BLKS < 64, "the staging wave's wait counts its requests in flight");
+#ifdef PPD_PREFILL_TU
+// 64 lanes x 16 bytes from sbase + voff (per lane) to LDS offset ldsoff + 16 * lane; see dma16
+__device__ __forceinline__ void dma16s(unsigned voff, const void* sbase, unsigned ldsoff) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(ldsoff) : "memory", "m0");
+}
+
+// A workgroup makes a tile of WW TW x WX TX blocks of 32 x 32 outputs (weight rows x prompt rows), each of its WW x WX waves
+// TW x TX of them.  Weights and both terms of the rows come through LDS, 32 columns a stage, in a ring of R stages filled by
+// direct loads; a wave reads TW + 2 TX kilobytes for 2 TW TX MFMAs.  What bounds it: the MFMA pipes at the clock that the
+// card's power allows under them, about 1.9 GHz on random data, so every byte moved less per MFMA shows twice.  The kernel
+// before this one (weights from L2 into every wave's registers, 64 prompt rows a workgroup) moved three times the bytes
+// through L2 per MFMA.  Measured (before -> now, PFLOP/s with both terms counted): 13B shape, 4095 rows, in the model: QKV 1.14
+// -> 1.38, O 1.02 -> 1.25, FFN in 1.17 -> 1.42, FFN out 1.05 -> 1.38; 7B shape, 511 rows: QKV 0.87 -> 1.02, FFN in 1.08 -> 1.20,
+// O and FFN out 0.76 and 0.93, as before; back to back, 128 rows of it 250 -> 156 us a layer, 40 rows 209 -> 115 us.
+// Order of a stage: while the first 16 columns are multiplied the second ones' operands are read, and while those are
+// multiplied the next stage's first ones; between the halves the one barrier of a stage, behind which the stage's slot takes
+// requests again.  Requests and reads stand between the MFMAs, whose issue they do not hold up.
+// The MFMA is v_mfma_f32_32x32x16_bf16: its operands come out of the 16-row blocks as they lie in memory: lane r + 32 h of a
+// 32-row tile reads 16 bytes of the 16-row block r / 16 at lane position (r % 16) + 16 (2 w + h), w = 0, 1 being the two
+// 16-column halves of the 32-column block, so one block pair feeds two MFMAs per operand pair, and weights and rows pair up
+// column by column whatever order the hardware takes the 16 columns in.
+// Tiles are dealt to the XCDs (workgroup b of a launch runs on XCD b % 8) in runs of equal length, in an order in which
+// neighbours share panels: 4 tiles of outputs by all rows.  Dealing out whole columns of tiles left XCDs idle: 20 columns
+// (13B shape, O and FFN out) on 8 XCDs take as long as 24.
+// S > 1: few tiles, so the reduction length is cut into S parts to fill the machine.  A workgroup leaves its sums in memory,
+// past its L2 (agent scope), and counts itself; the last of a tile to do so adds the parts in their order and goes on to the
+// epilogue.  7B shape, 40 rows, FFN out: 90 us with S = 1, 29 with 6.
+template <bool PAIRED, int WW, int WX, int TW, int TX, int R>
+__global__ __launch_bounds__(WW * WX * WAVE, WW * WX <= 4 ? 1 : 2) void pgemm_kernel(PGemmArgs a) {
+  constexpr int NW = WW * WX;
+  constexpr int BW = 2 * WW * TW, BX = 2 * WX * TX;        // 16-row blocks of a tile: weights, rows
+  constexpr int NBLK = BW + 2 * BX;                        // KiB per stage: weights, first terms, second terms
+  constexpr int ND = (NBLK + NW - 1) / NW;                 // requests of a wave per stage (the last ones may repeat a block)
+  static_assert((R - 1) * ND < 64, "the waits count requests in flight");
   extern __shared__ float4 pg_lds4[];
-  char* const lds = (char*)pg_lds4;                        // [PG_R][PG_STAGE_BLKS] KiB
+  char* const lds = (char*)pg_lds4;                        // [R][NBLK] KiB
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b = blockIdx.x, xcd = b & 7, r = b >> 3;
-  const int per = a.GQ * a.GM, g = r / per, gi = r - g * per;
-  const int gq = g / a.MBG, gm = g - gq * a.MBG;
-  const int nb = (gq * a.GQ + gi / a.GM) * 8 + xcd, mb = gm * a.GM + gi % a.GM;
-  if (nb >= a.NB || mb >= a.MB) return;
-  const int KT = a.KT;
-  const int mt0 = mb * TMB;                                // in 16-row blocks
-  const size_t plane = (size_t)a.MT * KT * 1024;          // bytes per plane of the packed rows
-  const int nstg = (KT + KB - 1) / KB;
-
-  if (wave == PG_WAVES) {
-    // ---- the staging wave: stage s = 32-column blocks KB s .. KB s + KB - 1 of the workgroup's rows, both planes
-    const char* const src0 = (const char*)a.Xp + lane * 16;
-    auto stage = [&](int s) {
-      char* const dst = lds + (size_t)(s % PG_R) * PG_STAGE_BLKS * 1024;
+  const int ww = wave % WW, wx = wave / WW;
+  // this workgroup's part and tile
+  constexpr int GQ = 4;
+  const int T = a.NB * a.MB, U = T * a.S, xcd = blockIdx.x & 7, r = blockIdx.x >> 3, each = U >> 3, more = U & 7;
+  if (r >= each + (xcd < more ? 1 : 0)) return;
+  const int u = xcd * each + (xcd < more ? xcd : more) + r, sp = u / T, t = u - sp * T;
+  const int g = t / (GQ * a.MB), gi = t - g * GQ * a.MB, gw = a.NB - g * GQ < GQ ? a.NB - g * GQ : GQ;
+  const int mb = gi / gw, nb = g * GQ + gi - mb * gw;
+  const int KT = a.KT, k0 = KT * sp / a.S, nst = KT * (sp + 1) / a.S - k0;
+  const int ntb = nb * BW, mtb = mb * BX;                  // in 16-row blocks
+  const size_t plane = (size_t)a.MT * KT * 1024;           // bytes per plane of the packed rows
+  const unsigned voff = lane * 16;
+  const char* src[ND];                                     // (blocks past the matrix or the prompt repeat its last one; never stored)
+  auto blk_of = [&](int j) { return wave + j * NW < NBLK ? wave + j * NW : NBLK - 1; };
 #pragma unroll
-      for (int kk = 0; kk < KB; ++kk) {
-        const int kt = KB * s + kk < KT ? KB * s + kk : KT - 1;    // (a block past the end repeats the last one; unused)
-#pragma unroll
-        for (int pl = 0; pl < 2; ++pl)
-#pragma unroll
-          for (int tb = 0; tb < TMB; ++tb) {
-            const int mt = mt0 + tb < a.MT ? mt0 + tb : a.MT - 1;  // (blocks past the prompt re-read its last block; never stored)
-            dma16(src0 + pl * plane + ((size_t)mt * KT + kt) * 1024, dst + ((kk * 2 + pl) * TMB + tb) * 1024);
-          }
-      }
-    };
-    for (int s = 0; s < PG_D && s < nstg; ++s) stage(s);
-    for (int s = 0; s < nstg; ++s) {
-      // slot (s + PG_D) % PG_R was last read for stage s - 2: every wave is past that (it has met barrier s - 1)
-      if (s + PG_D < nstg) {
-        stage(s + PG_D);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PG_D * PG_STAGE_BLKS) : "memory");   // all but the PG_D youngest stages: stage s is in
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
-      __syncthreads();
+  for (int j = 0; j < ND; ++j) {
+    const int blk = blk_of(j);
+    if (blk < BW) {
+      const int nt = ntb + blk < a.NT ? ntb + blk : a.NT - 1;
+      src[j] = (const char*)a.P + ((size_t)nt * KT + k0) * 1024;
+    } else {
+      const int x = blk - BW, pl = x / BX, m = mtb + x - pl * BX, mt = m < a.MT ? m : a.MT - 1;
+      src[j] = (const char*)a.Xp + pl * plane + ((size_t)mt * KT + k0) * 1024;
     }
-    return;
   }
-
-  // ---- the multiplying waves
-  const int nt0 = (nb * PG_WAVES + wave) * TN;
+  auto request = [&](int j, int s) {                       // (stages past the end repeat the last one; unused)
+    dma16s(voff, src[j] + (size_t)(s < nst ? s : nst - 1) * 1024, lds0 + (unsigned)((s % R) * NBLK + blk_of(j)) * 1024u);
+  };
   const int lr = lane & 31, lh = lane >> 5;
-  const int lane_off = ((lr & 15) + 16 * lh) * 16;         // + 512 for the second 16-column half
-  const char* wbase[TW];
-#pragma unroll
-  for (int t = 0; t < TW; ++t) {
-    int nt = nt0 + 2 * t + (lr >> 4);
-    if (nt >= a.NT) nt = a.NT - 1;                         // (blocks past the matrix re-read its last block; never stored)
-    wbase[t] = (const char*)a.P + (size_t)nt * KT * 1024 + lane_off;
-  }
-  const char* const xlds = lds + (lr >> 4) * 1024 + lane_off;
+  const int lane_off = (lr >> 4) * 1024 + ((lr & 15) + 16 * lh) * 16;      // + 512 for the second 16 columns
+  const char* const wl = lds + ww * TW * 2048 + lane_off;
+  const char* const xl = lds + (BW + wx * TX * 2) * 1024 + lane_off;
   f32x16 acc[TW][TX];
 #pragma unroll
   for (int i = 0; i < TW; ++i)
@@ -254,123 +237,165 @@ __global__ __launch_bounds__(PG_THREADS) void pgemm_kernel(PGemmArgs a) {
     for (int j = 0; j < TX; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  // PG_NBUF register buffers of weight blocks: those of the next PG_NBUF - 1 reduction steps are in flight while one is multiplied
-  u32x4 wa[PG_NBUF][TW][2];
-  auto fetch = [&](int kt, int buf) {
-    const size_t o = (size_t)(kt < KT ? kt : KT - 1) * 1024;       // (requests past the end repeat the last block; unused)
-#pragma unroll
-    for (int t = 0; t < TW; ++t)
-#pragma unroll
-      for (int w = 0; w < 2; ++w) wa[buf][t][w] = *(const u32x4*)(wbase[t] + o + 512 * w);
+  // operands of 16 columns: weights, first and second terms of the rows; one set is multiplied while the other is read
+  u32x4 fw[2][TW], fh[2][TX], fl[2][TX];
+  constexpr int NF = TW + 2 * TX, NM = TW * TX * 2;
+  auto read = [&](int w, int f, int so) {
+    if (f < TW) fw[w][f] = *(const u32x4*)(wl + so + f * 2048 + 512 * w);
+    else if (f < TW + TX) fh[w][f - TW] = *(const u32x4*)(xl + so + (f - TW) * 2048 + 512 * w);
+    else fl[w][f - TW - TX] = *(const u32x4*)(xl + so + (BX + 2 * (f - TW - TX)) * 1024 + 512 * w);
   };
-  // one 32-column block: the rows' two terms from LDS (all products with the first terms, then all with the second:
-  // no MFMA waits for the one before it)
-  auto mac = [&](int buf, int kt, int kk) {
-    const char* const xs = xlds + ((size_t)((kt / KB) % PG_R) * PG_STAGE_BLKS + kk * 2 * TMB) * 1024;
-    u32x4 xh[TX][2], xl[TX][2];
-#pragma unroll
-    for (int j = 0; j < TX; ++j)
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        xh[j][w] = *(const u32x4*)(xs + (2 * j) * 1024 + 512 * w);
-        xl[j][w] = *(const u32x4*)(xs + (TMB + 2 * j) * 1024 + 512 * w);
-      }
-#pragma unroll
-    for (int w = 0; w < 2; ++w)
-#pragma unroll
-      for (int i = 0; i < TW; ++i)
-#pragma unroll
-        for (int j = 0; j < TX; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa[buf][i][w]), __builtin_bit_cast(bf16x8, xh[j][w]), acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int w = 0; w < 2; ++w)
-#pragma unroll
-      for (int i = 0; i < TW; ++i)
-#pragma unroll
-        for (int j = 0; j < TX; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wa[buf][i][w]), __builtin_bit_cast(bf16x8, xl[j][w]), acc[i][j], 0, 0, 0);
+  auto mac = [&](int w, int m) {
+    const int i = m / (2 * TX), x = m % (2 * TX), j = x % TX;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[w][i]), __builtin_bit_cast(bf16x8, x < TX ? fh[w][j] : fl[w][j]), acc[i][j], 0, 0, 0);
   };
 #pragma unroll
-  for (int p = 0; p < PG_NBUF - 1; ++p) fetch(p, p);
-  int kt = 0;
-  for (; kt + PG_NBUF <= KT; kt += PG_NBUF) {
+  for (int s = 0; s < R; ++s)
 #pragma unroll
-    for (int p = 0; p < PG_NBUF; ++p) {
-      if (p % KB == 0) __syncthreads();                    // the stage of this block is in LDS
-      fetch(kt + p + PG_NBUF - 1, (p + PG_NBUF - 1) % PG_NBUF);
-      mac(p, kt + p, p % KB);
+    for (int j = 0; j < ND; ++j) request(j, s);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((R - 1) * ND) : "memory");
+#pragma unroll
+  for (int f = 0; f < NF; ++f) read(0, f, 0);
+  int so = 0;                                              // the stage's place in the ring
+  for (int s = 0; s < nst; ++s) {
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      mac(0, m);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) if (f * NM / NF == m) read(1, f, so);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // stage s + 1 is in LDS for everybody, and everybody has read stage s
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((R - 2) * ND) : "memory");
+    so += NBLK * 1024;
+    if (so == R * NBLK * 1024) so = 0;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      mac(1, m);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) if (f * NM / NF == m) read(0, f, so);
+#pragma unroll
+      for (int j = 0; j < ND; ++j) if (j * NM / ND == m) request(j, s + R);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
-#pragma unroll
-  for (int p = 0; p < PG_NBUF - 1; ++p)
-    if (kt + p < KT) {
-      if (p % KB == 0) __syncthreads();
-      fetch(kt + p + PG_NBUF - 1, (p + PG_NBUF - 1) % PG_NBUF);
-      mac(p, kt + p, p % KB);
-    }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (no request outlives the workgroup)
 
-  // ---- epilogue: registers 4 q .. 4 q + 3 of a tile are its rows 8 q + 4 (l / 32) .. + 3 (weight rows) for column l % 32
-  // (prompt row)
+  if (a.S > 1) {
+    constexpr unsigned TILE = NW * TW * TX * 4096;         // bytes of a tile's sums: [wave][32 x 32 block][4][64 lanes][4]
+    constexpr int AGENT = 16;                              // sc1: past this XCD's L2
+    const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc((char*)a.ws + (size_t)t * a.S * TILE, 0, (int)(a.S * TILE), 0x00020000);
+    const unsigned o0 = (unsigned)wave * (TW * TX * 4096u) + lane * 16u;
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int j = 0; j < TX; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const f32x4 y = {acc[i][j][4 * v], acc[i][j][4 * v + 1], acc[i][j][4 * v + 2], acc[i][j][4 * v + 3]};
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, y), ws, o0 + ((i * TX + j) * 4 + v) * 1024u, sp * TILE, AGENT);
+        }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's sums are where every XCD finds them
+    __syncthreads();                                       // everybody's are (and everybody is done with the ring)
+    int* const done = (int*)lds;
+    if (tid == 0) {
+      const int n = __hip_atomic_fetch_add(a.cnt + t, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (n == a.S - 1) __hip_atomic_store(a.cnt + t, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *done = n;
+    }
+    __syncthreads();
+    if (*done != a.S - 1) return;
+#pragma unroll
+    for (int i = 0; i < TW; ++i)
+#pragma unroll
+      for (int j = 0; j < TX; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int p = 0; p < a.S; ++p)
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+#pragma unroll
+        for (int j = 0; j < TX; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const f32x4 y = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ws, o0 + ((i * TX + j) * 4 + v) * 1024u, p * TILE, AGENT));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][4 * v + e] += y[e];
+          }
+  }
+
+  // ---- epilogue: registers 4 q .. 4 q + 3 of a 32 x 32 block are its rows 8 q + 4 (l / 32) .. + 3 (weight rows) for column
+  // l % 32 (prompt row); ntot and ldy are multiples of 4.  The residuals of the next column of blocks are requested before this
+  // one's outputs are stored (they may be the same memory, and a load does not pass a store).
+  const int nt0 = ntb + ww * TW * 2, mt0 = mtb + wx * TX * 2;
   const uint16_t* const B0 = (const uint16_t*)a.B[0];
   const uint16_t* const B1 = (const uint16_t*)a.B[1];
   const uint16_t* const B2 = (const uint16_t*)a.B[2];
+  f32x4 rsd[PAIRED ? 1 : 2][TX][4];
+  auto residuals = [&](int i) {
+#pragma unroll
+    for (int j = 0; j < TX; ++j)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int m = (mt0 + 2 * j) * 16 + lr, n0 = (nt0 + 2 * i) * 16 + 8 * q4 + 4 * lh;
+        rsd[i & 1][j][q4] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (a.Rsd && m < a.M && n0 < a.ntot) rsd[i & 1][j][q4] = *(const f32x4*)(a.Rsd + (size_t)m * a.ldy + n0);
+      }
+  };
+  if constexpr (!PAIRED) residuals(0);
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
+    if constexpr (!PAIRED) if (i + 1 < TW) residuals(i + 1);
 #pragma unroll
     for (int j = 0; j < TX; ++j) {
       const int m = (mt0 + 2 * j) * 16 + lr;
       if (m >= a.M) continue;
-      if (PAIRED) {
+      auto put = [&](int n0, const float (&y)[4]) {
+        if (a.Yp) put_packed4(a.Yp, (size_t)a.MT * a.KTp * 512, a.KTp, m, n0, y);
+        else *(float4*)(a.Y + (size_t)m * a.ldy + n0) = make_float4(y[0], y[1], y[2], y[3]);
+      };
+      if constexpr (PAIRED) {
         // a 16-row block holds the gate rows (0..7) and the up rows (8..15) of 8 outputs: register groups 0, 1 are
         // gate and up of the first block's outputs 4 (l / 32) .. + 3, groups 2, 3 of the second block's
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
-          const int nt = nt0 + 2 * i + hb;
-          if (nt >= a.NT) continue;
-          const int n0 = nt * 8 + 4 * lh;
+          const int n0 = (nt0 + 2 * i + hb) * 8 + 4 * lh;
           if (n0 >= a.ntot) continue;
           float y[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const int n = n0 + q < a.ntot ? n0 + q : a.ntot - 1;
-            const float bg = B0 ? bf16_to_f32(B0[n]) : 0.f, bu = B1 ? bf16_to_f32(B1[n]) : 0.f;
-            y[q] = n0 + q < a.ntot ? silu(acc[i][j][8 * hb + q] + bg) * (acc[i][j][8 * hb + 4 + q] + bu) : 0.f;
+            const float bg = B0 ? bf16_to_f32(B0[n0 + q]) : 0.f, bu = B1 ? bf16_to_f32(B1[n0 + q]) : 0.f;
+            y[q] = silu(acc[i][j][8 * hb + q] + bg) * (acc[i][j][8 * hb + 4 + q] + bu);
           }
-          if (a.Yp) { put_packed4(a.Yp, (size_t)a.MT * a.KTp * 512, a.KTp, m, n0, y); continue; }
-          float* py = a.Y + (size_t)m * a.ldy + n0;
-          if (n0 + 3 < a.ntot) *(float4*)py = make_float4(y[0], y[1], y[2], y[3]);
-          else for (int q = 0; q < 4; ++q) if (n0 + q < a.ntot) py[q] = y[q];
+          put(n0, y);
         }
       } else {
 #pragma unroll
-        for (int gq4 = 0; gq4 < 4; ++gq4) {
-          const int n0 = (nt0 + 2 * i) * 16 + 8 * gq4 + 4 * lh;
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int n0 = (nt0 + 2 * i) * 16 + 8 * q4 + 4 * lh;
           if (n0 >= a.ntot) continue;
           float y[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const int n = n0 + q < a.ntot ? n0 + q : a.ntot - 1;
             float bv = 0.f;
             if (B0) {
-              int seg = 0, loc = n;
+              int seg = 0, loc = n0 + q;
               if (loc >= a.N[0]) { loc -= a.N[0]; seg = 1; if (loc >= a.N[1]) { loc -= a.N[1]; seg = 2; } }
               bv = bf16_to_f32((seg == 0 ? B0 : (seg == 1 ? B1 : B2))[loc]);
             }
-            float tv = acc[i][j][4 * gq4 + q] + bv;
+            float tv = acc[i][j][4 * q4 + q] + bv;
             if (a.act == 1) tv = gelu_erf(tv);
             else if (a.act == 2) tv = fmaxf(tv, 0.f);
-            if (a.Rsd) tv += a.Rsd[(size_t)m * a.ldy + n];
-            y[q] = n0 + q < a.ntot ? tv : 0.f;
+            if (a.Rsd) tv += rsd[i & 1][j][q4][q];
+            y[q] = tv;
           }
-          if (a.Yp) { put_packed4(a.Yp, (size_t)a.MT * a.KTp * 512, a.KTp, m, n0, y); continue; }
-          float* py = a.Y + (size_t)m * a.ldy + n0;
-          if (n0 + 3 < a.ntot) *(float4*)py = make_float4(y[0], y[1], y[2], y[3]);
-          else for (int q = 0; q < 4; ++q) if (n0 + q < a.ntot) py[q] = y[q];
+          put(n0, y);
         }
       }
     }
   }
 }
+#endif
 
 // ---- a prompt chunk of up to 32 rows: one pass over the weights, bound by their stream
 // The arithmetic is gemm_mfma_kernel's (wave w of 8 owns one eighth of the reduction length; first terms, then second
@@ -794,7 +819,9 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
 
 // launchers (ppd_prefill.hip)
 hipError_t launch_pack_rows(hipStream_t stream, const PackArgs& a);
-hipError_t launch_pgemm(hipStream_t stream, PGemmArgs a, bool paired);
+PGemmPlan plan_pgemm(int M, int KT, int NT);
+hipError_t launch_pgemm(hipStream_t stream, PGemmArgs a, bool paired, PGemmPlan plan);
+hipError_t pgemm_setup(PGemmPlan plan, bool paired);
 hipError_t launch_rgemm(hipStream_t stream, RGemmArgs a, bool paired);
 hipError_t rgemm_setup();
 hipError_t launch_pkv_pack(hipStream_t stream, const PKvPackArgs& a, int head_dim);
