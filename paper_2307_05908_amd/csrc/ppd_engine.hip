@@ -103,7 +103,7 @@ struct ppd_ctx {
   int gmax1, gmax2;      // workgroup budget of an fp32 GEMM launch: one group / per group of a two-group launch
   int nchunk_max;
   // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
-  int fused, fused_grid, fused_lds, device;
+  int fused, fused_grid, fused_lds, fused_narrow, device;
   int chain;             // the round under way uses it
   int chain_pause;       // rounds that go without it after a launch gave up
   FusedArgs fused_args;
@@ -544,7 +544,7 @@ bool fused_plan(ppd_ctx* c) {
   const bool swiglu = d.act == 2;
   FusedArgs& a = c->fused_args;
   memset(&a, 0, sizeof a);
-  int tiles = 0, xmax = 0;
+  int tiles = 0, xmax = 0, most = 0;
   auto ph = [&](int i, int K, int ntot, int norm, bool paired, int act) {
     FPhase& p = a.ph[i];
     p.K = K; p.KT = (K + 31) / 32; p.NT = paired ? (ntot + 7) / 8 : (ntot + 15) / 16; p.ntot = ntot; p.nseg = i == 0 ? dm : ntot;
@@ -552,12 +552,14 @@ bool fused_plan(ppd_ctx* c) {
     p.wbytes = (unsigned)((size_t)p.NT * p.KT * 1024);
     const int nb8 = (p.KT + MG_WAVES - 1) / MG_WAVES, nbt = (nb8 + MG_BATCH - 1) / MG_BATCH;
     p.inv = (65536 + nbt - 1) / nbt;
+    if ((p.NT + G - 1) / G * nbt > most) most = (p.NT + G - 1) / G * nbt;
     if ((p.NT + G - 1) / G > tiles) tiles = (p.NT + G - 1) / G;
     if (p.KT * 128 > xmax) xmax = p.KT * 128;
     return (size_t)p.NT * p.KT * 1024 <= 0x7fffffffu;
   };
   if (!ph(0, dm, 3 * dm, d.norm, false, 0) || !ph(1, dm, dm, -1, false, 0) ||
       !ph(2, dm, F, d.norm, swiglu, swiglu ? 0 : (d.act == 0 ? 1 : 2)) || !ph(3, F, dm, -1, false, 0)) return false;
+  c->fused_narrow = most <= FU_RING;
   a.L = c->fl_tab;
   a.off_res = FU_LDS_G + fu_gain_bytes(dm) * (d.norm == 0 ? 2 : 1);
   a.off_part = a.off_res + (a.ph[1].NT + G - 1) / G * 64;
@@ -578,7 +580,7 @@ int run_main_row(ppd_ctx* c, int from, int to, int pmax) {
   if (c->chain) {
     FusedArgs a = c->fused_args;
     a.layer0 = from; a.nsteps = to - from;
-    HIPCHK(c, launch_fused(c->cur, a, c->d.head_dim, c->fused_grid, c->fused_lds));
+    HIPCHK(c, launch_fused(c->cur, a, c->d.head_dim, c->fused_narrow != 0, c->fused_grid, c->fused_lds));
     return PPD_OK;
   }
   for (int l = from; l < to; ++l) {
@@ -1232,7 +1234,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     if (e == hipSuccess) e = hipMemcpy(c->fl_tab, tab.data(), d.n_layers * sizeof(FLayer), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemsetD32(c->fl_part, (int)FU_EMPTY, npart);
     if (e == hipSuccess && fused_plan(c)) {
-      e = fused_setup(d.head_dim, c->fused_lds);
+      e = fused_setup(d.head_dim, c->fused_narrow != 0, c->fused_lds);
       c->fused = 1;
     }
   }

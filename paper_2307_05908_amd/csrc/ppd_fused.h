@@ -42,6 +42,11 @@ constexpr int FU_PACE = 8;                         // a wave requests a batch wh
 constexpr int FU_PACE_AHEAD = 0;                   // the same for what is requested ahead of a step (the helpers' few accesses
                                                    // go through the same queue)
 constexpr int FU_RING = 6;                         // register batches of MG_BATCH KiB per multiplying wave
+// NARROW instances of the kernel: every workgroup's share of every product fits the ring, so a layer is latency and no stream.
+// What is requested ahead goes out at once and only what is wanted, where the others wait for one batch before they request
+// the next, wanted or not: six memory latencies in the way of each product.  Measured (a plain token, us per layer,
+// without / with): OPT-like 256 wide 24.0 / 22.7, 768 28.4 / 26.1, 1024 29.9 / 27.1, LLaMA-like 512 27.0 / 25.2, 1024 30.1 / 28.4,
+// 2048 39.0 / 38.1; where shares do not fit: 2560 46.8 / 48.7, 4096 79.3 / 84.4.
 constexpr int FU_KV = FU_RING - 4;                 // the last four take an attention item's keys and values
 constexpr int FU_SLEEP = 4;                        // 64 clocks each, between two looks at pieces of a row that are not there yet
 constexpr int FU_MAX_WG = 256;
@@ -372,12 +377,13 @@ __device__ __forceinline__ void fu_help_attention(const FWg& w, FHelper& hp, int
 template <int PACE>
 __device__ __forceinline__ void fu_request(u32x4 (&buf)[MG_BATCH], unsigned lane16, const char* P, unsigned bytes, unsigned o, int n) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)P, 0, (int)bytes, 0x00020000);
-  __builtin_amdgcn_s_waitcnt(0xF70 | PACE);        // vmcnt(PACE)
+  if constexpr (PACE < 16) __builtin_amdgcn_s_waitcnt(0xF70 | PACE);        // vmcnt(PACE)
 #pragma unroll
   for (int j = 0; j < MG_BATCH; ++j) buf[j] = __builtin_amdgcn_raw_buffer_load_b128(r, lane16 + j * 1024u, j < n ? o : 0u, 2);   // 2: non-temporal
 }
 #define FU_REQUEST(slot, q) do { const FReq q_ = (q); fu_request<FU_PACE>(ring[slot], lane16, q_.P, q_.bytes, q_.o, q_.n); } while (0)
-#define FU_AHEAD(slot, q) do { const FReq q_ = (q); fu_request<FU_PACE_AHEAD>(ring[slot], lane16, q_.P, q_.bytes, q_.o, q_.n); } while (0)
+#define FU_AHEAD(slot, q) do { const FReq q_ = (q); if constexpr (!NARROW) fu_request<FU_PACE_AHEAD>(ring[slot], lane16, q_.P, q_.bytes, q_.o, q_.n); \
+    else if (q_.n > 0) fu_request<63>(ring[slot], lane16, q_.P, q_.bytes, q_.o, q_.n); } while (0)
 __device__ __forceinline__ FSeg fu_seg(const FWg& w, int i, int layer) {
   const auto& p = w.a->ph[i];
   const int KT = p.KT, nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
@@ -511,7 +517,7 @@ __device__ __forceinline__ FReq fu_current(FCursor& k, const FSeg& s) {
 }
 
 // One product: its first FU_RING batches are in the ring (slot j holds batch j), its end leaves the next one's there.
-template <int HD>
+template <int HD, bool NARROW>
 __device__ __forceinline__ void fu_product(const FWg& w, u32x4 (&ring)[FU_RING][MG_BATCH], uint32_t& tiles, int i, const FSeg& s, const FSeg& nx, int layer) {
   const int Q = s.Q;
   const int lane = fu_here(w.tid) & 63;
@@ -741,7 +747,7 @@ __device__ __forceinline__ void fu_attention(const FWg& w, u32x4 (&ring)[FU_RING
   fu_bar();
 }
 
-template <int HD>
+template <int HD, bool NARROW>
 __global__ __launch_bounds__(FU_THREADS) void decode_layers_kernel(FusedArgs args) {
   FWg w;
   w.a = (FArgs)__builtin_amdgcn_kernarg_segment_ptr();
@@ -798,7 +804,7 @@ __global__ __launch_bounds__(FU_THREADS) void decode_layers_kernel(FusedArgs arg
     const FSeg s = fu_seg(w, i, layer);
     FSeg nx = fu_seg(w, (i + 1) & 3, i == 3 && !end ? layer + 1 : layer);
     if (end) nx.Q = 0;
-    fu_product<HD>(w, ring, tiles, i, s, nx, layer);
+    fu_product<HD, NARROW>(w, ring, tiles, i, s, nx, layer);
     if (i == 0) {
       fu_attention<HD>(w, ring, wait, n >> 2, layer);
 #pragma unroll
@@ -809,7 +815,7 @@ __global__ __launch_bounds__(FU_THREADS) void decode_layers_kernel(FusedArgs arg
 #endif
 
 // launcher (ppd_fused.hip); grid: one workgroup per compute unit
-hipError_t launch_fused(hipStream_t stream, const FusedArgs& a, int head_dim, int grid, int lds);
-hipError_t fused_setup(int head_dim, int lds);
+hipError_t launch_fused(hipStream_t stream, const FusedArgs& a, int head_dim, bool narrow, int grid, int lds);
+hipError_t fused_setup(int head_dim, bool narrow, int lds);
 
 }  // namespace ppd
