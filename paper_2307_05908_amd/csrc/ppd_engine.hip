@@ -221,6 +221,55 @@ constexpr int PREFILL_CHUNK_FP32 = 8;
 // ---- bf16 models: MFMA GEMM on repacked weights
 constexpr size_t MG_LDS_MAX = 160 * 1024;
 
+// Products of narrow models (gemm_mfma_narrow_kernel): the tiles of a workgroup, 0 where the streaming kernel is the better one.
+// Up to 1024 columns a workgroup takes up to four tiles, so that there are no more of them than compute units; from there to 2048
+// (4096 without a norm) one, whose blocks fill the registers, and past some number of workgroups their turns cost more than the
+// streaming kernel's prologue does.  Measured (a PPD round of 12 layers, us, streaming / this kernel with up to 400, 700, 1100
+// workgroups): LLaMA-like 1280 wide, k = 3 430 / 403 392 384, 1536 543 / 526 513 501, 1792 556 / 540 525 529, 2048 593 / 575 573
+// 577; k = 8 1536 609 / 588 573 570, 2048 645 / 626 626 638.  Up to 256 workgroups with several tiles against 512 (narrower
+// models): 0.5 - 1 us a layer.
+int narrow_tiles(const MGemmArgs& a, int ngroups, int mmax) {
+  const int nb8 = (a.KT + MG_WAVES - 1) / MG_WAVES;
+  if (a.topk > 0 || mmax > MG_NARROW_ROWS || nb8 > (a.norm >= 0 ? 8 : 16)) return 0;
+  if (a.norm == 0) for (int g = 0; g < ngroups; ++g) if (!a.g[g].nb) return 0;
+  int t = 1;
+  while (nb8 <= 4 && t < 4 && (a.NT + t - 1) / t * ngroups > 256) t *= 2;
+  return (a.NT + t - 1) / t * ngroups <= (mmax <= 4 ? 1100 : 700) ? t : 0;
+}
+
+template <bool PAIRED, int NORM, int T, int NB>
+hipError_t narrow_go(hipStream_t st, const MGemmArgs& a, dim3 grid, int lds) {
+  const auto k = gemm_mfma_narrow_kernel<PAIRED, NORM, T, NB>;
+  if (a.KT == 0) return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);   // (setup)
+  hipLaunchKernelGGL(k, grid, dim3(MG_THREADS), lds, st, a);
+  return hipGetLastError();
+}
+template <bool PAIRED, int NORM>
+hipError_t narrow_go_t(hipStream_t st, const MGemmArgs& a, int nb8, int t, dim3 grid, int lds) {
+  if (nb8 <= 4)
+    return t == 1 ? narrow_go<PAIRED, NORM, 1, 4>(st, a, grid, lds) : (t == 2 ? narrow_go<PAIRED, NORM, 2, 4>(st, a, grid, lds) : narrow_go<PAIRED, NORM, 4, 4>(st, a, grid, lds));
+  if (nb8 <= 8) return narrow_go<PAIRED, NORM, 1, 8>(st, a, grid, lds);
+  if constexpr (NORM < 0) return narrow_go<PAIRED, NORM, 1, 16>(st, a, grid, lds);
+  return hipErrorInvalidValue;
+}
+hipError_t narrow_launch(hipStream_t st, const MGemmArgs& a, bool paired, int nb8, int t, dim3 grid, int lds) {
+  if (a.norm == 0) return paired ? narrow_go_t<true, 0>(st, a, nb8, t, grid, lds) : narrow_go_t<false, 0>(st, a, nb8, t, grid, lds);
+  if (a.norm == 1) return paired ? narrow_go_t<true, 1>(st, a, nb8, t, grid, lds) : narrow_go_t<false, 1>(st, a, nb8, t, grid, lds);
+  return paired ? hipErrorInvalidValue : narrow_go_t<false, -1>(st, a, nb8, t, grid, lds);
+}
+// the instances whose rows may take more LDS than a launch has by default (at most 8 rows of 4096: 134 KiB)
+hipError_t narrow_setup(int norm) {
+  MGemmArgs a; memset(&a, 0, sizeof a);
+  hipError_t e = hipSuccess;
+  for (const int nb8 : {8, 16}) {
+    a.norm = -1;
+    if (e == hipSuccess) e = narrow_launch(nullptr, a, false, nb8, 1, dim3(1), 0);
+  }
+  a.norm = norm;
+  for (const bool paired : {false, true}) if (e == hipSuccess) e = narrow_launch(nullptr, a, paired, 8, 1, dim3(1), 0);
+  return e;
+}
+
 // One logical GEMM for one or two row groups.  Everything goes into one launch when the staged rows of
 // the largest group fit LDS; otherwise every group is launched on its own, its rows in slices that fit
 // (each slice streams the weights again).
@@ -230,6 +279,11 @@ hipError_t launch_mgemm(ppd_ctx* c, MGemmArgs& a, int ngroups, bool paired) {
   a.wbytes = (unsigned)((size_t)a.NT * a.KT * 1024);
   int mmax = a.g[0].M;
   if (ngroups == 2 && a.g[1].M > mmax) mmax = a.g[1].M;
+  if (c->mg_passes_min == 1 && !(paired && a.norm < 0))
+    if (const int t = narrow_tiles(a, ngroups, mmax)) {
+      a.xrow = mg_xrow(a.KT);
+      return narrow_launch(c->cur, a, paired, (a.KT + MG_WAVES - 1) / MG_WAVES, t, dim3((a.NT + t - 1) / t, ngroups), mg_narrow_lds(a.KT, mmax, t));
+    }
   auto lds_with = [&](int M, int tiles, int passes) {
     int b, p, x;
     return (size_t)mg_lds_layout(a.K, M, a.norm, tiles, mg_xrow_pass(a.KT, passes), b, p, x);
@@ -1184,6 +1238,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = rgemm_setup();
+    if (e == hipSuccess) e = narrow_setup(d.norm);
     // the prompt pass's products with one tile shape (1 ..) and one cut of the reduction length (tests)
     c->pg_tile = env_int("PPD_PG_TILE", 0) - 1;
     c->pg_parts = env_int("PPD_PG_PARTS", 0);

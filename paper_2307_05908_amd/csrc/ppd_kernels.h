@@ -2181,4 +2181,189 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
   }
 }
 
+// Products of narrow models: a launch is a chain of latencies, not a stream.  A workgroup makes T tiles (blockIdx.x, + gridDim.x,
+// ...) and requests every operand of them at once: rows, gains, all of its weights (T NB blocks in each wave's registers), biases,
+// residuals.  The rows are worked on in units of 64 pieces of eight elements, a wave's part of one row in the norm's order of
+// additions; a wave has every eighth unit, so that no element is normalised or split twice in a workgroup, and the
+// statistics of all rows are made at the same time.  The arithmetic, and every order of additions, is gemm_mfma_kernel's.
+// Measured (two groups, us a layer of the parallel phase with its attention, gemm_mfma_kernel / this one): OPT-125m shape k = 3
+// 40 / 28, k = 8 49 / 30; 512 wide 34 / 18 and 46 / 21; each wave normalising its own blocks of all rows in registers, without a
+// barrier, was the slower way (k = 3 34): half of what a compute unit issued then were the same normalisations again.
+// NORM: -1 none, 0 LayerNorm (with a bias), 1 RMSNorm; NB: blocks of a wave's share at most.
+constexpr int MG_NARROW_ROWS = 8;            // of a group
+constexpr int MG_NARROW_LDS = 512;           // [2][MG_NARROW_ROWS][8] sums of the norm, then the partial sums, then the rows
+__host__ __device__ inline int mg_narrow_lds(int KT, int M, int T) { return MG_NARROW_LDS + T * MG_WAVES * M * 64 + M * mg_xrow(KT); }
+template <bool PAIRED, int NORM, int T, int NB>
+__global__ __launch_bounds__(MG_THREADS) void gemm_mfma_narrow_kernel(MGemmArgs a) {
+  extern __shared__ float4 lds4[];
+  char* const lds = (char*)lds4;
+  const MGemmGroup& G = a.g[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int M = G.M, K = a.K, KT = a.KT, grid = gridDim.x, xrow = a.xrow;
+  float* const red = (float*)lds;
+  float* const part = (float*)(lds + MG_NARROW_LDS);                   // [T][8 waves][M][16]
+  char* const xs = lds + MG_NARROW_LDS + T * MG_WAVES * M * 64;
+  // ---- requests.  Unit u: row u / nv, pieces 64 (u % nv) ..
+  constexpr int UM = MG_NARROW_ROWS * ((NB + 1) / 2) / MG_WAVES;       // units of a wave at most
+  const int nv = (K + 511) / 512, units = M * nv;
+  float x[UM][8]; u32x4 gq[UM], bq[UM];
+  auto unit = [&](int i, int& m, int& c) { const int u = wave + i * MG_WAVES; m = u / nv; c = (u - m * nv) * WAVE + lane; };
+#pragma unroll
+  for (int i = 0; i < UM; ++i)
+    if (wave + i * MG_WAVES < units) {
+      int m, c; unit(i, m, c);
+      const int k = c * 8 < K ? c * 8 : 0;
+      const float4* const px = (const float4*)(G.X + (size_t)m * a.ldx + k);
+      const float4 v = px[0], w = px[1];
+      x[i][0] = v.x; x[i][1] = v.y; x[i][2] = v.z; x[i][3] = v.w; x[i][4] = w.x; x[i][5] = w.y; x[i][6] = w.z; x[i][7] = w.w;
+      if constexpr (NORM >= 0) gq[i] = *(const u32x4*)((const uint16_t*)G.ng + k);
+      if constexpr (NORM == 0) bq[i] = *(const u32x4*)((const uint16_t*)G.nb + k);
+    }
+  const int nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
+  const int kb0 = wave * nb8 < KT ? wave * nb8 : KT;
+  const int nblk = (kb0 + nb8 < KT ? kb0 + nb8 : KT) - kb0;
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)G.P, 0, (int)a.wbytes, 0x00020000);
+  u32x4 w[T][NB];                              // (blocks past the share or the last tile re-read the start: never used)
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int tile = (int)blockIdx.x + t * grid;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      w[t][j] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16u, tile < a.NT && j < nblk ? (unsigned)(tile * KT + kb0 + j) * 1024u : 0u, 2);   // 2: non-temporal
+  }
+  // bias and residual of the output this thread will finish: row of the tile, row of the input, tile
+  constexpr int R = PAIRED ? 8 : 16;
+  const int orow = tid & (R - 1), ord = tid / R / M, ocol = tid / R - ord * M, n = ((int)blockIdx.x + ord * grid) * R + orow;
+  const bool out = ord < T && n < a.ntot;
+  const uint16_t* const B0 = (const uint16_t*)G.B[0];
+  const uint16_t* const B1 = (const uint16_t*)G.B[1];
+  const uint16_t* const B2 = (const uint16_t*)G.B[2];
+  uint32_t b0 = 0u, b1 = 0u; float rsd = 0.f;
+  if (out) {
+    if (PAIRED) {
+      if (B0) b0 = B0[n];
+      if (B1) b1 = B1[n];
+    } else if (B0) {
+      int seg = 0, loc = n;
+      if (loc >= a.N[0]) { loc -= a.N[0]; seg = 1; if (loc >= a.N[1]) { loc -= a.N[1]; seg = 2; } }
+      b0 = (seg == 0 ? B0 : (seg == 1 ? B1 : B2))[loc];
+    }
+    if (G.Rsd) rsd = G.Rsd[(size_t)ocol * a.ldy + n];
+  }
+  // ---- statistics: a unit's 64 pieces by butterfly, a row's units in order (what the norm's idle waves would add is zero)
+  auto combine = [&](const float* r) { float s = r[0]; for (int v = 1; v < nv; ++v) s += r[v]; return s + 0.f; };
+  float mu[UM], rs[UM];
+#pragma unroll
+  for (int i = 0; i < UM; ++i) { mu[i] = 0.f; rs[i] = 1.f; }
+  if constexpr (NORM == 0) {
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+      if (wave + i * MG_WAVES < units) {
+        int m, c; unit(i, m, c);
+        float sm = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sm += x[i][e];
+        sm = wave_sum(c * 8 < K ? sm : 0.f);
+        if (lane == 0) red[m * 8 + (c >> 6)] = sm;
+      }
+    __syncthreads();
+  }
+  if constexpr (NORM >= 0) {
+    float* const redB = red + MG_NARROW_ROWS * 8;
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+      if (wave + i * MG_WAVES < units) {
+        int m, c; unit(i, m, c);
+        if constexpr (NORM == 0) mu[i] = combine(red + m * 8) / (float)K;
+        float s2 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { const float d = x[i][e] - mu[i]; s2 = fmaf(d, d, s2); }
+        s2 = wave_sum(c * 8 < K ? s2 : 0.f);
+        if (lane == 0) redB[m * 8 + (c >> 6)] = s2;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+      if (wave + i * MG_WAVES < units) {
+        int m, c; unit(i, m, c);
+        rs[i] = 1.0f / sqrtf(combine(redB + m * 8) / (float)K + a.eps);
+      }
+  }
+  // ---- normalised, in two bf16 terms: hi(k .. k + 7) | lo(k .. k + 7) of a piece in 32 bytes
+#pragma unroll
+  for (int i = 0; i < UM; ++i)
+    if (wave + i * MG_WAVES < units) {
+      int m, c; unit(i, m, c);
+      float xv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xv[e] = x[i][e];
+      if constexpr (NORM >= 0) {
+        float gf[8]; WTr<bf16_t>::unpack(gq[i], gf);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xv[e] = (xv[e] - mu[i]) * rs[i] * gf[e];
+      }
+      if constexpr (NORM == 0) {
+        float bf[8]; WTr<bf16_t>::unpack(bq[i], bf);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xv[e] += bf[e];
+      }
+      uint32_t hp[4], lp[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){xv[2 * e], xv[2 * e + 1]}, bf16x2));
+        const float r0 = xv[2 * e] - __uint_as_float(hp[e] << 16), r1 = xv[2 * e + 1] - __uint_as_float(hp[e] & 0xffff0000u);
+        lp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
+      }
+      const bool in = c * 8 < K;
+      if (c < KT * 4) {
+        uint4* const px = (uint4*)(xs + m * xrow + c * 32);
+        px[0] = in ? make_uint4(hp[0], hp[1], hp[2], hp[3]) : make_uint4(0u, 0u, 0u, 0u);
+        px[1] = in ? make_uint4(lp[0], lp[1], lp[2], lp[3]) : make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+  __syncthreads();
+  // ---- multiply: lane l feeds column l % 16 (input row; lanes past M read row 0), the eight k of piece l / 16 of a block
+  const int bm = lane & 15, bc = lane >> 4;
+  const char* const xlane = xs + (bm < M ? bm : 0) * xrow + bc * 32 + kb0 * 128;
+  f32x4 acc[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    if (j < nblk) {                            // the same for the whole wave
+      const u32x4* const xp = (const u32x4*)(xlane + j * 128);
+      const bf16x8 bh = __builtin_bit_cast(bf16x8, xp[0]), bl = __builtin_bit_cast(bf16x8, xp[1]);
+#pragma unroll
+      for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t][j]), bh, acc[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t][j]), bl, acc[t], 0, 0, 0);
+    }
+  // lane l holds rows 4 (l / 16) .. + 3 of the tile for input row l % 16
+  if (bm < M)
+#pragma unroll
+    for (int t = 0; t < T; ++t) *(f32x4*)(part + ((t * MG_WAVES + wave) * M + bm) * 16 + bc * 4) = acc[t];
+  __syncthreads();
+  // ---- the eight partials of an output in wave order, bias, activation, residual
+  if (!out) return;
+  const float c0 = __uint_as_float(b0 << 16), c1 = __uint_as_float(b1 << 16);
+  const float* const pp = part + (ord * MG_WAVES * M + ocol) * 16 + orow;
+  float s = pp[0];
+#pragma unroll
+  for (int v = 1; v < MG_WAVES; ++v) s += pp[v * M * 16];
+  float y;
+  if (PAIRED) {
+    float u = pp[8];
+#pragma unroll
+    for (int v = 1; v < MG_WAVES; ++v) u += pp[v * M * 16 + 8];
+    y = silu(s + c0) * (u + c1);
+  } else {
+    y = s + c0;
+    if (a.act == 1) y = gelu_erf(y);
+    else if (a.act == 2) y = fmaxf(y, 0.f);
+  }
+  y += rsd;
+  G.Y[(size_t)ocol * a.ldy + n] = y;
+}
+
 }  // namespace ppd
