@@ -98,8 +98,8 @@ struct ppd_ctx {
   // captured rounds, with one launch per step of a layer and with the one-launch chain: 0 ppd round from layer 1,
   // 1 ppd round after a match, 2 plain step, 3 ppd round after a match whose candidates were predicted by the round before
   int use_graphs;
-  hipGraphExec_t graph[2][4];
-  int graph_chunks[2][4];   // attention grid (64-position chunks) each graph was captured with
+  hipGraphExec_t graph[2][2][4];  // [chain][past the short sequences (ATT_WHOLE chunks)][kind]
+  int graph_chunks[2][2][4];      // attention grid (64-position chunks) each graph was captured with
   int gmax1, gmax2;      // workgroup budget of an fp32 GEMM launch: one group / per group of a two-group launch
   int nchunk_max;
   // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
@@ -380,6 +380,9 @@ hipError_t mgemm_from(ppd_ctx* c, const GemmArgs& a, int ngroups, bool paired, v
   return launch_mgemm(c, m, ngroups, paired);
 }
 
+// Whether a head's few chunks go to one workgroup that merges them, too
+bool attn_whole_fits(int mmax, int pmax) { return mmax <= MAXM && pmax < ATT_WHOLE * ATT_CHUNK; }
+
 // A row group of one layer step: which layer, how many rows, first row in the
 // activation buffers, absolute position, and where the rows' own K/V go.
 struct RowGroup {
@@ -450,12 +453,19 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     a.rope = d.pos == 1 ? c->rope : nullptr;
     a.H = d.n_heads; a.d_model = dm; a.max_ctx = d.max_ctx; a.nchunk_max = c->nchunk_max;
     a.scale = 1.0f / sqrtf((float)d.head_dim);
-    { ProfScope ps(c, PPD_KC_ATTN, ngroups); HIPCHK(c, launch_attn(c, a, ngroups, pmax)); }
-    mg.H = d.n_heads; mg.HD = d.head_dim; mg.d_model = dm; mg.nchunk_max = c->nchunk_max;
     int mmax = rg[0].M; if (ngroups == 2 && rg[1].M > mmax) mmax = rg[1].M;
-    ProfScope ps(c, PPD_KC_ATTN_MERGE, ngroups);
-    hipLaunchKernelGGL(attn_merge_kernel, dim3(mmax, d.n_heads, ngroups), dim3(MERGE_THREADS), 0, c->cur, mg);
-    HIPCHK(c, hipGetLastError());
+    const bool whole = !rg[0].chunk && attn_whole_fits(mmax, pmax);
+    if (whole) {
+      const AttnWholeArgs w = {a, {mg.out[0], mg.out[1]}};
+      ProfScope ps(c, PPD_KC_ATTN, ngroups);
+      HIPCHK(c, d.head_dim == 64 ? launch_attn_whole<64>(c->cur, w, mmax, ngroups) : launch_attn_whole<128>(c->cur, w, mmax, ngroups));
+    } else {
+      { ProfScope ps(c, PPD_KC_ATTN, ngroups); HIPCHK(c, launch_attn(c, a, ngroups, pmax)); }
+      mg.H = d.n_heads; mg.HD = d.head_dim; mg.d_model = dm; mg.nchunk_max = c->nchunk_max;
+      ProfScope ps(c, PPD_KC_ATTN_MERGE, ngroups);
+      hipLaunchKernelGGL(attn_merge_kernel, dim3(mmax, d.n_heads, ngroups), dim3(MERGE_THREADS), 0, c->cur, mg);
+      HIPCHK(c, hipGetLastError());
+    }
   }
   // 3. output projection + residual
   if (stages & 2) {
@@ -804,7 +814,7 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
 // the captured rounds are captured anew
 hipError_t drop_graphs(ppd_ctx* c) {
   hipError_t e = hipSuccess;
-  for (auto& set : c->graph)
+  for (auto& chain : c->graph) for (auto& set : chain)
     for (hipGraphExec_t& g : set) if (g) {
       const hipError_t e1 = hipGraphExecDestroy(g);
       if (e == hipSuccess) e = e1;
@@ -848,14 +858,15 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   if (c->dev_pos_pending != pos && (rc = set_state(c, pos, -1))) return rc;
   const int pmax = pos + (kind == 2 ? 0 : 1);
   if (c->use_graphs && !c->prof && !again) {
-    // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least 4,
-    // at most the cache's), so that a sequence re-captures a handful of times instead of every 64 positions;
-    // chunks past a row's position return at once.
-    int nchunks = 4;
+    // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least ATT_WHOLE, which
+    // has a kernel and a graph of its own, then 4, at most the cache's), so that a sequence re-captures a handful of times
+    // instead of every 64 positions; chunks past a row's position return at once.
+    int nchunks = ATT_WHOLE;
     while (nchunks < pmax / ATT_CHUNK + 1) nchunks *= 2;
     if (nchunks > c->nchunk_max) nchunks = c->nchunk_max;
-    hipGraphExec_t& graph = c->graph[c->chain][kind];
-    int& graph_chunks = c->graph_chunks[c->chain][kind];
+    const int longer = nchunks > ATT_WHOLE;
+    hipGraphExec_t& graph = c->graph[c->chain][longer][kind];
+    int& graph_chunks = c->graph_chunks[c->chain][longer][kind];
     if (graph && graph_chunks < nchunks) {
       HIPCHK(c, hipGraphExecDestroy(graph));
       graph = nullptr;
@@ -1262,6 +1273,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
       c->spec = 2 * c->dbar == d.n_layers && !c->early_head && need <= MG_LDS_MAX && env_int("PPD_SPEC", 1) != 2;
     }
   }
+  if (e == hipSuccess) { const AttnWholeArgs w{}; e = d.head_dim == 64 ? launch_attn_whole<64>(nullptr, w, 0, 0) : launch_attn_whole<128>(nullptr, w, 0, 0); }
   // the main token's layers in one launch, one workgroup per compute unit (PPD_FUSED=2: one launch per step; PPD_MGPASSES
   // asks for the launches whose staging passes it sets)
   if (e == hipSuccess) e = hipGetDevice(&c->device);

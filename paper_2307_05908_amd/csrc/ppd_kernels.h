@@ -1003,6 +1003,161 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
   }
 }
 
+// Short sequences (at most ATT_WHOLE chunks of positions): a head of a group is one workgroup's, four waves for every chunk, and the
+// chunks are merged where they are, so that the launch of attn_merge_kernel goes.  The arithmetic of a chunk, and of the merge
+// of one chunk per slice, is those kernels'.  Bound by its chain of latencies (the rows, the cached blocks, four barriers).
+// Measured (a PPD round of a 12-layer model, us, both kernels / this one): fp32 256 wide, k = 3, position 20 196 / 171, 105 214 / 197; OPT-like 768 347 / 329, 362 / 353; LLaMA-like 1024 327 / 311,
+// 389 / 380; 4096 1354 / 1341, 1270 / 1256.  With four chunks to a workgroup the larger one loses what the launch costs: OPT-like
+// 768 at 100 362 / 353, at 200 364 / 365; LLaMA-like 1024 at 200 324 / 340 (and 343 where its idle waves loaded, too).
+constexpr int ATT_WHOLE = 2;
+constexpr int ATT_WHOLE_THREADS = ATT_WHOLE * ATT_THREADS;
+template <int HD> __host__ __device__ constexpr int attn_whole_lds_floats(int M) {
+  return M * (ATT_WHOLE * ATT_WAVES * HD + 3 * HD + ATT_WHOLE * ATT_CHUNK + 2 * ATT_WHOLE + 1);
+}
+struct AttnWholeArgs { AttnArgs a; float* out[2]; };      // out: [M][d_model] of either group
+template <int HD>
+__global__ __launch_bounds__(ATT_WHOLE_THREADS) void attn_whole_kernel(AttnWholeArgs w) {
+  extern __shared__ float4 lds4[];
+  float* lds = (float*)lds4;
+  const AttnArgs& a = w.a;
+  const AttnGroup& G = a.g[blockIdx.y];
+  constexpr int NS = HD / 16, half = HD / 2, WAVES = ATT_WHOLE * ATT_WAVES, POS = ATT_WHOLE * ATT_CHUNK;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = blockIdx.x, p = a.ds->pos + G.pos_off, M = G.M, nc = p / ATT_CHUNK + 1;
+  if (nc > ATT_WHOLE) return;         // (the host launches this kernel for no such position)
+  float* raw = lds;                   // [M][3][HD]
+  float* ored = lds;                  // [WAVES][M][HD], written only after the barriers that follow the rotation
+  float* qs = lds + M * WAVES * HD;   // [M][HD]
+  float* ko = qs + M * HD;            // [M][HD]
+  float* vo = ko + M * HD;            // [M][HD]
+  float* sc = vo + M * HD;            // [M][POS]
+  float* st = sc + M * POS;           // [M][ATT_WHOLE][2]: largest score, sum of a chunk
+  float* so = st + M * 2 * ATT_WHOLE; // [M] weight of the own position
+  {
+    const int nfl = M * 3 * HD;
+    for (int f0 = wave * 256; f0 < nfl; f0 += WAVES * 256) {
+      const int f = f0 + lane * 4;
+      if (f < nfl) {
+        const int m = f / (3 * HD), r = f - m * (3 * HD), sec = r / HD, i = r - sec * HD;
+        dma16(G.qkv + (size_t)m * 3 * a.d_model + (size_t)sec * a.d_model + (size_t)h * HD + i, raw + f0);
+      }
+    }
+  }
+  const int ci = tid % HD;
+  float2 cz = make_float2(1.f, 0.f);
+  if (a.rope) cz = a.rope[(size_t)p * half + (ci < half ? ci : ci - half)];
+  // this wave's block, keys, then values; nothing for a chunk past the position
+  const bool mine = wave / ATT_WAVES < nc;
+  const size_t hb = (size_t)h * kv_blocks(a.max_ctx) + (size_t)wave;
+  const char* kb = (const char*)G.Kc + hb * (NS * 1024) + lane * 16;
+  const char* vb = (const char*)G.Vc + hb * (NS * 1024) + lane * 16;
+  f32x4_t kreg[NS], vreg[NS];
+  if (mine) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) kreg[s] = __builtin_nontemporal_load((const f32x4_t*)(kb + s * 1024));
+#pragma unroll
+    for (int s = 0; s < NS; ++s) vreg[s] = __builtin_nontemporal_load((const f32x4_t*)(vb + s * 1024));
+    // the rows' own loads have arrived once only the 2 NS block loads are outstanding
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NS) : "memory");
+  } else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("s_barrier" ::: "memory");
+  for (int idx = tid; idx < M * HD; idx += ATT_WHOLE_THREADS) {
+    const int m = idx / HD, i = idx - m * HD;     // i == ci: ATT_WHOLE_THREADS is a multiple of HD
+    const float* r = raw + m * 3 * HD;
+    float q = r[i], k = r[HD + i];
+    const float v = r[2 * HD + i];
+    if (a.rope) {
+      const int ip = i < half ? i + half : i - half;
+      const float qo = r[ip], kk = r[HD + ip];
+      if (i < half) { q = fmaf(q, cz.x, -(qo * cz.y)); k = fmaf(k, cz.x, -(kk * cz.y)); }
+      else          { q = fmaf(q, cz.x, qo * cz.y);    k = fmaf(k, cz.x, kk * cz.y); }
+    }
+    qs[m * HD + i] = q * a.scale;
+    ko[m * HD + i] = k;
+    vo[m * HD + i] = v;
+  }
+  __syncthreads();
+  // scores of the wave's 16 positions (see attn_kernel)
+  const int bn = lane & 15, bc = lane >> 4;
+  const int bm = bn < M ? bn : 0;
+  if (mine) {
+    f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const f32x4_t q4 = *(const f32x4_t*)(qs + bm * HD + 16 * s + 4 * bc);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sacc = __builtin_amdgcn_mfma_f32_16x16x4f32(kreg[s][u], q4[u], sacc, 0, 0, 0);
+    }
+    if (bn < M) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const int j = 16 * wave + 4 * bc + jj;
+        if (j != p) sc[bn * POS + j] = j < p ? sacc[jj] : -INFINITY;
+      }
+    }
+  }
+  for (int m = wave; m < M; m += WAVES) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < HD / WAVE; ++e) s = fmaf(qs[m * HD + lane + e * WAVE], ko[m * HD + lane + e * WAVE], s);
+    s = wave_sum(s);
+    if (lane == 0) sc[m * POS + p] = s;
+  }
+  __syncthreads();
+  // softmax numerators of a chunk: one wave per row and chunk, one position per lane
+  for (int u = wave; u < M * nc; u += WAVES) {
+    const int m = u / nc, c = u - m * nc, j = c * ATT_CHUNK + lane;
+    const float v = sc[m * POS + j];
+    const float mx = wave_max(v);
+    const float e = expf(v - mx);
+    const float sum = wave_sum(e);
+    sc[m * POS + j] = j == p ? 0.f : e;             // the own position is added outside the MFMAs
+    if (j == p) so[m] = e;
+    if (lane == 0) { st[(m * ATT_WHOLE + c) * 2] = mx; st[(m * ATT_WHOLE + c) * 2 + 1] = sum; }
+  }
+  __syncthreads();
+  // weighted values of the wave's block
+  if (mine) {
+    const f32x4_t p4 = *(const f32x4_t*)(sc + bm * POS + 16 * wave + 4 * bc);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      f32x4_t oacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) oacc = __builtin_amdgcn_mfma_f32_16x16x4f32(vreg[s][u], p4[u], oacc, 0, 0, 0);
+      if (bn < M) *(f32x4_t*)(ored + (wave * M + bn) * HD + 16 * s + 4 * bc) = oacc;
+    }
+  }
+  __syncthreads();
+  // of every chunk the four blocks in wave order and the rows' own position, then the chunks in their order
+  for (int idx = tid; idx < M * HD; idx += ATT_WHOLE_THREADS) {
+    const int m = idx / HD, i = idx - m * HD;
+    const float* const sm = st + m * ATT_WHOLE * 2;
+    float gm = -INFINITY, oo = 0.f, ll = 0.f;
+    for (int c = 0; c < nc; ++c) gm = fmaxf(gm, sm[2 * c]);
+    for (int c = 0; c < nc; ++c) {
+      const float* const oc = ored + ((size_t)c * ATT_WAVES * M + m) * HD + i;
+      float o = oc[0];
+#pragma unroll
+      for (int v = 1; v < ATT_WAVES; ++v) o += oc[(size_t)v * M * HD];
+      if (c == nc - 1) o = fmaf(so[m], vo[m * HD + i], o);
+      const float wgt = expf(sm[2 * c] - gm);
+      oo = fmaf(wgt, o, oo);
+      ll = fmaf(wgt, sm[2 * c + 1], ll);
+    }
+    w.out[blockIdx.y][(size_t)m * a.d_model + (size_t)h * HD + i] = oo / ll;
+    if (G.own_cache) {
+      const size_t base = (size_t)h * kv_blocks(a.max_ctx) * (KV_BLOCK * HD);
+      G.Kc[base + k_index(p, i, HD)] = ko[m * HD + i];
+      G.Vc[base + v_index(p, i, HD)] = vo[m * HD + i];
+    } else {
+      const size_t d = ((size_t)m * a.H + h) * HD + i;
+      G.tailK[d] = ko[m * HD + i];
+      G.tailV[d] = vo[m * HD + i];
+    }
+  }
+}
+
 // Prompt chunk: rows m = 0..M-1 sit at consecutive positions p + m.  Their keys (rotated exactly as the
 // attention kernel rotates a row's own key) and values go into the cache before the chunk's attention runs,
 // so that every row finds the rows before it there.  One workgroup per (row, head), one thread per component.

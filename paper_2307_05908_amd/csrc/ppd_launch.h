@@ -20,6 +20,9 @@ hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups,
 
 template <int HD>
 hipError_t launch_attn_t(hipStream_t stream, const AttnArgs& a, int mmax, dim3 grid, bool causal);
+// attn_whole_kernel; ngroups 0: its LDS is set up
+template <int HD>
+hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups);
 
 // Workgroups per group for a GEMM with `nsets` row sets (gemm_kernel): each workgroup has four waves and
 // every wave takes ceil(nsets / waves) sets, so pick the count in [gmax/2, gmax] that wastes the fewest
