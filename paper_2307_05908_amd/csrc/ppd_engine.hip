@@ -600,6 +600,14 @@ int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
   return PPD_OK;
 }
 
+// Models whose products are all gemm_mfma_narrow_kernel's: there a launch takes no longer than an exchange of the one-launch chain,
+// and the attention is spread over more workgroups.  Measured (a plain token of 12 layers, us, chain / launches, at positions
+// 40 / 600 / 1400): OPT-like 512 wide 301 / 249, 313 / 289, 320 / 296; 768 315 / 280, 330 / 323, 338 / 337; 1024 327 / 271, 341 / 320,
+// 348 / 338; LLaMA-like 384 282 / 250, 299 / 286, 311 / 290; 1024 346 / 293, 365 / 328, 382 / 341.  Up to 320 the chain is within 2 us a
+// layer either way (OPT-like 320 276 / 249, 291 / 289, at 150 274 / 277) and stays.  From 1152 on the chain is the better one past
+// the short sequences (1280 389 / 390 at 600, 407 / 414 at 1400).
+bool launches_pay(const ppd_model_dims& d) { return d.d_model > 320 && d.d_model <= 1024 && d.d_ff <= 4096; }
+
 // The arguments of a one-launch chain of layers on row 0 that do not change, and its layout of a compute unit's LDS; false: it does
 // not fit.
 bool fused_plan(ppd_ctx* c) {
@@ -1277,7 +1285,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   // the main token's layers in one launch, one workgroup per compute unit (PPD_FUSED=2: one launch per step; PPD_MGPASSES
   // asks for the launches whose staging passes it sets)
   if (e == hipSuccess) e = hipGetDevice(&c->device);
-  if (e == hipSuccess && c->mfma && env_int("PPD_FUSED", 1) != 2 && c->mg_passes_min == 1 && c->device < MAX_DEVICES &&
+  if (e == hipSuccess && c->mfma && env_int("PPD_FUSED", 1) != 2 && c->mg_passes_min == 1 && c->device < MAX_DEVICES && !launches_pay(d) &&
       cache_layer_bytes(c) < ((size_t)1 << 32)) {
     int cus = 0;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
