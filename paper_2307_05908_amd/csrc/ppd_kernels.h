@@ -1338,6 +1338,7 @@ constexpr int SAMP_MEMU = 8;     // loads in flight per thread when keys and wei
 constexpr int SAMP_NT = 64;      // thresholds at which sample_weights_kernel leaves mass and count: 1/8 apart down to 4 below the
                                  // largest logit, then 1/4 apart to 12 below
 constexpr int SAMP_CAP = 6144;   // tokens between two thresholds that are searched in LDS
+constexpr int SAMP_SOLO = 512;   // of those, what one wave searches alone
 struct SampleArgs {
   const float* z; int n;     // logits [n]
   int mode, ks;              // 1 top-k sampling (ks kept), 2 top-p sampling
@@ -1379,9 +1380,10 @@ __device__ __forceinline__ double wave_sum_f64(double v) {     // same scheme as
 
 __device__ inline uint32_t samp_threshold(float zmax, int j) { return samp_key(zmax - (j <= 32 ? 0.125f * (float)j : 4.f + 0.25f * (float)(j - 32))); }
 
-// Keys and weights of all tokens, one per thread, and how much lies at or above each threshold (in one fixed order: wave
-// by wave, then workgroup by workgroup).  In the sampling kernel, one workgroup, the exponentials alone took 30 us at 50272
-// tokens and every look at them another 5.
+// Keys and weights of all tokens, one per thread, and how much lies at or above each threshold (in one fixed order: token by
+// token, wave by wave, then workgroup by workgroup).  In the sampling kernel, one workgroup, the exponentials alone took 30 us
+// at 50272 tokens and every look at them another 5.  A sum over the wave's lanes for each threshold was four thousand
+// instructions of every wave: 19 us, 5 now (50272 tokens, logits of standard deviation 4).
 __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs a) {
   constexpr int NW = SAMP_THREADS / WAVE;
   __shared__ float s_red[NW];
@@ -1401,13 +1403,21 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs
   const double w = in ? exp((double)z - (double)mx) : 0.0;
   a.keys[i] = key;
   a.w[i] = w;
-  for (int j = 0; j <= SAMP_NT; ++j) {
-    const bool ge = j < SAMP_NT ? key >= samp_threshold(mx, j) : key != 0u;
-    const unsigned long long b = __ballot(ge);
-    double m = 0.0;
-    if (b) m = wave_sum_f64(ge ? w : 0.0);
-    if (lane == 0) { s_m[wave][j] = m; s_c[wave][j] = __popcll(b); }
+  // lane j has threshold j, and the wave's tokens come by in turn, those below the last threshold left out
+  static_assert(SAMP_NT == WAVE, "a threshold per lane");
+  const uint32_t thr = samp_threshold(mx, lane);
+  double m = 0.0; int c = 0;
+  for (unsigned long long todo = __ballot(key >= samp_threshold(mx, SAMP_NT - 1)); todo; todo &= todo - 1) {
+    const int l = __builtin_ctzll(todo);
+    const double wl = lane_f64(w, l);
+    const bool ge = (uint32_t)__builtin_amdgcn_readlane((int)key, l) >= thr;
+    m += ge ? wl : 0.0;
+    c += ge ? 1 : 0;
   }
+  s_m[wave][lane] = m; s_c[wave][lane] = c;
+  m = wave_sum_f64(w);
+  const int all = __popcll(__ballot(key != 0u));
+  if (lane == 0) { s_m[wave][SAMP_NT] = m; s_c[wave][SAMP_NT] = all; }
   __syncthreads();
   if (tid <= SAMP_NT) {
     double m = 0.0; int c = 0;
@@ -1420,8 +1430,9 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs
 // The draw.  What bounds it is one workgroup's latency: a search first finds the two thresholds its key lies between, collects
 // the tokens between them in LDS (in a fixed order) and fixes the key's bits on those alone; while they are more than
 // SAMP_CAP (a flat softmax, the tail below the last threshold) it looks through all tokens for a bit, until they are fewer.
-// Measured (top-p 0.95), both kernels: 50272 tokens 358 -> 65 + 17 us (bit by bit over all tokens, keys and weights re-read
-// from L2), 32000 tokens 112 -> 51 + 19 us (the same with keys and weights on chip).
+// Measured (top-p 0.95), both kernels: 50272 tokens 358 us bit by bit over all tokens, 65 + 17 with the thresholds; logits of
+// standard deviation 4: 76 + 19 -> 25 + 5 us.  What went: workgroups' sums awaited one by one, a second look at every key where
+// a thread has a token to collect (a memory latency for each of its keys, in turn), a barrier for every bit.
 // In the far tail (p = 0.999, logits of standard deviation 4), 50272 / 32000 / 16000 tokens: every bit over all tokens 306 / 191 /
 // 113 us, until few are left 151 / 106 / 76.
 __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
@@ -1435,17 +1446,30 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   __shared__ double s_gm[SAMP_NT + 1]; __shared__ int s_gc[SAMP_NT + 1];
   __shared__ double s_w[SAMP_CAP];
   __shared__ uint32_t s_key[SAMP_CAP];
+  __shared__ int s_id[SAMP_CAP];
   __shared__ int s_off[NW];
+  __shared__ double s_above; __shared__ uint32_t s_kappa; __shared__ int s_nabove, s_ties;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = a.n;
   float mx = -INFINITY;
   for (int b = tid; b < a.nblk; b += SAMP_THREADS) mx = fmaxf(mx, a.pk_val[(size_t)b * MAXM]);
   mx = wave_max(mx);
   if (lane == 0) s_redf[wave] = mx;
-  if (tid <= SAMP_NT) {
-    double m = 0.0; int c = 0;
+  // (through LDS, by all threads: a thread per threshold waiting for one workgroup's sums after the other took longer)
+  {
+    constexpr int ROWS = SAMP_CAP / (SAMP_NT + 1);
     const int nb = a.npad / SAMP_THREADS;
-    for (int b = 0; b < nb; ++b) { m += a.pm[(size_t)b * (SAMP_NT + 1) + tid]; c += a.pc[(size_t)b * (SAMP_NT + 1) + tid]; }
-    s_gm[tid] = m; s_gc[tid] = c;
+    double m = 0.0; int c = 0;
+    for (int b0 = 0; b0 < nb; b0 += ROWS) {
+      const int rows = nb - b0 < ROWS ? nb - b0 : ROWS, at = b0 * (SAMP_NT + 1);
+      for (int e = tid; e < rows * (SAMP_NT + 1); e += SAMP_THREADS) { s_w[e] = a.pm[at + e]; s_id[e] = a.pc[at + e]; }
+      __syncthreads();
+      if (tid <= SAMP_NT) {
+#pragma unroll 8
+        for (int b = 0; b < rows; ++b) { m += s_w[b * (SAMP_NT + 1) + tid]; c += s_id[b * (SAMP_NT + 1) + tid]; }
+      }
+      __syncthreads();
+    }
+    if (tid <= SAMP_NT) { s_gm[tid] = m; s_gc[tid] = c; }
   }
   __syncthreads();
   mx = s_redf[0];
@@ -1454,6 +1478,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
 
   // ---- mass and number of the tokens whose key is at least kth, every thread gets both: of the nl collected ones, or of all
   int par = 0, nl = 0;
+  bool collected = false;          // the last search's tokens are in LDS, nl of them
   auto sum_up = [&](double m, int c, double& mass, int& count) {
     m = wave_sum_f64(m);
     if (lane == 0) { s_m[par][wave] = m; s_c[par][wave] = c; }
@@ -1491,8 +1516,8 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   const double S = s_gm[SAMP_NT];
   auto search = [&](int kind, double T, int K, uint32_t& kappa, double& above, int& nabove, int& ties) {
     auto meets = [&](double g, int c) { return kind == 0 ? g >= T : (kind == 1 ? g > T : c >= K); };
-    int j = 0;
-    while (j < SAMP_NT && !meets(s_gm[j], s_gc[j])) ++j;         // (the same for every thread)
+    const unsigned long long at_least = __ballot(meets(s_gm[lane], s_gc[lane]));
+    const int j = at_least ? __builtin_ctzll(at_least) : SAMP_NT;   // the first threshold that does (the same for every thread)
     uint32_t lo = j < SAMP_NT ? samp_threshold(mx, j) : 1u;
     const uint32_t top = j > 0 ? samp_threshold(mx, j - 1) - 1u : samp_key(mx);
     int c_at = s_gc[j], c_hi = j > 0 ? s_gc[j - 1] : 0;          // tokens at or above the prefix, above the range in question
@@ -1525,18 +1550,25 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
     // over all tokens until few enough are left, then on those, collected in LDS
     while (bit >= 0 && c_at - c_hi > SAMP_CAP) fix_bit(G_all);
     const bool list = c_at - c_hi <= SAMP_CAP;
+    collected = list;
     const double A = g_hi;
     const int cA = c_hi;
     if (list) {
       // the tokens in question, first <= key <= last, thread by thread
       const uint32_t first = pre > lo ? pre : lo, rest = pre | (bit < 0 ? 0u : (2u << bit) - 1u), last = rest < top ? rest : top;
       int mine = 0;
+      unsigned long long which = 0;                              // (up to 64 tokens of a thread: the ones to collect)
+#pragma unroll 2
       for (int i0 = tid; i0 < a.npad; i0 += SAMP_THREADS * SAMP_MEMU) {
         uint32_t k[SAMP_MEMU];
 #pragma unroll
         for (int q = 0; q < SAMP_MEMU; ++q) k[q] = a.keys[i0 + q * SAMP_THREADS];
 #pragma unroll
-        for (int q = 0; q < SAMP_MEMU; ++q) mine += k[q] >= first && k[q] <= last ? 1 : 0;
+        for (int q = 0; q < SAMP_MEMU; ++q) {
+          const bool in = k[q] >= first && k[q] <= last;
+          mine += in ? 1 : 0;
+          which |= (unsigned long long)in << ((i0 / SAMP_THREADS + q) & 63);
+        }
       }
       int incl = mine;
 #pragma unroll
@@ -1549,12 +1581,50 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       nl = 0;
       for (int w = 0; w < NW; ++w) nl += s_off[w];
       if (nl > SAMP_CAP) nl = SAMP_CAP;
-      if (mine)
+      auto take = [&](int i, uint32_t k) { s_key[at] = k; s_id[at] = i; s_w[at] = a.w[i]; ++at; };
+      if (a.npad <= 64 * SAMP_THREADS) {
+        for (; which && at < SAMP_CAP; which &= which - 1) {
+          const int i = tid + __builtin_ctzll(which) * SAMP_THREADS;
+          take(i, a.keys[i]);
+        }
+      } else if (mine) {
         for (int i = tid; i < a.npad; i += SAMP_THREADS) {
           const uint32_t k = a.keys[i];
-          if (k >= first && k <= last && at < SAMP_CAP) { s_key[at] = k; s_w[at] = a.w[i]; ++at; }
+          if (k >= first && k <= last && at < SAMP_CAP) take(i, k);
         }
+      }
       __syncthreads();
+    }
+    // few tokens: the first wave goes on alone, without a barrier (the same sums: 64 tokens at a time, in their order)
+    if (list && nl <= SAMP_SOLO) {
+      if (wave == 0) {
+        auto G = [&](uint32_t kth, double& mass, int& count) {
+          mass = 0.0; count = 0;
+          for (int e = lane; e < (nl + WAVE - 1) / WAVE * WAVE; e += WAVE) {
+            const bool ge = e < nl && s_key[e] >= kth;
+            mass += wave_sum_f64(ge ? s_w[e] : 0.0);
+            count += __popcll(__ballot(ge));
+          }
+          mass += A; count += cA;
+        };
+        while (bit >= 0 && c_at - c_hi != 1) fix_bit(G);
+        const bool single = c_at - c_hi == 1;
+        uint32_t least = 0xffffffffu;
+        for (int e = lane; e < nl; e += WAVE) if (s_key[e] >= pre) least = min(least, s_key[e]);
+#pragma unroll
+        for (int o = WAVE / 2; o >= 1; o >>= 1) least = min(least, (uint32_t)__shfl_xor((int)least, o));
+        double ab = g_hi; int nab = c_hi, ti = 1;
+        if (!single) {
+          ab = 0.0; nab = 0; double g; int c;
+          if (least != 0xffffffffu) G(least + 1u, ab, nab);
+          G(least, g, c);
+          ti = c - nab > 0 ? c - nab : 1;
+        }
+        if (lane == 0) { s_kappa = least; s_above = ab; s_nabove = nab; s_ties = ti; }
+      }
+      __syncthreads();
+      kappa = s_kappa; above = s_above; nabove = s_nabove; ties = s_ties;
+      return;
     }
     auto G = [&](uint32_t kth, double& mass, int& count) {
       if (list) { G_list(kth, mass, count); mass += A; count += cA; }
@@ -1613,7 +1683,8 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   if (tid == 0) { s_min = 0x7fffffff; s_prefix = 0u; s_need = r; }
   __syncthreads();
   if (r == 1) {
-    for (int i = tid; i < n; i += SAMP_THREADS) if (a.keys[i] == kappa) atomicMin(&s_min, i);
+    if (collected) { for (int e = tid; e < nl; e += SAMP_THREADS) if (s_key[e] == kappa) atomicMin(&s_min, s_id[e]); }
+    else for (int i = tid; i < n; i += SAMP_THREADS) if (a.keys[i] == kappa) atomicMin(&s_min, i);
     __syncthreads();
     if (tid == 0) a.ds->sampled = s_min;
     return;
