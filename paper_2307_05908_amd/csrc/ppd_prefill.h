@@ -249,6 +249,46 @@ __global__ __launch_bounds__(WW * WX * WAVE, WW * WX <= 4 ? 1 : 2) void pgemm_ke
     const int i = m / (2 * TX), x = m % (2 * TX), j = x % TX;
     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fw[w][i]), __builtin_bit_cast(bf16x8, x < TX ? fh[w][j] : fl[w][j]), acc[i][j], 0, 0, 0);
   };
+  // what the epilogue adds: registers 4 q .. 4 q + 3 of a 32 x 32 block are its rows 8 q + 4 (l / 32) .. + 3 (weight rows) for
+  // column l % 32 (prompt row); ntot, ldy and the segments' rows are multiples of 4.  Small tiles, a latency's work, ask for it
+  // before their operands; the others behind the loop, a column of blocks ahead (their registers are taken until then).  The residuals of
+  // the next column are requested before this one's outputs are stored: they may be the same memory, and a load does not pass a store.
+  // Behind the loop, one bias at a time, it took as long as the product of a narrow model: OPT-125m shape, 127 rows, us before / now: QKV
+  // 11.1 / 8.3, O 10.5 / 8.2, FFN in 10.4 / 8.3, FFN out 13.0 / 11.2; 500 rows 15.8 / 12.5, 10.9 / 8.2, 15.6 / 13.1, 16.9 / 14.4.
+  const int nt0 = ntb + ww * TW * 2, mt0 = mtb + wx * TX * 2;
+  const uint16_t* const B0 = (const uint16_t*)a.B[0];
+  const uint16_t* const B1 = (const uint16_t*)a.B[1];
+  const uint16_t* const B2 = (const uint16_t*)a.B[2];
+  constexpr bool EARLY = TW * TX <= 2;
+  constexpr int NR = EARLY ? TW : 2;
+  f32x4 rsd[PAIRED ? 1 : NR][TX][4];
+  uint2 bias[PAIRED ? 1 : NR][4];              // (registers: of the next column only where they are enough)
+  constexpr bool AHEAD = EARLY || TW * TX < 10;
+  auto biases = [&](int i) {
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const int n0 = (nt0 + 2 * i) * 16 + 8 * q4 + 4 * (lane >> 5);
+      bias[i % NR][q4] = make_uint2(0u, 0u);
+      if (B0 && n0 < a.ntot) {
+        int loc = n0; const uint16_t* b = B0;
+        if (loc >= a.N[0]) { loc -= a.N[0]; b = B1; if (loc >= a.N[1]) { loc -= a.N[1]; b = B2; } }
+        bias[i % NR][q4] = *(const uint2*)(b + loc);
+      }
+    }
+  };
+  auto residuals = [&](int i) {
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+      for (int j = 0; j < TX; ++j) {
+        const int m = (mt0 + 2 * j) * 16 + (lane & 31), n0 = (nt0 + 2 * i) * 16 + 8 * q4 + 4 * (lane >> 5);
+        rsd[i % NR][j][q4] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (a.Rsd && m < a.M && n0 < a.ntot) rsd[i % NR][j][q4] = *(const f32x4*)(a.Rsd + (size_t)m * a.ldy + n0);
+      }
+  };
+  if constexpr (!PAIRED && EARLY)
+#pragma unroll
+    for (int i = 0; i < TW; ++i) { biases(i); residuals(i); }
 #pragma unroll
   for (int s = 0; s < R; ++s)
 #pragma unroll
@@ -324,28 +364,15 @@ __global__ __launch_bounds__(WW * WX * WAVE, WW * WX <= 4 ? 1 : 2) void pgemm_ke
           }
   }
 
-  // ---- epilogue: registers 4 q .. 4 q + 3 of a 32 x 32 block are its rows 8 q + 4 (l / 32) .. + 3 (weight rows) for column
-  // l % 32 (prompt row); ntot and ldy are multiples of 4.  The residuals of the next column of blocks are requested before this
-  // one's outputs are stored (they may be the same memory, and a load does not pass a store).
-  const int nt0 = ntb + ww * TW * 2, mt0 = mtb + wx * TX * 2;
-  const uint16_t* const B0 = (const uint16_t*)a.B[0];
-  const uint16_t* const B1 = (const uint16_t*)a.B[1];
-  const uint16_t* const B2 = (const uint16_t*)a.B[2];
-  f32x4 rsd[PAIRED ? 1 : 2][TX][4];
-  auto residuals = [&](int i) {
-#pragma unroll
-    for (int j = 0; j < TX; ++j)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int m = (mt0 + 2 * j) * 16 + lr, n0 = (nt0 + 2 * i) * 16 + 8 * q4 + 4 * lh;
-        rsd[i & 1][j][q4] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (a.Rsd && m < a.M && n0 < a.ntot) rsd[i & 1][j][q4] = *(const f32x4*)(a.Rsd + (size_t)m * a.ldy + n0);
-      }
-  };
-  if constexpr (!PAIRED) residuals(0);
+  // ---- epilogue
+  if constexpr (!PAIRED && !EARLY) { residuals(0); if constexpr (AHEAD) biases(0); }
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
-    if constexpr (!PAIRED) if (i + 1 < TW) residuals(i + 1);
+    if constexpr (!PAIRED && !EARLY) {
+      if (i + 1 < TW) residuals(i + 1);
+      if constexpr (!AHEAD) biases(i);
+      else if (i + 1 < TW) biases(i + 1);
+    }
 #pragma unroll
     for (int j = 0; j < TX; ++j) {
       const int m = (mt0 + 2 * j) * 16 + lr;
@@ -377,16 +404,12 @@ __global__ __launch_bounds__(WW * WX * WAVE, WW * WX <= 4 ? 1 : 2) void pgemm_ke
           float y[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            float bv = 0.f;
-            if (B0) {
-              int seg = 0, loc = n0 + q;
-              if (loc >= a.N[0]) { loc -= a.N[0]; seg = 1; if (loc >= a.N[1]) { loc -= a.N[1]; seg = 2; } }
-              bv = bf16_to_f32((seg == 0 ? B0 : (seg == 1 ? B1 : B2))[loc]);
-            }
+            const uint32_t bw = q < 2 ? bias[i % NR][q4].x : bias[i % NR][q4].y;
+            const float bv = __uint_as_float(q & 1 ? bw & 0xffff0000u : bw << 16);
             float tv = acc[i][j][4 * q4 + q] + bv;
             if (a.act == 1) tv = gelu_erf(tv);
             else if (a.act == 2) tv = fmaxf(tv, 0.f);
-            if (a.Rsd) tv += rsd[i & 1][j][q4][q];
+            if (a.Rsd) tv += rsd[i % NR][j][q4][q];
             y[q] = tv;
           }
           put(n0, y);
