@@ -237,9 +237,11 @@ int narrow_tiles(const MGemmArgs& a, int ngroups, int mmax) {
   return (a.NT + t - 1) / t * ngroups <= (mmax <= 4 ? 1100 : 700) ? t : 0;
 }
 
-template <bool PAIRED, int NORM, int T, int NB>
+template <bool PAIRED, int NORM, int T, int NB, bool MERGE = false>
 hipError_t narrow_go(hipStream_t st, const MGemmArgs& a, dim3 grid, int lds) {
-  const auto k = gemm_mfma_narrow_kernel<PAIRED, NORM, T, NB>;
+  if constexpr (NORM < 0 && !PAIRED && NB <= 8 && !MERGE)
+    if (a.nmerge > 0) return narrow_go<PAIRED, NORM, T, NB, true>(st, a, grid, lds);
+  const auto k = gemm_mfma_narrow_kernel<PAIRED, NORM, T, NB, MERGE>;
   if (a.KT == 0) return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);   // (setup)
   hipLaunchKernelGGL(k, grid, dim3(MG_THREADS), lds, st, a);
   return hipGetLastError();
@@ -257,17 +259,30 @@ hipError_t narrow_launch(hipStream_t st, const MGemmArgs& a, bool paired, int nb
   if (a.norm == 1) return paired ? narrow_go_t<true, 1>(st, a, nb8, t, grid, lds) : narrow_go_t<false, 1>(st, a, nb8, t, grid, lds);
   return paired ? hipErrorInvalidValue : narrow_go_t<false, -1>(st, a, nb8, t, grid, lds);
 }
-// the instances whose rows may take more LDS than a launch has by default (at most 8 rows of 4096: 134 KiB)
-hipError_t narrow_setup(int norm) {
-  MGemmArgs a; memset(&a, 0, sizeof a);
-  hipError_t e = hipSuccess;
-  for (const int nb8 : {8, 16}) {
-    a.norm = -1;
-    if (e == hipSuccess) e = narrow_launch(nullptr, a, false, nb8, 1, dim3(1), 0);
-  }
-  a.norm = norm;
-  for (const bool paired : {false, true}) if (e == hipSuccess) e = narrow_launch(nullptr, a, paired, 8, 1, dim3(1), 0);
+// a model's instances whose rows may take more LDS than a launch has by default (at most 8 rows of 4096: 134 KiB)
+hipError_t narrow_setup(const ppd_model_dims& d) {
+  auto set = [](int K, int norm, bool paired, int nmerge) {
+    MGemmArgs a; memset(&a, 0, sizeof a);
+    a.norm = norm; a.nmerge = nmerge;
+    const int KT = (K + 31) / 32, nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
+    if (nb8 > (norm >= 0 ? 8 : 16) || mg_narrow_lds(KT, MG_NARROW_ROWS, 1) <= 64 * 1024) return hipSuccess;
+    return narrow_launch(nullptr, a, paired, nb8, 1, dim3(1), 0);
+  };
+  hipError_t e = set(d.d_model, d.norm, false, 0);
+  if (e == hipSuccess && d.act == 2) e = set(d.d_model, d.norm, true, 0);
+  if (e == hipSuccess) e = set(d.d_model, -1, false, 0);
+  if (e == hipSuccess) e = set(d.d_model, -1, false, 1);
+  if (e == hipSuccess) e = set(d.d_ff, -1, false, 0);
   return e;
+}
+
+// Whether the output projection merges the attention's partials itself (positions up to pmax).  More than 1024 columns of more than
+// four rows are several units of work for every wave: a PPD round of 1536 columns, k = 8, 554 / 558 us without / with; k = 3 505 / 492.
+bool merges_itself(const ppd_ctx* c, int ngroups, int mmax, int pmax) {
+  if (!c->mfma || c->mg_passes_min != 1 || pmax / ATT_CHUNK >= MG_MERGE) return false;
+  MGemmArgs a; memset(&a, 0, sizeof a);
+  a.KT = (c->d.d_model + 31) / 32; a.NT = (c->d.d_model + 15) / 16; a.norm = -1;
+  return a.KT <= (mmax <= 4 ? 8 : 4) * MG_WAVES && narrow_tiles(a, ngroups, mmax) > 0;
 }
 
 // One logical GEMM for one or two row groups.  Everything goes into one launch when the staged rows of
@@ -284,6 +299,7 @@ hipError_t launch_mgemm(ppd_ctx* c, MGemmArgs& a, int ngroups, bool paired) {
       a.xrow = mg_xrow(a.KT);
       return narrow_launch(c->cur, a, paired, (a.KT + MG_WAVES - 1) / MG_WAVES, t, dim3((a.NT + t - 1) / t, ngroups), mg_narrow_lds(a.KT, mmax, t));
     }
+  if (a.nmerge > 0) return hipErrorInvalidValue;     // (only that kernel merges)
   auto lds_with = [&](int M, int tiles, int passes) {
     int b, p, x;
     return (size_t)mg_lds_layout(a.K, M, a.norm, tiles, mg_xrow_pass(a.KT, passes), b, p, x);
@@ -365,8 +381,12 @@ hipError_t launch_attn(ppd_ctx* c, const AttnArgs& a, int ngroups, int pmax) {
 }
 
 // the same launch described for the MFMA kernel: P[g] = group g's repacked weights
-hipError_t mgemm_from(ppd_ctx* c, const GemmArgs& a, int ngroups, bool paired, void* const* P) {
+hipError_t mgemm_from(ppd_ctx* c, const GemmArgs& a, int ngroups, bool paired, void* const* P, const MergeArgs* merge = nullptr, int nmerge = 0) {
   MGemmArgs m; memset(&m, 0, sizeof m);
+  if (merge) {
+    m.nmerge = nmerge; m.H = merge->H; m.HD = merge->HD; m.nchunk_max = merge->nchunk_max; m.ds = merge->ds;
+    for (int g = 0; g < ngroups; ++g) { m.g[g].part = merge->part[g]; m.g[g].pos_off = merge->pos_off[g]; }
+  }
   for (int g = 0; g < ngroups; ++g) {
     const GemmGroup& s = a.g[g];
     MGemmGroup& t = m.g[g];
@@ -422,9 +442,10 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     HIPCHK(c, launch_gemm(c, a, ngroups, false));
   }
   // 2. RoPE + KV write + attention partials, then merge
+  MergeArgs mg; memset(&mg, 0, sizeof mg);
+  int nmerge = 0;            // > 0: chunks that the output projection merges
   if (stages & 1) {
     AttnArgs a; memset(&a, 0, sizeof a);
-    MergeArgs mg; memset(&mg, 0, sizeof mg);
     const size_t part_row = (size_t)d.n_heads * c->nchunk_max * (d.head_dim + 2);
     for (int g = 0; g < ngroups; ++g) {
       AttnGroup& G = a.g[g];
@@ -462,9 +483,12 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     } else {
       { ProfScope ps(c, PPD_KC_ATTN, ngroups); HIPCHK(c, launch_attn(c, a, ngroups, pmax)); }
       mg.H = d.n_heads; mg.HD = d.head_dim; mg.d_model = dm; mg.nchunk_max = c->nchunk_max;
-      ProfScope ps(c, PPD_KC_ATTN_MERGE, ngroups);
-      hipLaunchKernelGGL(attn_merge_kernel, dim3(mmax, d.n_heads, ngroups), dim3(MERGE_THREADS), 0, c->cur, mg);
-      HIPCHK(c, hipGetLastError());
+      if ((stages & 2) && !rg[0].chunk && merges_itself(c, ngroups, mmax, pmax)) nmerge = pmax / ATT_CHUNK + 1;
+      else {
+        ProfScope ps(c, PPD_KC_ATTN_MERGE, ngroups);
+        hipLaunchKernelGGL(attn_merge_kernel, dim3(mmax, d.n_heads, ngroups), dim3(MERGE_THREADS), 0, c->cur, mg);
+        HIPCHK(c, hipGetLastError());
+      }
     }
   }
   // 3. output projection + residual
@@ -480,7 +504,7 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     ProfScope ps(c, PPD_KC_GEMM_O, ngroups);
     if (c->mfma) {
       void* P[2] = {c->LP[rg[0].layer].o, ngroups == 2 ? c->LP[rg[1].layer].o : nullptr};
-      HIPCHK(c, mgemm_from(c, a, ngroups, false, P));
+      HIPCHK(c, mgemm_from(c, a, ngroups, false, P, nmerge ? &mg : nullptr, nmerge));
     } else
     HIPCHK(c, launch_gemm(c, a, ngroups, false));
   }
@@ -602,11 +626,10 @@ int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
 
 // Models whose products are all gemm_mfma_narrow_kernel's: there a launch takes no longer than an exchange of the one-launch chain,
 // and the attention is spread over more workgroups.  Measured (a plain token of 12 layers, us, chain / launches, at positions
-// 40 / 600 / 1400): OPT-like 512 wide 301 / 249, 313 / 289, 320 / 296; 768 315 / 280, 330 / 323, 338 / 337; 1024 327 / 271, 341 / 320,
-// 348 / 338; LLaMA-like 384 282 / 250, 299 / 286, 311 / 290; 1024 346 / 293, 365 / 328, 382 / 341.  Up to 320 the chain is within 2 us a
-// layer either way (OPT-like 320 276 / 249, 291 / 289, at 150 274 / 277) and stays.  From 1152 on the chain is the better one past
-// the short sequences (1280 389 / 390 at 600, 407 / 414 at 1400).
-bool launches_pay(const ppd_model_dims& d) { return d.d_model > 320 && d.d_model <= 1024 && d.d_ff <= 4096; }
+// 40 / 140 / 480): OPT-like 512 wide 301 / 249, 300 / 251, 313 / 255; 768 315 / 280, 315 / 283, 330 / 289; 1024 327 / 271, 328 / 275,
+// 341 / 282; LLaMA-like 1024 346 / 293, 358 / 283, 365 / 328.  Up to 256 columns the difference is the smallest (OPT-like 259 / 241 at
+// 140) and the chain stays.  From 1152 on it is the better one past the short sequences (1536 419 / 427 at 230, 424 / 465 at 480).
+bool launches_pay(const ppd_model_dims& d) { return d.d_model > 256 && d.d_model <= 1024 && d.d_ff <= 4096; }
 
 // The arguments of a one-launch chain of layers on row 0 that do not change, and its layout of a compute unit's LDS; false: it does
 // not fit.
@@ -1257,7 +1280,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = rgemm_setup();
-    if (e == hipSuccess) e = narrow_setup(d.norm);
+    if (e == hipSuccess) e = narrow_setup(d);
     // the prompt pass's products with one tile shape (1 ..) and one cut of the reduction length (tests)
     c->pg_tile = env_int("PPD_PG_TILE", 0) - 1;
     c->pg_parts = env_int("PPD_PG_PARTS", 0);
@@ -1281,7 +1304,6 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
       c->spec = 2 * c->dbar == d.n_layers && !c->early_head && need <= MG_LDS_MAX && env_int("PPD_SPEC", 1) != 2;
     }
   }
-  if (e == hipSuccess) { const AttnWholeArgs w{}; e = d.head_dim == 64 ? launch_attn_whole<64>(nullptr, w, 0, 0) : launch_attn_whole<128>(nullptr, w, 0, 0); }
   // the main token's layers in one launch, one workgroup per compute unit (PPD_FUSED=2: one launch per step; PPD_MGPASSES
   // asks for the launches whose staging passes it sets)
   if (e == hipSuccess) e = hipGetDevice(&c->device);

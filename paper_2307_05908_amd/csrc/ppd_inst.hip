@@ -90,9 +90,7 @@ hipError_t launch_attn_t(hipStream_t stream, const AttnArgs& a, int mmax, dim3 g
 
 template <int HD>
 hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups) {
-  constexpr int lds_most = sizeof(float) * attn_whole_lds_floats<HD>(MAXM);
-  static_assert(lds_most <= 160 * 1024, "MAXM rows fit LDS");
-  if (ngroups == 0) return hipFuncSetAttribute((const void*)attn_whole_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_most);
+  static_assert(sizeof(float) * attn_whole_lds_floats<HD>(MAXM) <= 64 * 1024, "MAXM rows fit the default dynamic LDS limit");
   if (mmax < 1 || mmax > MAXM) return hipErrorInvalidValue;
   attn_whole_kernel<HD><<<dim3(w.a.H, ngroups), dim3(ATT_WHOLE_THREADS), sizeof(float) * (size_t)attn_whole_lds_floats<HD>(mmax), stream>>>(w);
   return hipGetLastError();

@@ -1978,6 +1978,7 @@ struct MGemmGroup {
   const void* B[3];   // biases per row segment or null (paired: B[0] gate, B[1] up)
   const void* ng; const void* nb;  // gain / bias of the fused norm
   int M;              // rows, 1..16
+  const float* part; int pos_off;  // nmerge > 0: the rows are these attention partials, merged (see MergeArgs)
 };
 struct MGemmArgs {
   MGemmGroup g[2];
@@ -1994,6 +1995,8 @@ struct MGemmArgs {
   int tiles_wg;     // ceil(NT / gridDim.x); gridDim.x <= NT
   unsigned wbytes;  // NT * KT * 1024
   int passes;       // the reduction length is staged in LDS in this many passes (1: whole rows; > 1 only without a fused norm)
+  int nmerge;       // gemm_mfma_narrow_kernel without a norm: chunks of positions that may be in use, up to MG_MERGE; 0: X has the rows
+  int H, HD, nchunk_max; const DevState* ds;
 };
 
 // LDS bytes between staged rows: the row itself, moved off a multiple of 256 so that neighbouring rows
@@ -2419,8 +2422,15 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
 constexpr int MG_NARROW_ROWS = 8;            // of a group
 constexpr int MG_NARROW_LDS = 512;           // [2][MG_NARROW_ROWS][8] sums of the norm, then the partial sums, then the rows
 __host__ __device__ inline int mg_narrow_lds(int KT, int M, int T) { return MG_NARROW_LDS + T * MG_WAVES * M * 64 + M * mg_xrow(KT); }
-template <bool PAIRED, int NORM, int T, int NB>
+// MERGE: the rows are attention partials of up to MG_MERGE chunks, which every workgroup merges for itself, a piece per thread, in
+// attn_merge_kernel's slices and order, and a launch goes.  (Where a workgroup had to merge the whole row one thread per component,
+// before a streaming kernel's prologue, it lost: 16 against 15 us of a 4096-wide model.)  Measured (a PPD round of 12 layers, k = 3,
+// us, with the merge's launch / without): OPT-like 768 wide at 140 positions 360 / 335, at 480 367 / 342; LLaMA-like 1024 375 / 344
+// at 140; a plain token of the 768 wide one 310 / 283 and 321 / 289.
+constexpr int MG_MERGE = 8;
+template <bool PAIRED, int NORM, int T, int NB, bool MERGE = false>
 __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_narrow_kernel(MGemmArgs a) {
+  static_assert(!MERGE || (NORM < 0 && !PAIRED), "the output projection");
   extern __shared__ float4 lds4[];
   char* const lds = (char*)lds4;
   const MGemmGroup& G = a.g[blockIdx.y];
@@ -2435,6 +2445,24 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_narrow_kernel(MGemmArgs 
   const int nv = (K + 511) / 512, units = M * nv;
   float x[UM][8]; u32x4 gq[UM], bq[UM];
   auto unit = [&](int i, int& m, int& c) { const int u = wave + i * MG_WAVES; m = u / nv; c = (u - m * nv) * WAVE + lane; };
+  // (partials of chunks past the position are read, as far as there may be any, and left out)
+  float2 pt[MERGE ? MG_MERGE : 1][5];
+  auto partials = [&](int i) {
+    int m, c; unit(i, m, c);
+    const int k = c * 8 < K ? c * 8 : 0, h = k / a.HD;
+    const float* const p0 = G.part + (((size_t)m * a.H + h) * a.nchunk_max) * (a.HD + 2);
+#pragma unroll
+    for (int q = 0; q < MG_MERGE; ++q)
+      if (q < a.nmerge) {
+        const float* const pq = p0 + (size_t)q * (a.HD + 2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pt[q][e] = ((const float2*)(pq + (k - h * a.HD)))[e];
+        pt[q][4] = *(const float2*)(pq + a.HD);
+      }
+  };
+  if constexpr (MERGE) {
+    if (wave < units) partials(0);
+  } else
 #pragma unroll
   for (int i = 0; i < UM; ++i)
     if (wave + i * MG_WAVES < units) {
@@ -2476,6 +2504,42 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_narrow_kernel(MGemmArgs 
       b0 = (seg == 0 ? B0 : (seg == 1 ? B1 : B2))[loc];
     }
     if (G.Rsd) rsd = G.Rsd[(size_t)ocol * a.ldy + n];
+  }
+  if constexpr (MERGE) {
+    const int nc = (a.ds->pos + G.pos_off) / ATT_CHUNK + 1;
+#pragma unroll
+    for (int i = 0; i < UM; ++i)
+      if (wave + i * MG_WAVES < units) {
+        if (i > 0) partials(i);
+        float gm = -INFINITY, ll = 0.f, oo[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        auto add = [&](float wq, const float2 (&t)[5], float (&o)[8], float& l) {
+          l = fmaf(wq, t[4].y, l);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { o[2 * e] = fmaf(wq, t[e].x, o[2 * e]); o[2 * e + 1] = fmaf(wq, t[e].y, o[2 * e + 1]); }
+        };
+#pragma unroll
+        for (int q = 0; q < MG_MERGE; ++q) if (q < nc) gm = fmaxf(gm, pt[q][4].x);
+        if (a.HD == 64) {                      // a slice has one chunk
+#pragma unroll
+          for (int q = 0; q < MG_MERGE; ++q) if (q < nc) add(expf(pt[q][4].x - gm), pt[q], oo, ll);
+        } else {                               // chunks q and q + 4 are a slice
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (q < nc) {
+              const bool two = q + 4 < nc;
+              const float ms = two ? fmaxf(pt[q][4].x, pt[q + 4][4].x) : pt[q][4].x;
+              float2 sl[5] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+              float os[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+              add(expf(pt[q][4].x - ms), pt[q], os, sl[4].y);
+              if (two) add(expf(pt[q + 4][4].x - ms), pt[q + 4], os, sl[4].y);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) sl[e] = make_float2(os[2 * e], os[2 * e + 1]);
+              add(expf(ms - gm), sl, oo, ll);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[i][e] = oo[e] / ll;
+      }
   }
   // ---- statistics: a unit's 64 pieces by butterfly, a row's units in order (what the norm's idle waves would add is zero)
   auto combine = [&](const float* r) { float s = r[0]; for (int v = 1; v < nv; ++v) s += r[v]; return s + 0.f; };

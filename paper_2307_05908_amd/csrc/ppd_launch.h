@@ -20,7 +20,7 @@ hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups,
 
 template <int HD>
 hipError_t launch_attn_t(hipStream_t stream, const AttnArgs& a, int mmax, dim3 grid, bool causal);
-// attn_whole_kernel; ngroups 0: its LDS is set up
+// attn_whole_kernel; mmax: the largest row count of the groups
 template <int HD>
 hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups);
 

@@ -31,3 +31,26 @@ def test_narrow_products_are_the_streaming_kernels_bit_exact(family, d_model, d_
         np.testing.assert_array_equal(a[0], b[0])
         np.testing.assert_array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
         assert a[2] == b[2]
+
+
+@pytest.mark.parametrize("family,d_model,k", [("opt", 128, 8), ("opt", 576, 3), ("opt", 1024, 8), ("llama", 256, 8), ("llama", 1152, 3), ("llama", 1152, 8)])
+@pytest.mark.parametrize("n_prompt", [125, 189, 252, 318, 506])
+def test_partials_merged_in_the_output_projection_bit_exact(family, d_model, k, n_prompt, monkeypatch):
+    """Up to eight chunks of positions, across their boundaries and across the first position beyond them: the merge's own launch
+    and order on the other side."""
+    hd = 64 if family == "opt" else 128
+    cfg = small_cfg(family, d_model=d_model, n_heads=d_model // hd, head_dim=hd, d_ff=520, vocab=700, n_layers=2, exit_layer=1, alpha=0.1,
+                    max_ctx=560, n_prompt=n_prompt, n_gen=10)
+    dev = binding.upload_model(pi.make_model(cfg))
+    prompt = pi.make_prompt(cfg)
+    got = []
+    for passes in (None, "2"):
+        if passes:
+            monkeypatch.setenv("PPD_MGPASSES", passes)
+        P = binding.PPD(cfg, dev, k=k)
+        got.append([gpu_generate(P, prompt, cfg.n_gen, mode) for mode in ("plain", "ppd")])
+        P.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a[0], b[0])
+        np.testing.assert_array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
+        assert a[2] == b[2]
