@@ -628,10 +628,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs a) {
 }
 
 // Reduction lengths of at most 1024, fp32 weights: a launch is a chain of latencies, not a stream.  Every operand of an output
-// (rows, gains, weight row, bias, residual) is requested at once; every wave normalises the rows for itself, so that
+// (rows, gains, weight row, bias, residual) is requested at once; one row is normalised by every wave for itself, so that
 // nothing waits at a barrier or goes through LDS; a wave owns LR outputs (4 in head launches, whose lists are per workgroup).
 // The additions are gemm_body's, in its order: block j of 256 elements is wave j's share of a row's statistics there,
 // and lane l's products 4 l .. 4 l + 3 of blocks 0, 1, ... are its products here.
+// Several rows behind a norm are normalised by one wave of the workgroup each and shared through LDS (every wave for itself: a PPD
+// round of 12 layers, k = 3 / 8, us, before / now: 256 wide 179 / 170 and 219 / 198, 512 248 / 236 and 363 / 325, 1024 454 / 425 and 674 / 550).
 // Measured (K = 256, one row / one and three rows): norm-fused projections of 768 / 1024
 // outputs 11.1 / 11.9 -> 3.8 / 4.3 us with one and three rows, 7.5 -> 2.5 us with one; 1024 logits 8.7 -> 4.0 us.
 constexpr int GEMM_SMALL_K = 1024;
@@ -644,12 +646,22 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_small_kernel(GemmArgs a) {
   const int M = G.M, K = a.K;
   constexpr int WROWS = PAIRED ? 2 * LR : LR;
   const int n0 = ((int)blockIdx.x * GEMM_WAVES + wave) * LR;
-  float4 x[MT][NB], gn[NB], bs[NB], w[WROWS][NB];
+  // several rows behind a norm: a wave normalises rows wave, wave + 4 only, and has the others' from LDS
+  constexpr bool SHARE = MT > 1;
+  constexpr int OWN = SHARE ? MT / GEMM_WAVES : 1;
+  __shared__ float4 xsh[SHARE ? MT : 1][SHARE ? NB * WAVE : 1];
+  const bool share = SHARE && a.norm >= 0;
+  float4 x[MT][NB], xo[OWN][NB], gn[NB], bs[NB], w[WROWS][NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int k = 256 * j + 4 * lane, kc = k < K ? k : 0;
+    if (share) {
 #pragma unroll
-    for (int m = 0; m < MT; ++m) x[m][j] = m < M ? *(const float4*)(G.X + (size_t)m * a.ldx + kc) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = 0; i < OWN; ++i) { const int m = wave + i * GEMM_WAVES; xo[i][j] = *(const float4*)(G.X + (size_t)(m < M ? m : 0) * a.ldx + kc); }
+    } else {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) x[m][j] = m < M ? *(const float4*)(G.X + (size_t)m * a.ldx + kc) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     if (a.norm >= 0) {
       const float* g = (const float*)G.ng + kc;
       gn[j] = make_float4(g[0], g[1], g[2], g[3]);
@@ -684,43 +696,59 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_small_kernel(GemmArgs a) {
 #pragma unroll
       for (int m = 0; m < MT; ++m) x[m][j] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
+      for (int i = 0; i < OWN; ++i) xo[i][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
       for (int i = 0; i < WROWS; ++i) w[i][j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-  if (a.norm >= 0) {
+  auto normalise = [&](float4 (&v)[NB]) {
     auto combine4 = [&](const float (&r)[4]) { return ((r[0] + r[1]) + r[2]) + r[3]; };
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-      if (m >= M) continue;
-      float mu = 0.f, r[4] = {0.f, 0.f, 0.f, 0.f};
-      if (a.norm == 0) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          float s = 0.f;
-          s += x[m][j].x; s += x[m][j].y; s += x[m][j].z; s += x[m][j].w;
-          r[j] = wave_sum(s);
-        }
-        mu = combine4(r) / (float)K;
-      }
+    float mu = 0.f, r[4] = {0.f, 0.f, 0.f, 0.f};
+    if (a.norm == 0) {
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
-        float s2 = 0.f;
-        if (256 * j + 4 * lane < K) {
-          const float d0 = x[m][j].x - mu, d1 = x[m][j].y - mu, d2 = x[m][j].z - mu, d3 = x[m][j].w - mu;
-          s2 = fmaf(d0, d0, s2); s2 = fmaf(d1, d1, s2); s2 = fmaf(d2, d2, s2); s2 = fmaf(d3, d3, s2);
-        }
-        r[j] = wave_sum(s2);
+        float s = 0.f;
+        s += v[j].x; s += v[j].y; s += v[j].z; s += v[j].w;
+        r[j] = wave_sum(s);
       }
-      const float rs = 1.0f / sqrtf(combine4(r) / (float)K + a.eps);
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-        if (256 * j + 4 * lane < K) {
-          float4 v = x[m][j];
-          v.x = (v.x - mu) * rs * gn[j].x; v.y = (v.y - mu) * rs * gn[j].y; v.z = (v.z - mu) * rs * gn[j].z; v.w = (v.w - mu) * rs * gn[j].w;
-          if (G.nb) { v.x += bs[j].x; v.y += bs[j].y; v.z += bs[j].z; v.w += bs[j].w; }
-          x[m][j] = v;
-        }
+      mu = combine4(r) / (float)K;
     }
-  }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float s2 = 0.f;
+      if (256 * j + 4 * lane < K) {
+        const float d0 = v[j].x - mu, d1 = v[j].y - mu, d2 = v[j].z - mu, d3 = v[j].w - mu;
+        s2 = fmaf(d0, d0, s2); s2 = fmaf(d1, d1, s2); s2 = fmaf(d2, d2, s2); s2 = fmaf(d3, d3, s2);
+      }
+      r[j] = wave_sum(s2);
+    }
+    const float rs = 1.0f / sqrtf(combine4(r) / (float)K + a.eps);
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      if (256 * j + 4 * lane < K) {
+        float4 u = v[j];
+        u.x = (u.x - mu) * rs * gn[j].x; u.y = (u.y - mu) * rs * gn[j].y; u.z = (u.z - mu) * rs * gn[j].z; u.w = (u.w - mu) * rs * gn[j].w;
+        if (G.nb) { u.x += bs[j].x; u.y += bs[j].y; u.z += bs[j].z; u.w += bs[j].w; }
+        v[j] = u;
+      }
+  };
+  if constexpr (SHARE) {
+    if (share) {
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) {
+        const int m = wave + i * GEMM_WAVES;
+        if (m < M) {
+          normalise(xo[i]);
+#pragma unroll
+          for (int j = 0; j < NB; ++j) xsh[m][j * WAVE + lane] = xo[i][j];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) x[m][j] = m < M ? xsh[m][j * WAVE + lane] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  } else if (a.norm >= 0) normalise(x[0]);
   float acc[WROWS][MT];
 #pragma unroll
   for (int i = 0; i < WROWS; ++i)
