@@ -553,11 +553,14 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
 // and normalise the rows in every workgroup, which takes longer with every row, where run_chunk_layer has packing launches and
 // reads two tiles of rows from L2 whatever their number.  Measured (whole prompt, run_chunk_layer / run_layer, ms): 4096
 // columns 2 rows 3.51 / 3.07, 4 rows 3.35 / 3.28, 6 rows 3.38 / 3.47; 5120 columns 6.46 / 5.37, 6.51 / 5.74, 5 rows 6.53 / 5.90;
-// 2048 columns 0.97 / 0.88, 0.97 / 0.96; 1024 columns 2 rows 0.68 / 0.73.  Rows that do not fit LDS whole would read the
+// 2048 columns 0.97 / 0.88, 0.97 / 0.96.  Rows that do not fit LDS whole would read the
 // weights twice.
+// Narrow models (gemm_mfma_narrow_kernel has 8 rows as it has 4): the same, us of 12 layers: OPT-like 768 columns 2 rows 495 / 389, 8 rows
+// 507 / 468; 256 406 / 359 and 432 / 380; LLaMA-like 1024 526 / 409 and 533 / 468.
 constexpr int FEW_ROWS_MAX = 5;
 int few_rows(const ppd_model_dims& d) {
   const int dm = d.d_model;
+  if (dm <= 1024 && d.d_ff <= 4096) return MG_NARROW_ROWS;
   if (dm < 2048) return 1;
   const int nt = d.act == 2 ? (d.d_ff + 7) / 8 : (d.d_ff + 15) / 16, tiles = ((nt > 3 * dm / 16 ? nt : 3 * dm / 16) + 255) / 256;
   int m = dm > 4096 ? FEW_ROWS_MAX : 4;
