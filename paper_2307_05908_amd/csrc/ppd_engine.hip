@@ -223,14 +223,14 @@ constexpr size_t MG_LDS_MAX = 160 * 1024;
 
 // Products of narrow models (gemm_mfma_narrow_kernel): the tiles of a workgroup, 0 where the streaming kernel is the better one.
 // Up to 1024 columns a workgroup takes up to four tiles, so that there are no more of them than compute units; from there to 2048
-// (4096 without a norm) one, whose blocks fill the registers, and past some number of workgroups their turns cost more than the
-// streaming kernel's prologue does.  Measured (a PPD round of 12 layers, us, streaming / this kernel with up to 400, 700, 1100
-// workgroups): LLaMA-like 1280 wide, k = 3 430 / 403 392 384, 1536 543 / 526 513 501, 1792 556 / 540 525 529, 2048 593 / 575 573
-// 577; k = 8 1536 609 / 588 573 570, 2048 645 / 626 626 638.  Up to 256 workgroups with several tiles against 512 (narrower
-// models): 0.5 - 1 us a layer.
+// (4096 without a norm and with up to 2048 outputs) one, whose blocks fill the registers, and past some number of workgroups their
+// turns cost more than the streaming kernel's prologue does.  Measured (a PPD round of 12 layers, us, streaming / this kernel with
+// up to 400, 700, 1100 workgroups): LLaMA-like 1280 wide, k = 3 430 / 403 392 384, 1536 543 / 526 513 501, 1792 556 / 540 525 529,
+// 2048 593 / 575 573 577; k = 8 1536 609 / 588 573 570, 2048 645 / 626 626 638.  Output projection of 4096 columns, two groups, k = 3 / 8:
+// 14.2 / 14.5 and 15.1 / 17.2.  Up to 256 workgroups with several tiles against 512 (narrower models): 0.5 - 1 us a layer.
 int narrow_tiles(const MGemmArgs& a, int ngroups, int mmax) {
   const int nb8 = (a.KT + MG_WAVES - 1) / MG_WAVES;
-  if (a.topk > 0 || mmax > MG_NARROW_ROWS || nb8 > (a.norm >= 0 ? 8 : 16)) return 0;
+  if (a.topk > 0 || mmax > MG_NARROW_ROWS || nb8 > (a.norm >= 0 || a.NT > 128 ? 8 : 16)) return 0;
   if (a.norm == 0) for (int g = 0; g < ngroups; ++g) if (!a.g[g].nb) return 0;
   int t = 1;
   while (nb8 <= 4 && t < 4 && (a.NT + t - 1) / t * ngroups > 256) t *= 2;
