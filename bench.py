@@ -34,7 +34,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # (paper_2307_05908_amd/ppd_pmc_probe), see profiles/.  A property of the kernel source it was collected on.
 MEASURED_TRAFFIC = {("llama7b", 3): 361.77e6}
 # sha1 of csrc/ppd_kernels.h when the counters were collected: a changed kernel source voids the figure (null is printed)
-TRAFFIC_KERNELS_SHA1 = "5eea54dee0512961b6e0cd6b84d4c697de5ece52"
+TRAFFIC_KERNELS_SHA1 = "37878aa9d642c7d187f7285b7c720b5dec3a90f0"
 TRAFFIC_SOURCE = "profiles/llama7b_ppd_k3_traffic.txt"
 
 
