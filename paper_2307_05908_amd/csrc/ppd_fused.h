@@ -13,7 +13,7 @@
 // before it waits for anything: 256 workgroups hold 48 MiB that way, about seven microseconds of the stream.
 // Meanwhile the helpers add up the step's outputs, publish them, and bring the next step's row into LDS; they have no
 // weight requests in flight, so nothing of this queues behind the ring (a wave's loads return in order).
-// Measured (MI355X, context 512, one token): 7B shape 3.09 -> 2.60 ms.  (Widths from 384 to 1024, the OPT-125m shape among them,
+// Measured (MI355X, context 512, one token): 7B shape 3.09 -> 2.60 ms.  (Widths from 320 to 1024, the OPT-125m shape among them,
 // go launch by launch again: launches_pay, ppd_engine.hip.)  Every 1000 positions
 // take about 1 us a layer from that: the attention's items pay for their barriers, and the launches are the faster way
 // from some 4000 - 12000 positions on (the rule and its figures: chain_pays, ppd_engine.hip).
