@@ -1435,7 +1435,8 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs
   static_assert(SAMP_NT == WAVE, "a threshold per lane");
   const uint32_t thr = samp_threshold(mx, lane);
   double m = 0.0; int c = 0;
-  for (unsigned long long todo = __ballot(key >= samp_threshold(mx, SAMP_NT - 1)); todo; todo &= todo - 1) {
+  const bool counts = key >= samp_threshold(mx, SAMP_NT - 1);
+  for (unsigned long long todo = __ballot(counts); todo; todo &= todo - 1) {
     const int l = __builtin_ctzll(todo);
     const double wl = lane_f64(w, l);
     const bool ge = (uint32_t)__builtin_amdgcn_readlane((int)key, l) >= thr;
@@ -1443,7 +1444,9 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs
     c += ge ? 1 : 0;
   }
   s_m[wave][lane] = m; s_c[wave][lane] = c;
-  m = wave_sum_f64(w);
+  // All tokens: what the last threshold has and, on top, what lies below it.  (Where nothing does, the two are one sum to the last
+  // bit: a mass that all tokens together reach is reached at the last threshold, too, and no search goes below it for nothing.)
+  m = lane_f64(m, SAMP_NT - 1) + wave_sum_f64(counts ? 0.0 : w);
   const int all = __popcll(__ballot(key != 0u));
   if (lane == 0) { s_m[wave][SAMP_NT] = m; s_c[wave][SAMP_NT] = all; }
   __syncthreads();

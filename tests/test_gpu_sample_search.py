@@ -44,3 +44,28 @@ def test_draw_is_the_oracles(vocab, factor, mode, ks, p):
 def test_draw_among_more_tokens_than_are_collected(vocab, factor, mode, ks, p):
     """Equal logits, flat softmaxes and long tails: the range in question holds more tokens than LDS does."""
     test_draw_is_the_oracles(vocab, factor, mode, min(ks, vocab - 1), p)
+
+
+@pytest.mark.parametrize("p", [1 - 2.0 ** -53, 1 - 2.0 ** -52])
+@pytest.mark.parametrize("vocab,factor", [(1000, 1.0), (5003, 3.6), (32000, 1.0), (50272, 3.6)])
+def test_nearly_all_of_a_flat_softmax_is_kept(vocab, factor, p):
+    """No token lies below the last threshold, and the mass asked for is an ulp from that of all tokens: the sums on both sides
+    of the comparison have to be the same sum.  (Every position's logits are another rounding of it; the token that the oracle
+    draws does not depend on the last bits of the kept mass, of which the draw leaves 2^-24 at least.)"""
+    cfg = small_cfg("opt", vocab=vocab, n_layers=2, exit_layer=1, n_gen=80)
+    m = pi.make_model(cfg)
+    scaled_head(m, factor)
+    P = binding.PPD(cfg, binding.upload_model(m))
+    P.ppd_set_sampling(oracle.TOP_P, 0, p, SEED)
+    prompt = [int(x) for x in pi.make_prompt(cfg)]
+    P.ppd_prefill(prompt)
+    wrong = []
+    for t in range(cfg.n_gen):
+        tok = P.plain_greedy_step()
+        z = P.ppd_get_logits().astype(np.float64)
+        assert z.max() - z.min() < 11.75                 # (the last threshold lies 11.75 below the largest logit)
+        want = oracle.sample(z, oracle.TOP_P, 0, p, oracle.uniform(SEED, len(prompt) + t))
+        if tok != want:
+            wrong.append((t, tok, want))
+    P.close()
+    assert not wrong
