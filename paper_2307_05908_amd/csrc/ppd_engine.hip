@@ -83,6 +83,7 @@ struct ppd_ctx {
   float *pf_ws; int *pf_cnt;         // partial sums of products whose reduction length is cut, parts done per tile (made when first needed)
   unsigned pg_ready;                 // bit 2 t + paired: that kernel's LDS is set up
   int pg_tile, pg_parts;             // >= 0, > 0: the tile and the cut of every product of the pass (tests)
+  size_t pg_ws_bytes;                // what pf_ws and pf_cnt take
   int dev_pos_pending;   // host mirror of the device state's pending position (-1: unknown)
   uint16_t *rp_x, *rp_a, *rp_f;      // packed two-term rows of a prompt chunk: normalised rows, attention outputs, feed-forward activations (zero beyond d_ff)
   // sampling-based final prediction (Appendix B): 0 arg max, 1 top-k sampling, 2 top-p sampling
@@ -1046,23 +1047,35 @@ int prefill_tiled(ppd_ctx* c, int rows) {
   // QKV, O, FFN in, FFN out
   PGemmPlan plan[4];
   const int nk[4][2] = {{(3 * dm + 15) / 16, dm}, {(dm + 15) / 16, dm}, {swiglu ? (F + 7) / 8 : (F + 15) / 16, dm}, {(dm + 15) / 16, F}};
+  bool cut = true;             // the reduction length may be cut: there is memory for the parts' sums
   for (int i = 0; i < 4; ++i) {
     const int KT = (nk[i][1] + 31) / 32;
-    plan[i] = plan_pgemm(rows, KT, nk[i][0]);
-    if (c->pg_tile >= 0) plan[i].tile = c->pg_tile < PG_TILES ? c->pg_tile : PG_TILES - 1;
-    if (c->pg_parts > 0) plan[i].S = c->pg_parts < KT ? c->pg_parts : KT;
+    auto choose = [&] {
+      plan[i] = plan_pgemm(rows, KT, nk[i][0], cut || c->pg_parts > 0);
+      if (c->pg_tile >= 0) plan[i].tile = c->pg_tile < PG_TILES ? c->pg_tile : PG_TILES - 1;
+      if (c->pg_parts > 0) plan[i].S = c->pg_parts < KT ? c->pg_parts : KT;
+      if (!cut) plan[i].S = 1;
+    };
+    choose();
+    if (plan[i].S > 1 && !c->pf_ws) {
+      void* ws = nullptr;
+      const hipError_t e = hipMalloc(&ws, c->pg_ws_bytes);
+      if (e == hipErrorOutOfMemory) {          // whole products need none
+        (void)hipGetLastError();
+        cut = false;
+        choose();
+      } else {
+        HIPCHK(c, e);
+        c->owned.push_back(ws);
+        HIPCHK(c, hipMemsetAsync((char*)ws + PG_WS_BYTES, 0, PG_MAX_TILES * sizeof(int), c->cur));
+        c->pf_ws = (float*)ws; c->pf_cnt = (int*)((char*)ws + PG_WS_BYTES);
+      }
+    }
     const int paired = i == 2 && swiglu ? 1 : 0;
     const unsigned bit = 1u << (2 * plan[i].tile + paired);
     if (!(c->pg_ready & bit)) {
       HIPCHK(c, pgemm_setup(plan[i], paired != 0));
       c->pg_ready |= bit;
-    }
-    if (plan[i].S > 1 && !c->pf_ws) {
-      void* ws = nullptr;
-      HIPCHK(c, hipMalloc(&ws, PG_WS_BYTES + PG_MAX_TILES * sizeof(int)));
-      c->owned.push_back(ws);
-      HIPCHK(c, hipMemsetAsync((char*)ws + PG_WS_BYTES, 0, PG_MAX_TILES * sizeof(int), c->cur));
-      c->pf_ws = (float*)ws; c->pf_cnt = (int*)((char*)ws + PG_WS_BYTES);
     }
   }
   auto pack = [&](const float* X, int ld, int K, const void* g, const void* b, int norm) -> hipError_t {
@@ -1287,6 +1300,8 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     // the prompt pass's products with one tile shape (1 ..) and one cut of the reduction length (tests)
     c->pg_tile = env_int("PPD_PG_TILE", 0) - 1;
     c->pg_parts = env_int("PPD_PG_PARTS", 0);
+    // (PPD_PG_WS=2: more than any GPU has, so that the allocation fails; tests)
+    c->pg_ws_bytes = env_int("PPD_PG_WS", 1) == 2 ? (size_t)1 << 60 : PG_WS_BYTES + PG_MAX_TILES * sizeof(int);
     // head launches: the same balanced grid as any other GEMM; a workgroup keeps at most
     // HEAD_MAX_ROWS logits = 16 tiles
     c->mg_passes_min = env_int("PPD_MGPASSES", 1);

@@ -848,7 +848,7 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
 
 // launchers (ppd_prefill.hip)
 hipError_t launch_pack_rows(hipStream_t stream, const PackArgs& a);
-PGemmPlan plan_pgemm(int M, int KT, int NT);
+PGemmPlan plan_pgemm(int M, int KT, int NT, bool cut);
 hipError_t launch_pgemm(hipStream_t stream, PGemmArgs a, bool paired, PGemmPlan plan);
 hipError_t pgemm_setup(PGemmPlan plan, bool paired);
 hipError_t launch_rgemm(hipStream_t stream, RGemmArgs a, bool paired);

@@ -31,7 +31,8 @@ constexpr PGemmTile pg_tiles[PG_TILES] = {
 // (a fourth-power mean of the two); cutting the reduction length adds the way through memory.  Fitted to 280 products (20 matrices
 // of 768 x 768 to 27648 x 5120, 33 to 4095 rows) with every tile and cut: the choice is 1.0 % from the best one in the
 // geometric mean, 12 % at worst, and 1.49 times the speed of the kernel before (at worst 1.5 % slower: 320 rows, 22016 x 4096).
-PGemmPlan plan_pgemm(int M, int KT, int NT) {
+// (cut: whether the reduction length may be cut)
+PGemmPlan plan_pgemm(int M, int KT, int NT, bool cut) {
   const int MT = (M + 15) / 16;
   PGemmPlan best = {0, 1};
   float tbest = 0.f;
@@ -40,7 +41,7 @@ PGemmPlan plan_pgemm(int M, int KT, int NT) {
     const int64_t T = (int64_t)((NT + 2 * p.ww * p.tw - 1) / (2 * p.ww * p.tw)) * ((MT + 2 * p.wx * p.tx - 1) / (2 * p.wx * p.tx));
     const size_t bytes = (size_t)p.ww * p.wx * p.tw * p.tx * 4096;
     for (const int S : {1, 2, 3, 4, 6, 8}) {
-      if (S > 1 && (KT < 6 * S || T > PG_MAX_TILES || T * S * bytes > PG_WS_BYTES)) break;
+      if (S > 1 && (!cut || KT < 6 * S || T > PG_MAX_TILES || T * S * bytes > PG_WS_BYTES)) break;
       const int64_t m = (T * S + 255) / 256;
       const float comp = (float)m * (float)((KT + S - 1) / S) * p.stage + (float)((m + p.per - 1) / p.per) * p.rest;
       const float mem = (float)NT * (float)KT * (1024.f / 4.05e6f);

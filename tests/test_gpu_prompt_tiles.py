@@ -50,3 +50,22 @@ def test_every_tile_and_cut_agrees_with_the_row_chunks(name, tile, parts, monkey
         # tests of longer prompts have the same bound)
         assert np.abs(z - r).max() <= 1e-4
         np.testing.assert_array_equal(z.view(np.uint32), z2.view(np.uint32))     # the parts are added in their order
+
+
+@pytest.mark.parametrize("name", list(CFG))
+def test_products_stay_whole_where_the_parts_sums_cannot_be_allocated(name, monkeypatch):
+    """(PPD_PG_WS=2 asks for more memory than a GPU has.)  The prompt runs as with PPD_PG_PARTS=1, bit for bit, the calls behind
+    it find no error left over, and so does the rule's own choice, which cuts some of these products."""
+    dev, _ = _reference(name, monkeypatch)
+    got = []
+    for env in ({"PPD_PG_PARTS": "1"}, {"PPD_PG_PARTS": "3", "PPD_PG_WS": "2"}, {"PPD_PG_WS": "2"}):
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        P = binding.PPD(CFG[name], dev, k=1)
+        got.append(_generate(P))
+        P.close()
+        for k in env:
+            monkeypatch.delenv(k)
+    for z, z2, z3 in zip(*got):
+        np.testing.assert_array_equal(z.view(np.uint32), z2.view(np.uint32))
+        assert np.abs(z - z3).max() <= 1e-4                  # (another tile may be the better one; the bound is the one above)
