@@ -240,8 +240,12 @@ int narrow_tiles(const MGemmArgs& a, int ngroups, int mmax) {
 
 template <bool PAIRED, int NORM, int T, int NB, bool MERGE = false>
 hipError_t narrow_go(hipStream_t st, const MGemmArgs& a, dim3 grid, int lds) {
-  if constexpr (NORM < 0 && !PAIRED && NB <= 8 && !MERGE)
-    if (a.nmerge > 0) return narrow_go<PAIRED, NORM, T, NB, true>(st, a, grid, lds);
+  // (the output projection of the widths that merges_itself takes has one tile per workgroup and shares of up to 8 blocks)
+  if constexpr (!MERGE)
+    if (a.nmerge > 0) {
+      if constexpr (NORM < 0 && !PAIRED && T == 1 && NB <= 8) return narrow_go<PAIRED, NORM, T, NB, true>(st, a, grid, lds);
+      else return hipErrorInvalidValue;
+    }
   const auto k = gemm_mfma_narrow_kernel<PAIRED, NORM, T, NB, MERGE>;
   if (a.KT == 0) return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);   // (setup)
   hipLaunchKernelGGL(k, grid, dim3(MG_THREADS), lds, st, a);
@@ -266,7 +270,7 @@ hipError_t narrow_setup(const ppd_model_dims& d) {
     MGemmArgs a; memset(&a, 0, sizeof a);
     a.norm = norm; a.nmerge = nmerge;
     const int KT = (K + 31) / 32, nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
-    if (nb8 > (norm >= 0 ? 8 : 16) || mg_narrow_lds(KT, MG_NARROW_ROWS, 1) <= 64 * 1024) return hipSuccess;
+    if (nb8 > (norm >= 0 || nmerge ? 8 : 16) || mg_narrow_lds(KT, MG_NARROW_ROWS, 1) <= 64 * 1024) return hipSuccess;
     return narrow_launch(nullptr, a, paired, nb8, 1, dim3(1), 0);
   };
   hipError_t e = set(d.d_model, d.norm, false, 0);
