@@ -484,7 +484,7 @@ int run_layer(ppd_ctx* c, int ngroups, const RowGroup* rg, int pmax, int stages 
     if (whole) {
       const AttnWholeArgs w = {a, {mg.out[0], mg.out[1]}};
       ProfScope ps(c, PPD_KC_ATTN, ngroups);
-      HIPCHK(c, d.head_dim == 64 ? launch_attn_whole<64>(c->cur, w, mmax, ngroups) : launch_attn_whole<128>(c->cur, w, mmax, ngroups));
+      HIPCHK(c, d.head_dim == 64 ? launch_attn_whole<64>(c->cur, w, mmax, ngroups, pmax) : launch_attn_whole<128>(c->cur, w, mmax, ngroups, pmax));
     } else {
       { ProfScope ps(c, PPD_KC_ATTN, ngroups); HIPCHK(c, launch_attn(c, a, ngroups, pmax)); }
       mg.H = d.n_heads; mg.HD = d.head_dim; mg.d_model = dm; mg.nchunk_max = c->nchunk_max;
@@ -922,6 +922,8 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
       HIPCHK(c, e);
       graph_chunks = nchunks;
     }
+    // (chunks past those it was captured for would be left out: attn_kernel's grid, attn_whole_kernel's workgroups)
+    if (pmax / ATT_CHUNK >= graph_chunks) HIPCHK(c, hipErrorInvalidValue);
     HIPCHK(c, hipGraphLaunch(graph, c->stream));
   } else {
     if ((rc = issue_round(c, kind, pmax, again))) return rc;

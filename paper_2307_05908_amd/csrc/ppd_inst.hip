@@ -89,19 +89,19 @@ hipError_t launch_attn_t(hipStream_t stream, const AttnArgs& a, int mmax, dim3 g
 }
 
 template <int HD>
-hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups) {
+hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups, int pmax) {
   static_assert(sizeof(float) * attn_whole_lds_floats<HD>(MAXM) <= 64 * 1024, "MAXM rows fit the default dynamic LDS limit");
-  if (mmax < 1 || mmax > MAXM) return hipErrorInvalidValue;
+  if (mmax < 1 || mmax > MAXM || pmax >= ATT_WHOLE * ATT_CHUNK) return hipErrorInvalidValue;
   attn_whole_kernel<HD><<<dim3(w.a.H, ngroups), dim3(ATT_WHOLE_THREADS), sizeof(float) * (size_t)attn_whole_lds_floats<HD>(mmax), stream>>>(w);
   return hipGetLastError();
 }
 
 #if PPD_INST == 4
 template hipError_t launch_attn_t<128>(hipStream_t, const AttnArgs&, int, dim3, bool);
-template hipError_t launch_attn_whole<128>(hipStream_t, const AttnWholeArgs&, int, int);
+template hipError_t launch_attn_whole<128>(hipStream_t, const AttnWholeArgs&, int, int, int);
 #elif PPD_INST == 5
 template hipError_t launch_attn_t<64>(hipStream_t, const AttnArgs&, int, dim3, bool);
-template hipError_t launch_attn_whole<64>(hipStream_t, const AttnWholeArgs&, int, int);
+template hipError_t launch_attn_whole<64>(hipStream_t, const AttnWholeArgs&, int, int, int);
 #endif
 #endif
 

@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(ATT_WHOLE_THREADS) void attn_whole_kernel(AttnWhole
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x, p = a.ds->pos + G.pos_off, M = G.M, nc = p / ATT_CHUNK + 1;
-  if (nc > ATT_WHOLE) return;         // (the host launches this kernel for no such position)
+  if (nc > ATT_WHOLE) return;         // (its launcher refuses such a position, and run_round_once a graph captured for fewer chunks)
   float* raw = lds;                   // [M][3][HD]
   float* ored = lds;                  // [WAVES][M][HD], written only after the barriers that follow the rotation
   float* qs = lds + M * WAVES * HD;   // [M][HD]

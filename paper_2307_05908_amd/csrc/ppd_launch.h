@@ -20,9 +20,9 @@ hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups,
 
 template <int HD>
 hipError_t launch_attn_t(hipStream_t stream, const AttnArgs& a, int mmax, dim3 grid, bool causal);
-// attn_whole_kernel; mmax: the largest row count of the groups
+// attn_whole_kernel; mmax: the largest row count of the groups, pmax: the largest position any row may sit at
 template <int HD>
-hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups);
+hipError_t launch_attn_whole(hipStream_t stream, const AttnWholeArgs& w, int mmax, int ngroups, int pmax);
 
 // Workgroups per group for a GEMM with `nsets` row sets (gemm_kernel): each workgroup has four waves and
 // every wave takes ceil(nsets / waves) sets, so pick the count in [gmax/2, gmax] that wastes the fewest
