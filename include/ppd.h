@@ -197,7 +197,12 @@ int ppd_set_sampling(ppd_ctx *ctx, int mode, int top_k, double top_p, uint64_t s
 int ppd_get_stats(const ppd_ctx *ctx, ppd_stats *out);
 
 /* Rounds are replayed as captured HIP graphs (one per round shape) unless profiling is on;
- * on = 0 issues every launch eagerly instead.  Results are identical either way. */
+ * on = 0 issues every launch eagerly instead.  Results are identical either way.
+ * While a round is being captured (a fraction of a millisecond, in ppd_step and plain_greedy_step), HIP refuses a
+ * synchronous hipMemcpy or hipMemset and hipDeviceSynchronize to every thread of the process, and such a call takes
+ * the capture with it.  No entry point of this library makes one, and a round whose capture is lost goes launch by
+ * launch; a program whose own threads make such calls beside decoding ones switches the replay off (here, or with
+ * PPD_GRAPHS=2 in the environment at ppd_create). */
 int ppd_set_graphs(ppd_ctx *ctx, int on);
 
 /* The early prediction of Sec. 3 on its own, outside any context: logits = head . Norm(h) for one

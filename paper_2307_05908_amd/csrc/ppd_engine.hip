@@ -887,6 +887,32 @@ struct WorkScope {
   }
 };
 
+// Captures a round with an attention grid of nchunks; false: not now.  A synchronous copy, a fill or a device synchronisation of any
+// thread of the process invalidates a capture that is under way (and fails itself), and launches go on failing on the stream after
+// it has ended: so it has a stream to itself, and the round goes launch by launch.
+bool capture_round(ppd_ctx* c, int kind, int nchunks, hipGraphExec_t* exec) {
+  const int last = c->last_hip;
+  hipStream_t st = nullptr;
+  hipGraph_t g = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed);
+  if (e == hipSuccess) {
+    c->cur = st;
+    const int rc = issue_round(c, kind, nchunks * ATT_CHUNK - 1);
+    c->cur = c->stream;
+    e = hipStreamEndCapture(st, &g);
+    if (rc && e == hipSuccess) e = hipErrorStreamCaptureInvalidated;
+  }
+  if (e == hipSuccess) e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
+  if (g) (void)hipGraphDestroy(g);
+  if (st) (void)hipStreamDestroy(st);
+  if (e == hipSuccess) return true;
+  (void)hipGetLastError();
+  c->last_hip = last;
+  *exec = nullptr;
+  return false;
+}
+
 // Run one round: set the device state, replay (or capture, or issue eagerly) the launches,
 // wait, read token and match index from pinned memory.
 int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
@@ -896,6 +922,7 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   // the device already holds this position as pending when the previous call was a round at pos - 1
   if (c->dev_pos_pending != pos && (rc = set_state(c, pos, -1))) return rc;
   const int pmax = pos + (kind == 2 ? 0 : 1);
+  hipGraphExec_t replay = nullptr;
   if (c->use_graphs && !c->prof && !again) {
     // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least ATT_WHOLE, which
     // has a kernel and a graph of its own, then 4, at most the cache's), so that a sequence re-captures a handful of times
@@ -910,24 +937,13 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
       HIPCHK(c, hipGraphExecDestroy(graph));
       graph = nullptr;
     }
-    if (!graph) {
-      hipGraph_t g = nullptr;
-      HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-      rc = issue_round(c, kind, nchunks * ATT_CHUNK - 1);
-      hipError_t e = hipStreamEndCapture(c->stream, &g);
-      if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
-      HIPCHK(c, e);
-      e = hipGraphInstantiate(&graph, g, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(g);
-      HIPCHK(c, e);
-      graph_chunks = nchunks;
-    }
+    if (!graph && capture_round(c, kind, nchunks, &graph)) graph_chunks = nchunks;
     // (chunks past those it was captured for would be left out: attn_kernel's grid, attn_whole_kernel's workgroups)
-    if (pmax / ATT_CHUNK >= graph_chunks) HIPCHK(c, hipErrorInvalidValue);
-    HIPCHK(c, hipGraphLaunch(graph, c->stream));
-  } else {
-    if ((rc = issue_round(c, kind, pmax, again))) return rc;
+    if (graph && pmax / ATT_CHUNK >= graph_chunks) HIPCHK(c, hipErrorInvalidValue);
+    replay = graph;
   }
+  if (replay) HIPCHK(c, hipGraphLaunch(replay, c->stream));
+  else if ((rc = issue_round(c, kind, pmax, again))) return rc;
   c->dev_pos_pending = -1;                       // (unknown until the round is known to have run)
   // The round's last kernel writes token and match index to pinned memory and then the count of finished rounds:
   // poll that word instead of sleeping in a stream synchronisation (the wake-up costs more than a round's tail).
@@ -1128,6 +1144,13 @@ int prefill_tiled(ppd_ctx* c, int rows) {
   return PPD_OK;
 }
 
+// (on the context's stream: a copy on the null stream fails while another thread's context captures a round, and so does the capture.
+// Measured, 32000 logits behind a round: copy on the null stream 52 us, asynchronous copy and wait 61, this 30.)
+int copy_logits(ppd_ctx* c, float* host, const float* dev) {
+  HIPCHK(c, hipMemcpyWithStream(host, dev, (size_t)c->d.vocab * sizeof(float), hipMemcpyDeviceToHost, c->stream));
+  return PPD_OK;
+}
+
 }  // namespace
 
 namespace ppd {
@@ -1210,7 +1233,9 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   const size_t RC = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
   const size_t RB = R > RC ? R : RC;   // activation rows: a round's 1 + k, or a prompt chunk
   const size_t RL = d.wdtype == 1 ? c->few_rows : PREFILL_CHUNK_FP32, RS = R > RL ? R : RL;   // those that go through run_layer
-  hipError_t e = hipSuccess;
+  // (every fill and copy below goes to this stream, see copy_logits)
+  hipError_t e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
+  c->cur = c->stream;
   auto alloc = [&](void** p, size_t bytes) { if (e == hipSuccess) e = hipMalloc(p, bytes); };
   alloc((void**)&c->Kc, (size_t)d.n_layers * cache_layer_bytes(c));
   alloc((void**)&c->Vc, (size_t)d.n_layers * cache_layer_bytes(c));
@@ -1223,7 +1248,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     alloc((void**)&c->rp_x, packed_bytes(PREFILL_CHUNK, (int)dm));
     alloc((void**)&c->rp_a, packed_bytes(PREFILL_CHUNK, (int)dm));
     alloc((void**)&c->rp_f, packed_bytes(PREFILL_CHUNK, d.d_ff));
-    if (e == hipSuccess) e = hipMemset(c->rp_f, 0, packed_bytes(PREFILL_CHUNK, d.d_ff));
+    if (e == hipSuccess) e = hipMemsetAsync(c->rp_f, 0, packed_bytes(PREFILL_CHUNK, d.d_ff), c->stream);
   }
   alloc((void**)&c->ffn, RS * (size_t)d.d_ff * sizeof(float));
   alloc((void**)&c->part, RB * d.n_heads * (size_t)c->nchunk_max * (d.head_dim + 2) * sizeof(float));
@@ -1245,8 +1270,6 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->host_result, (2 + MAXM + 1) * sizeof(int32_t), hipHostMallocMapped);
   if (e == hipSuccess) memset(c->host_result, 0, (2 + MAXM + 1) * sizeof(int32_t));
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->host_result_dev, c->host_result, 0);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
-  c->cur = c->stream;
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming);
   if (e == hipSuccess && d.pos == 1) {
     // (cos, sin) of pos * theta^(-2i/hd), evaluated in double on the host
@@ -1257,12 +1280,12 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
         double ang = (double)p * pow((double)d.rope_theta, -2.0 * i / d.head_dim);
         tab[(size_t)p * half + i] = make_float2((float)cos(ang), (float)sin(ang));
       }
-    e = hipMemcpy(c->rope, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice);
+    e = hipMemcpyWithStream(c->rope, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice, c->stream);
   }
-  if (e == hipSuccess) e = hipMemset(c->ds, 0, sizeof(DevState));
+  if (e == hipSuccess) e = hipMemsetAsync(c->ds, 0, sizeof(DevState), c->stream);
   // the attention MFMAs read whole 16-position blocks: positions not yet written must hold finite numbers
-  if (e == hipSuccess) e = hipMemset(c->Kc, 0, (size_t)d.n_layers * cache_layer_bytes(c));
-  if (e == hipSuccess) e = hipMemset(c->Vc, 0, (size_t)d.n_layers * cache_layer_bytes(c));
+  if (e == hipSuccess) e = hipMemsetAsync(c->Kc, 0, (size_t)d.n_layers * cache_layer_bytes(c), c->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(c->Vc, 0, (size_t)d.n_layers * cache_layer_bytes(c), c->stream);
   c->mfma = d.wdtype == 1;
   if (e == hipSuccess && c->mfma) {
     // repack every linear weight into MFMA blocks (owned copies), on the context's stream and after whatever
@@ -1352,15 +1375,15 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     alloc((void**)&c->fl_ex, nex * sizeof(float));
     alloc((void**)&c->fl_part, npart * sizeof(float));
     alloc((void**)&c->h_save, R * dm * sizeof(float));
-    if (e == hipSuccess) e = hipMemcpy(c->fl_tab, tab.data(), d.n_layers * sizeof(FLayer), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemsetD32(c->fl_part, (int)FU_EMPTY, npart);
+    if (e == hipSuccess) e = hipMemcpyWithStream(c->fl_tab, tab.data(), d.n_layers * sizeof(FLayer), hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = hipMemsetD32Async(c->fl_part, (int)FU_EMPTY, npart, c->stream);
     if (e == hipSuccess && fused_plan(c)) {
       e = fused_setup(d.head_dim, c->fused_narrow != 0, c->fused_lds);
       c->fused = 1;
     }
   }
-  // (the fills and copies above went to the null stream, which the context's own stream does not wait for)
-  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);      // (what the caller has queued on the default stream, too)
   if (e != hipSuccess) {
     g_create_hip_error = (int)e;
     (void)hipGetLastError();
@@ -1477,9 +1500,7 @@ int plain_greedy_step(ppd_ctx* c, int32_t* out_token) {
 int ppd_get_logits(ppd_ctx* c, float* host_logits) {
   if (!c || !host_logits) return PPD_EINVAL;
   if (c->n_ctx < 0) return PPD_ESTATE;
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, hipMemcpy(host_logits, c->logits, (size_t)c->d.vocab * sizeof(float), hipMemcpyDeviceToHost));
-  return PPD_OK;
+  return copy_logits(c, host_logits, c->logits);
 }
 
 int ppd_get_early_logits(ppd_ctx* c, float* host_logits) {
@@ -1488,9 +1509,7 @@ int ppd_get_early_logits(ppd_ctx* c, float* host_logits) {
   // a round that started from a speculative prediction has its early logits in the half of early_spec that
   // its position's parity selects (the position of the last round's main token is n_ctx - 1)
   const float* src = c->last_kind == 3 ? c->early_spec + (size_t)((c->n_ctx - 1) & 1) * c->d.vocab : c->early_logits;
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, hipMemcpy(host_logits, src, (size_t)c->d.vocab * sizeof(float), hipMemcpyDeviceToHost));
-  return PPD_OK;
+  return copy_logits(c, host_logits, src);
 }
 
 int ppd_get_stats(const ppd_ctx* c, ppd_stats* out) {
