@@ -888,24 +888,28 @@ struct WorkScope {
 };
 
 // Captures a round with an attention grid of nchunks; false: not now.  A synchronous copy, a fill or a device synchronisation of any
-// thread of the process invalidates a capture that is under way (and fails itself), and launches go on failing on the stream after
-// it has ended: so it has a stream to itself, and the round goes launch by launch.
+// thread of the process invalidates a capture that is under way (and fails itself), and launches go on failing on the stream until
+// another capture has come to a good end: an empty one, then the round goes launch by launch.  (A stream made for each capture, left to
+// itself where it fails: 250 us more for a capture that takes 60 to 440.)
 bool capture_round(ppd_ctx* c, int kind, int nchunks, hipGraphExec_t* exec) {
   const int last = c->last_hip;
-  hipStream_t st = nullptr;
   hipGraph_t g = nullptr;
-  hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed);
+  hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
   if (e == hipSuccess) {
-    c->cur = st;
     const int rc = issue_round(c, kind, nchunks * ATT_CHUNK - 1);
-    c->cur = c->stream;
-    e = hipStreamEndCapture(st, &g);
-    if (rc && e == hipSuccess) e = hipErrorStreamCaptureInvalidated;
+    e = hipStreamEndCapture(c->stream, &g);
+    if (e != hipSuccess) {
+      for (int i = 0; i < 16; ++i) {             // (the same may happen to the empty one)
+        hipGraph_t none = nullptr;
+        (void)hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
+        const hipError_t e1 = hipStreamEndCapture(c->stream, &none);
+        if (none) (void)hipGraphDestroy(none);
+        if (e1 == hipSuccess) break;
+      }
+    } else if (rc) e = hipErrorStreamCaptureInvalidated;
   }
   if (e == hipSuccess) e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
-  if (st) (void)hipStreamDestroy(st);
   if (e == hipSuccess) return true;
   (void)hipGetLastError();
   c->last_hip = last;

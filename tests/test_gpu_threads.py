@@ -56,3 +56,38 @@ def test_captures_beside_another_threads_calls(family):
     for a in got:
         np.testing.assert_array_equal(a[0], ref_q[0])
         np.testing.assert_array_equal(a[1].view(np.uint32), ref_q[1].view(np.uint32))
+
+
+def test_rounds_whose_captures_are_lost_are_run_all_the_same():
+    """The caller's own thread synchronises the device beside a decoding one: HIP takes the capture with it (that call may
+    fail, which is the caller's to see), the rounds go on."""
+    import torch
+    cfg = small_cfg("tiny", n_layers=4, exit_layer=2, max_ctx=200, n_gen=12)
+    P = binding.PPD(cfg, binding.upload_model(pi.make_model(cfg)))
+    prompt = pi.make_prompt(cfg, 20)
+    ref = gpu_generate(P, prompt, cfg.n_gen, "ppd")
+    done, refused = threading.Event(), [0]
+
+    def synchronise():
+        while not done.is_set():
+            try:
+                torch.cuda.synchronize()
+            except RuntimeError:
+                refused[0] += 1
+
+    t = threading.Thread(target=synchronise)
+    t.start()
+    try:
+        for i in range(400):
+            if i >= 20 and refused[0] >= 3:
+                break
+            P.ppd_set_sampling(0)
+            got = gpu_generate(P, prompt, cfg.n_gen, "ppd")
+            np.testing.assert_array_equal(got[0], ref[0])
+            np.testing.assert_array_equal(got[1].view(np.uint32), ref[1].view(np.uint32))
+    finally:
+        done.set()
+        t.join()
+        P.close()
+        time.sleep(0.1)
+    assert refused[0] > 0            # (a capture was lost)
