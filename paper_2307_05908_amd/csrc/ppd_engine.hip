@@ -99,8 +99,8 @@ struct ppd_ctx {
   // captured rounds, with one launch per step of a layer and with the one-launch chain: 0 ppd round from layer 1,
   // 1 ppd round after a match, 2 plain step, 3 ppd round after a match whose candidates were predicted by the round before
   int use_graphs;
-  hipGraphExec_t graph[2][2][4];  // [chain][past the short sequences (ATT_WHOLE chunks)][kind]
-  int graph_chunks[2][2][4];      // attention grid (64-position chunks) each graph was captured with
+  hipGraphExec_t graph[2][3][4];  // [chain][sequences of up to ATT_WHOLE, up to MG_MERGE, more chunks: other kernels][kind]
+  int graph_chunks[2][3][4];      // attention grid (64-position chunks) each graph was captured with
   int gmax1, gmax2;      // workgroup budget of an fp32 GEMM launch: one group / per group of a two-group launch
   int nchunk_max;
   // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
@@ -928,15 +928,16 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   const int pmax = pos + (kind == 2 ? 0 : 1);
   hipGraphExec_t replay = nullptr;
   if (c->use_graphs && !c->prof && !again) {
-    // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least ATT_WHOLE, which
-    // has a kernel and a graph of its own, then 4, at most the cache's), so that a sequence re-captures a handful of times
-    // instead of every 64 positions; chunks past a row's position return at once.
+    // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least ATT_WHOLE, at most the
+    // cache's), so that a sequence re-captures a handful of times instead of every 64 positions; chunks past a row's position return
+    // at once.  Lengths that run other kernels have graphs of their own, which a longer sequence before them leaves as they are (768
+    // wide, position 140 behind one of 600, a plain token / PPD round: 317 / 374 us with that one's graph, 290 / 348 with their own).
     int nchunks = ATT_WHOLE;
     while (nchunks < pmax / ATT_CHUNK + 1) nchunks *= 2;
     if (nchunks > c->nchunk_max) nchunks = c->nchunk_max;
-    const int longer = nchunks > ATT_WHOLE;
-    hipGraphExec_t& graph = c->graph[c->chain][longer][kind];
-    int& graph_chunks = c->graph_chunks[c->chain][longer][kind];
+    const int length = nchunks > MG_MERGE ? 2 : (nchunks > ATT_WHOLE ? 1 : 0);
+    hipGraphExec_t& graph = c->graph[c->chain][length][kind];
+    int& graph_chunks = c->graph_chunks[c->chain][length][kind];
     if (graph && graph_chunks < nchunks) {
       HIPCHK(c, hipGraphExecDestroy(graph));
       graph = nullptr;
