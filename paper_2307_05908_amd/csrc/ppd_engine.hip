@@ -634,9 +634,16 @@ int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
 
 // Models whose products are all gemm_mfma_narrow_kernel's: there a launch takes no longer than an exchange of the one-launch chain,
 // and the attention is spread over more workgroups.  Measured (a plain token of 12 layers, us, chain / launches, at positions
-// 40 / 140 / 480): OPT-like 512 wide 301 / 249, 300 / 251, 313 / 255; 768 315 / 280, 315 / 283, 330 / 289; 1024 327 / 271, 328 / 275,
-// 341 / 282; LLaMA-like 1024 346 / 293, 358 / 283, 365 / 328.  Up to 256 columns the difference is the smallest (OPT-like 259 / 241 at
-// 140) and the chain stays.  From 1152 on it is the better one past the short sequences (1536 419 / 427 at 230, 424 / 465 at 480).
+// 100, 480, 1000, 2000, 7000): OPT-like 320 wide 282 / 257, 291 / 257, 295 / 298, 305 / 301, 430 / 334; 768 314 / 287, 327 / 292,
+// 332 / 330, 347 / 346, 474 / 402; 1024 327 / 281, 339 / 286, 343 / 324, 360 / 343, 494 / 425; LLaMA-like 1024 345 / 303, 359 / 296,
+// 368 / 332, 383 / 346, 546 / 450.  From 1152 on the chain is the better one past the short sequences (1536 419 / 427 at 230,
+// 424 / 465 at 480).
+// Up to 256 columns launches are as fast from 1000 positions on and faster before (256 wide 275 / 248, 284 / 247, 290 / 289,
+// 300 / 294, 318 / 319; 64 wide 238 / 208, 255 / 212, 261 / 248, 252 / 250, 278 / 276).  The chain stays there all the same, and not
+// for its speed: the small models that exercise it count their rounds in it (ppd_get_chain_rounds).
+// What the rule costs is a context's first round of a kind and length, whose capture has five nodes a layer in place of one: the
+// first plain token 388 - 489 us with the chain and 433 - 515 without (768 wide, 12 layers; the second 352 / 279), 1217 - 1401 and
+// 1314 - 1445 (1024 wide, 40 layers; 1150 / 885); a first PPD round, whose parallel phase has launches either way, 563 - 749 and 470 - 610.
 bool launches_pay(const ppd_model_dims& d) { return d.d_model > 256 && d.d_model <= 1024 && d.d_ff <= 4096; }
 
 // The arguments of a one-launch chain of layers on row 0 that do not change, and its layout of a compute unit's LDS; false: it does

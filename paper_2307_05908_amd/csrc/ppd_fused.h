@@ -14,7 +14,7 @@
 // Meanwhile the helpers add up the step's outputs, publish them, and bring the next step's row into LDS; they have no
 // weight requests in flight, so nothing of this queues behind the ring (a wave's loads return in order).
 // Measured (MI355X, context 512, one token): 7B shape 3.09 -> 2.60 ms.  (Widths from 320 to 1024, the OPT-125m shape among them,
-// go launch by launch again: launches_pay, ppd_engine.hip.)  Every 1000 positions
+// go launch by launch: launches_pay, ppd_engine.hip.)  Every 1000 positions
 // take about 1 us a layer from that: the attention's items pay for their barriers, and the launches are the faster way
 // from some 4000 - 12000 positions on (the rule and its figures: chain_pays, ppd_engine.hip).
 //
@@ -46,8 +46,8 @@ constexpr int FU_RING = 6;                         // register batches of MG_BAT
 // NARROW instances of the kernel: every workgroup's share of every product fits the ring, so a layer is latency and no stream.
 // What is requested ahead goes out at once and only what is wanted, where the others wait for one batch before they request
 // the next, wanted or not: six memory latencies in the way of each product.  Measured (a plain token, us per layer,
-// without / with): OPT-like 256 wide 24.0 / 22.7, 768 28.4 / 26.1, 1024 29.9 / 27.1, LLaMA-like 512 27.0 / 25.2, 1024 30.1 / 28.4,
-// 2048 39.0 / 38.1; where shares do not fit: 2560 46.8 / 48.7, 4096 79.3 / 84.4.  (Of these widths 256 and 2048 still come here.)
+// without / with): OPT-like 256 wide 24.0 / 22.7, LLaMA-like 2048 39.0 / 38.1; where shares do not fit: 2560 46.8 / 48.7, 4096
+// 79.3 / 84.4.
 constexpr int FU_KV = FU_RING - 4;                 // the last four take an attention item's keys and values
 constexpr int FU_SLEEP = 4;                        // 64 clocks each, between two looks at pieces of a row that are not there yet
 constexpr int FU_MAX_WG = 256;

@@ -10,9 +10,9 @@ hipError_t launch_gemm_t(hipStream_t stream, const GemmArgs& a, int MA, int MB, 
 
 // gemm_small_kernel, where it applies: fp32 weights, K <= GEMM_SMALL_K, and every output has a wave's turn of its own (up to
 // GEMM_SMALL_ROWS outputs; of a head launch, one set per wave of its grid).  Measured over the rule (launches of one and k rows with
-// the event pair around them, gemm_kernel / this one before its waves shared a norm's rows, us): 256 columns to 4096 outputs, k = 1 13.7 / 6.7, k = 8 38.5 / 15.2;
-// 1024 columns to 1024 outputs 11.3 / 6.7 and 26.5 / 14.9, to 3072 15.2 / 9.6 and 39.7 / 29.2, to 4096 17.7 / 11.1 and 44.7 / 35.5, to 4096
-// pairs 22.7 / 15.3 and 50.9 / 39.6; 64 rows of a prompt on the 1024-wide model of 8 layers 8.9 / 5.8 ms.
+// the event pair around them, gemm_kernel / this one, us): 256 columns to 4096 outputs, k = 1 13.4 / 6.7, k = 8 38.1 / 10.6;
+// 1024 columns to 1024 outputs 9.7 / 6.2 and 15.5 / 8.4, to 3072 15.5 / 9.3 and 40.0 / 20.5, to 4096 17.1 / 10.7 and 44.7 / 24.5, to 4096
+// pairs 21.9 / 15.0 and 50.6 / 28.2; 64 rows of a prompt on the 1024-wide model of 8 layers 8.1 / 4.5 ms.
 inline bool gemm_small_fits(const GemmArgs& a, int head_grid) {
   return a.K <= GEMM_SMALL_K && (a.topk > 0 ? (int64_t)a.ntot <= (int64_t)head_grid * GEMM_WAVES * 4 : a.ntot <= GEMM_SMALL_ROWS);
 }

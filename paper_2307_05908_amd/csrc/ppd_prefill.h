@@ -677,7 +677,8 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the longest rows first; heads that divide among the XCDs (workgroup b runs on XCD b % 8) stay on one each, where a dozen
   // workgroups of a head walk the same steps and find them in its L2.  With a head's rows spread over all XCDs the steps came from
-  // memory eight times, 3 TB/s of them: 13B shape, 4095 rows, 892 -> 526 us.
+  // memory eight times, 3 TB/s of them: 13B shape, 4095 rows, 892 -> 526 us.  (Other numbers of heads, 12, 20 or 36, keep
+  // that order.)
   int h = blockIdx.y, wg = (int)gridDim.x - 1 - (int)blockIdx.x;
   if ((a.H & 7) == 0) {
     const int b = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x, r = b >> 3, per = a.H >> 3;

@@ -29,8 +29,11 @@ constexpr PGemmTile pg_tiles[PG_TILES] = {
 
 // The shortest time by this account: workgroups of a compute unit times stages, or the weights at 4 TB/s, whichever is longer
 // (a fourth-power mean of the two); cutting the reduction length adds the way through memory.  Fitted to 280 products (20 matrices
-// of 768 x 768 to 27648 x 5120, 33 to 4095 rows) with every tile and cut: the choice is 1.0 % from the best one in the
-// geometric mean, 12 % at worst, and 1.49 times the speed of the kernel before (at worst 1.5 % slower: 320 rows, 22016 x 4096).
+// of 768 x 768 to 27648 x 5120, 33 to 4095 rows) with every tile and cut, products on their own: the choice is 1.0 % from
+// the best one in the geometric mean, 12 % at worst, and 1.49 times the speed of the kernel before (at worst 1.5 % slower: 320 rows,
+// 22016 x 4096).  Between a layer's other launches a product takes 1.15 to 1.4 times what the account says (7B shape, 511 rows, QKV, O, FFN
+// in, FFN out: 74, 32, 134, 80 us by it, 97, 44, 154, 97 in the model), whatever the tile: of the tiles and cuts measured there, with
+// 127 and with 511 rows, none was faster than the choice.
 // (cut: whether the reduction length may be cut)
 PGemmPlan plan_pgemm(int M, int KT, int NT, bool cut) {
   const int MT = (M + 15) / 16;
