@@ -32,9 +32,9 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # HBM bytes per launch of the roofline kernel (the two-group FFN-in GEMM) from rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled
 # by a copy kernel of known size, keyed by (configuration, k); collected with the counter probe on the C ABI
 # (paper_2307_05908_amd/ppd_pmc_probe), see profiles/.  A property of the kernel source it was collected on.
-MEASURED_TRAFFIC = {("llama7b", 3): 361.77e6}
+MEASURED_TRAFFIC = {("llama7b", 3): 361.78e6}
 # sha1 of csrc/ppd_kernels.h when the counters were collected: a changed kernel source voids the figure (null is printed)
-TRAFFIC_KERNELS_SHA1 = "37878aa9d642c7d187f7285b7c720b5dec3a90f0"
+TRAFFIC_KERNELS_SHA1 = "2d324bb427d2f4cce1900181ab0a34a56b1dda8d"
 TRAFFIC_SOURCE = "profiles/llama7b_ppd_k3_traffic.txt"
 
 
