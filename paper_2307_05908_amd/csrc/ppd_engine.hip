@@ -897,7 +897,7 @@ struct WorkScope {
 // Captures a round with an attention grid of nchunks; false: not now.  A synchronous copy, a fill or a device synchronisation of any
 // thread of the process invalidates a capture that is under way (and fails itself), and launches go on failing on the stream until
 // another capture has come to a good end: an empty one, then the round goes launch by launch.  (A stream made for each capture, left to
-// itself where it fails: 250 us more for a capture that takes 60 to 440.)
+// itself where it fails: 60 - 160 us to make and give back, beside a capture's 60 - 440.)
 bool capture_round(ppd_ctx* c, int kind, int nchunks, hipGraphExec_t* exec) {
   const int last = c->last_hip;
   hipGraph_t g = nullptr;
