@@ -1157,7 +1157,7 @@ int prefill_tiled(ppd_ctx* c, int rows) {
 }
 
 // (on the context's stream: a copy on the null stream fails while another thread's context captures a round, and so does the capture.
-// Measured, 32000 logits behind a round: copy on the null stream 52 us, asynchronous copy and wait 61, this 30.)
+// Measured behind a round, copy on the null stream / this: 1024 logits 33 / 21 us, 32000 33 / 33.)
 int copy_logits(ppd_ctx* c, float* host, const float* dev) {
   HIPCHK(c, hipMemcpyWithStream(host, dev, (size_t)c->d.vocab * sizeof(float), hipMemcpyDeviceToHost, c->stream));
   return PPD_OK;
