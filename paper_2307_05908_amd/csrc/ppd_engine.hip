@@ -1398,6 +1398,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);      // (what the caller has queued on the default stream, too)
   if (e != hipSuccess) {
     g_create_hip_error = (int)e;
+    if (c->stream) (void)hipStreamSynchronize(c->stream);     // (fills and repacking that are under way)
     (void)hipGetLastError();
     free_all(c);
     int rc = (e == hipErrorOutOfMemory) ? PPD_ENOMEM : PPD_EHIP;
