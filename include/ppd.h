@@ -97,7 +97,7 @@ typedef struct {
   uint64_t rounds;            /* tokens emitted by ppd_step */
   uint64_t matches;           /* rounds with matched == 1 */
   uint64_t runs;              /* N of Sec. 4.1: rounds that started from layer 1 */
-  uint64_t main_layer_rows;   /* layer executions of the main token: latency in time units */
+  uint64_t main_layer_rows;   /* layer executions of the main token (x_0's in ppd_prefill count with the first round): latency in time units */
   uint64_t branch_layer_rows; /* layer executions of candidate rows */
   uint64_t plain_steps;       /* tokens emitted by plain_greedy_step */
   uint64_t weight_bytes;      /* weight bytes the launched kernels had to stream */
@@ -139,7 +139,12 @@ int ppd_reset(ppd_ctx *ctx);
 /* Feed a prompt (HOST int32 ids, n_prompt >= 1).  The algorithm starts from
  * one start token x_0; reading taken for prompts: positions 0..n_prompt-2 are
  * run through all d layers to fill the KV cache, the last prompt token
- * becomes x_0 with match = False.  Implies ppd_reset.  PPD_ECTX if
+ * becomes x_0 with match = False.  bf16 models: x_0 goes with them through
+ * all layers but the last where its row costs less there than in a pass of
+ * its own (prompts of one chunk or of the first kind below, unless it makes
+ * a further row of tiles; PPD_PREFILL_LAST=2 in the environment at
+ * ppd_create: never); the first step then takes it
+ * through the last layer only.  Implies ppd_reset.  PPD_ECTX if
  * n_prompt > max_ctx; PPD_EINVAL for ids outside [0, vocab).
  * bf16 models with prompts of more than 32 tokens: all prompt rows go through
  * a layer at once (tiled MFMA GEMMs on rows split into two bf16 terms,

@@ -55,6 +55,7 @@ struct ppd_ctx {
   // activation rows: max(1 + k, rows of a prompt chunk; in att and ffn those of the chunks that run_layer takes); row 0: main
   // token, rows 1..k: candidates
   float *h;              // [rows][d_model]
+  float *h_exit;         // [d_model] x_0 behind the exit layer, where the prompt pass has taken it through the layers (prompt_ran)
   float *qkv;            // [rows][3*d_model]
   float *att;            // [rows][d_model]
   float *ffn;            // [rows][d_ff]
@@ -70,6 +71,7 @@ struct ppd_ctx {
   int spec;
   int last_kind;         // kind of the last round (which buffer holds its early logits)
   int prefill_chunk;     // prompt positions per chunk
+  int prefill_last;      // x_0 goes through all layers but the last with the prompt's other rows
   int few_rows;          // chunks of up to so many rows of a bf16 model go through the decode step's launches
   // compute-bound prompt pass (bf16 models, prompts of at least PREFILL_TILED_MIN rows): all rows at once through
   // tiled MFMA GEMMs and causal attention over two-term operand blocks; its buffers are made at the first such prompt
@@ -97,10 +99,11 @@ struct ppd_ctx {
   int32_t rounds_seen;   // value of that counter after the last round the host waited for
   int32_t *host_result_dev; // the same memory as the GPU sees it
   // captured rounds, with one launch per step of a layer and with the one-launch chain: 0 ppd round from layer 1,
-  // 1 ppd round after a match, 2 plain step, 3 ppd round after a match whose candidates were predicted by the round before
+  // 1 ppd round after a match, 2 plain step, 3 ppd round after a match whose candidates were predicted by the round before,
+  // 4 and 5 ppd round and plain step on an x_0 that the prompt pass ran
   int use_graphs;
-  hipGraphExec_t graph[2][3][4];  // [chain][sequences of up to ATT_WHOLE, up to MG_MERGE, more chunks: other kernels][kind]
-  int graph_chunks[2][3][4];      // attention grid (64-position chunks) each graph was captured with
+  hipGraphExec_t graph[2][3][6];  // [chain][sequences of up to ATT_WHOLE, up to MG_MERGE, more chunks: other kernels][kind]
+  int graph_chunks[2][3][6];      // attention grid (64-position chunks) each graph was captured with
   int gmax1, gmax2;      // workgroup budget of an fp32 GEMM launch: one group / per group of a two-group launch
   int nchunk_max;
   // bf16 models: the main token's layers in one launch (ppd_fused.h); 0: one launch per step of a layer
@@ -115,6 +118,7 @@ struct ppd_ctx {
   // round state
   int n_ctx;      // absolute position of the pending token x_t (-1: no prefill yet)
   int matched;    // the pending token already went through layers 1..nb (its h is row 0)
+  int prompt_ran; // the pending token is x_0 and went through layers 1..d-1 with the prompt (its h is row 0, that of the exit layer h_exit)
   int finished;   // last token was EOS
   int have_early;
   ppd_stats st;
@@ -730,7 +734,8 @@ int set_state(ppd_ctx* c, int pos, int tok) {
 // kernel.  early: top-k -> candidates, which it also embeds as rows 1..k at the next position.
 // final: arg max, verification; with adopt, the matching candidate's row and KV tails are adopted.
 // With speculative early prediction the adopting head also runs on the candidate rows (see ppd_ctx::spec).
-int run_head(ppd_ctx* c, bool early, bool adopt) {
+// X: the rows, where they are not the activation rows.
+int run_head(ppd_ctx* c, bool early, bool adopt, const float* X = nullptr) {
   const ppd_model_dims& d = c->d;
   const bool spec = c->spec && adopt && !early;
   // top-k sampling with few kept tokens is drawn from the head's block lists inside the selection kernel;
@@ -742,7 +747,7 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
   {
     GemmArgs a; memset(&a, 0, sizeof a);
     GemmGroup& G = a.g[0];
-    G.X = c->h; G.Y = early ? c->early_logits : c->logits; G.Rsd = nullptr;
+    G.X = X ? X : c->h; G.Y = early ? c->early_logits : c->logits; G.Rsd = nullptr;
     G.W[0] = (early && c->early_head) ? c->early_head : c->lm_head;
     G.ng = c->lnf_g; G.nb = d.norm == 0 ? c->lnf_b : nullptr; G.M = spec ? 1 + c->k : 1;
     a.K = d.d_model; a.N[0] = d.vocab; a.ntot = d.vocab; a.ldx = d.d_model; a.ldy = d.vocab;
@@ -801,14 +806,17 @@ int run_head(ppd_ctx* c, bool early, bool adopt) {
 // floats of the chain's attention partials (rounded up to whole 16-byte pieces)
 size_t fl_part_floats(const ppd_ctx* c) { return ((size_t)c->d.n_heads * c->nchunk_max * (c->d.head_dim + 2) + 3) & ~(size_t)3; }
 
-// layers the main token goes through alone in a round, from the round's first one on
-int chain_from(const ppd_ctx* c, int kind) { return kind == 1 || kind == 3 ? c->nb : 0; }
-int chain_layers(const ppd_ctx* c, int kind) { return (kind == 2 ? c->d.n_layers : c->dbar) - chain_from(c, kind); }
+// Kinds of rounds.  0: PPD round from layer 1 (after a miss or a prefill);
+// 1: PPD round after a match (layers 1..d-dbar were run by the matching candidate row);
+// 2: plain greedy step; 3: PPD round after a match whose candidates the previous round's final head
+// already predicted and embedded (speculative early prediction): parallel phase and final head only;
+// 4, 5: PPD round and plain step on the x_0 that the prompt pass has taken through all layers but the last.
 
-// The launches of one round.  kind 0: PPD round from layer 1 (after a miss or a prefill);
-// kind 1: PPD round after a match (layers 1..d-dbar were run by the matching candidate row);
-// kind 2: plain greedy step; kind 3: PPD round after a match whose candidates the previous round's final head
-// already predicted and embedded (speculative early prediction): parallel phase and final head only.  pmax bounds the positions touched (attention grid size only).
+// layers the main token goes through alone in a round, from the round's first one on
+int chain_from(const ppd_ctx* c, int kind) { return kind >= 4 ? c->d.n_layers - 1 : (kind == 1 || kind == 3 ? c->nb : 0); }
+int chain_layers(const ppd_ctx* c, int kind) { return (kind == 2 || kind >= 4 ? c->d.n_layers : c->dbar) - chain_from(c, kind); }
+
+// The launches of one round.  pmax bounds the positions touched (attention grid size only).
 int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   const int d = c->d.n_layers, dbar = c->dbar, nb = c->nb, k = c->k;
   const int from = chain_from(c, kind);
@@ -836,6 +844,17 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
     if ((rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
     if ((rc = run_main_row(c, 0, d, pmax))) return rc;
     return run_head(c, false, false);
+  }
+  if (kind >= 4) {
+    // x_0: its last layer; then the early prediction from what the prompt pass kept, and the candidates by themselves
+    if ((rc = run_main_row(c, from, d, pmax))) return rc;
+    if (kind == 5) return run_head(c, false, false);
+    if ((rc = run_head(c, true, false, c->h_exit))) return rc;
+    for (int j = 0; j < nb; ++j) {
+      RowGroup g{j, k, 1, 1, true};
+      if ((rc = run_layer(c, 1, &g, pmax))) return rc;
+    }
+    return run_head(c, false, true);
   }
   // main token up to the exit layer
   if (kind == 0 && (rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
@@ -932,7 +951,7 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   // reads nothing else of the caller's)
   // the device already holds this position as pending when the previous call was a round at pos - 1
   if (c->dev_pos_pending != pos && (rc = set_state(c, pos, -1))) return rc;
-  const int pmax = pos + (kind == 2 ? 0 : 1);
+  const int pmax = pos + (kind == 2 || kind == 5 ? 0 : 1);
   hipGraphExec_t replay = nullptr;
   if (c->use_graphs && !c->prof && !again) {
     // Attention grid of the captured round: the chunks the round needs, rounded up to a power of two (at least ATT_WHOLE, at most the
@@ -1022,9 +1041,15 @@ void account_round(ppd_ctx* c, int kind, int pos) {
   const uint64_t wl = ((uint64_t)4 * d.d_model * d.d_model + (uint64_t)(d.act == 2 ? 3 : 2) * d.d_model * d.d_ff) * c->wbytes;
   const uint64_t wh = (uint64_t)d.vocab * d.d_model * c->wbytes;
   const uint64_t kvp = (uint64_t)2 * d.d_model * c->kvbytes;    // K and V of one position of one layer
-  if (kind == 2) {
-    c->st.weight_bytes += d.n_layers * wl + wh;
-    c->st.kv_bytes += (uint64_t)d.n_layers * pos * kvp;
+  if (kind == 2 || kind == 5) {
+    const int layers = kind == 2 ? d.n_layers : 1;
+    c->st.weight_bytes += layers * wl + wh;
+    c->st.kv_bytes += (uint64_t)layers * pos * kvp;
+    return;
+  }
+  if (kind == 4) {
+    c->st.weight_bytes += (uint64_t)(1 + c->nb) * wl + 2 * wh;
+    c->st.kv_bytes += (uint64_t)pos * kvp + (uint64_t)c->nb * (pos + 1) * kvp;
     return;
   }
   const int solo = c->dbar - (kind == 0 ? 0 : c->nb);
@@ -1034,7 +1059,7 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 
 void free_all(ppd_ctx* c) {
   (void)drop_graphs(c);
-  void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->qkv, c->att, c->ffn, c->part, c->logits,
+  void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->h_exit, c->qkv, c->att, c->ffn, c->part, c->logits,
                  c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
                  c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
   for (void* p : dev) (void)hipFree(p);
@@ -1047,8 +1072,15 @@ void free_all(ppd_ctx* c) {
 
 constexpr int PREFILL_TILED_MIN = 32;      // rows: prompts of at least 33 tokens
 
-// The whole prompt (rows 0 .. rows-1 at positions 0 .. rows-1) through all layers: fills the cache.
-int prefill_tiled(ppd_ctx* c, int rows) {
+// x_0's row of the prompt pass for the first round: behind the exit layer to h_exit (the early prediction's), at the end to row 0
+int keep_row(ppd_ctx* c, float* to, const float* row) {
+  hipLaunchKernelGGL(keep_row_kernel, dim3((c->d.d_model + 255) / 256), dim3(256), 0, c->cur, to, row, c->d.d_model);
+  HIPCHK(c, hipGetLastError());
+  return PPD_OK;
+}
+
+// The whole prompt (rows 0 .. rows-1 at positions 0 .. rows-1) through all layers: fills the cache.  last: the last row is x_0.
+int prefill_tiled(ppd_ctx* c, int rows, bool last) {
   const ppd_model_dims& d = c->d;
   const int dm = d.d_model, F = d.d_ff;
   const bool bias = d.has_bias != 0, swiglu = d.act == 2;
@@ -1145,6 +1177,7 @@ int prefill_tiled(ppd_ctx* c, int rows) {
       PAttnArgs pa; memset(&pa, 0, sizeof pa);
       pa.Qp = c->pf_qp; pa.Kp = c->pf_kp; pa.Vp = c->pf_vp; pa.outp = c->pf_xa;
       pa.M = rows; pa.H = d.n_heads; pa.d_model = dm; pa.JP = pk.JP;
+      pa.last = last; pa.max_ctx = d.max_ctx; pa.qkv = c->pf_qkv; pa.rope = pk.rope; pa.Kc = pk.Kc; pa.Vc = pk.Vc; pa.scale = pk.scale;
       HIPCHK(c, launch_pattn(c->cur, pa, d.head_dim));
     }
     HIPCHK(c, gemm(c->pf_xa, P.o, dm, dm, 0, 0, false, bias ? w.bo : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0, plan[1]));
@@ -1152,8 +1185,33 @@ int prefill_tiled(ppd_ctx* c, int rows) {
     if (swiglu) HIPCHK(c, gemm(c->pf_xp, P.fin, dm, F, F, 0, true, bias ? w.b_in : nullptr, nullptr, nullptr, nullptr, nullptr, F, 0, plan[2], c->pf_xf));
     else HIPCHK(c, gemm(c->pf_xp, P.fin, dm, F, 0, 0, false, bias ? w.b_in : nullptr, nullptr, nullptr, nullptr, nullptr, F, d.act == 0 ? 1 : 2, plan[2], c->pf_xf));
     HIPCHK(c, gemm(c->pf_xf, P.fout, F, dm, 0, 0, false, bias ? w.b_out : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0, plan[3]));
+    if (last && l + 1 == c->dbar && (rc = keep_row(c, c->h_exit, c->pf_h + (size_t)(rows - 1) * dm))) return rc;
   }
-  return PPD_OK;
+  return last ? keep_row(c, c->h, c->pf_h + (size_t)(rows - 1) * dm) : PPD_OK;
+}
+
+// Whether x_0, the prompt's last token, goes through the layers with the rows before it, all but the last layer, in which the first
+// round takes it on (from there on its row is alone, as in any round).  That saves the first round a pass over nearly all weights;
+// it is left out where the prompt is more than one chunk, or one more row costs the tiled products (by their account, times what they take
+// between a layer's other launches) more than the decode step does.  Measured (prompt and one plain token, us, x_0 by itself / with the
+// prompt): 7B shape, 8 layers, 2 rows 1372 / 915, 32 1707 / 1183, 65 1841 / 1567, 256 2778 / 2282, 512 3973 / 3525, 1024 6727 / 6275, but
+// 257 2776 / 2777 and 513 3964 / 3983 (by itself either way); 13B shape, 8 layers, 4096 rows 33.5 / 32.5 ms; OPT-125m shape, 9 rows
+// 796 / 641, 128 1043 / 784.  fp32 models, whose rounds are replayed launches of 2 - 4 us, gain nothing: 256 wide, 2 rows 212 / 235, 16
+// 370 / 369, a PPD round behind 16 401 / 431.
+bool takes_x0(const ppd_ctx* c, int n_prompt, bool tiled) {
+  if (!c->mfma || !c->prefill_last || n_prompt < 2) return false;
+  if (!tiled) return n_prompt <= c->prefill_chunk;
+  const ppd_model_dims& d = c->d;
+  const int dm = d.d_model, F = d.d_ff, rows = n_prompt - 1;
+  const int nk[4][2] = {{(3 * dm + 15) / 16, dm}, {(dm + 15) / 16, dm}, {d.act == 2 ? (F + 7) / 8 : (F + 15) / 16, dm}, {(dm + 15) / 16, F}};
+  float more = 0.f, bytes = 0.f;
+  for (const auto& p : nk) {
+    const int KT = (p[1] + 31) / 32;
+    more += plan_pgemm(rows + 1, KT, p[0], true).us - plan_pgemm(rows, KT, p[0], true).us;
+    bytes += (float)p[0] * (float)KT * 1024.f;
+  }
+  const float step = bytes / 5.2e6f;             // us, a layer of a plain token
+  return 1.25f * more < (step > 20.f ? step : 20.f);
 }
 
 // (on the context's stream: a copy on the null stream fails while another thread's context captures a round, and so does the capture.
@@ -1229,6 +1287,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     const int cap = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
     c->prefill_chunk = env_int("PPD_PREFILL_CHUNK", cap);
     if (c->prefill_chunk > cap) c->prefill_chunk = cap;
+    c->prefill_last = env_int("PPD_PREFILL_LAST", 1) != 2;
     c->few_rows = few_rows(d);
     // the compute-bound pass takes prompts of bf16 models unless the row-chunk path is asked for (PPD_PREFILL_CHUNK
     // set, or PPD_PREFILL_TILED=2)
@@ -1254,6 +1313,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   alloc((void**)&c->tailK, (size_t)c->nb * k * dm * c->kvbytes);
   alloc((void**)&c->tailV, (size_t)c->nb * k * dm * c->kvbytes);
   alloc((void**)&c->h, RB * dm * sizeof(float));
+  alloc((void**)&c->h_exit, dm * sizeof(float));
   alloc((void**)&c->qkv, RB * 3 * dm * sizeof(float));
   alloc((void**)&c->att, RS * dm * sizeof(float));
   if (d.wdtype == 1) {
@@ -1412,7 +1472,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
 int ppd_reset(ppd_ctx* c) {
   if (!c) return PPD_EINVAL;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->n_ctx = -1; c->matched = 0; c->finished = 0; c->have_early = 0; c->dev_pos_pending = -1;
+  c->n_ctx = -1; c->matched = 0; c->prompt_ran = 0; c->finished = 0; c->have_early = 0; c->dev_pos_pending = -1;
   memset(&c->st, 0, sizeof c->st);
   return PPD_OK;
 }
@@ -1435,9 +1495,11 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
   // token-by-token pass (PPD_PREFILL_CHUNK=1 runs exactly that), the weights are streamed once per chunk
   const int chunk = c->prefill_chunk;
   const bool tiled = c->prefill_tiled && n_prompt - 1 >= PREFILL_TILED_MIN;
-  if (tiled) rc = prefill_tiled(c, n_prompt - 1);
-  for (int i = 0; !tiled && i + 1 < n_prompt && !rc; i += chunk) {
-    const int m = n_prompt - 1 - i < chunk ? n_prompt - 1 - i : chunk;
+  const bool last = takes_x0(c, n_prompt, tiled);
+  const int rows = last ? n_prompt : n_prompt - 1;
+  if (tiled) rc = prefill_tiled(c, rows, last);
+  for (int i = 0; !tiled && i < rows && !rc; i += chunk) {
+    const int m = rows - i < chunk ? rows - i : chunk;
     rc = set_state(c, i, -1);
     if (!rc) {
       EmbedArgs ea = embed_args(c, c->prompt_dev + i, m, 0, 0);
@@ -1453,13 +1515,15 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
       // (the last layer's rows are read by no one: its keys and values are all that a prompt leaves there; run_layer's first
       // stage runs its attention, too, whose kernel writes them where there is one row)
       rc = c->mfma && m > c->few_rows ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
+      if (!rc && last && i + m == rows && l + 1 == c->dbar) rc = keep_row(c, c->h_exit, c->h + (size_t)(m - 1) * c->d.d_model);
     }
+    if (!rc && last && i + m == rows) rc = keep_row(c, c->h, c->h + (size_t)(m - 1) * c->d.d_model);
   }
   c->prof = prof;
   if (rc) return rc;
   if ((rc = set_state(c, n_prompt - 1, prompt[n_prompt - 1]))) return rc;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->n_ctx = n_prompt - 1; c->matched = 0; c->finished = 0;
+  c->n_ctx = n_prompt - 1; c->matched = 0; c->prompt_ran = last; c->finished = 0;
   return PPD_OK;
 }
 
@@ -1469,13 +1533,15 @@ int ppd_step(ppd_ctx* c, int32_t* out_tokens, int max_out, ppd_step_info* info) 
   if (c->finished) return 0;
   const int pos = c->n_ctx;
   if (pos + 1 >= c->d.max_ctx) return PPD_ECTX;   // the candidates sit at position pos+1
-  const int kind = c->matched ? (c->spec ? 3 : 1) : 0;
+  const int kind = c->prompt_ran ? 4 : (c->matched ? (c->spec ? 3 : 1) : 0);
+  c->prompt_ran = 0;                             // (a round that fails leaves x_0 to one that starts from its embedding)
   int rc = run_round(c, kind, pos);
   if (rc) return rc;
   account_round(c, kind, pos);
   const int tok = c->host_result[0], midx = c->host_result[1];
-  if (kind == 0) c->st.runs += 1;
-  c->st.main_layer_rows += (uint64_t)(c->dbar - (kind == 0 ? 0 : c->nb)) + c->nb;
+  const bool first = kind == 0 || kind == 4;     // (x_0's rows of the prompt pass are the round's)
+  if (first) c->st.runs += 1;
+  c->st.main_layer_rows += (uint64_t)(c->dbar - (first ? 0 : c->nb)) + c->nb;
   c->st.branch_layer_rows += (uint64_t)c->k * c->nb;
   c->n_ctx = pos + 1;
   c->matched = midx >= 0;
@@ -1498,9 +1564,11 @@ int plain_greedy_step(ppd_ctx* c, int32_t* out_token) {
   if (c->finished) return 0;
   const int pos = c->n_ctx;
   if (pos >= c->d.max_ctx) return PPD_ECTX;
-  int rc = run_round(c, 2, pos);
+  const int kind = c->prompt_ran ? 5 : 2;
+  c->prompt_ran = 0;
+  int rc = run_round(c, kind, pos);
   if (rc) return rc;
-  account_round(c, 2, pos);
+  account_round(c, kind, pos);
   c->n_ctx = pos + 1;
   c->matched = 0;
   c->last_kind = 2;

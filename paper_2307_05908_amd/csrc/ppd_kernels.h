@@ -151,6 +151,11 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* p, size_t
 __global__ void set_state_kernel(DevState* ds, int pos, int tok) {
   if (threadIdx.x == 0) { ds->pos = pos; ds->pos_pending = pos; if (tok >= 0) ds->next_tok = tok; }
 }
+// One row of activations to another place (x_0's, from the prompt pass to the first round)
+__global__ __launch_bounds__(256) void keep_row_kernel(float* to, const float* row, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) to[i] = row[i];
+}
 // First launch of every round: the position the previous round (or set_state_kernel) left pending becomes the
 // current one; take_next: the round uses the candidates the previous round predicted for it
 // (host_cand: the candidates' copy in pinned host memory, for the round's record).

@@ -121,7 +121,7 @@ __global__ __launch_bounds__(MG_THREADS) void pack_rows_kernel(PackArgs a) {
 
 // ---- tiled GEMM
 // How a product is cut: tile shape (index into pg_tiles) and number of parts of the reduction length
-struct PGemmPlan { int tile, S; };
+struct PGemmPlan { int tile, S; float us; };     // us: the time by plan_pgemm's account
 constexpr int PG_TILES = 7;
 struct PGemmArgs {
   const uint16_t* Xp;   // packed rows [2][MT][KT][64][8]
@@ -584,6 +584,11 @@ struct PAttnArgs {
   const uint16_t* Qp; const uint16_t* Kp; const uint16_t* Vp;
   uint16_t* outp;       // the outputs in packed two-term form [2][MT][d_model / 32][64][8] (rows of the output projection)
   int M, H, d_model, JP;
+  int gx;               // workgroups of a head (launch_pattn fills this)
+  // last: row M - 1 is the first round's and attends in fp32 to the cache, as it would in a round
+  int last, max_ctx;
+  const float* qkv; const float2* rope; const float* Kc; const float* Vc;
+  float scale;
 };
 // bytes of each of Qp, Kp, Vp
 inline size_t pattn_stage_bytes(int M, int H, int HD) { return (size_t)2 * H * ((M + 31) / 32) * (HD / 16) * 1024; }
@@ -662,6 +667,96 @@ __global__ __launch_bounds__(256) void pkv_pack_kernel(PKvPackArgs a) {
   }
 }
 
+// The last row of a prompt against the keys and values in the fp32 cache, one workgroup per head, beside those of pattn_kernel's
+// other rows (whose two-term operands made up a third of the error of a row's logits: 7B shape, 512 tokens, distance of the first
+// token's logits from 64 bits 7.0e-5 with the last row among them, 5.4e-5 with it by itself in a round).  What bounds it: a wave's
+// blocks of 16 positions one after the other, 16 KiB of keys and values each, the next one's requested a block ahead; it ends before the
+// others do.  A lane i + 16 c has four components of position i's key per 16 components, and of four positions' values component
+// 16 s + i (see k_index, v_index).
+template <int HD>
+__device__ __forceinline__ void pattn_last_row(const PAttnArgs& a, int h, float* lds) {
+  constexpr int CT = HD / 16, half = HD / 2, NW = 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, c = lane >> 4, m = a.M - 1;
+  float* const qs = lds;                                   // [HD], then the waves' outputs [NW][HD], maxima and sums [NW]
+  if (tid < HD) {
+    const float* r = a.qkv + (size_t)m * 3 * a.d_model + (size_t)h * HD;
+    float q = r[tid];
+    if (a.rope) {
+      const float2 w = a.rope[(size_t)m * half + (tid < half ? tid : tid - half)];
+      const float o = r[tid < half ? tid + half : tid - half];
+      q = tid < half ? fmaf(q, w.x, -(o * w.y)) : fmaf(q, w.x, o * w.y);
+    }
+    qs[tid] = q * a.scale;
+  }
+  __syncthreads();
+  float4 q[CT];
+#pragma unroll
+  for (int s = 0; s < CT; ++s) q[s] = *(const float4*)(qs + 16 * s + 4 * c);
+  const size_t base = (size_t)h * kv_blocks(a.max_ctx) * (KV_BLOCK * HD) + lane * 4;
+  const int nblk = m / KV_BLOCK + 1;
+  float4 kn[CT], vn[CT];
+  auto request = [&](int b) {                              // (past the last block: that one again, unused)
+    const size_t o = base + (size_t)(b < nblk ? b : nblk - 1) * (KV_BLOCK * HD);
+#pragma unroll
+    for (int s = 0; s < CT; ++s) { kn[s] = *(const float4*)(a.Kc + o + s * 256); vn[s] = *(const float4*)(a.Vc + o + s * 256); }
+  };
+  float mx = -INFINITY, l = 0.f, acc[CT];
+#pragma unroll
+  for (int s = 0; s < CT; ++s) acc[s] = 0.f;
+  request(wave);
+  for (int b = wave; b < nblk; b += NW) {
+    float4 k[CT], v[CT];
+#pragma unroll
+    for (int s = 0; s < CT; ++s) { k[s] = kn[s]; v[s] = vn[s]; }
+    request(b + NW);
+    float z = 0.f;
+#pragma unroll
+    for (int s = 0; s < CT; ++s) { z = fmaf(q[s].x, k[s].x, z); z = fmaf(q[s].y, k[s].y, z); z = fmaf(q[s].z, k[s].z, z); z = fmaf(q[s].w, k[s].w, z); }
+    z += __shfl_xor(z, 16, WAVE);
+    z += __shfl_xor(z, 32, WAVE);
+    if (b * KV_BLOCK + i > m) z = -INFINITY;
+    float bm = z;
+#pragma unroll
+    for (int o = 1; o < 16; o *= 2) bm = fmaxf(bm, __shfl_xor(bm, o, WAVE));
+    const float mnew = fmaxf(mx, bm), resc = __builtin_amdgcn_exp2f(mx - mnew);    // (finite: a block's first position is a row's)
+    mx = mnew;
+    const float p = __builtin_amdgcn_exp2f(z - mnew);
+    l = fmaf(l, resc, p);
+    const float p0 = __shfl(p, 4 * c, WAVE), p1 = __shfl(p, 4 * c + 1, WAVE), p2 = __shfl(p, 4 * c + 2, WAVE), p3 = __shfl(p, 4 * c + 3, WAVE);
+#pragma unroll
+    for (int s = 0; s < CT; ++s) {
+      float t = acc[s] * resc;
+      t = fmaf(p0, v[s].x, t); t = fmaf(p1, v[s].y, t); t = fmaf(p2, v[s].z, t); t = fmaf(p3, v[s].w, t);
+      acc[s] = t;
+    }
+  }
+#pragma unroll
+  for (int o = 1; o < 16; o *= 2) l += __shfl_xor(l, o, WAVE);
+  float* const wo = lds + HD;
+  float* const wm = wo + NW * HD;
+#pragma unroll
+  for (int s = 0; s < CT; ++s) {
+    acc[s] += __shfl_xor(acc[s], 16, WAVE);
+    acc[s] += __shfl_xor(acc[s], 32, WAVE);
+    if (c == 0) wo[wave * HD + 16 * s + i] = acc[s];
+  }
+  if (lane == 0) { wm[wave] = mx; wm[NW + wave] = l; }
+  __syncthreads();
+  if (tid >= HD) return;
+  float top = wm[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) top = fmaxf(top, wm[w]);
+  float num = 0.f, den = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {                           // (a wave without a block adds zeros)
+    const float f = __builtin_amdgcn_exp2f(wm[w] - top);
+    num = fmaf(f, wo[w * HD + tid], num);
+    den = fmaf(f, wm[NW + w], den);
+  }
+  const int MT = (a.M + 15) / 16, KT = a.d_model / 32;
+  put_packed1(a.outp, (size_t)MT * KT * 512, KT, m, h * HD + tid, num / den);
+}
+
 // A workgroup is 4 waves of one head; a wave owns QT consecutive 16-row query tiles (the columns of its MFMAs),
 // the workgroup 64 QT consecutive rows.  The workgroup walks the 32-row steps of keys and values up to its last
 // row: a step's blocks (keys hi, lo; values hi, lo: 4 HD / 16 KiB) come into LDS by direct loads, a step ahead of
@@ -679,10 +774,16 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
   // workgroups of a head walk the same steps and find them in its L2.  With a head's rows spread over all XCDs the steps came from
   // memory eight times, 3 TB/s of them: 13B shape, 4095 rows, 892 -> 526 us.  (Other numbers of heads, 12, 20 or 36, keep
   // that order.)
-  int h = blockIdx.y, wg = (int)gridDim.x - 1 - (int)blockIdx.x;
+  // (The workgroups of the last row, where there are any, are the first H.)
+  int b = blockIdx.x;
+  if (a.last) {
+    if (b < a.H) { pattn_last_row<HD>(a, b, (float*)lds); return; }
+    b -= a.H;
+  }
+  int h = b / a.gx, wg = a.gx - 1 - (b - h * a.gx);
   if ((a.H & 7) == 0) {
-    const int b = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x, r = b >> 3, per = a.H >> 3;
-    h = (b & 7) + 8 * (r % per); wg = (int)gridDim.x - 1 - r / per;
+    const int r = b >> 3, per = a.H >> 3;
+    h = (b & 7) + 8 * (r % per); wg = a.gx - 1 - r / per;
   }
   const int MT2 = 2 * a.JP;
   const int qt0 = (wg * 4 + wave) * QT;                    // this wave's first tile (may lie past the prompt: then it only helps to load)
@@ -836,7 +937,7 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
       const float l1 = __shfl(lt, bn + 16, WAVE), l2 = __shfl(lt, bn + 32, WAVE), l3 = __shfl(lt, bn + 48, WAVE);
       lt = ((__shfl(lt, bn, WAVE) + l1) + l2) + l3;
     }
-    if (mrow >= a.M) continue;
+    if (mrow >= a.M - (a.last ? 1 : 0)) continue;
     const float inv = 1.0f / lt;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {

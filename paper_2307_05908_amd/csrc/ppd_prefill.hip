@@ -37,7 +37,7 @@ constexpr PGemmTile pg_tiles[PG_TILES] = {
 // (cut: whether the reduction length may be cut)
 PGemmPlan plan_pgemm(int M, int KT, int NT, bool cut) {
   const int MT = (M + 15) / 16;
-  PGemmPlan best = {0, 1};
+  PGemmPlan best = {0, 1, 0.f};
   float tbest = 0.f;
   for (int c = 0; c < PG_TILES; ++c) {
     const PGemmTile& p = pg_tiles[c];
@@ -50,7 +50,7 @@ PGemmPlan plan_pgemm(int M, int KT, int NT, bool cut) {
       const float mem = (float)NT * (float)KT * (1024.f / 4.05e6f);
       float t = sqrtf(sqrtf(comp * comp * comp * comp + mem * mem * mem * mem));
       if (S > 1) t += 1.95f + 0.305e-6f * (float)bytes * (float)(T * S) + 1.455e-5f * (float)bytes * (float)S;
-      if ((c == 0 && S == 1) || t < tbest) { tbest = t; best = {c, S}; }
+      if ((c == 0 && S == 1) || t < tbest) { tbest = t; best = {c, S, t}; }
     }
   }
   return best;
@@ -144,9 +144,10 @@ hipError_t launch_pkv_pack(hipStream_t stream, const PKvPackArgs& a, int head_di
 }
 
 template <int HD, int QT>
-static hipError_t launch_pattn_t(hipStream_t stream, const PAttnArgs& a) {
+static hipError_t launch_pattn_t(hipStream_t stream, PAttnArgs a) {
   const int MT = (a.M + 15) / 16;
-  const dim3 grid((MT + 4 * QT - 1) / (4 * QT), a.H);
+  a.gx = (MT + 4 * QT - 1) / (4 * QT);
+  const dim3 grid((a.gx + (a.last ? 1 : 0)) * a.H);
   const size_t lds = (size_t)2 * (4 * (HD / 32) + 2 * (HD / 16)) * 1024;
   hipLaunchKernelGGL((pattn_kernel<HD, QT>), grid, dim3(256), lds, stream, a);
   return hipGetLastError();
@@ -154,6 +155,7 @@ static hipError_t launch_pattn_t(hipStream_t stream, const PAttnArgs& a) {
 
 hipError_t launch_pattn(hipStream_t stream, const PAttnArgs& a, int head_dim) {
   if (a.M < 1 || a.JP != (a.M + 31) / 32 || (head_dim != 64 && head_dim != 128) || a.d_model % 32) return hipErrorInvalidValue;
+  if (a.last && (!a.qkv || !a.Kc || !a.Vc || a.M > a.max_ctx)) return hipErrorInvalidValue;
   // rows per workgroup (64 QT): two query tiles per wave once the prompt gives enough workgroups (four would leave
   // one wave per SIMD: measured slower)
   const bool two = a.M >= 1024;
