@@ -27,7 +27,7 @@ hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups,
   return launch_gemm_small_t<4>(stream, a, mmax, paired, grid);
 }
 #elif PPD_INST < 4 || PPD_INST == 6
-// Whether one row's gains are requested with the row.  It puts the weights off, which pays where a wave streams several sets of
+// Whether one row's gains are requested with the row.  (bf16 rows of up to 5120 elements are early_kernel's by now.)  It puts the weights off, which pays where a wave streams several sets of
 // rows of some length.  Measured (early prediction over bf16 weights, last / first, us): 2752 elements 32000 logits 47.5 / 46.2,
 // 12000 29.4 / 29.4, 5065 20.8 / 21.7, 1000 16.0 / 16.9; 4096 elements 59.5 / 58.9, 34.1 / 36.3, 25.2 / 26.6, 18.4 / 19.2; 1032
 // elements 34.7 / 34.7, 24.3 / 25.1, 18.3 / 18.9, 14.6 / 15.1.  fp32 weights: first everywhere (a plain token of a 3072-wide
