@@ -87,6 +87,7 @@ struct ppd_ctx {
   int pg_tile, pg_parts;             // >= 0, > 0: the tile and the cut of every product of the pass (tests)
   size_t pg_ws_bytes;                // what pf_ws and pf_cnt take
   int dev_pos_pending;   // host mirror of the device state's pending position (-1: unknown)
+  float *rp_s;           // partial sums of a prompt chunk's narrow products (sgemm_kernel)
   uint16_t *rp_x, *rp_a, *rp_f;      // packed two-term rows of a prompt chunk: normalised rows, attention outputs, feed-forward activations (zero beyond d_ff)
   // sampling-based final prediction (Appendix B): 0 arg max, 1 top-k sampling, 2 top-p sampling
   int samp_mode, samp_k; double samp_p; uint64_t samp_seed;
@@ -580,32 +581,48 @@ int few_rows(const ppd_model_dims& d) {
   return m;
 }
 
+// x_0's row of the prompt pass for the first round: behind the exit layer to h_exit (the early prediction's), at the end to row 0
+int keep_row(ppd_ctx* c, float* to, const float* row) {
+  hipLaunchKernelGGL(keep_row_kernel, dim3((c->d.d_model + 255) / 256), dim3(256), 0, c->cur, to, row, c->d.d_model);
+  HIPCHK(c, hipGetLastError());
+  return PPD_OK;
+}
+
 // One transformer layer for the M <= PREFILL_CHUNK rows of a prompt chunk of a bf16 model (M > few_rows), the first of them at the
 // device state's position.  Row for row the arithmetic of run_layer.
-int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
+// keep: x_0's row, as it comes into this layer, goes to h_exit.
+int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax, bool keep) {
   const ppd_model_dims& d = c->d;
   const int dm = d.d_model, F = d.d_ff;
   const bool bias = d.has_bias != 0, swiglu = d.act == 2;
   const LayerW& w = c->L[l];
   const ppd_ctx::LayerP& P = c->LP[l];
-  auto pack = [&](const void* g, const void* b) -> hipError_t {
+  // sum_bias: of the product whose partial sums are in rp_s
+  auto pack = [&](const void* g, const void* b, bool sum, const void* sum_bias) -> hipError_t {
     PackArgs p; memset(&p, 0, sizeof p);
     p.X = c->h; p.ld = dm; p.M = M; p.K = dm; p.KT = (dm + 31) / 32; p.MT = 2; p.g = g; p.b = d.norm == 0 ? b : nullptr;
     p.norm = d.norm; p.eps = d.norm_eps; p.out = c->rp_x;
+    if (sum) { p.S = c->rp_s; p.bias = bias ? sum_bias : nullptr; }
     return launch_pack_rows(c->cur, p);
   };
+  auto narrow = [&](const uint16_t* Xp, const void* W, int K) -> hipError_t {
+    SGemmArgs g; memset(&g, 0, sizeof g);
+    g.Xp = Xp; g.P = W; g.S = c->rp_s; g.M = M; g.KT = (K + 31) / 32; g.NT = (dm + 15) / 16; g.ntot = dm;
+    return launch_sgemm(c->cur, g);
+  };
   auto gemm = [&](const uint16_t* Xp, const void* W, int K, int n0, int n12, bool paired, const void* b0, const void* b1, const void* b2,
-                  const float* rsd, float* Y, int ldy, int act, uint16_t* Yp = nullptr) -> hipError_t {
+                  float* Y, int ldy, int act, uint16_t* Yp = nullptr) -> hipError_t {
     RGemmArgs g; memset(&g, 0, sizeof g);
     g.Xp = Xp; g.P = W; g.B[0] = bias ? b0 : nullptr; g.B[1] = bias ? b1 : nullptr; g.B[2] = bias ? b2 : nullptr;
-    g.Rsd = rsd; g.Y = Y; g.Yp = Yp; g.KTp = (n0 + 31) / 32; g.M = M; g.KT = (K + 31) / 32;
+    g.Y = Y; g.Yp = Yp; g.KTp = (n0 + 31) / 32; g.M = M; g.KT = (K + 31) / 32;
     g.N[0] = n0; g.N[1] = g.N[2] = n12; g.ntot = n0 + 2 * n12;
     g.NT = paired ? (n0 + 7) / 8 : (g.ntot + 15) / 16;
     g.ldy = ldy; g.act = act;
     return launch_rgemm(c->cur, g, paired);
   };
-  HIPCHK(c, pack(w.ln1_g, w.ln1_b));
-  HIPCHK(c, gemm(c->rp_x, P.qkv, dm, dm, dm, false, w.bq, w.bk, w.bv, nullptr, c->qkv, 3 * dm, 0));
+  HIPCHK(c, pack(w.ln1_g, w.ln1_b, l > 0, l > 0 ? c->L[l - 1].b_out : nullptr));
+  if (keep) { const int rc = keep_row(c, c->h_exit, c->h + (size_t)(M - 1) * dm); if (rc) return rc; }
+  HIPCHK(c, gemm(c->rp_x, P.qkv, dm, dm, dm, false, w.bq, w.bk, w.bv, c->qkv, 3 * dm, 0));
   // keys and values of all rows of the chunk go into the cache first; then the rows attend, each to the rows before it
   float* const Kc = (float*)(c->Kc + (size_t)l * cache_layer_bytes(c));
   float* const Vc = (float*)(c->Vc + (size_t)l * cache_layer_bytes(c));
@@ -629,10 +646,10 @@ int run_chunk_layer(ppd_ctx* c, int l, int M, int pmax) {
     hipLaunchKernelGGL(attn_merge_kernel, dim3(M, d.n_heads, 1), dim3(MERGE_THREADS), 0, c->cur, mg);
     HIPCHK(c, hipGetLastError());
   }
-  HIPCHK(c, gemm(c->rp_a, P.o, dm, dm, 0, false, w.bo, nullptr, nullptr, c->h, c->h, dm, 0));
-  HIPCHK(c, pack(w.ln2_g, w.ln2_b));
-  HIPCHK(c, gemm(c->rp_x, P.fin, dm, F, 0, swiglu, w.b_in, nullptr, nullptr, nullptr, nullptr, F, swiglu ? 0 : (d.act == 0 ? 1 : 2), c->rp_f));
-  HIPCHK(c, gemm(c->rp_f, P.fout, F, dm, 0, false, w.b_out, nullptr, nullptr, c->h, c->h, dm, 0));
+  HIPCHK(c, narrow(c->rp_a, P.o, dm));
+  HIPCHK(c, pack(w.ln2_g, w.ln2_b, true, w.bo));
+  HIPCHK(c, gemm(c->rp_x, P.fin, dm, F, 0, swiglu, w.b_in, nullptr, nullptr, nullptr, F, swiglu ? 0 : (d.act == 0 ? 1 : 2), c->rp_f));
+  HIPCHK(c, narrow(c->rp_f, P.fout, F));       // (the next layer's packing adds them up; the last layer ends above)
   return PPD_OK;
 }
 
@@ -1060,7 +1077,7 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 void free_all(ppd_ctx* c) {
   (void)drop_graphs(c);
   void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->h_exit, c->qkv, c->att, c->ffn, c->part, c->logits,
-                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
+                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_s, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
                  c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
   for (void* p : dev) (void)hipFree(p);
   for (void* p : c->owned) (void)hipFree(p);
@@ -1071,13 +1088,6 @@ void free_all(ppd_ctx* c) {
 }
 
 constexpr int PREFILL_TILED_MIN = 32;      // rows: prompts of at least 33 tokens
-
-// x_0's row of the prompt pass for the first round: behind the exit layer to h_exit (the early prediction's), at the end to row 0
-int keep_row(ppd_ctx* c, float* to, const float* row) {
-  hipLaunchKernelGGL(keep_row_kernel, dim3((c->d.d_model + 255) / 256), dim3(256), 0, c->cur, to, row, c->d.d_model);
-  HIPCHK(c, hipGetLastError());
-  return PPD_OK;
-}
 
 // The whole prompt (rows 0 .. rows-1 at positions 0 .. rows-1) through all layers: fills the cache.  last: the last row is x_0.
 int prefill_tiled(ppd_ctx* c, int rows, bool last) {
@@ -1319,6 +1329,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   if (d.wdtype == 1) {
     alloc((void**)&c->rp_x, packed_bytes(PREFILL_CHUNK, (int)dm));
     alloc((void**)&c->rp_a, packed_bytes(PREFILL_CHUNK, (int)dm));
+    alloc((void**)&c->rp_s, (size_t)MG_WAVES * PREFILL_CHUNK * dm * sizeof(float));
     alloc((void**)&c->rp_f, packed_bytes(PREFILL_CHUNK, d.d_ff));
     if (e == hipSuccess) e = hipMemsetAsync(c->rp_f, 0, packed_bytes(PREFILL_CHUNK, d.d_ff), c->stream);
   }
@@ -1397,6 +1408,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MG_LDS_MAX);
     if (e == hipSuccess) e = rgemm_setup();
+    if (e == hipSuccess) e = sgemm_setup();
     if (e == hipSuccess) e = narrow_setup(d);
     // the prompt pass's products with one tile shape (1 ..) and one cut of the reduction length (tests)
     c->pg_tile = env_int("PPD_PG_TILE", 0) - 1;
@@ -1514,8 +1526,12 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
       g.chunk = m > 1;
       // (the last layer's rows are read by no one: its keys and values are all that a prompt leaves there; run_layer's first
       // stage runs its attention, too, whose kernel writes them where there is one row)
-      rc = c->mfma && m > c->few_rows ? run_chunk_layer(c, l, m, i + m - 1) : run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
-      if (!rc && last && i + m == rows && l + 1 == c->dbar) rc = keep_row(c, c->h_exit, c->h + (size_t)(m - 1) * c->d.d_model);
+      const bool exit_row = last && i + m == rows;
+      if (c->mfma && m > c->few_rows) rc = run_chunk_layer(c, l, m, i + m - 1, exit_row && l == c->dbar);
+      else {
+        rc = run_layer(c, 1, &g, i + m - 1, l == c->d.n_layers - 1 ? 1 : 15);
+        if (!rc && exit_row && l + 1 == c->dbar) rc = keep_row(c, c->h_exit, c->h + (size_t)(m - 1) * c->d.d_model);
+      }
     }
     if (!rc && last && i + m == rows) rc = keep_row(c, c->h, c->h + (size_t)(m - 1) * c->d.d_model);
   }

@@ -10,7 +10,7 @@
 //                       contiguous kilobyte); products exact in fp32 as in decoding
 //   pkv_pack_kernel     queries, keys, values of the prompt rows -> two-term operand blocks, and keys and values into
 //                       the fp32 cache in the decode path's layout
-//   rgemm_kernel        the GEMMs of a prompt chunk of up to 32 rows, in the decode path's summation order
+//   rgemm_kernel, sgemm_kernel   the GEMMs of a prompt chunk of up to 32 rows, in the decode path's summation order
 //   pattn_kernel        causal attention of all prompt rows on the same MFMA (three products per pair of two-term
 //                       operands), key/value steps staged through LDS for the four waves of a workgroup, running softmax
 //
@@ -35,6 +35,8 @@ struct PackArgs {
   int norm;                      // -1 none, 0 LayerNorm, 1 RMSNorm
   float eps;
   uint16_t* out;                 // [2][MT][KT][64][8]
+  // S != null: the rows are still to be added up: X (which takes them) + bias + the eight partial sums that sgemm_kernel left
+  const float* S; const void* bias;   // [8][M][K]; bias or null
 };
 
 __device__ __forceinline__ void split2(const float (&xv)[8], uint4& hi, uint4& lo) {
@@ -63,6 +65,30 @@ __global__ __launch_bounds__(MG_THREADS) void pack_rows_kernel(PackArgs a) {
   const size_t plane = (size_t)a.MT * a.KT * 512;        // bf16 elements per plane
   const float* x = a.X + (size_t)m * a.ld;
   const bool live = m < a.M;
+  if (a.S && live) {
+    // (a thread finds what it writes here: its own pieces)
+    float* const xw = (float*)x;
+    const size_t share = (size_t)a.M * K;
+    for (int c = tid; c * 8 < K; c += MG_THREADS) {
+      float4 v[MG_WAVES][2], r[2];
+      const float* s = a.S + (size_t)m * K + c * 8;
+#pragma unroll
+      for (int w = 0; w < MG_WAVES; ++w) { v[w][0] = *(const float4*)(s + w * share); v[w][1] = *(const float4*)(s + w * share + 4); }
+      r[0] = ((const float4*)(xw + c * 8))[0]; r[1] = ((const float4*)(xw + c * 8))[1];
+      u32x4 bq = {0u, 0u, 0u, 0u};
+      if (a.bias) bq = *(const u32x4*)((const char*)a.bias + (size_t)c * 16);
+      float bf[8]; WTr<bf16_t>::unpack(bq, bf);
+      // the order of the decode step's epilogue: the shares in turn, the bias, the residual
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float4 y = v[0][h];
+#pragma unroll
+        for (int w = 1; w < MG_WAVES; ++w) { y.x += v[w][h].x; y.y += v[w][h].y; y.z += v[w][h].z; y.w += v[w][h].w; }
+        y.x = (y.x + bf[4 * h]) + r[h].x; y.y = (y.y + bf[4 * h + 1]) + r[h].y; y.z = (y.z + bf[4 * h + 2]) + r[h].z; y.w = (y.w + bf[4 * h + 3]) + r[h].w;
+        ((float4*)(xw + c * 8))[h] = y;
+      }
+    }
+  }
   auto combine8 = [&](const float* r) { return ((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]; };
   float mu = 0.f, rs = 1.f;
   if (a.norm >= 0 && live) {
@@ -427,14 +453,13 @@ __global__ __launch_bounds__(WW * WX * WAVE, WW * WX <= 4 ? 1 : 2) void pgemm_ke
 // of fp32 do not fit LDS whole, and the staging passes took most of the time (7B shape, 16 rows: 30 us of staging in a
 // 45 us FFN-in launch).  Every block of rows feeds TT weight tiles, so that L2 hands out (1 + 2 MT / TT) kilobytes per
 // kilobyte of weights.  Measured (7B shape, 26 rows, all layers): two 16-row chunks through gemm_mfma_kernel 9.0 ms,
-// one chunk through this kernel 4.3 ms (attention and its row split included); per layer QKV 24 us, O 15, FFN-in 37,
-// FFN-out 35.  What is left over the weights' stream is the L2 traffic: with one tile per workgroup (O, FFN-out) the rows are
-// four times the weights; six tiles at once instead of twice three took FFN-in from 42 to 37 us.
+// one chunk through this kernel 4.3 ms (attention and its row split included); per layer QKV 24 us, FFN-in 37.  What is left
+// over the weights' stream is the L2 traffic: six tiles at once instead of twice three took FFN-in from 42 to 37 us.
+// (O and FFN-out are sgemm_kernel's.)
 struct RGemmArgs {
   const uint16_t* Xp;   // packed rows [2 planes][2][KT][64][8] (always two 16-row tiles; see PackArgs)
   const void* P;        // repacked weights [NT][KT][64][8]
   const void* B[3];     // biases per row segment or null (paired: B[0] gate, B[1] up)
-  const float* Rsd;     // residual rows [M][ldy] or null
   float* Y;             // [M][ldy], or
   uint16_t* Yp; int KTp;   // the outputs as packed rows [2][2][KTp][64][8]
   int M, KT, NT, N[3], ntot, ldy;
@@ -523,7 +548,7 @@ __global__ __launch_bounds__(MG_THREADS) void rgemm_kernel(RGemmArgs a) {
     for (; c_g < ngrp; ++c_g) put();                       // a wave without a share adds zeros
   }
   __syncthreads();
-  // the eight partials of an output in wave order, bias, activation, residual
+  // the eight partials of an output in wave order, bias, activation
   constexpr int R = PAIRED ? 8 : 16;
   const uint16_t* const B0 = (const uint16_t*)a.B[0];
   const uint16_t* const B1 = (const uint16_t*)a.B[1];
@@ -553,9 +578,100 @@ __global__ __launch_bounds__(MG_THREADS) void rgemm_kernel(RGemmArgs a) {
       if (a.act == 1) y = gelu_erf(y);
       else if (a.act == 2) y = fmaxf(y, 0.f);
     }
-    y += a.Rsd ? a.Rsd[(size_t)m * a.ldy + n] : 0.f;
+    y += 0.f;      // (where the decode step adds the residual: -0 becomes 0)
     if (a.Yp) put_packed1(a.Yp, (size_t)2 * a.KTp * 512, a.KTp, m, n, y);
     else a.Y[(size_t)m * a.ldy + n] = y;
+  }
+}
+#endif
+
+// ---- the products of such a chunk whose outputs are few: one share of the reduction length per workgroup
+// Workgroup (share, group): its waves take a 16-row weight tile each of the group, over the share of the reduction length that a wave
+// of rgemm_kernel has, so that the rows' blocks of the share come into LDS once for all of them; the eight shares' sums go to memory and
+// pack_rows_kernel, which reads the rows next, adds them in their order.  Block b of a launch is share b % 8: an XCD's workgroups read the same rows.
+// The rows come in phases of SG_PB blocks, two buffers.
+// What bounds it: what a compute unit can request at a time; the rows of 32 are still a third of its bytes (rgemm_kernel, with one tile to
+// a workgroup, read four bytes of rows for one of weights).  7B shape, 27 rows: O 15.5 -> 9.7 us, FFN-out 33.7 -> 27, the sums in pack_rows_kernel
+// 5.0 -> 6.2 (two of them).  A prompt of 27 tokens and its first token, 8 layers, rgemm_kernel / this, us: 7B shape 1179 / 1073 (9 tokens 1003 / 972), 13B 1656 /
+// 1497 (1410 / 1347), 8192 wide, 2 layers, 874 / 840, 3072 wide 878 / 796, 2048 689 / 610, 1024 495 / 438, OPT-125m shape (12 layers) 675 / 570.  Eight blocks ahead and phases
+// of 16 the same within 1 % but for the 13B shape, 1542: its 320 workgroups fit two to a compute unit with the smaller phases.
+struct SGemmArgs {
+  const uint16_t* Xp;   // packed rows [2 planes][2][KT][64][8]
+  const void* P;        // repacked weights [NT][KT][64][8]
+  float* S;             // [8][M][ntot]
+  int M, KT, NT, ntot;
+};
+constexpr int SG_RING = 4;           // weight blocks in flight per wave
+constexpr int SG_PB = 8;             // blocks of a phase: 32 KiB for 32 rows
+static_assert(SG_PB >= SG_RING, "a phase's requests are done when the ring behind them has come round");
+
+#ifdef PPD_PREFILL_TU
+template <int MT>
+__global__ __launch_bounds__(MG_THREADS) void sgemm_kernel(SGemmArgs a) {
+  extern __shared__ float4 sg_lds4[];
+  char* const lds = (char*)sg_lds4;                        // [2][SG_PB][2 planes][MT] KiB
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), W = (int)blockDim.x >> 6;
+  const int share = blockIdx.x & 7, nt = ((int)blockIdx.x >> 3) * W + wave, KT = a.KT;
+  const int nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
+  const int kb0 = share * nb8 < KT ? share * nb8 : KT;
+  const int nblk = (kb0 + nb8 < KT ? kb0 + nb8 : KT) - kb0;
+  const int np = (nblk + SG_PB - 1) / SG_PB;
+  auto stage = [&](int p) {
+    const int s0 = p * SG_PB, n = (nblk - s0 < SG_PB ? nblk - s0 : SG_PB) * 2 * MT;
+    char* const to = lds + (size_t)(p & 1) * SG_PB * 2 * MT * 1024;
+    for (int u = wave; u < n; u += W) {
+      const int s = u / (2 * MT), v = u - s * 2 * MT, pl = v / MT, m = v - pl * MT;
+      dma16((const char*)a.Xp + ((size_t)(pl * 2 + m) * KT + kb0 + s0 + s) * 1024 + lane * 16, to + u * 1024);
+    }
+  };
+  if (np > 0) stage(0);
+  // the wave's run of the tile as a buffer of its own: what is asked for past its end is not read (and neither is a tile past the last)
+  const __amdgpu_buffer_rsrc_t run = __builtin_amdgcn_make_buffer_rsrc((char*)a.P + ((size_t)(nt < a.NT ? nt : 0) * KT + (nblk ? kb0 : 0)) * 1024, 0,
+                                                                        nt < a.NT ? nblk * 1024 : 0, 0x00020000);
+  u32x4 ring[SG_RING];
+  unsigned o = lane * 16;
+  auto request = [&](int i) { ring[i] = __builtin_amdgcn_raw_buffer_load_b128(run, o, 0, 2); o += 1024; };      // 2: non-temporal
+#pragma unroll
+  for (int i = 0; i < SG_RING; ++i) request(i);
+  f32x4 acc[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) acc[m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int p = 0; p < np; ++p) {
+    // this phase's rows have arrived: they were requested before the newest SG_RING weight blocks; everybody is done with the other buffer
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(SG_RING) : "memory");
+    if (p + 1 < np) stage(p + 1);
+    const int n = nblk - p * SG_PB < SG_PB ? nblk - p * SG_PB : SG_PB;
+    const char* const x = lds + (size_t)(p & 1) * SG_PB * 2 * MT * 1024 + lane * 16;
+    auto block = [&](int s, int i) {
+      const bf16x8 w = __builtin_bit_cast(bf16x8, ring[i]);
+      u32x4 xh[MT], xl[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        xh[m] = *(const u32x4*)(x + (s * 2 * MT + m) * 1024);
+        xl[m] = *(const u32x4*)(x + (s * 2 * MT + MT + m) * 1024);
+      }
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, __builtin_bit_cast(bf16x8, xh[m]), acc[m], 0, 0, 0);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, __builtin_bit_cast(bf16x8, xl[m]), acc[m], 0, 0, 0);
+      request(i);
+    };
+    int s = 0;
+    for (; s + SG_RING <= n; s += SG_RING) {
+#pragma unroll
+      for (int i = 0; i < SG_RING; ++i) block(s + i, i);
+    }
+#pragma unroll
+    for (int i = 0; i < SG_RING; ++i) if (s + i < n) block(s + i, i);     // (in the last phase only)
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (no request outlives the workgroup)
+  const int n0 = nt * 16 + 4 * (lane >> 4);
+  if (nt >= a.NT || n0 >= a.ntot) return;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int row = 16 * m + (lane & 15);
+    if (row < a.M) *(float4*)(a.S + ((size_t)share * a.M + row) * a.ntot + n0) = make_float4(acc[m][0], acc[m][1], acc[m][2], acc[m][3]);
   }
 }
 #endif
@@ -955,6 +1071,8 @@ hipError_t launch_pgemm(hipStream_t stream, PGemmArgs a, bool paired, PGemmPlan 
 hipError_t pgemm_setup(PGemmPlan plan, bool paired);
 hipError_t launch_rgemm(hipStream_t stream, RGemmArgs a, bool paired);
 hipError_t rgemm_setup();
+hipError_t launch_sgemm(hipStream_t stream, const SGemmArgs& a);
+hipError_t sgemm_setup();
 hipError_t launch_pkv_pack(hipStream_t stream, const PKvPackArgs& a, int head_dim);
 hipError_t launch_pattn(hipStream_t stream, const PAttnArgs& a, int head_dim);
 // bytes of the packed form of M rows of K columns

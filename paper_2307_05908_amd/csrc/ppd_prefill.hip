@@ -10,6 +10,7 @@ namespace ppd {
 
 hipError_t launch_pack_rows(hipStream_t stream, const PackArgs& a) {
   if (a.M < 1 || a.K < 8 || (a.K & 7) || (a.ld & 3) || a.MT < (a.M + 15) / 16 || a.KT != (a.K + 31) / 32) return hipErrorInvalidValue;
+  if (a.S && ((a.K & 7) || a.ld != a.K)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(pack_rows_kernel, dim3((a.MT + 7) / 8 * 128), dim3(MG_THREADS), 0, stream, a);
   return hipGetLastError();
 }
@@ -132,6 +133,24 @@ hipError_t rgemm_setup() {
   hipError_t e = hipSuccess;
   for (auto f : {rgemm_setup_t<true, 4>, rgemm_setup_t<true, 6>, rgemm_setup_t<false, 4>, rgemm_setup_t<false, 6>})
     if (e == hipSuccess) e = f();
+  return e;
+}
+
+hipError_t launch_sgemm(hipStream_t stream, const SGemmArgs& a) {
+  if (a.M < 1 || a.M > 32 || a.KT < 1 || a.NT < 1 || a.ntot > a.NT * 16 || (a.ntot & 3)) return hipErrorInvalidValue;
+  // a wave per tile, and so many waves to a workgroup that there are some 256 workgroups
+  const int W = a.NT >= 192 ? 8 : (a.NT >= 96 ? 4 : 2);
+  const int grid = (a.NT + W - 1) / W * 8;
+  const int nb8 = (a.KT + MG_WAVES - 1) / MG_WAVES, MT = a.M > 16 ? 2 : 1;
+  const size_t lds = (size_t)(nb8 > SG_PB ? 2 * SG_PB : nb8) * 2 * MT * 1024;
+  if (MT == 2) hipLaunchKernelGGL(sgemm_kernel<2>, dim3(grid), dim3(W * WAVE), lds, stream, a);
+  else hipLaunchKernelGGL(sgemm_kernel<1>, dim3(grid), dim3(W * WAVE), lds, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t sgemm_setup() {
+  hipError_t e = hipFuncSetAttribute((const void*)sgemm_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * SG_PB * 2 * 1024);
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)sgemm_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * SG_PB * 4 * 1024);
   return e;
 }
 
