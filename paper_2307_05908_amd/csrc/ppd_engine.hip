@@ -86,7 +86,8 @@ struct ppd_ctx {
   unsigned pg_ready;                 // bit 2 t + paired: that kernel's LDS is set up
   int pg_tile, pg_parts;             // >= 0, > 0: the tile and the cut of every product of the pass (tests)
   size_t pg_ws_bytes;                // what pf_ws and pf_cnt take
-  int dev_pos_pending;   // host mirror of the device state's pending position (-1: unknown)
+  int dev_pos;           // host mirror of the device state's position (-1: unknown)
+  int row0;              // row 0 holds the pending token's embedding, or the row that stands for it (matched, prompt_ran)
   float *rp_s;           // partial sums of a prompt chunk's narrow products (sgemm_kernel)
   uint16_t *rp_x, *rp_a, *rp_f;      // packed two-term rows of a prompt chunk: normalised rows, attention outputs, feed-forward activations (zero beyond d_ff)
   // sampling-based final prediction (Appendix B): 0 arg max, 1 top-k sampling, 2 top-p sampling
@@ -743,7 +744,7 @@ int run_embed(ppd_ctx* c, const int32_t* ids_dev, int rows, int row0, int pos_of
 int set_state(ppd_ctx* c, int pos, int tok) {
   hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, c->cur, c->ds, pos, tok);
   HIPCHK(c, hipGetLastError());
-  c->dev_pos_pending = pos;
+  c->dev_pos = pos;
   return PPD_OK;
 }
 
@@ -751,8 +752,9 @@ int set_state(ppd_ctx* c, int pos, int tok) {
 // kernel.  early: top-k -> candidates, which it also embeds as rows 1..k at the next position.
 // final: arg max, verification; with adopt, the matching candidate's row and KV tails are adopted.
 // With speculative early prediction the adopting head also runs on the candidate rows (see ppd_ctx::spec).
-// X: the rows, where they are not the activation rows.
-int run_head(ppd_ctx* c, bool early, bool adopt, const float* X = nullptr) {
+// X: the rows, where they are not the activation rows.  take_next: the candidates are those that the round before predicted.
+// The final selection also leaves the next round's position, and row 0 as that round begins with it.
+int run_head(ppd_ctx* c, bool early, bool adopt, const float* X = nullptr, bool take_next = false) {
   const ppd_model_dims& d = c->d;
   const bool spec = c->spec && adopt && !early;
   // top-k sampling with few kept tokens is drawn from the head's block lists inside the selection kernel;
@@ -796,6 +798,10 @@ int run_head(ppd_ctx* c, bool early, bool adopt, const float* X = nullptr) {
   s.vocab = d.vocab;
   const int T = select_threads(s.nblk * s.kk);
   dim3 grid(1, 1);
+  if (!early) {
+    s.next = embed_args(c, nullptr, 1, 0, 1); s.max_ctx = d.max_ctx; s.take_next = take_next ? 1 : 0;
+    grid = dim3((d.d_model + 4 * T - 1) / (4 * T), 1);     // (four columns of the next row a thread)
+  }
   if (early) {
     s.emb = embed_args(c, nullptr, c->k, 1, 1);
     grid = dim3((d.d_model + T - 1) / T, c->k);
@@ -838,27 +844,22 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   const int d = c->d.n_layers, dbar = c->dbar, nb = c->nb, k = c->k;
   const int from = chain_from(c, kind);
   int rc;
-  {
+  if (c->chain || restore) {
     BeginArgs b; memset(&b, 0, sizeof b);
-    b.ds = c->ds; b.take_next = kind == 3 ? 1 : 0; b.host_cand = c->host_result_dev + 2;
-    int grid = 1;
-    if (c->chain || restore) {
-      if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain_layers(c, kind) * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
-      // (what the launch that gave up left of the attention partials goes, too: see FusedArgs::part)
-      else { b.ex = (u32x4*)c->fl_part; b.n16 = fl_part_floats(c) / 4; b.empty = FU_EMPTY; }
-      b.h = c->h; b.save = c->h_save; b.nsave = (1 + k) * c->d.d_model; b.restore = restore ? 1 : 0;
-      grid = 512;
-    }
+    b.ds = c->ds;
+    if (!restore) { b.ex = (u32x4*)c->fl_ex; b.n16 = (size_t)chain_layers(c, kind) * fu_ex_row(c->d.d_model, c->d.d_ff) / 4; b.empty = FU_EMPTY; }
+    // (what the launch that gave up left of the attention partials goes, too: see FusedArgs::part)
+    else { b.ex = (u32x4*)c->fl_part; b.n16 = fl_part_floats(c) / 4; b.empty = FU_EMPTY; }
+    b.h = c->h; b.save = c->h_save; b.nsave = (1 + k) * c->d.d_model; b.restore = restore ? 1 : 0;
     if (restore) {
       const ClearKvArgs kv = {(float*)c->Kc, (float*)c->Vc, c->ds, c->d.n_heads, c->d.head_dim, c->d.max_ctx, from};
       hipLaunchKernelGGL(clear_kv_kernel, dim3(c->d.n_heads, d - from), dim3(c->d.head_dim), 0, c->cur, kv);
       HIPCHK(c, hipGetLastError());
     }
-    hipLaunchKernelGGL(begin_round_kernel, dim3(grid), dim3(256), 0, c->cur, b);
+    hipLaunchKernelGGL(begin_round_kernel, dim3(512), dim3(256), 0, c->cur, b);
     HIPCHK(c, hipGetLastError());
   }
   if (kind == 2) {
-    if ((rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
     if ((rc = run_main_row(c, 0, d, pmax))) return rc;
     return run_head(c, false, false);
   }
@@ -874,7 +875,6 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
     return run_head(c, false, true);
   }
   // main token up to the exit layer
-  if (kind == 0 && (rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
   if (from < dbar) {
     ProfScope phase(c, PPD_KC_PHASE, 1);
     if ((rc = run_main_row(c, from, dbar, pmax))) return rc;
@@ -890,7 +890,7 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
     }
   }
   // final prediction, verification, adoption
-  return run_head(c, false, true);
+  return run_head(c, false, true, nullptr, kind == 3);
 }
 
 // the captured rounds are captured anew
@@ -966,8 +966,10 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   int rc;
   // (work the caller queued on its stream before ppd_prefill -- the weights -- was waited for there; a round
   // reads nothing else of the caller's)
-  // the device already holds this position as pending when the previous call was a round at pos - 1
-  if (c->dev_pos_pending != pos && (rc = set_state(c, pos, -1))) return rc;
+  // the device already holds this position when the previous call was a round at pos - 1
+  if (c->dev_pos != pos && (rc = set_state(c, pos, -1))) return rc;
+  if (!c->row0 && !again && (rc = run_embed(c, &c->ds->next_tok, 1, 0, 0))) return rc;
+  c->row0 = 0;                                   // (until the round is known to have run)
   const int pmax = pos + (kind == 2 || kind == 5 ? 0 : 1);
   hipGraphExec_t replay = nullptr;
   if (c->use_graphs && !c->prof && !again) {
@@ -992,7 +994,7 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
   }
   if (replay) HIPCHK(c, hipGraphLaunch(replay, c->stream));
   else if ((rc = issue_round(c, kind, pmax, again))) return rc;
-  c->dev_pos_pending = -1;                       // (unknown until the round is known to have run)
+  c->dev_pos = -1;                       // (unknown until the round is known to have run)
   // The round's last kernel writes token and match index to pinned memory and then the count of finished rounds:
   // poll that word instead of sleeping in a stream synchronisation (the wake-up costs more than a round's tail).
   // Profiled rounds, and a round that does not report in time, take the synchronisation (which also surfaces errors).
@@ -1015,7 +1017,8 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
     std::atomic_thread_fence(std::memory_order_acquire);
     c->rounds_seen = want;
   }
-  c->dev_pos_pending = c->host_result[0] < 0 ? pos : pos + 1;   // left by the round's final selection
+  c->dev_pos = c->host_result[0] < 0 ? pos : pos + 1;   // left by the round's final selection
+  c->row0 = 1;
   if (c->prof) prof_collect(c);
   return PPD_OK;
 }
@@ -1275,7 +1278,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   if (!c) return PPD_ENOMEM;
   c->d = d; c->k = k; c->dbar = exit_layer; c->nb = d.n_layers - exit_layer;
   c->user_stream = (hipStream_t)hip_stream;
-  c->dev_pos_pending = -1;
+  c->dev_pos = -1;
   c->wbytes = d.wdtype == 0 ? 4 : 2;
   c->tok_emb = w->tok_emb; c->pos_emb = w->pos_emb; c->lnf_g = w->lnf_g; c->lnf_b = w->lnf_b;
   c->lm_head = w->lm_head; c->early_head = w->early_head;
@@ -1484,7 +1487,7 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
 int ppd_reset(ppd_ctx* c) {
   if (!c) return PPD_EINVAL;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->n_ctx = -1; c->matched = 0; c->prompt_ran = 0; c->finished = 0; c->have_early = 0; c->dev_pos_pending = -1;
+  c->n_ctx = -1; c->matched = 0; c->prompt_ran = 0; c->finished = 0; c->have_early = 0; c->dev_pos = -1;
   memset(&c->st, 0, sizeof c->st);
   return PPD_OK;
 }
@@ -1535,11 +1538,12 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
     }
     if (!rc && last && i + m == rows) rc = keep_row(c, c->h, c->h + (size_t)(m - 1) * c->d.d_model);
   }
+  if (!rc) rc = set_state(c, n_prompt - 1, prompt[n_prompt - 1]);
+  if (!rc && !last) rc = run_embed(c, &c->ds->next_tok, 1, 0, 0);
   c->prof = prof;
   if (rc) return rc;
-  if ((rc = set_state(c, n_prompt - 1, prompt[n_prompt - 1]))) return rc;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->n_ctx = n_prompt - 1; c->matched = 0; c->prompt_ran = last; c->finished = 0;
+  c->n_ctx = n_prompt - 1; c->matched = 0; c->prompt_ran = last; c->row0 = 1; c->finished = 0;
   return PPD_OK;
 }
 
@@ -1550,9 +1554,9 @@ int ppd_step(ppd_ctx* c, int32_t* out_tokens, int max_out, ppd_step_info* info) 
   const int pos = c->n_ctx;
   if (pos + 1 >= c->d.max_ctx) return PPD_ECTX;   // the candidates sit at position pos+1
   const int kind = c->prompt_ran ? 4 : (c->matched ? (c->spec ? 3 : 1) : 0);
-  c->prompt_ran = 0;                             // (a round that fails leaves x_0 to one that starts from its embedding)
+  c->prompt_ran = 0;
   int rc = run_round(c, kind, pos);
-  if (rc) return rc;
+  if (rc) { c->matched = 0; return rc; }         // (what a round that fails leaves is no row to go on from: the next one embeds its token)
   account_round(c, kind, pos);
   const int tok = c->host_result[0], midx = c->host_result[1];
   const bool first = kind == 0 || kind == 4;     // (x_0's rows of the prompt pass are the round's)
@@ -1582,6 +1586,7 @@ int plain_greedy_step(ppd_ctx* c, int32_t* out_token) {
   if (pos >= c->d.max_ctx) return PPD_ECTX;
   const int kind = c->prompt_ran ? 5 : 2;
   c->prompt_ran = 0;
+  if (c->matched) { c->matched = 0; c->row0 = 0; }       // (row 0 holds the adopted row: this step starts from the embedding)
   int rc = run_round(c, kind, pos);
   if (rc) return rc;
   account_round(c, kind, pos);

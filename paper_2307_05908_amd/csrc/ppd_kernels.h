@@ -39,16 +39,16 @@ constexpr int ATT_WAVES = ATT_THREADS / WAVE;
 constexpr int ATT_CHUNK = 64;       // positions per workgroup; chunk c covers [c*64, (c+1)*64)
 constexpr int MAXM = 8;
 
-// Round state in device memory, written by the tiny state kernel before a round and by the
-// selection kernels during it; read by every kernel that needs a position or a token id.
+// Round state in device memory, written by the tiny state kernel behind a prompt and by the
+// selection kernels of a round; read by every kernel that needs a position or a token id.
 struct DevState {
-  int32_t pos;        // absolute position of the main token x_t
+  int32_t pos;        // absolute position of the main token x_t (a round's final selection leaves the next round's)
   int32_t next_tok;   // id of x_t
   int32_t result[2];  // token x_{t+1}, match_idx of the last final selection
   int32_t cand[MAXM]; // early top-k ids
-  int32_t cand_next[MAXM]; // candidates of the next round, predicted at the end of a matching round
+  int32_t cand_next[2][MAXM]; // candidates of the next round, predicted at the end of a matching round, in the half its position's parity selects
   int32_t sampled;    // final prediction drawn by the sampling kernel (sampling-based variants)
-  int32_t pos_pending; // position of the next round: set explicitly, or left by a round's final selection (pos + 1)
+  uint32_t sel_done;   // workgroups of a final selection that are done (zero between launches)
   int32_t seq;         // rounds finished since the context was created (the host waits for the next value)
   int32_t aborted;     // a workgroup of the round's one-launch chain of layers gave up waiting: the round's results are void
 };
@@ -149,35 +149,24 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* p, size_t
 }
 // take_next: the round about to start uses the candidates the previous round predicted for it
 __global__ void set_state_kernel(DevState* ds, int pos, int tok) {
-  if (threadIdx.x == 0) { ds->pos = pos; ds->pos_pending = pos; if (tok >= 0) ds->next_tok = tok; }
+  if (threadIdx.x == 0) { ds->pos = pos; if (tok >= 0) ds->next_tok = tok; }
 }
 // One row of activations to another place (x_0's, from the prompt pass to the first round)
 __global__ __launch_bounds__(256) void keep_row_kernel(float* to, const float* row, int n) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) to[i] = row[i];
 }
-// First launch of every round: the position the previous round (or set_state_kernel) left pending becomes the
-// current one; take_next: the round uses the candidates the previous round predicted for it
-// (host_cand: the candidates' copy in pinned host memory, for the round's record).
-// For rounds with a one-launch chain of layers (ex != null): the buffers of its steps' outputs are marked empty, and the
+// First launch of a round with a one-launch chain of layers: the buffers of its steps' outputs are marked empty (ex), and the
 // activation rows are kept (save) so that the round can be run again if the launch has to give up; restore: this is
-// that second run.
+// that second run.  (Other rounds begin with their first layer: what a round finds in the state and in row 0 the one before left there.)
 struct BeginArgs {
-  DevState* ds; int take_next; int32_t* host_cand;
+  DevState* ds;
   u32x4* ex; size_t n16; uint32_t empty;     // 16-byte pieces to fill
   float* h; float* save; int nsave; int restore;
 };
 __global__ __launch_bounds__(256) void begin_round_kernel(BeginArgs a) {
   const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
-  if (t == 0) {
-    a.ds->pos = a.ds->pos_pending;
-    a.ds->aborted = 0;
-  }
-  if (t < MAXM && a.take_next) {
-    const int32_t c = a.ds->cand_next[t];
-    a.ds->cand[t] = c;
-    a.host_cand[t] = c;
-  }
+  if (t == 0) a.ds->aborted = 0;
   const u32x4 e = {a.empty, a.empty, a.empty, a.empty};
   for (size_t i = t; i < a.n16; i += stride) a.ex[i] = e;
   for (size_t i = t; i < (size_t)a.nsave; i += stride) { if (a.restore) a.h[i] = a.save[i]; else a.save[i] = a.h[i]; }
@@ -1227,7 +1216,7 @@ __global__ void chunk_kv_kernel(ChunkKvArgs a) {
 struct ClearKvArgs { float* Kc; float* Vc; const DevState* ds; int H, HD, max_ctx, layer0; };
 #ifdef PPD_ENGINE_TU
 __global__ void clear_kv_kernel(ClearKvArgs a) {
-  const int i = threadIdx.x, pos = a.ds->pos_pending;
+  const int i = threadIdx.x, pos = a.ds->pos;
   const size_t base = ((size_t)(a.layer0 + blockIdx.y) * a.H + blockIdx.x) * kv_blocks(a.max_ctx) * (KV_BLOCK * a.HD);
   a.Kc[base + k_index(pos, i, a.HD)] = 0.f;
   a.Vc[base + v_index(pos, i, a.HD)] = 0.f;
@@ -1319,7 +1308,9 @@ struct SelectArgs {
   DevState* ds;
   int32_t* host_result; // device-visible pinned host memory: [0] token, [1] match_idx (mode 1), [2..2+k) candidates (mode 0),
                         // [2 + MAXM] number of finished rounds, written after the rest (mode 1): the host polls it
-  EmbedArgs emb;        // candidate rows (mode 0)
+  EmbedArgs emb;        // candidate rows (mode 0; mode 1 with spec)
+  EmbedArgs next;       // mode 1: row 0 of the next round, unless that one begins with an adopted row
+  int take_next;        // mode 1: the round's candidates are those that the round before predicted (cand_next)
   // adoption (mode 1)
   float* h;                 // [1+k][d_model]: row 0 main, rows 1.. candidates
   const float* tailK; const float* tailV;   // [nb][k][H][hd]
@@ -1866,6 +1857,7 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
     }
     __syncthreads();
   }
+  const int pos = a.ds->pos;
   if (a.ds->aborted) {      // the one-launch chain of layers gave up: nothing of this round is taken over, the host runs it again
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
       a.host_result[0] = -1;
@@ -1877,43 +1869,61 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
     return;
   }
   const int token = id_in_vocab(a.samp_topk > 0 ? s_tok : (a.sampled ? a.ds->sampled : win[0]), a.vocab);
+  const int32_t* const cand = a.take_next ? a.ds->cand_next[pos & 1] : a.ds->cand;
   if (tid == 0) {
     int midx = -1;
-    for (int q = 0; q < a.k; ++q) if (a.ds->cand[q] == token) { midx = q; break; }
+    for (int q = 0; q < a.k; ++q) if (cand[q] == token) { midx = q; break; }
     s_midx = midx;
   }
   __syncthreads();
   const int midx = s_midx;
   if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
     a.ds->result[0] = token; a.ds->result[1] = midx; a.ds->next_tok = token;
-    a.ds->pos_pending = a.ds->pos + 1;      // the next round's position (its first launch takes it over)
     a.host_result[0] = token; a.host_result[1] = midx;
+    if (a.take_next) for (int q = 0; q < a.k; ++q) a.host_result[2 + q] = cand[q];
     // the round's record is complete: let the host see it, then the new count
     const int32_t seq = a.ds->seq + 1;
     a.ds->seq = seq;
     __threadfence_system();
     *(volatile int32_t*)(a.host_result + 2 + MAXM) = seq;
   }
-  if (midx < 0 || a.nb == 0) return;
+  // The next round's position, once every workgroup is done with this one's
+  const int nwg = gridDim.x * gridDim.y;
+  auto leave = [&] {
+    __syncthreads();
+    if (tid == 0 && (nwg == 1 || atomicInc(&a.ds->sel_done, nwg - 1) == (unsigned)nwg - 1)) a.ds->pos = pos + 1;
+  };
+  const int pos_next = pos + 1;
+  if (midx < 0 || a.nb == 0) {
+    // the next round's row 0 is the token's embedding
+    if (pos_next < a.max_ctx) {
+      const EmbedArgs e = a.next;
+      for (int i = ((int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x) * T + tid; i < e.d_model; i += nwg * T) {
+        float v = WTr<WT>::load1(e.tok_emb, (size_t)token * e.d_model + i);
+        if (e.pos_emb) v += WTr<WT>::load1(e.pos_emb, (size_t)pos_next * e.d_model + i);
+        e.h[i] = v;
+      }
+    }
+    return leave();
+  }
   // adoption: block (l, which), l < nb, copies one layer's K or V tail; block (0,0) also the hidden row.
   // With speculative early prediction the grid has further blocks (l >= nb) that prepare the next round.
   const int l = blockIdx.x;
-  const int pos_next = a.ds->pos + 1;
   if (l >= a.nb) {
-    if (!a.spec) return;
+    if (!a.spec) return leave();
     const int b = l - a.nb, nblocks = gridDim.x - a.nb;
     if (blockIdx.y == 0) {
       // the matching row's logits are the next round's early logits
       const float* src = a.spec_logits + (size_t)midx * a.vocab;
       float* dst = a.early_spec + (size_t)(pos_next & 1) * a.vocab;
       for (int i = b * T + tid; i < a.vocab; i += nblocks * T) dst[i] = src[i];
-      return;
+      return leave();
     }
     // the next round's candidates: top-k of the matching row's logits; then, column by column (each thread
     // its own columns, so no thread waits for another): the matching row becomes row 0, and the candidates'
     // embeddings become rows 1..k, one position on
     merge_row(1 + midx, a.k);
-    if (b == 0 && tid < a.k) a.ds->cand_next[tid] = win[tid];
+    if (b == 0 && tid < a.k) a.ds->cand_next[pos_next & 1][tid] = win[tid];
     const EmbedArgs e = a.emb;
     const int pos2 = pos_next + 1;
     for (int i = b * T + tid; i < a.d_model; i += nblocks * T) {
@@ -1925,7 +1935,7 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
           e.h[(size_t)r * e.d_model + i] = v;
         }
     }
-    return;
+    return leave();
   }
   if (!a.spec && l == 0 && blockIdx.y == 0)
     for (int i = tid; i < a.d_model; i += T) a.h[i] = a.h[(size_t)(1 + midx) * a.d_model + i];
@@ -1937,6 +1947,7 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
     const size_t o = (size_t)hh * a.head_floats + (blockIdx.y == 0 ? k_index(pos_next, i, a.hd) : v_index(pos_next, i, a.hd));
     dst[o] = src[idx];
   }
+  leave();
 }
 
 }  // namespace ppd
