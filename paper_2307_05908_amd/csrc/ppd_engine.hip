@@ -82,6 +82,7 @@ struct ppd_ctx {
   uint16_t *pf_xa;       // the attention outputs (written by the attention kernel),
   uint16_t *pf_xf;       // the feed-forward activations (written by the FFN-in GEMM; zero beyond d_ff)
   uint16_t *pf_qp, *pf_kp, *pf_vp;   // one layer's queries, keys, values as two-term operand blocks of the prompt attention
+  float *pf_last;                    // partial results of x_0's attention, and counts of them (see PAttnArgs)
   float *pf_ws; int *pf_cnt;         // partial sums of products whose reduction length is cut, parts done per tile (made when first needed)
   unsigned pg_ready;                 // bit 2 t + paired: that kernel's LDS is set up
   int pg_tile, pg_parts;             // >= 0, > 0: the tile and the cut of every product of the pass (tests)
@@ -1080,7 +1081,7 @@ void account_round(ppd_ctx* c, int kind, int pos) {
 void free_all(ppd_ctx* c) {
   (void)drop_graphs(c);
   void* dev[] = {c->Kc, c->Vc, c->tailK, c->tailV, c->h, c->h_exit, c->qkv, c->att, c->ffn, c->part, c->logits,
-                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_s, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
+                 c->early_logits, c->early_spec, c->samp_w, c->samp_keys, c->samp_pm, c->samp_pc, c->rp_s, c->rp_x, c->rp_a, c->rp_f, c->pf_h, c->pf_qkv, c->pf_xp, c->pf_xa, c->pf_xf, c->pf_qp, c->pf_kp, c->pf_vp, c->pf_last, c->rope, c->ds, c->prompt_dev, c->pk_val, c->pk_idx,
                  c->fl_tab, c->fl_ex, c->fl_part, c->h_save};
   for (void* p : dev) (void)hipFree(p);
   for (void* p : c->owned) (void)hipFree(p);
@@ -1111,6 +1112,10 @@ int prefill_tiled(ppd_ctx* c, int rows, bool last) {
     HIPCHK(c, hipMalloc((void**)&c->pf_kp, pattn_stage_bytes((int)R, d.n_heads, d.head_dim)));
     HIPCHK(c, hipMalloc((void**)&c->pf_vp, pattn_stage_bytes((int)R, d.n_heads, d.head_dim)));
     c->pf_rows = (int)R;
+  }
+  if (last && !c->pf_last) {
+    HIPCHK(c, hipMalloc((void**)&c->pf_last, pattn_last_bytes(d.n_heads, d.head_dim)));
+    HIPCHK(c, hipMemsetAsync(c->pf_last, 0, pattn_last_bytes(d.n_heads, d.head_dim), c->cur));
   }
   // (the packed layouts depend on the row count: the padding columns of the activations are cleared per prompt)
   HIPCHK(c, hipMemsetAsync(c->pf_xf, 0, packed_bytes(rows, F), c->cur));
@@ -1190,7 +1195,7 @@ int prefill_tiled(ppd_ctx* c, int rows, bool last) {
       PAttnArgs pa; memset(&pa, 0, sizeof pa);
       pa.Qp = c->pf_qp; pa.Kp = c->pf_kp; pa.Vp = c->pf_vp; pa.outp = c->pf_xa;
       pa.M = rows; pa.H = d.n_heads; pa.d_model = dm; pa.JP = pk.JP;
-      pa.last = last; pa.max_ctx = d.max_ctx; pa.qkv = c->pf_qkv; pa.rope = pk.rope; pa.Kc = pk.Kc; pa.Vc = pk.Vc; pa.scale = pk.scale;
+      pa.last = last; pa.max_ctx = d.max_ctx; pa.lpart = c->pf_last; pa.lcnt = (unsigned*)(c->pf_last + (size_t)d.n_heads * PA_SPLIT * (d.head_dim + 2)); pa.qkv = c->pf_qkv; pa.rope = pk.rope; pa.Kc = pk.Kc; pa.Vc = pk.Vc; pa.scale = pk.scale;
       HIPCHK(c, launch_pattn(c->cur, pa, d.head_dim));
     }
     HIPCHK(c, gemm(c->pf_xa, P.o, dm, dm, 0, 0, false, bias ? w.bo : nullptr, nullptr, nullptr, c->pf_h, c->pf_h, dm, 0, plan[1]));

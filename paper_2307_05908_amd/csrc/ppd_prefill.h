@@ -703,9 +703,13 @@ struct PAttnArgs {
   int gx;               // workgroups of a head (launch_pattn fills this)
   // last: row M - 1 is the first round's and attends in fp32 to the cache, as it would in a round
   int last, max_ctx;
+  int sp; float* lpart; unsigned* lcnt;    // its workgroups per head (launch_pattn), their partial results [H][PA_SPLIT][HD + 2], those done (zero between launches)
   const float* qkv; const float2* rope; const float* Kc; const float* Vc;
   float scale;
 };
+constexpr int PA_SPLIT = 16;
+// bytes of lpart, with lcnt behind it
+inline size_t pattn_last_bytes(int H, int HD) { return (size_t)H * (PA_SPLIT * (HD + 2) + 1) * sizeof(float); }
 // bytes of each of Qp, Kp, Vp
 inline size_t pattn_stage_bytes(int M, int H, int HD) { return (size_t)2 * H * ((M + 31) / 32) * (HD / 16) * 1024; }
 
@@ -783,14 +787,15 @@ __global__ __launch_bounds__(256) void pkv_pack_kernel(PKvPackArgs a) {
   }
 }
 
-// The last row of a prompt against the keys and values in the fp32 cache, one workgroup per head, beside those of pattn_kernel's
+// The last row of a prompt against the keys and values in the fp32 cache, up to PA_SPLIT workgroups per head, beside those of pattn_kernel's
 // other rows (whose two-term operands made up a third of the error of a row's logits: 7B shape, 512 tokens, distance of the first
 // token's logits from 64 bits 7.0e-5 with the last row among them, 5.4e-5 with it by itself in a round).  What bounds it: a wave's
-// blocks of 16 positions one after the other, 16 KiB of keys and values each, the next one's requested a block ahead; it ends before the
-// others do.  A lane i + 16 c has four components of position i's key per 16 components, and of four positions' values component
-// 16 s + i (see k_index, v_index).
+// blocks of 16 positions one after the other, 16 KiB of keys and values each, some 3 us of latency: two of them to a wave, up to 512 positions,
+// and the workgroup of a head that is done last merges (the others' results are past their L2).  With one workgroup per head the launch
+// took as long as that: 333 rows 20 -> 34 us.  A lane i + 16 c has four components of position i's key per 16
+// components, and of four positions' values component 16 s + i (see k_index, v_index).
 template <int HD>
-__device__ __forceinline__ void pattn_last_row(const PAttnArgs& a, int h, float* lds) {
+__device__ __forceinline__ void pattn_last_row(const PAttnArgs& a, int h, int part, float* lds) {
   constexpr int CT = HD / 16, half = HD / 2, NW = 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, c = lane >> 4, m = a.M - 1;
   float* const qs = lds;                                   // [HD], then the waves' outputs [NW][HD], maxima and sums [NW]
@@ -819,12 +824,13 @@ __device__ __forceinline__ void pattn_last_row(const PAttnArgs& a, int h, float*
   float mx = -INFINITY, l = 0.f, acc[CT];
 #pragma unroll
   for (int s = 0; s < CT; ++s) acc[s] = 0.f;
-  request(wave);
-  for (int b = wave; b < nblk; b += NW) {
+  const int stride = a.sp * NW;
+  request(part * NW + wave);
+  for (int b = part * NW + wave; b < nblk; b += stride) {
     float4 k[CT], v[CT];
 #pragma unroll
     for (int s = 0; s < CT; ++s) { k[s] = kn[s]; v[s] = vn[s]; }
-    request(b + NW);
+    request(b + stride);
     float z = 0.f;
 #pragma unroll
     for (int s = 0; s < CT; ++s) { z = fmaf(q[s].x, k[s].x, z); z = fmaf(q[s].y, k[s].y, z); z = fmaf(q[s].z, k[s].z, z); z = fmaf(q[s].w, k[s].w, z); }
@@ -858,17 +864,39 @@ __device__ __forceinline__ void pattn_last_row(const PAttnArgs& a, int h, float*
   }
   if (lane == 0) { wm[wave] = mx; wm[NW + wave] = l; }
   __syncthreads();
-  if (tid >= HD) return;
-  float top = wm[0];
+  float top = wm[0], num = 0.f, den = 0.f;                 // (finite: a workgroup's first wave has a block)
 #pragma unroll
   for (int w = 1; w < NW; ++w) top = fmaxf(top, wm[w]);
-  float num = 0.f, den = 0.f;
+  const int i0 = tid < HD ? tid : 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {                           // (a wave without a block adds zeros)
     const float f = __builtin_amdgcn_exp2f(wm[w] - top);
-    num = fmaf(f, wo[w * HD + tid], num);
+    num = fmaf(f, wo[w * HD + i0], num);
     den = fmaf(f, wm[NW + w], den);
   }
+  if (a.sp > 1) {
+    float* const mine = a.lpart + (size_t)(h * PA_SPLIT + part) * (HD + 2);
+    auto put = [](float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto get = [](float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (tid < HD) put(mine + tid, num);
+    if (tid == 0) { put(mine + HD, top); put(mine + HD + 1, den); }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (where every XCD finds them)
+    __syncthreads();
+    int* const done = (int*)(wm + 2 * NW);
+    if (tid == 0) *done = atomicInc(a.lcnt + h, a.sp - 1) == (unsigned)a.sp - 1;
+    __syncthreads();
+    if (!*done) return;
+    top = -INFINITY;
+    for (int p = 0; p < a.sp; ++p) top = fmaxf(top, get(a.lpart + (size_t)(h * PA_SPLIT + p) * (HD + 2) + HD));
+    num = den = 0.f;
+    for (int p = 0; p < a.sp; ++p) {
+      float* const q = a.lpart + (size_t)(h * PA_SPLIT + p) * (HD + 2);
+      const float f = __builtin_amdgcn_exp2f(get(q + HD) - top);
+      num = fmaf(f, get(q + i0), num);
+      den = fmaf(f, get(q + HD + 1), den);
+    }
+  }
+  if (tid >= HD) return;
   const int MT = (a.M + 15) / 16, KT = a.d_model / 32;
   put_packed1(a.outp, (size_t)MT * KT * 512, KT, m, h * HD + tid, num / den);
 }
@@ -890,12 +918,10 @@ __global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void pattn_kernel(PAttnArgs
   // workgroups of a head walk the same steps and find them in its L2.  With a head's rows spread over all XCDs the steps came from
   // memory eight times, 3 TB/s of them: 13B shape, 4095 rows, 892 -> 526 us.  (Other numbers of heads, 12, 20 or 36, keep
   // that order.)
-  // (The workgroups of the last row, where there are any, are the first H.)
-  int b = blockIdx.x;
-  if (a.last) {
-    if (b < a.H) { pattn_last_row<HD>(a, b, (float*)lds); return; }
-    b -= a.H;
-  }
+  // (The workgroups of the last row, where there are any, come behind them all: in front of them they held up the longest ones, 7B shape, 2000
+  // rows, 149 -> 163 us.)
+  const int b = blockIdx.x;
+  if (b >= a.gx * a.H) { const int r = b - a.gx * a.H; pattn_last_row<HD>(a, r % a.H, r / a.H, (float*)lds); return; }
   int h = b / a.gx, wg = a.gx - 1 - (b - h * a.gx);
   if ((a.H & 7) == 0) {
     const int r = b >> 3, per = a.H >> 3;

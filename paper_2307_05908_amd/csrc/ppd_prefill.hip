@@ -166,7 +166,10 @@ template <int HD, int QT>
 static hipError_t launch_pattn_t(hipStream_t stream, PAttnArgs a) {
   const int MT = (a.M + 15) / 16;
   a.gx = (MT + 4 * QT - 1) / (4 * QT);
-  const dim3 grid((a.gx + (a.last ? 1 : 0)) * a.H);
+  const int nblk = (a.M + 15) / 16;                  // blocks of positions of the last row: two to a wave of its workgroups
+  a.sp = nblk <= 8 ? 1 : (nblk + 7) / 8;
+  if (a.sp > PA_SPLIT) a.sp = PA_SPLIT;
+  const dim3 grid((a.gx + (a.last ? a.sp : 0)) * a.H);
   const size_t lds = (size_t)2 * (4 * (HD / 32) + 2 * (HD / 16)) * 1024;
   hipLaunchKernelGGL((pattn_kernel<HD, QT>), grid, dim3(256), lds, stream, a);
   return hipGetLastError();
@@ -174,7 +177,7 @@ static hipError_t launch_pattn_t(hipStream_t stream, PAttnArgs a) {
 
 hipError_t launch_pattn(hipStream_t stream, const PAttnArgs& a, int head_dim) {
   if (a.M < 1 || a.JP != (a.M + 31) / 32 || (head_dim != 64 && head_dim != 128) || a.d_model % 32) return hipErrorInvalidValue;
-  if (a.last && (!a.qkv || !a.Kc || !a.Vc || a.M > a.max_ctx)) return hipErrorInvalidValue;
+  if (a.last && (!a.qkv || !a.Kc || !a.Vc || !a.lpart || !a.lcnt || a.M > a.max_ctx)) return hipErrorInvalidValue;
   // rows per workgroup (64 QT): two query tiles per wave once the prompt gives enough workgroups (four would leave
   // one wave per SIMD: measured slower)
   const bool two = a.M >= 1024;
