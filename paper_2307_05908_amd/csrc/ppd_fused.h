@@ -374,13 +374,14 @@ __device__ __forceinline__ void fu_help_attention(const FWg& w, FHelper& hp, int
 }
 
 // ---- the multiplying waves
-// Every batch is requested in full: blocks that are not wanted re-read the start of the buffer and are never used.
+// Every batch is requested in full: blocks that are not wanted are asked for past the end of the buffer, and not read.  (The start of the
+// buffer in their place: a plain token of 8 layers, 256 wide 207 -> 196 us, 1536 298 -> 293, 2048 348 -> 346, 4096 the same.)
 template <int PACE>
 __device__ __forceinline__ void fu_request(u32x4 (&buf)[MG_BATCH], unsigned lane16, const char* P, unsigned bytes, unsigned o, int n) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)P, 0, (int)bytes, 0x00020000);
   if constexpr (PACE < 16) __builtin_amdgcn_s_waitcnt(0xF70 | PACE);        // vmcnt(PACE)
 #pragma unroll
-  for (int j = 0; j < MG_BATCH; ++j) buf[j] = __builtin_amdgcn_raw_buffer_load_b128(r, lane16 + j * 1024u, j < n ? o : 0u, 2);   // 2: non-temporal
+  for (int j = 0; j < MG_BATCH; ++j) buf[j] = __builtin_amdgcn_raw_buffer_load_b128(r, j < n ? lane16 + j * 1024u : bytes, j < n ? o : 0u, 2);   // 2: non-temporal
 }
 #define FU_REQUEST(slot, q) do { const FReq q_ = (q); fu_request<FU_PACE>(ring[slot], lane16, q_.P, q_.bytes, q_.o, q_.n); } while (0)
 #define FU_AHEAD(slot, q) do { const FReq q_ = (q); if constexpr (!NARROW) fu_request<FU_PACE_AHEAD>(ring[slot], lane16, q_.P, q_.bytes, q_.o, q_.n); \

@@ -1979,7 +1979,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int MG_THREADS = 512;     // 8 waves: each takes one eighth of the reduction length of a 16-row tile
 constexpr int MG_WAVES = MG_THREADS / WAVE;
 constexpr int MG_BATCH = 4;         // 1 KiB blocks requested per register batch
-constexpr int MG_RING = 4;          // register batches in flight per wave
+// Register batches in flight per wave.  (Four are 1 % slower, and so is one: 7B shape, 8 layers, a PPD round behind a match 679 / 672 us, 13B 970 / 969
+// and behind 4096 tokens 1152 / 1147, OPT-125m shape 295 / 292; three 682, 969, 1152, 293.)
+constexpr int MG_RING = 2;
 constexpr int MG_EP = 2;            // outputs per thread whose bias and residual are requested in the prologue
 constexpr int MG_LDS_HLOG = 2048;   // byte offsets: [0, 2048) norm statistics, then 1 KiB of head logits,
 constexpr int MG_LDS_G = 3072;      // then the norm's gain (and bias), the partial sums, the staged rows
@@ -2168,8 +2170,7 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
 
   // ---- 3. the weight stream: wave w owns k-blocks [kb0, kb0 + nblk) of every tile blockIdx.x,
   // + gridDim.x, ...; MG_BATCH blocks per batch, MG_RING batches in flight.  Every batch is always
-  // requested in full: slots past the wave's share (or past the last tile) re-read the start of the
-  // matrix, which is in the cache by then, and are never used.
+  // requested in full, as a buffer of its own that ends with the wave's share: nothing is read for slots past it (or past the last tile).
   const int nb8 = (KT + MG_WAVES - 1) / MG_WAVES;
   const int kb0 = wave * nb8 < KT ? wave * nb8 : KT;
   const int nblk = (kb0 + nb8 < KT ? kb0 + nb8 : KT) - kb0;
@@ -2182,29 +2183,17 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
   const int NBT = MP ? nbp / MG_BATCH : (nb8 + MG_BATCH - 1) / MG_BATCH;   // batches per tile (and pass), the same for every wave
   const int sst = P == 1 ? nb8 : nbp;                        // blocks between two waves' staged runs
   const int Q = P * ntiles * NBT;
-  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)G.P, 0, (int)a.wbytes, 0x00020000);
   const unsigned lane16 = lane * 16;
   int l_p = 0, l_tile = 0, l_b = 0;     // pass, tile ordinal and batch inside the tile of the next request
   auto issue = [&](u32x4 (&buf)[MG_BATCH]) {
-    if constexpr (!MP) {
-      const bool live = l_tile < ntiles;
-      const unsigned base = (unsigned)(((int)blockIdx.x + l_tile * grid) * KT + kb0 + l_b * MG_BATCH) * 1024u;
+    const bool live = MP ? l_p < P : l_tile < ntiles;
+    const int s0 = (MP ? l_p * nbp : 0) + l_b * MG_BATCH, left = live ? nblk - s0 : 0, n = left < 0 ? 0 : (left < MG_BATCH ? left : MG_BATCH);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((char*)G.P + (unsigned)(((int)blockIdx.x + l_tile * grid) * KT + kb0 + s0) * 1024u, 0, n * 1024, 0x00020000);
 #pragma unroll
-      for (int j = 0; j < MG_BATCH; ++j) {
-        const bool ok = live && l_b * MG_BATCH + j < nblk;
-        buf[j] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, ok ? base + j * 1024u : 0u, 2);   // 2: non-temporal
-      }
-      if (++l_b == NBT) { l_b = 0; ++l_tile; }
-    } else {
-      const bool live = l_p < P;
-      const int s0 = l_p * nbp + l_b * MG_BATCH;
-      const unsigned base = (unsigned)(((int)blockIdx.x + l_tile * grid) * KT + kb0 + s0) * 1024u;
-#pragma unroll
-      for (int j = 0; j < MG_BATCH; ++j) {
-        const bool ok = live && s0 + j < nblk;
-        buf[j] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, ok ? base + j * 1024u : 0u, 2);
-      }
-      if (++l_b == NBT) { l_b = 0; if (++l_tile == ntiles) { l_tile = 0; ++l_p; } }
+    for (int j = 0; j < MG_BATCH; ++j) buf[j] = __builtin_amdgcn_raw_buffer_load_b128(r, lane16 + j * 1024u, 0, 2);   // 2: non-temporal
+    if (++l_b == NBT) {
+      l_b = 0; ++l_tile;
+      if (MP && l_tile == ntiles) { l_tile = 0; ++l_p; }
     }
   };
   // One batch per wave is what a compute unit keeps in flight: it goes out now, the rest of the ring
@@ -2525,13 +2514,16 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_narrow_kernel(MGemmArgs 
   const int kb0 = wave * nb8 < KT ? wave * nb8 : KT;
   const int nblk = (kb0 + nb8 < KT ? kb0 + nb8 : KT) - kb0;
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)G.P, 0, (int)a.wbytes, 0x00020000);
-  u32x4 w[T][NB];                              // (blocks past the share or the last tile re-read the start: never used)
+  // Blocks past the share or the last tile lie past the buffer's end: nothing is read for them.  (Re-reading the start of the matrix instead, one
+  // kilobyte that every wave of the launch asked for, took a tenth of a narrow model's token: 384 wide, 12 layers, 262 -> 234 us, 768
+  // 289 -> 264, its PPD round 320 -> 298.)
+  u32x4 w[T][NB];
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int tile = (int)blockIdx.x + t * grid;
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-      w[t][j] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16u, tile < a.NT && j < nblk ? (unsigned)(tile * KT + kb0 + j) * 1024u : 0u, 2);   // 2: non-temporal
+      w[t][j] = __builtin_amdgcn_raw_buffer_load_b128(wres, tile < a.NT && j < nblk ? (unsigned)(tile * KT + kb0 + j) * 1024u + lane * 16u : a.wbytes, 0, 2);   // 2: non-temporal
   }
   // bias and residual of the output this thread will finish: row of the tile, row of the input, tile
   constexpr int R = PAIRED ? 8 : 16;

@@ -487,20 +487,20 @@ __global__ __launch_bounds__(MG_THREADS) void rgemm_kernel(RGemmArgs a) {
   const unsigned lane16 = lane * 16, plane = KT * 2048u;
   u32x4 wa[D][TT], xh[D][MT], xl[D][MT];
   int l_g = 0, l_s = 0;
-  // every step is requested in full: what lies past the wave's share re-reads the start of the matrix and is never used
+  // every step is requested in full: what lies past the wave's share is asked for past the end of the matrix, and not read
   auto request = [&](int d) {
     const bool live = l_g < ngrp;
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
       const int ord = l_g * TT + t;
-      const unsigned o = live && ord < ntiles ? (unsigned)(((int)blockIdx.x + ord * grid) * KT + kb0 + l_s) * 1024u : 0u;
-      wa[d][t] = __builtin_amdgcn_raw_buffer_load_b128(wres, lane16, o, 2);      // 2: non-temporal
+      const unsigned o = live && ord < ntiles ? (unsigned)(((int)blockIdx.x + ord * grid) * KT + kb0 + l_s) * 1024u + lane16 : a.wbytes;
+      wa[d][t] = __builtin_amdgcn_raw_buffer_load_b128(wres, o, 0, 2);      // 2: non-temporal
     }
-    const unsigned xo = live ? (unsigned)(kb0 + l_s) * 1024u : 0u;
+    const unsigned xo = (unsigned)(kb0 + l_s) * 1024u + lane16;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-      xh[d][m] = __builtin_amdgcn_raw_buffer_load_b128(xres, lane16, xo + m * KT * 1024u, 0);
-      xl[d][m] = __builtin_amdgcn_raw_buffer_load_b128(xres, lane16, xo + m * KT * 1024u + plane, 0);
+      xh[d][m] = __builtin_amdgcn_raw_buffer_load_b128(xres, live ? xo + m * KT * 1024u : KT * 4096u, 0, 0);
+      xl[d][m] = __builtin_amdgcn_raw_buffer_load_b128(xres, live ? xo + m * KT * 1024u + plane : KT * 4096u, 0, 0);
     }
     if (++l_s >= nblk) { l_s = 0; ++l_g; }
   };
