@@ -141,9 +141,10 @@ int ppd_reset(ppd_ctx *ctx);
  * run through all d layers to fill the KV cache, the last prompt token
  * becomes x_0 with match = False.  bf16 models: x_0 goes with them through
  * all layers but the last where its row costs less there than in a pass of
- * its own (prompts of one chunk or of the first kind below, unless it makes
- * a further row of tiles; PPD_PREFILL_LAST=2 in the environment at
- * ppd_create: never); the first step then takes it
+ * its own (prompts of one chunk; prompts of the first kind below unless it
+ * makes a further row of tiles or tokens are drawn, whose seeds are to give
+ * what they give with x_0 by itself; PPD_PREFILL_LAST=2 in the environment
+ * at ppd_create: never); the first step then takes it
  * through the last layer only.  Implies ppd_reset.  PPD_ECTX if
  * n_prompt > max_ctx; PPD_EINVAL for ids outside [0, vocab).
  * bf16 models with prompts of more than 32 tokens: all prompt rows go through

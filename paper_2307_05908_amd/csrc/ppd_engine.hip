@@ -1210,7 +1210,9 @@ int prefill_tiled(ppd_ctx* c, int rows, bool last) {
 
 // Whether x_0, the prompt's last token, goes through the layers with the rows before it, all but the last layer, in which the first
 // round takes it on (from there on its row is alone, as in any round).  That saves the first round a pass over nearly all weights;
-// it is left out where the prompt is more than one chunk, or one more row costs the tiled products (by their account, times what they take
+// it is left out where the prompt is more than one chunk, where tokens are drawn and the row would take the compute-bound pass's roundings (a draw
+// decides on the last bits of the masses: some tenth of the sequences of 16 tokens behind 128 goes another way then, and a seed is to
+// give the tokens that it gave), or where one more row costs the tiled products (by their account, times what they take
 // between a layer's other launches) more than the decode step does.  Measured (prompt and one plain token, us, x_0 by itself / with the
 // prompt): 7B shape, 8 layers, 2 rows 1372 / 915, 32 1707 / 1183, 65 1841 / 1567, 256 2778 / 2282, 512 3973 / 3525, 1024 6727 / 6275, but
 // 257 2776 / 2777 and 513 3964 / 3983 (by itself either way); 13B shape, 8 layers, 4096 rows 33.5 / 32.5 ms; OPT-125m shape, 9 rows
@@ -1219,6 +1221,7 @@ int prefill_tiled(ppd_ctx* c, int rows, bool last) {
 bool takes_x0(const ppd_ctx* c, int n_prompt, bool tiled) {
   if (!c->mfma || !c->prefill_last || n_prompt < 2) return false;
   if (!tiled) return n_prompt <= c->prefill_chunk;
+  if (c->samp_mode) return false;
   const ppd_model_dims& d = c->d;
   const int dm = d.d_model, F = d.d_ff, rows = n_prompt - 1;
   const int nk[4][2] = {{(3 * dm + 15) / 16, dm}, {(dm + 15) / 16, dm}, {d.act == 2 ? (F + 7) / 8 : (F + 15) / 16, dm}, {(dm + 15) / 16, F}};
