@@ -1363,6 +1363,7 @@ constexpr int SAMP_NT = 64;      // thresholds at which sample_weights_kernel le
                                  // largest logit, then 1/4 apart to 12 below
 constexpr int SAMP_CAP = 6144;   // tokens between two thresholds that are searched in LDS
 constexpr int SAMP_SOLO = 512;   // of those, what one wave searches alone
+constexpr int SAMP_KEEP = 64;    // keys of a thread of sample_kernel that stay in its registers
 struct SampleArgs {
   const float* z; int n;     // logits [n]
   int mode, ks;              // 1 top-k sampling (ks kept), 2 top-p sampling
@@ -1458,7 +1459,8 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_weights_kernel(SampleArgs
 // the tokens between them in LDS (in a fixed order) and fixes the key's bits on those alone; while they are more than
 // SAMP_CAP (a flat softmax, the tail below the last threshold) it looks through all tokens for a bit, until they are fewer.
 // Measured (top-p 0.95), both kernels: 50272 tokens 358 us bit by bit over all tokens, 65 + 17 with the thresholds; logits of
-// standard deviation 4: 76 + 19 -> 25 + 5 us.  What went: workgroups' sums awaited one by one, a second look at every key where
+// standard deviation 4: 76 + 19 -> 25 + 5 us, 22.5 + 5 with every thread's keys in its registers for both searches and requested behind the sums (in
+// front of them: 24; as 64-bit addresses: 54, most of it spilled).  What went: workgroups' sums awaited one by one, a second look at every key where
 // a thread has a token to collect (a memory latency for each of its keys, in turn), a barrier for every bit.
 // In the far tail (p = 0.999, logits of standard deviation 4), 50272 / 32000 / 16000 tokens: every bit over all tokens 306 / 191 /
 // 113 us, until few are left 151 / 106 / 76.
@@ -1479,16 +1481,37 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = a.n;
   float mx = -INFINITY;
   for (int b = tid; b < a.nblk; b += SAMP_THREADS) mx = fmaxf(mx, a.pk_val[(size_t)b * MAXM]);
-  mx = wave_max(mx);
-  if (lane == 0) s_redf[wave] = mx;
-  // (through LDS, by all threads: a thread per threshold waiting for one workgroup's sums after the other took longer)
+  // both searches look through all keys: up to SAMP_KEEP a thread are requested once (zero: no token), behind what is needed before them
+  const bool keep = a.npad <= SAMP_KEEP * SAMP_THREADS;
+  const __amdgpu_buffer_rsrc_t keys = __builtin_amdgcn_make_buffer_rsrc(a.keys, 0, a.npad * 4, 0x00020000);
+  uint32_t kr[SAMP_KEEP];
   {
-    constexpr int ROWS = SAMP_CAP / (SAMP_NT + 1);
+    // the workgroups' sums (through LDS, by all threads: a thread per threshold waiting for one workgroup's sums after the other took longer)
+    constexpr int ROWS = SAMP_CAP / (SAMP_NT + 1), PER = (ROWS * (SAMP_NT + 1) + SAMP_THREADS - 1) / SAMP_THREADS;
     const int nb = a.npad / SAMP_THREADS;
     double m = 0.0; int c = 0;
     for (int b0 = 0; b0 < nb; b0 += ROWS) {
-      const int rows = nb - b0 < ROWS ? nb - b0 : ROWS, at = b0 * (SAMP_NT + 1);
-      for (int e = tid; e < rows * (SAMP_NT + 1); e += SAMP_THREADS) { s_w[e] = a.pm[at + e]; s_id[e] = a.pc[at + e]; }
+      const int rows = nb - b0 < ROWS ? nb - b0 : ROWS, at = b0 * (SAMP_NT + 1), ne = rows * (SAMP_NT + 1);
+      double pm[PER]; int pc[PER];
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int e = tid + q * SAMP_THREADS < ne ? tid + q * SAMP_THREADS : 0;
+        pm[q] = a.pm[at + e]; pc[q] = a.pc[at + e];
+      }
+      if (b0 == 0) {
+#pragma unroll
+        for (int q0 = 0; q0 < SAMP_KEEP; q0 += SAMP_MEMU)
+#pragma unroll
+          for (int q = q0; q < q0 + SAMP_MEMU; ++q)
+            kr[q] = keep && q0 * SAMP_THREADS < a.npad ? __builtin_amdgcn_raw_buffer_load_b32(keys, tid * 4, q * SAMP_THREADS * 4, 0) : 0u;
+        mx = wave_max(mx);
+        if (lane == 0) s_redf[wave] = mx;
+      }
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int e = tid + q * SAMP_THREADS;
+        if (e < ne) { s_w[e] = pm[q]; s_id[e] = pc[q]; }
+      }
       __syncthreads();
       if (tid <= SAMP_NT) {
 #pragma unroll 8
@@ -1584,7 +1607,19 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       // the tokens in question, first <= key <= last, thread by thread
       const uint32_t first = pre > lo ? pre : lo, rest = pre | (bit < 0 ? 0u : (2u << bit) - 1u), last = rest < top ? rest : top;
       int mine = 0;
-      unsigned long long which = 0;                              // (up to 64 tokens of a thread: the ones to collect)
+      static_assert(SAMP_KEEP <= 64, "a bit of the mask each");
+      unsigned long long which = 0;                              // (keep: the ones to collect)
+      if (keep) {
+        // (few of a wave's keys are in question: four of them cost one comparison)
+        const uint32_t d = last - first;
+#pragma unroll
+        for (int q = 0; q < SAMP_KEEP; q += 4) {
+          const uint32_t r0 = kr[q] - first, r1 = kr[q + 1] - first, r2 = kr[q + 2] - first, r3 = kr[q + 3] - first;
+          if (__ballot(min(min(r0, r1), min(r2, r3)) <= d))
+            which |= (unsigned long long)((r0 <= d ? 1u : 0u) | (r1 <= d ? 2u : 0u) | (r2 <= d ? 4u : 0u) | (r3 <= d ? 8u : 0u)) << q;
+        }
+        mine = __popcll(which);
+      } else
 #pragma unroll 2
       for (int i0 = tid; i0 < a.npad; i0 += SAMP_THREADS * SAMP_MEMU) {
         uint32_t k[SAMP_MEMU];
@@ -1594,7 +1629,6 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
         for (int q = 0; q < SAMP_MEMU; ++q) {
           const bool in = k[q] >= first && k[q] <= last;
           mine += in ? 1 : 0;
-          which |= (unsigned long long)in << ((i0 / SAMP_THREADS + q) & 63);
         }
       }
       int incl = mine;
@@ -1609,7 +1643,7 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       for (int w = 0; w < NW; ++w) nl += s_off[w];
       if (nl > SAMP_CAP) nl = SAMP_CAP;
       auto take = [&](int i, uint32_t k) { s_key[at] = k; s_id[at] = i; s_w[at] = a.w[i]; ++at; };
-      if (a.npad <= 64 * SAMP_THREADS) {
+      if (keep) {
         for (; which && at < SAMP_CAP; which &= which - 1) {
           const int i = tid + __builtin_ctzll(which) * SAMP_THREADS;
           take(i, a.keys[i]);
@@ -1622,17 +1656,18 @@ __global__ __launch_bounds__(SAMP_THREADS) void sample_kernel(SampleArgs a) {
       }
       __syncthreads();
     }
-    // few tokens: the first wave goes on alone, without a barrier (the same sums: 64 tokens at a time, in their order)
+    // few tokens: the first wave goes on alone, without a barrier, its lanes adding their own tokens (every 64th) first
     if (list && nl <= SAMP_SOLO) {
       if (wave == 0) {
         auto G = [&](uint32_t kth, double& mass, int& count) {
-          mass = 0.0; count = 0;
+          double m = 0.0;
+          count = 0;
           for (int e = lane; e < (nl + WAVE - 1) / WAVE * WAVE; e += WAVE) {
             const bool ge = e < nl && s_key[e] >= kth;
-            mass += wave_sum_f64(ge ? s_w[e] : 0.0);
+            m += ge ? s_w[e] : 0.0;
             count += __popcll(__ballot(ge));
           }
-          mass += A; count += cA;
+          mass = wave_sum_f64(m) + A; count += cA;
         };
         while (bit >= 0 && c_at - c_hi != 1) fix_bit(G);
         const bool single = c_at - c_hi == 1;
@@ -1828,7 +1863,7 @@ __global__ __launch_bounds__(T) void select_kernel(SelectArgs a) {
     merge_block_lists<T>(a.pk_val + (size_t)prow * a.pk_stride * MAXM, a.pk_idx + (size_t)prow * a.pk_stride * MAXM,
                       a.nblk, a.kk, nk, wv, wi, win, winv);
   };
-  merge_row(0, a.mode == 0 ? a.k : (a.samp_topk > 0 ? a.samp_topk : 1));
+  if (a.mode == 0 || !a.sampled) merge_row(0, a.mode == 0 ? a.k : (a.samp_topk > 0 ? a.samp_topk : 1));     // (a drawn token needs no arg max)
   if (a.mode == 0) {
     // candidates and their rows; block x handles row blockIdx.y
     if (blockIdx.x == 0 && blockIdx.y == 0 && tid < a.k) { a.ds->cand[tid] = win[tid]; a.host_result[2 + tid] = win[tid]; }
