@@ -2117,9 +2117,8 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
   const int ntiles = (int)blockIdx.x + (a.tiles_wg - 1) * grid < a.NT ? a.tiles_wg : a.tiles_wg - 1;
   int off_b, off_part, off_x;
   mg_lds_layout(K, M, a.norm, a.tiles_wg, xrow, off_b, off_part, off_x);
-  float* stat = (float*)lds;                  // mu[16], rstd[16], redA[16][8], redB[16][8]
-  float* redA = stat + 32;
-  float* redB = stat + 32 + 16 * MG_WAVES;
+  float* redA = (float*)lds;                  // [16][8] each
+  float* redB = redA + 16 * MG_WAVES;
   float* hlog = (float*)(lds + off_x);        // head launches: [M][HEAD_MAX_ROWS] logits, over the staged rows once those are done with
 
   // ---- 1. input rows (and the norm's gain and bias) into LDS, fp32 as they are: wave w takes the
@@ -2144,24 +2143,23 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
     }
   };
   {
-    if (MP && npass > 1) dma_pass(0);
+    if constexpr (MP) dma_pass(0);
     else {
-      const int U = (K + 255) >> 8;
+      // (its own share of every row, and of the gains: without a norm a wave waits for no other before its first product)
+      const int e0 = wave * nb8_ * 32, e1 = e0 + nb8_ * 32 < K ? e0 + nb8_ * 32 : K;
       for (int m = 0; m < M; ++m)
-        for (int u = wave; u < U; u += MG_WAVES) {
-          const int kk = u * 256 + lane * 4;
-          if (kk < K) dma16(G.X + (size_t)m * a.ldx + kk, lds + off_x + m * xrow + u * 1024);
+        for (int k0 = e0; k0 < e1; k0 += 256) {
+          const int kk = k0 + lane * 4;
+          if (kk < e1) dma16(G.X + (size_t)m * a.ldx + kk, lds + off_x + m * xrow + k0 * 4);
         }
-    }
-    if (a.norm >= 0) {
-      const int Ug = (K + 511) >> 9;
-      for (int u = wave; u < Ug; u += MG_WAVES) {
-        const int kk = u * 512 + lane * 8;
-        if (kk < K) {
-          dma16((const uint16_t*)G.ng + kk, lds + MG_LDS_G + u * 1024);
-          if (a.norm == 0 && G.nb) dma16((const uint16_t*)G.nb + kk, lds + off_b + u * 1024);
+      if (a.norm >= 0)
+        for (int k0 = e0; k0 < e1; k0 += 512) {
+          const int kk = k0 + lane * 8;
+          if (kk < e1) {
+            dma16((const uint16_t*)G.ng + kk, lds + MG_LDS_G + k0 * 2);
+            if (a.norm == 0 && G.nb) dma16((const uint16_t*)G.nb + kk, lds + off_b + k0 * 2);
+          }
         }
-      }
     }
   }
 
@@ -2241,12 +2239,13 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
   // floats k .. k+7 (k a multiple of 8) then hold hi(k..k+7) | lo(k..k+7).  One fixed order per row:
   // thread t sums the 8-element chunks t, t + 512, ... in turn, butterfly inside each wave, the eight
   // wave sums in index order.  LayerNorm: mean first, then the squared deviations.
-  // everything requested before the weight stream has arrived once only the MG_BATCH newest loads
-  // are outstanding; then the workgroup's rows are complete in LDS
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(MG_BATCH) : "memory");
-  const int nchunk = KT * 4;                  // 32-byte chunks (8 elements) per staged row
+  // everything a wave has requested before its weights has arrived once only the MG_BATCH newest loads
+  // are outstanding
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MG_BATCH) : "memory");
   auto combine8 = [&](const float* r) { return ((((((r[0] + r[1]) + r[2]) + r[3]) + r[4]) + r[5]) + r[6]) + r[7]; };
-  if (a.norm >= 0) {
+  float mu_l = 0.f, rs_l = 1.f;               // lane m: of row m
+  if (MP || a.norm >= 0) asm volatile("s_barrier" ::: "memory");     // the workgroup's rows are complete in LDS
+  if (!MP && a.norm >= 0) {
     if (a.norm == 0) {
       for (int m = 0; m < M; ++m) {
         float sm = 0.f;
@@ -2273,78 +2272,70 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
       s2 = wave_sum(s2);
       if (lane == 0) redB[m * MG_WAVES + wave] = s2;
     }
-    __syncthreads();
-    if (tid < M) {
-      stat[tid] = a.norm == 0 ? combine8(redA + tid * MG_WAVES) / (float)K : 0.f;
-      stat[16 + tid] = 1.0f / sqrtf(combine8(redB + tid * MG_WAVES) / (float)K + a.eps);
-    }
-    __syncthreads();
+    __syncthreads();                          // (and nobody reads another wave's share of the rows any more)
+    const int m = lane < M ? lane : 0;
+    mu_l = a.norm == 0 ? combine8(redA + m * MG_WAVES) / (float)K : 0.f;
+    rs_l = 1.0f / sqrtf(combine8(redB + m * MG_WAVES) / (float)K + a.eps);
   }
-  // (with passes: the same split, for the runs of one pass; chunks outside every wave's share become zeros)
-  auto convert_rows = [&](int pass) {
-  const int nch = (MP && npass > 1) ? nbp_ * 32 : nchunk;
-  if constexpr (MP) {
-    if (npass > 1) {
-      // (no fused norm with passes; whether a chunk lies inside a wave's share is the same for every row)
-      for (int c = tid; c < nch; c += MG_THREADS) {
-        const bool inside = pass_col(pass, c * 8) >= 0;
-        for (int m = 0; m < M; ++m) {
-          char* px = lds + off_x + m * xrow + c * 32;
-          float xv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          if (inside) {
-            const float4 v = ((const float4*)px)[0], w = ((const float4*)px)[1];
-            xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w; xv[4] = w.x; xv[5] = w.y; xv[6] = w.z; xv[7] = w.w;
-          }
-          uint32_t hp[4], lp[4];
+  // hi = bf16(x) (the hardware's round-to-nearest-even pair conversion), lo = bf16(x - hi)
+  auto split_to = [](char* px, const float (&xv)[8]) {
+    uint32_t hp[4], lp[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            hp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){xv[2 * e], xv[2 * e + 1]}, bf16x2));
-            const float r0 = xv[2 * e] - __uint_as_float(hp[e] << 16), r1 = xv[2 * e + 1] - __uint_as_float(hp[e] & 0xffff0000u);
-            lp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
-          }
-          ((uint4*)px)[0] = make_uint4(hp[0], hp[1], hp[2], hp[3]);
-          ((uint4*)px)[1] = make_uint4(lp[0], lp[1], lp[2], lp[3]);
-        }
-      }
-      return;
+    for (int e = 0; e < 4; ++e) {
+      hp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){xv[2 * e], xv[2 * e + 1]}, bf16x2));
+      const float r0 = xv[2 * e] - __uint_as_float(hp[e] << 16), r1 = xv[2 * e + 1] - __uint_as_float(hp[e] & 0xffff0000u);
+      lp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
     }
-  }
-  for (int m = 0; m < M; ++m) {
-    const float mu = a.norm >= 0 ? stat[m] : 0.f, rs = a.norm >= 0 ? stat[16 + m] : 1.f;
-    for (int c = tid; c < nch; c += MG_THREADS) {
-      char* px = lds + off_x + m * xrow + c * 32;
-      float xv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if ((MP && npass > 1) ? pass_col(pass, c * 8) >= 0 : c * 8 < K) {
-        const float4 v = ((const float4*)px)[0], w = ((const float4*)px)[1];
-        xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w; xv[4] = w.x; xv[5] = w.y; xv[6] = w.z; xv[7] = w.w;
-        if (a.norm >= 0) {
-          const u32x4 gq = *(const u32x4*)(lds + MG_LDS_G + c * 16);
-          float gf[8]; WTr<bf16_t>::unpack(gq, gf);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) xv[e] = (xv[e] - mu) * rs * gf[e];
-          if (a.norm == 0 && G.nb) {
-            const u32x4 bq = *(const u32x4*)(lds + off_b + c * 16);
-            float bf[8]; WTr<bf16_t>::unpack(bq, bf);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) xv[e] += bf[e];
-          }
-        }
-      }
-      // hi = bf16(x) (the hardware's round-to-nearest-even pair conversion), lo = bf16(x - hi)
-      uint32_t hp[4], lp[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        hp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){xv[2 * e], xv[2 * e + 1]}, bf16x2));
-        const float r0 = xv[2 * e] - __uint_as_float(hp[e] << 16), r1 = xv[2 * e + 1] - __uint_as_float(hp[e] & 0xffff0000u);
-        lp[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){r0, r1}, bf16x2));
-      }
-      ((uint4*)px)[0] = make_uint4(hp[0], hp[1], hp[2], hp[3]);
-      ((uint4*)px)[1] = make_uint4(lp[0], lp[1], lp[2], lp[3]);
-    }
-  }
+    ((uint4*)px)[0] = make_uint4(hp[0], hp[1], hp[2], hp[3]);
+    ((uint4*)px)[1] = make_uint4(lp[0], lp[1], lp[2], lp[3]);
   };
-  convert_rows(0);
-  __syncthreads();
+  // (with passes: the split for the runs of one pass; chunks outside every wave's share become zeros)
+  auto convert_rows = [&](int pass) {
+    // (no fused norm with passes; whether a chunk lies inside a wave's share is the same for every row)
+    for (int c = tid; c < nbp_ * 32; c += MG_THREADS) {
+      const bool inside = pass_col(pass, c * 8) >= 0;
+      for (int m = 0; m < M; ++m) {
+        char* px = lds + off_x + m * xrow + c * 32;
+        float xv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (inside) {
+          const float4 v = ((const float4*)px)[0], w = ((const float4*)px)[1];
+          xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w; xv[4] = w.x; xv[5] = w.y; xv[6] = w.z; xv[7] = w.w;
+        }
+        split_to(px, xv);
+      }
+    }
+  };
+  if constexpr (MP) {
+    convert_rows(0);
+    __syncthreads();
+  } else {
+    // a wave's own share; its columns past the row's end become zeros
+    for (int m = 0; m < M; ++m) {
+      const float mu = lane_f32(mu_l, m), rs = lane_f32(rs_l, m);
+      for (int c = kb0 * 4 + lane; c < (kb0 + nblk) * 4; c += WAVE) {
+        char* px = lds + off_x + m * xrow + c * 32;
+        float xv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (c * 8 < K) {
+          const float4 v = ((const float4*)px)[0], w = ((const float4*)px)[1];
+          xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w; xv[4] = w.x; xv[5] = w.y; xv[6] = w.z; xv[7] = w.w;
+          if (a.norm >= 0) {
+            const u32x4 gq = *(const u32x4*)(lds + MG_LDS_G + c * 16);
+            float gf[8]; WTr<bf16_t>::unpack(gq, gf);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xv[e] = (xv[e] - mu) * rs * gf[e];
+            if (a.norm == 0 && G.nb) {
+              const u32x4 bq = *(const u32x4*)(lds + off_b + c * 16);
+              float bf[8]; WTr<bf16_t>::unpack(bq, bf);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) xv[e] += bf[e];
+            }
+          }
+        }
+        split_to(px, xv);
+      }
+    }
+    asm volatile("" ::: "memory");            // (a wave's own LDS operations stay in order)
+  }
 #pragma unroll
   for (int r = 1; r < MG_RING; ++r) issue(ring[r]);
 
