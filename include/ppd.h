@@ -154,9 +154,8 @@ int ppd_reset(ppd_ctx *ctx);
  * bit-identical with, a token-by-token pass (every decode step after it is
  * the same arithmetic either way).  Otherwise, or with PPD_PREFILL_TILED=2 /
  * PPD_PREFILL_CHUNK=n in the environment at ppd_create, the prompt goes
- * through the decode kernels in chunks of consecutive positions (32 for
- * bf16 weights, 8 for fp32; n lowers it): one pass over the weights per
- * chunk, every row's arithmetic that of a one-token pass, the cache equal to
+ * through the decode kernels in chunks of 32 consecutive positions (n
+ * lowers it): one pass over the weights per chunk, every row's arithmetic that of a one-token pass, the cache equal to
  * a token-by-token prefill bit for bit (n = 1 runs exactly that).
  * Buffers of the first kind are allocated at the first such prompt and grow
  * with the longest prompt seen (PPD_ENOMEM / PPD_EHIP if that fails). */

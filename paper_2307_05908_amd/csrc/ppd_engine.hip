@@ -191,7 +191,8 @@ hipError_t launch_gemm(ppd_ctx* c, GemmArgs& a, int ngroups, bool paired) {
   if (c->wbytes == 4 && gemm_small_fits(a, c->head_grid)) return launch_gemm_small(c->cur, a, ngroups, paired, c->head_grid);
   const int vec = 16 / c->wbytes;
   const int gmax = ngroups == 2 ? c->gmax2 : c->gmax1;
-  const int mmax = ngroups == 2 ? (a.g[1].M > a.g[0].M ? a.g[1].M : a.g[0].M) : a.g[0].M;
+  // (the rows of a prompt chunk eight to a workgroup)
+  const int rows = ngroups == 2 ? (a.g[1].M > a.g[0].M ? a.g[1].M : a.g[0].M) : a.g[0].M, mmax = rows < MAXM ? rows : MAXM;
   const int x_budget = GEMM_X_FLOATS / mmax;   // k elements of x per row that fit the LDS tile
   // rows a wave streams together: 4, or 2 when 4 would leave waves of the grid without a set
   int wr = 4;
@@ -208,10 +209,10 @@ hipError_t launch_gemm(ppd_ctx* c, GemmArgs& a, int ngroups, bool paired) {
   int gx;
   if (a.topk > 0) gx = c->head_grid;
   else gx = pick_grid(nsets, gmax);
-  dim3 grid(gx, ngroups);
+  dim3 grid(gx, ngroups, (rows + MAXM - 1) / MAXM);
   size_t lds = (GEMM_LDS_HDR + (size_t)mmax * a.KC + (a.topk > 0 ? HEAD_MAX_ROWS : 0)) * sizeof(float);
   int MB = ngroups == 2 ? a.g[1].M : 0;
-  const int MA = a.g[0].M;
+  const int MA = ngroups == 2 ? a.g[0].M : mmax;
   if (c->wbytes == 4) {
     if (wr == 4) return paired ? launch_gemm_t<float, true, 4>(c->cur, a, MA, MB, grid, lds)
                                : launch_gemm_t<float, false, 4>(c->cur, a, MA, MB, grid, lds);
@@ -222,9 +223,11 @@ hipError_t launch_gemm(ppd_ctx* c, GemmArgs& a, int ngroups, bool paired) {
 }
 
 // rows of a prompt chunk (ppd_prefill takes this many positions at a time through a layer: one pass over the weights per
-// chunk instead of per token): two MFMA tiles' columns for bf16 models (rgemm_kernel), the 8 rows of the fp32 GEMM otherwise
+// chunk instead of per token): two MFMA tiles' columns for bf16 models (rgemm_kernel); of fp32 models each workgroup of a GEMM takes
+// eight, and a chunk of 32 four times as many of them, which idle compute units and the caches take.  fp32, prompt and first token, us,
+// chunks of 8 / of 32: 256 wide, 4 layers, 10 tokens 318 / 262, 512 tokens 7388 / 2123; 512 wide, 6 layers, 16735 / 5516;
+// 1024 wide, 4 layers, 16576 / 9212; 2048 wide, 2 layers, 25171 / 19897; up to 9 tokens nothing changes.
 constexpr int PREFILL_CHUNK = 32;
-constexpr int PREFILL_CHUNK_FP32 = 8;
 
 // ---- bf16 models: MFMA GEMM on repacked weights
 constexpr size_t MG_LDS_MAX = 160 * 1024;
@@ -1305,9 +1308,8 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
   c->n_ctx = -1;
   c->use_graphs = env_int("PPD_GRAPHS", 1) != 2;      // PPD_GRAPHS=2 switches graph replay off
   {
-    const int cap = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
-    c->prefill_chunk = env_int("PPD_PREFILL_CHUNK", cap);
-    if (c->prefill_chunk > cap) c->prefill_chunk = cap;
+    c->prefill_chunk = env_int("PPD_PREFILL_CHUNK", PREFILL_CHUNK);
+    if (c->prefill_chunk > PREFILL_CHUNK) c->prefill_chunk = PREFILL_CHUNK;
     c->prefill_last = env_int("PPD_PREFILL_LAST", 1) != 2;
     c->few_rows = few_rows(d);
     // the compute-bound pass takes prompts of bf16 models unless the row-chunk path is asked for (PPD_PREFILL_CHUNK
@@ -1322,9 +1324,8 @@ int ppd_create(const ppd_model_dims* dims, const ppd_weights* w, int k, int exit
     c->head_grid = head_grid_valu(d.vocab, c->gmax1);
   }
   const size_t dm = d.d_model, R = 1 + k;
-  const size_t RC = d.wdtype == 1 ? PREFILL_CHUNK : PREFILL_CHUNK_FP32;
-  const size_t RB = R > RC ? R : RC;   // activation rows: a round's 1 + k, or a prompt chunk
-  const size_t RL = d.wdtype == 1 ? c->few_rows : PREFILL_CHUNK_FP32, RS = R > RL ? R : RL;   // those that go through run_layer
+  const size_t RB = R > PREFILL_CHUNK ? R : PREFILL_CHUNK;   // activation rows: a round's 1 + k, or a prompt chunk
+  const size_t RL = d.wdtype == 1 ? c->few_rows : PREFILL_CHUNK, RS = R > RL ? R : RL;   // those that go through run_layer
   // (every fill and copy below goes to this stream, see copy_logits)
   hipError_t e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
   c->cur = c->stream;

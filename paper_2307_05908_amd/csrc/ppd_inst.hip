@@ -19,9 +19,9 @@ static hipError_t launch_gemm_small_t(hipStream_t stream, const GemmArgs& a, int
 hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups, bool paired, int head_grid) {
   int mmax = a.g[0].M;
   if (ngroups == 2 && a.g[1].M > mmax) mmax = a.g[1].M;
-  if (!gemm_small_fits(a, head_grid) || mmax < 1 || mmax > MAXM || ngroups < 1 || ngroups > 2) return hipErrorInvalidValue;
+  if (!gemm_small_fits(a, head_grid) || mmax < 1 || ngroups < 1 || ngroups > 2 || mmax > (ngroups == 1 ? 65535 * MAXM : MAXM)) return hipErrorInvalidValue;
   if (a.topk > 0 && (ngroups != 1 || mmax != 1 || paired || head_grid > a.ntot)) return hipErrorInvalidValue;
-  const dim3 grid(a.topk > 0 ? head_grid : (a.ntot + GEMM_WAVES - 1) / GEMM_WAVES, ngroups);
+  const dim3 grid(a.topk > 0 ? head_grid : (a.ntot + GEMM_WAVES - 1) / GEMM_WAVES, ngroups, (mmax + MAXM - 1) / MAXM);
   if (a.K <= 256) return launch_gemm_small_t<1>(stream, a, mmax, paired, grid);
   if (a.K <= 512) return launch_gemm_small_t<2>(stream, a, mmax, paired, grid);
   return launch_gemm_small_t<4>(stream, a, mmax, paired, grid);

@@ -203,7 +203,7 @@ __global__ void embed_kernel(EmbedArgs a) {
 }
 
 // ------------------------------------------------------------------ skinny GEMM
-// Y[m][n] = epilogue( sum_k norm(X)[m][k] * W[n][k] ), M <= 8 rows per group.
+// Y[m][n] = epilogue( sum_k norm(X)[m][k] * W[n][k] ), M <= 8 rows per group and workgroup.
 // The layer forward of the main process and of the sub-processes (Algorithm 2);
 // the sub-processes' k rows share one pass over their layer's weights.
 //
@@ -242,14 +242,14 @@ __device__ __forceinline__ float silu(float u) { return u / (1.0f + expf(-u)); }
 // a register batch is always 8 loads per lane: WR rows x (8 / WR) k-blocks.
 // GF: one row's gains are requested with the row (see gains_first).
 template <typename WT, int MT, bool PAIRED, int WR, bool GF>
-__device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G, float* lds) {
+__device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G, float* lds, int r0 = 0) {
   constexpr int VEC = WTr<WT>::VEC;
   constexpr int BK = WAVE * VEC;                 // k elements per block
   constexpr int NBK = GEMM_BATCH / WR;           // k-blocks per batch
   constexpr int SPAN = NBK * BK;                 // k elements per batch
   constexpr int LR = PAIRED ? WR / 2 : WR;       // logical rows per set
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int M = G.M, K = a.K, KC = a.KC;
+  const int M = MT == MAXM && G.M - r0 > MT ? MT : G.M - r0, K = a.K, KC = a.KC;
   float4* xs4 = (float4*)(lds + GEMM_LDS_HDR);  // [MT][KC/4] float4; for VEC == 8 the two halves of every 8-group are split
 
   const int nsets = (a.ntot + LR - 1) / LR;
@@ -336,7 +336,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
     for (int i = 0; i < XR; ++i) {
       xr[i] = make_float4(0.f, 0.f, 0.f, 0.f);
       const int m = i / spr, kk = (i - m * spr) * 1024 + tid * 4;
-      if (m < M && kk < K) xr[i] = *(const float4*)(G.X + (size_t)m * a.ldx + kk);
+      if (m < M && kk < K) xr[i] = *(const float4*)(G.X + (size_t)(r0 + m) * a.ldx + kk);
     }
     // One row, GF: its gains come with it (later they would wait behind the weights).  GR float4 slots of a thread, 4096 elements,
     // are what the registers take: with 8 of them a workgroup fewer fits a compute unit; the rest of a longer row's gains is
@@ -412,7 +412,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
     if (a.norm >= 0) {
       if (a.norm == 0) {
         for (int m = 0; m < M; ++m) {
-          const float* x = G.X + (size_t)m * a.ldx;
+          const float* x = G.X + (size_t)(r0 + m) * a.ldx;
           float sm = 0.f;
           for (int i = tid * 4; i < K; i += 1024) {
             float4 v = *(const float4*)(x + i);
@@ -424,7 +424,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
         __syncthreads();
       }
       for (int m = 0; m < M; ++m) {
-        const float* x = G.X + (size_t)m * a.ldx;
+        const float* x = G.X + (size_t)(r0 + m) * a.ldx;
         const float mu = a.norm == 0 ? combine4(redA + m * GEMM_WAVES) / (float)K : 0.f;
         float s2 = 0.f;
         for (int i = tid * 4; i < K; i += 1024) {
@@ -451,7 +451,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
       int m = idx / KC, kk = idx - m * KC;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);          // zero tail: weights beyond K are zero too
       if (kk < kc) {
-        v = *(const float4*)(G.X + (size_t)m * a.ldx + k0 + kk);
+        v = *(const float4*)(G.X + (size_t)(r0 + m) * a.ldx + k0 + kk);
         if (a.norm >= 0) {
           float mu = stat[m], rs = stat[MAXM + m];
           float xv[4] = {v.x, v.y, v.z, v.w};
@@ -502,7 +502,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
           pb[r] = G.B[seg] ? WTr<WT>::load1(G.B[seg], loc) : 0.f;
         }
 #pragma unroll
-        for (int m = 0; m < MT; ++m) prs[r][m] = (G.Rsd && m < M) ? G.Rsd[(size_t)m * a.ldy + n] : 0.f;
+        for (int m = 0; m < MT; ++m) prs[r][m] = (G.Rsd && m < M) ? G.Rsd[(size_t)(r0 + m) * a.ldy + n] : 0.f;
       }
     }
     const int k0 = single ? 0 : (c_b / bpc) * KC;
@@ -558,7 +558,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
               else if (a.act == 2) y = fmaxf(y, 0.f);
             }
             y += prs[r][m];
-            G.Y[(size_t)m * a.ldy + n] = y;
+            G.Y[(size_t)(r0 + m) * a.ldy + n] = y;
             if (a.topk > 0 && m == 0) hlog[(c_it * GEMM_WAVES + wave) * LR + r] = y;
           }
         }
@@ -612,12 +612,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const GemmGroup& G,
   }
 }
 
-// MA rows in group 0, MB rows in group 1 (MB == 0: single-group launch)
+// MA rows in group 0, MB rows in group 1 (MB == 0: single-group launch; of 8 rows, blockIdx.z counts eights of rows of a prompt chunk)
 template <typename WT, int MA, int MB, bool PAIRED, int WR, bool GF = true>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs a) {
   extern __shared__ float4 lds4[];
   float* lds = (float*)lds4;
-  if (MB == 0 || blockIdx.y == 0) gemm_body<WT, MA, PAIRED, WR, GF>(a, a.g[0], lds);
+  if (MB == 0 || blockIdx.y == 0) gemm_body<WT, MA, PAIRED, WR, GF>(a, a.g[0], lds, MA == MAXM ? (int)blockIdx.z * MAXM : 0);
   else gemm_body<WT, (MB < 1 ? 1 : MB), PAIRED, WR, GF>(a, a.g[1], lds);
 }
 
@@ -628,6 +628,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs a) {
 // and lane l's products 4 l .. 4 l + 3 of blocks 0, 1, ... are its products here.
 // Several rows behind a norm are normalised by one wave of the workgroup each and shared through LDS (every wave for itself: a PPD
 // round of 12 layers, k = 3 / 8, us, before / now: 256 wide 179 / 170 and 219 / 198, 512 248 / 236 and 363 / 325, 1024 454 / 425 and 674 / 550).
+// A prompt chunk of more than 8 rows is so many workgroups more, 8 rows each: the weights of such models come from L2, and 32 rows take as long as 8.
 // Measured (K = 256, one row / one and three rows): norm-fused projections of 768 / 1024
 // outputs 11.1 / 11.9 -> 3.8 / 4.3 us with one and three rows, 7.5 -> 2.5 us with one; 1024 logits 8.7 -> 4.0 us.
 constexpr int GEMM_SMALL_K = 1024;
@@ -637,7 +638,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_small_kernel(GemmArgs a) {
   __shared__ float hlog[GEMM_WAVES * LR];
   const GemmGroup& G = a.g[blockIdx.y];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int M = G.M, K = a.K;
+  const int r0 = MT == MAXM ? (int)blockIdx.z * MAXM : 0;      // (the next rows of a prompt chunk)
+  const int M = MT == MAXM && G.M - r0 > MT ? MT : G.M - r0, K = a.K;
   constexpr int WROWS = PAIRED ? 2 * LR : LR;
   const int n0 = ((int)blockIdx.x * GEMM_WAVES + wave) * LR;
   // several rows behind a norm: a wave normalises rows wave, wave + 4 only, and has the others' from LDS
@@ -651,10 +653,10 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_small_kernel(GemmArgs a) {
     const int k = 256 * j + 4 * lane, kc = k < K ? k : 0;
     if (share) {
 #pragma unroll
-      for (int i = 0; i < OWN; ++i) { const int m = wave + i * GEMM_WAVES; xo[i][j] = *(const float4*)(G.X + (size_t)(m < M ? m : 0) * a.ldx + kc); }
+      for (int i = 0; i < OWN; ++i) { const int m = wave + i * GEMM_WAVES; xo[i][j] = *(const float4*)(G.X + (size_t)(r0 + (m < M ? m : 0)) * a.ldx + kc); }
     } else {
 #pragma unroll
-      for (int m = 0; m < MT; ++m) x[m][j] = m < M ? *(const float4*)(G.X + (size_t)m * a.ldx + kc) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int m = 0; m < MT; ++m) x[m][j] = m < M ? *(const float4*)(G.X + (size_t)(r0 + m) * a.ldx + kc) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if (a.norm >= 0) {
       const float* g = (const float*)G.ng + kc;
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_small_kernel(GemmArgs a) {
       pb[i] = G.B[s] ? ((const float*)G.B[s])[loc] : 0.f;
     }
 #pragma unroll
-    for (int m = 0; m < MT; ++m) prs[r][m] = (G.Rsd && m < M) ? G.Rsd[(size_t)m * a.ldy + n] : 0.f;
+    for (int m = 0; m < MT; ++m) prs[r][m] = (G.Rsd && m < M) ? G.Rsd[(size_t)(r0 + m) * a.ldy + n] : 0.f;
   }
   // past the end of the row: zeros on both sides
 #pragma unroll
@@ -771,7 +773,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_small_kernel(GemmArgs a) {
       }
       y += prs[r][m];
       if (lane == 0 && n0 + r < a.ntot) {
-        G.Y[(size_t)m * a.ldy + n0 + r] = y;
+        G.Y[(size_t)(r0 + m) * a.ldy + n0 + r] = y;
         if (LR > 1 && m == 0) hlog[wave * LR + r] = y;
       }
     }

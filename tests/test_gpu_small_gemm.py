@@ -89,6 +89,24 @@ def test_prompt_rows_are_the_one_row_pass_bit_exact(act, d_model, monkeypatch):
         np.testing.assert_array_equal(z.view(np.uint32), rz.view(np.uint32))
 
 
+@pytest.mark.parametrize("act,d_model,d_ff", [(pi.ACT_SWIGLU, 256, 1000), (pi.ACT_GELU, 1024, 1024), (pi.ACT_SWIGLU, 640, 4104), (pi.ACT_GELU, 1088, 1032)])
+def test_chunks_of_32_rows_are_the_one_row_pass_bit_exact(act, d_model, d_ff, monkeypatch):
+    """Prompts around 8, 16, 24 and 32 rows, eight to a workgroup: all products in the short-row kernel, at its longest rows, and some or
+    all of them in the streaming one, against one row and eight rows at a time."""
+    cfg = fp32_cfg(act, d_model, d_ff).replace(max_ctx=80)
+    dev = binding.upload_model(pi.make_model(cfg))
+    runs = []
+    for chunk in (None, "1", "8"):
+        if chunk:
+            monkeypatch.setenv("PPD_PREFILL_CHUNK", chunk)
+        P = binding.PPD(cfg, dev, k=3)
+        runs.append([gpu_generate(P, pi.make_prompt(cfg, n), 2, mode)[1] for n in (9, 10, 17, 18, 25, 32, 33, 34, 42, 67) for mode in ("ppd", "plain")])
+        P.close()
+    for z, *others in zip(*runs):
+        for rz in others:
+            np.testing.assert_array_equal(z.view(np.uint32), rz.view(np.uint32))
+
+
 @pytest.mark.parametrize("act,d_model,d_ff,k", [(pi.ACT_SWIGLU, 192, 520, 3), (pi.ACT_SWIGLU, 640, 1016, 8), (pi.ACT_GELU, 1024, 1024, 5), (pi.ACT_RELU, 448, 2048, 1)])
 def test_short_rows_match_the_oracle(act, d_model, d_ff, k):
     cfg = fp32_cfg(act, d_model, d_ff)
