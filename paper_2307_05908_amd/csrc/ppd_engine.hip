@@ -312,7 +312,13 @@ hipError_t launch_mgemm(ppd_ctx* c, MGemmArgs& a, int ngroups, bool paired) {
   if (c->mg_passes_min == 1 && !(paired && a.norm < 0))
     if (const int t = narrow_tiles(a, ngroups, mmax)) {
       a.xrow = mg_xrow(a.KT);
-      return narrow_launch(c->cur, a, paired, (a.KT + MG_WAVES - 1) / MG_WAVES, t, dim3((a.NT + t - 1) / t, ngroups), mg_narrow_lds(a.KT, mmax, t));
+      const int nb8 = (a.KT + MG_WAVES - 1) / MG_WAVES;
+      // Few tiles of long rows are bound by what a compute unit can read: two workgroups to a tile where that leaves no more of them than
+      // units.  Us a plain token / a PPD round of 12 layers, k = 3, before and after: 768 wide, 3072 feed-forward columns 262 -> 258 and
+      // 290 -> 288, 1024 / 4096 279 -> 275 and 339 -> 336; shares of up to 4 blocks gain nothing (384 wide 226 -> 231), quarters neither
+      // (768 wide 266), nor halves past the units (up to 512 workgroups: 281).
+      a.halves = t == 1 && !paired && nb8 > 4 && 2 * a.NT * ngroups <= 256;
+      return narrow_launch(c->cur, a, paired, nb8, t, dim3((a.NT + t - 1) / t << a.halves, ngroups), mg_narrow_lds(a.KT, mmax, t));
     }
   if (a.nmerge > 0) return hipErrorInvalidValue;     // (only that kernel merges)
   auto lds_with = [&](int M, int tiles, int passes) {

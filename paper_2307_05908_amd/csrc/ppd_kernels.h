@@ -2083,6 +2083,7 @@ struct MGemmArgs {
   int passes;       // the reduction length is staged in LDS in this many passes (1: whole rows; > 1 only without a fused norm)
   int nmerge;       // gemm_mfma_narrow_kernel without a norm: chunks of positions that may be in use, up to MG_MERGE; 0: X has the rows
   int H, HD, nchunk_max; const DevState* ds;
+  int halves;       // gemm_mfma_narrow_kernel, a tile per workgroup and no pairs: 1: two workgroups share a tile, eight of its rows each
 };
 
 // LDS bytes between staged rows: the row itself, moved off a multiple of 256 so that neighbouring rows
@@ -2545,17 +2546,22 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_narrow_kernel(MGemmArgs 
   // Blocks past the share or the last tile lie past the buffer's end: nothing is read for them.  (Re-reading the start of the matrix instead, one
   // kilobyte that every wave of the launch asked for, took a tenth of a narrow model's token: 384 wide, 12 layers, 262 -> 234 us, 768
   // 289 -> 264, its PPD round 320 -> 298.)
+  // Half a tile per workgroup: lanes l % 16 of the other eight rows have nothing to read, and their rows' outputs are the other workgroup's
+  constexpr bool CUT = T == 1 && !PAIRED;
+  const int cut = CUT ? a.halves : 0, sub = (int)blockIdx.x & cut;
+  const bool mine = !cut || (lane >> 3 & 1) == sub;
   u32x4 w[T][NB];
 #pragma unroll
   for (int t = 0; t < T; ++t) {
-    const int tile = (int)blockIdx.x + t * grid;
+    const int tile = CUT ? (int)blockIdx.x >> cut : (int)blockIdx.x + t * grid;
 #pragma unroll
     for (int j = 0; j < NB; ++j)
-      w[t][j] = __builtin_amdgcn_raw_buffer_load_b128(wres, tile < a.NT && j < nblk ? (unsigned)(tile * KT + kb0 + j) * 1024u + lane * 16u : a.wbytes, 0, 2);   // 2: non-temporal
+      w[t][j] = __builtin_amdgcn_raw_buffer_load_b128(wres, mine && tile < a.NT && j < nblk ? (unsigned)(tile * KT + kb0 + j) * 1024u + lane * 16u : a.wbytes, 0, 2);   // 2: non-temporal
   }
   // bias and residual of the output this thread will finish: row of the tile, row of the input, tile
-  constexpr int R = PAIRED ? 8 : 16;
-  const int orow = tid & (R - 1), ord = tid / R / M, ocol = tid / R - ord * M, n = ((int)blockIdx.x + ord * grid) * R + orow;
+  const int R = PAIRED ? 8 : 16 >> cut, rsh = PAIRED ? 3 : 4 - cut;
+  const int orow = (tid & (R - 1)) + (sub << rsh), ord = (tid >> rsh) / M, ocol = (tid >> rsh) - ord * M;
+  const int n = CUT ? ((int)blockIdx.x >> cut) * 16 + orow : ((int)blockIdx.x + ord * grid) * R + orow;
   const bool out = ord < T && n < a.ntot;
   const uint16_t* const B0 = (const uint16_t*)G.B[0];
   const uint16_t* const B1 = (const uint16_t*)G.B[1];

@@ -54,3 +54,23 @@ def test_partials_merged_in_the_output_projection_bit_exact(family, d_model, k, 
         np.testing.assert_array_equal(a[0], b[0])
         np.testing.assert_array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
         assert a[2] == b[2]
+
+
+@pytest.mark.parametrize("family,d_model,d_ff,k", [
+    ("opt", 64, 4096, 2), ("opt", 128, 1024, 8), ("opt", 128, 1032, 8), ("opt", 1024, 1032, 3), ("opt", 1088, 1032, 3), ("llama", 2048, 4096, 4), ("llama", 2176, 1032, 1)])
+def test_half_tiles_are_the_streaming_kernels_bit_exact(family, d_model, d_ff, k, monkeypatch):
+    """Two workgroups to a tile: shares of 4 and of 5 blocks, the most tiles of one and of two groups and more, with and without the merge of partials."""
+    hd = 64 if family == "opt" else 128
+    cfg = small_cfg(family, d_model=d_model, n_heads=d_model // hd, head_dim=hd, d_ff=d_ff, n_layers=3, exit_layer=2, alpha=0.1, n_prompt=63, n_gen=6)
+    dev = binding.upload_model(pi.make_model(cfg))
+    got = []
+    for passes in (None, "2"):
+        if passes:
+            monkeypatch.setenv("PPD_MGPASSES", passes)
+        P = binding.PPD(cfg, dev, k=k)
+        got.append([gpu_generate(P, pi.make_prompt(cfg), cfg.n_gen, mode) for mode in ("plain", "ppd")])
+        P.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a[0], b[0])
+        np.testing.assert_array_equal(a[1].view(np.uint32), b[1].view(np.uint32))
+        assert a[2] == b[2]
