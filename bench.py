@@ -32,9 +32,9 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # HBM bytes per launch of the roofline kernel (the two-group FFN-in GEMM) from rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled
 # by a copy kernel of known size, keyed by (configuration, k); collected with the counter probe on the C ABI
 # (paper_2307_05908_amd/ppd_pmc_probe), see profiles/.  A property of the kernel source it was collected on.
-MEASURED_TRAFFIC = {("llama7b", 3): 361.78e6}
+MEASURED_TRAFFIC = {("llama7b", 3): 361.71e6}
 # sha1 of csrc/ppd_kernels.h when the counters were collected: a changed kernel source voids the figure (null is printed)
-TRAFFIC_KERNELS_SHA1 = "2d324bb427d2f4cce1900181ab0a34a56b1dda8d"
+TRAFFIC_KERNELS_SHA1 = "f37a0588b13279c6f0c7f0476c7bf2bc02dc59ca"
 TRAFFIC_SOURCE = "profiles/llama7b_ppd_k3_traffic.txt"
 
 
@@ -366,28 +366,28 @@ def main():
         lat2 = us("attn.g2") + us("attn_merge.g2")
         small = us("select.g1")
 
-        def est(layers1, layers2, heads, embeds):
+        def est(layers1, layers2, heads):
             # (the layers of a chain as measured; all others by the fit)
             l1 = 0 if chain_us else layers1
             bytes_ = (l1 + 2 * layers2) * wl + heads * head_b
             launches = 4 * (l1 + layers2) + heads
             stream_ms = bytes_ / (rate * 1e9) * 1e3
-            fixed_ms = (launches * t_fixed + l1 * lat1 + layers2 * lat2 + heads * small + embeds * us("embed.g1")) / 1e3
+            fixed_ms = (launches * t_fixed + l1 * lat1 + layers2 * lat2 + heads * small) / 1e3
             return bytes_, launches, stream_ms, fixed_ms, layers1 * chain_us / 1e3
 
         solo_after_hit = e - nb
         spec = 2 * e == d and cfg.wdtype == pi.WD_BF16
-        cases = {"plain_token": (est(d, 0, 1, 1), wall_plain / K * 1e3),
-                 "ppd_round_after_miss": (est(e, nb, 2, 1), float(round_ms[~after_hit].mean()) if (~after_hit).any() else None),
-                 "ppd_round_after_hit": (est(solo_after_hit, nb, 1 if spec else 2, 0), float(round_ms[after_hit].mean()) if after_hit.any() else None)}
+        cases = {"plain_token": (est(d, 0, 1), wall_plain / K * 1e3),
+                 "ppd_round_after_miss": (est(e, nb, 2), float(round_ms[~after_hit].mean()) if (~after_hit).any() else None),
+                 "ppd_round_after_hit": (est(solo_after_hit, nb, 1 if spec else 2), float(round_ms[after_hit].mean()) if after_hit.any() else None)}
         # The event pair around every bracketed launch is part of the bracketed durations: what it adds per launch is
         # read off the roofline kernel (bracketed single launches against the burst between two events), and taken
-        # out of every launch of a case (6 per layer step, 2 per head pass, the embedding).
+        # out of every launch of a case (6 per layer step, 2 per head pass).
         bracket_us = 0.0
         if burst1_ms and "gemm_ffn_in.g1" in kernels:
             bracket_us = max(0.0, kernels["gemm_ffn_in.g1"]["avg_us"] - burst1_ms * 1e3)
         by_launch = 0 if chain_us else 1
-        n_launch = {"plain_token": 6 * d * by_launch + 3, "ppd_round_after_miss": 6 * (e * by_launch + nb) + 5,
+        n_launch = {"plain_token": 6 * d * by_launch + 2, "ppd_round_after_miss": 6 * (e * by_launch + nb) + 4,
                     "ppd_round_after_hit": 6 * (solo_after_hit * by_launch + nb) + (2 if spec else 4)}
         cases = {n: ((m[0], m[1], m[2], m[3] - n_launch[n] * bracket_us / 1e3, m[4]), meas) for n, (m, meas) in cases.items()}
         model_fit = {"form": "t = the main token's layers in the one-launch chain, as measured (chain_ms) + bytes / rate + launches * t_fixed (GEMM launches) + latency-bound kernels (attention, merge, selection) as measured",
