@@ -591,7 +591,7 @@ __global__ __launch_bounds__(MG_THREADS) void rgemm_kernel(RGemmArgs a) {
 // pack_rows_kernel, which reads the rows next, adds them in their order.  Block b of a launch is share b % 8: an XCD's workgroups read the same rows.
 // The rows come in phases of SG_PB blocks, two buffers.
 // What bounds it: what a compute unit can request at a time; the rows of 32 are still a third of its bytes (rgemm_kernel, with one tile to
-// a workgroup, read four bytes of rows for one of weights).  7B shape, 27 rows: O 15.5 -> 9.7 us, FFN-out 33.7 -> 27, the sums in pack_rows_kernel
+// a workgroup, read four bytes of rows for one of weights).  7B shape, 27 rows: O 15.5 -> 9.2 us, FFN-out 33.7 -> 22, the sums in pack_rows_kernel
 // 5.0 -> 6.2 (two of them).  A prompt of 27 tokens and its first token, 8 layers, rgemm_kernel / this, us: 7B shape 1179 / 1073 (9 tokens 1003 / 972), 13B 1656 /
 // 1497 (1410 / 1347), 8192 wide, 2 layers, 874 / 840, 3072 wide 878 / 796, 2048 689 / 610, 1024 495 / 438, OPT-125m shape (12 layers) 675 / 570.  Eight blocks ahead and phases
 // of 16 the same within 1 % but for the 13B shape, 1542: its 320 workgroups fit two to a compute unit with the smaller phases.
