@@ -142,10 +142,13 @@ int ppd_reset(ppd_ctx *ctx);
  * becomes x_0 with match = False.  bf16 models: x_0 goes with them through
  * all layers but the last where its row costs less there than in a pass of
  * its own (prompts of one chunk; prompts of the first kind below unless it
- * makes a further row of tiles or tokens are drawn, whose seeds are to give
- * what they give with x_0 by itself; PPD_PREFILL_LAST=2 in the environment
- * at ppd_create: never); the first step then takes it
- * through the last layer only.  Implies ppd_reset.  PPD_ECTX if
+ * makes a further row of tiles or tokens are drawn; PPD_PREFILL_LAST=2 in
+ * the environment at ppd_create: never); the first step then takes it
+ * through the last layer only.  A seed gives the tokens that it gives with
+ * x_0 by itself, whether ppd_set_sampling comes before or behind this call:
+ * a first step that draws its token behind a prompt of the first kind takes
+ * x_0 through all layers.  (Behind a first step that did not, later draws
+ * see the keys and values that x_0 has from the prompt pass.)  Implies ppd_reset.  PPD_ECTX if
  * n_prompt > max_ctx; PPD_EINVAL for ids outside [0, vocab).
  * bf16 models with prompts of more than 32 tokens: all prompt rows go through
  * a layer at once (tiled MFMA GEMMs on rows split into two bf16 terms,

@@ -121,7 +121,8 @@ struct ppd_ctx {
   // round state
   int n_ctx;      // absolute position of the pending token x_t (-1: no prefill yet)
   int matched;    // the pending token already went through layers 1..nb (its h is row 0)
-  int prompt_ran; // the pending token is x_0 and went through layers 1..d-1 with the prompt (its h is row 0, that of the exit layer h_exit)
+  int prompt_ran; // the pending token is x_0 and went through layers 1..d-1 with the prompt (its h is row 0, that of the exit layer h_exit): 1 with the
+                  // decode step's bits, 2 with the compute-bound pass's roundings
   int finished;   // last token was EOS
   int have_early;
   ppd_stats st;
@@ -1244,6 +1245,16 @@ bool takes_x0(const ppd_ctx* c, int n_prompt, bool tiled) {
   return 1.25f * more < (step > 20.f ? step : 20.f);
 }
 
+// Whether the round about to start takes x_0 on from where the prompt pass has left it.  Not with the compute-bound pass's roundings where the
+// round draws its token, also where sampling was switched on behind ppd_prefill: x_0 then starts from its embedding, and its keys and values are
+// written anew.
+bool goes_on_with_x0(ppd_ctx* c) {
+  const int ran = c->prompt_ran;
+  c->prompt_ran = 0;
+  if (ran == 2 && c->samp_mode) c->row0 = 0;
+  return ran && c->row0;
+}
+
 // (on the context's stream: a copy on the null stream fails while another thread's context captures a round, and so does the capture.
 // Measured behind a round, copy on the null stream / this: 1024 logits 33 / 21 us, 32000 33 / 33.)
 int copy_logits(ppd_ctx* c, float* host, const float* dev) {
@@ -1558,7 +1569,7 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
   c->prof = prof;
   if (rc) return rc;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->n_ctx = n_prompt - 1; c->matched = 0; c->prompt_ran = last; c->row0 = 1; c->finished = 0;
+  c->n_ctx = n_prompt - 1; c->matched = 0; c->prompt_ran = last ? (tiled ? 2 : 1) : 0; c->row0 = 1; c->finished = 0;
   return PPD_OK;
 }
 
@@ -1568,8 +1579,7 @@ int ppd_step(ppd_ctx* c, int32_t* out_tokens, int max_out, ppd_step_info* info) 
   if (c->finished) return 0;
   const int pos = c->n_ctx;
   if (pos + 1 >= c->d.max_ctx) return PPD_ECTX;   // the candidates sit at position pos+1
-  const int kind = c->prompt_ran ? 4 : (c->matched ? (c->spec ? 3 : 1) : 0);
-  c->prompt_ran = 0;
+  const int kind = goes_on_with_x0(c) ? 4 : (c->matched ? (c->spec ? 3 : 1) : 0);
   int rc = run_round(c, kind, pos);
   if (rc) { c->matched = 0; return rc; }         // (what a round that fails leaves is no row to go on from: the next one embeds its token)
   account_round(c, kind, pos);
@@ -1599,8 +1609,7 @@ int plain_greedy_step(ppd_ctx* c, int32_t* out_token) {
   if (c->finished) return 0;
   const int pos = c->n_ctx;
   if (pos >= c->d.max_ctx) return PPD_ECTX;
-  const int kind = c->prompt_ran ? 5 : 2;
-  c->prompt_ran = 0;
+  const int kind = goes_on_with_x0(c) ? 5 : 2;
   if (c->matched) { c->matched = 0; c->row0 = 0; }       // (row 0 holds the adopted row: this step starts from the embedding)
   int rc = run_round(c, kind, pos);
   if (rc) return rc;

@@ -76,6 +76,40 @@ def test_x0_with_a_long_prompt(name, monkeypatch):
         assert np.abs(g[2] - r[2]).max() <= TOL[cfg.wdtype] / 100, n
 
 
+@pytest.mark.parametrize("mode,ks,p", [(1, 3, 1.0), (2, 0, 0.95)])
+@pytest.mark.parametrize("name", ["opt", "opt_wider", "llama", "llama_late"])
+def test_a_seed_draws_what_it_draws_with_x0_by_itself(name, mode, ks, p, monkeypatch):
+    """Sampling switched on before or behind the prompt, and with PPD_PREFILL_LAST=2: the same tokens, logits and early logits."""
+    cfg = CASES[name].replace(max_ctx=200, n_gen=4)
+    dev = binding.upload_model(pi.make_model(cfg))
+
+    def draw(P, n, behind, plain):
+        P.ppd_set_sampling(0)
+        if not behind:
+            P.ppd_set_sampling(mode, ks, p, 20230713)
+        P.ppd_prefill(pi.make_prompt(cfg, n))
+        if behind:
+            P.ppd_set_sampling(mode, ks, p, 20230713)
+        out = []
+        for t in range(cfg.n_gen):
+            out.append(np.float32(P.plain_greedy_step() if plain else P.ppd_step()[0]))
+            out.extend(P.ppd_get_logits())
+            if not plain:
+                out.extend(P.ppd_get_early_logits())
+        return np.array(out, np.float32)
+
+    P = binding.PPD(cfg, dev, k=3)
+    monkeypatch.setenv("PPD_PREFILL_LAST", "2")
+    Q = binding.PPD(cfg, dev, k=3)
+    for n in (20, 33, 64, 128, 177):
+        for plain in (False, True):
+            ref = draw(Q, n, False, plain)
+            for X, behind in ((P, False), (P, True), (Q, True)):
+                np.testing.assert_array_equal(draw(X, n, behind, plain).view(np.uint32), ref.view(np.uint32), err_msg=f"{n} {behind} {plain}")
+    P.close()
+    Q.close()
+
+
 def test_a_prompt_that_fills_the_context_window():
     cfg = small_cfg("llama", max_ctx=70)
     dev = binding.upload_model(pi.make_model(cfg))

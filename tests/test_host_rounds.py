@@ -1,0 +1,55 @@
+"""What the host launches for a round, on the CPU: the library over a stand-in for the HIP runtime that writes the calls down
+(hip_stand_in.c), in a process of its own."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("si") / "hip_stand_in.so")
+    subprocess.check_call(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_stand_in.c")])
+    return so
+
+
+def run(stand_in, body, **env):
+    from paper_2307_05908_amd import binding
+    binding.load_library()                                     # (built if nothing is)
+    e = {k: v for k, v in os.environ.items() if not k.startswith("PPD_")}
+    r = subprocess.run([sys.executable, "-c", "from host_rounds import *\n" + body, stand_in], cwd=HERE, env=dict(e, **env),
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-4000:]
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("plain", [False, True])
+def test_sampling_switched_on_behind_a_long_prompt_starts_from_the_embedding(stand_in, mode, plain):
+    """A seed's tokens do not depend on whether ppd_set_sampling comes before or behind ppd_prefill: x_0 goes through all layers by
+    itself either way."""
+    run(stand_in, f"""
+mode, plain = {mode}, {plain}
+C = Context()
+C.prefill(64)
+_, taken = C.step(plain)                                       # (the arg max: x_0 went with the prompt)
+C.sample(mode, 3, 0.9, 7)
+C.prefill(64)
+_, alone = C.step(plain)
+assert len(alone) > len(taken)
+C.sample(0)
+C.prefill(64)
+assert C.step(plain)[1] == taken
+C.prefill(64)
+C.sample(mode, 3, 0.9, 7)
+before, late = C.step(plain)
+assert late == alone, (late, alone)
+assert [k for k in before if k.startswith("embed_kernel")], before
+C.sample(0)
+C.prefill(20)                                                  # one chunk: the decode step's bits, x_0 stays with the prompt
+C.sample(mode, 3, 0.9, 7)
+assert len(C.step(plain)[1]) < len(alone)
+C.close()
+""", PPD_FUSED="2")
