@@ -92,12 +92,13 @@ typedef struct {
   int32_t cand[PPD_MAX_K]; /* early top-k ids, by (logit descending, id ascending); entries >= k are -1 */
 } ppd_step_info;
 
-/* Counters in the units of Sec. 4: one layer on one token = one unit. */
+/* Counters in the units of Sec. 4: one layer on one token = one unit.  Layers that x_0 has gone through in
+ * ppd_prefill count with the first round, in rows and in bytes; the prompt's other rows are not counted. */
 typedef struct {
   uint64_t rounds;            /* tokens emitted by ppd_step */
   uint64_t matches;           /* rounds with matched == 1 */
   uint64_t runs;              /* N of Sec. 4.1: rounds that started from layer 1 */
-  uint64_t main_layer_rows;   /* layer executions of the main token (x_0's in ppd_prefill count with the first round): latency in time units */
+  uint64_t main_layer_rows;   /* layer executions of the main token: latency in time units */
   uint64_t branch_layer_rows; /* layer executions of candidate rows */
   uint64_t plain_steps;       /* tokens emitted by plain_greedy_step */
   uint64_t weight_bytes;      /* weight bytes the launched kernels had to stream */

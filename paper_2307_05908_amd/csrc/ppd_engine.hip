@@ -1067,20 +1067,16 @@ int run_round(ppd_ctx* c, int kind, int pos) {
   return run_round_once(c, kind, pos, true);
 }
 
+// (x_0's layers in the prompt pass count with the first round, in bytes as in layer rows: one pass over their weights, keys and values)
 void account_round(ppd_ctx* c, int kind, int pos) {
+  if (kind >= 4) kind = kind == 4 ? 0 : 2;
   const ppd_model_dims& d = c->d;
   const uint64_t wl = ((uint64_t)4 * d.d_model * d.d_model + (uint64_t)(d.act == 2 ? 3 : 2) * d.d_model * d.d_ff) * c->wbytes;
   const uint64_t wh = (uint64_t)d.vocab * d.d_model * c->wbytes;
   const uint64_t kvp = (uint64_t)2 * d.d_model * c->kvbytes;    // K and V of one position of one layer
-  if (kind == 2 || kind == 5) {
-    const int layers = kind == 2 ? d.n_layers : 1;
-    c->st.weight_bytes += layers * wl + wh;
-    c->st.kv_bytes += (uint64_t)layers * pos * kvp;
-    return;
-  }
-  if (kind == 4) {
-    c->st.weight_bytes += (uint64_t)(1 + c->nb) * wl + 2 * wh;
-    c->st.kv_bytes += (uint64_t)pos * kvp + (uint64_t)c->nb * (pos + 1) * kvp;
+  if (kind == 2) {
+    c->st.weight_bytes += d.n_layers * wl + wh;
+    c->st.kv_bytes += (uint64_t)d.n_layers * pos * kvp;
     return;
   }
   const int solo = c->dbar - (kind == 0 ? 0 : c->nb);

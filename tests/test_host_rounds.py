@@ -53,3 +53,25 @@ C.sample(mode, 3, 0.9, 7)
 assert len(C.step(plain)[1]) < len(alone)
 C.close()
 """, PPD_FUSED="2")
+
+
+@pytest.mark.parametrize("last", ["1", "2"])
+def test_the_first_rounds_counters_fit_each_other(stand_in, last):
+    """Bytes and layer rows of a first round count the same layers, whether x_0 went with the prompt or not: what the bytes hold over
+    the rows' weights is whole passes over the LM head, keys and values are those of the rows."""
+    run(stand_in, """
+nb, wl, wh, kv = 3, 2 * (4 * 256 * 256 + 3 * 256 * 696), 2 * 1237 * 256, 2 * 256 * 4
+C = Context()
+for n in (1, 20, 64):
+    C.prefill(n)
+    C.step()
+    s = C.stats()
+    assert s["main_layer_rows"] == 6 and s["branch_layer_rows"] == 3 * nb
+    assert s["weight_bytes"] == (6 + nb) * wl + 2 * wh, (n, s)
+    assert s["kv_bytes"] == (6 * (n - 1) + nb * n) * kv, (n, s)
+    C.prefill(n)
+    C.step(plain=True)
+    s = C.stats()
+    assert s["weight_bytes"] == 6 * wl + wh and s["kv_bytes"] == 6 * (n - 1) * kv, (n, s)
+C.close()
+""", PPD_FUSED="2", PPD_PREFILL_LAST=last)
