@@ -904,7 +904,7 @@ int issue_round(ppd_ctx* c, int kind, int pmax, bool restore = false) {
   return run_head(c, false, true, nullptr, kind == 3);
 }
 
-// the captured rounds are captured anew
+// the captured rounds are captured anew (the stream must be idle)
 hipError_t drop_graphs(ppd_ctx* c) {
   hipError_t e = hipSuccess;
   for (auto& chain : c->graph) for (auto& set : chain)
@@ -995,6 +995,8 @@ int run_round_once(ppd_ctx* c, int kind, int pos, bool again) {
     hipGraphExec_t& graph = c->graph[c->chain][length][kind];
     int& graph_chunks = c->graph_chunks[c->chain][length][kind];
     if (graph && graph_chunks < nchunks) {
+      // (the round before has been heard of by its last kernel's word, not waited for: its launch may still be retiring)
+      HIPCHK(c, hipStreamSynchronize(c->stream));
       HIPCHK(c, hipGraphExecDestroy(graph));
       graph = nullptr;
     }

@@ -63,6 +63,7 @@ err_t hipGraphLaunch(void *e, void *s) {
   (void)s;
   line("G", "");
   for (int i = 0; i < g->n; ++i) line("K", g->node[i]);
+  if (last_launch) last_launch->under_way = 0;             /* (has ended before this round reports) */
   g->under_way = 1; last_launch = g;
   pinned[0] = si_token; pinned[1] = si_match; pinned[SEQ] += 1;
   return 0;
@@ -75,7 +76,7 @@ err_t hipGraphExecDestroy(void *e) {
   free(g);
   return 0;
 }
-err_t hipStreamSynchronize(void *s) { if (s && last_launch) last_launch->under_way = 0; line("S", ""); return 0; }      /* (whatever ran before has ended with it) */
+err_t hipStreamSynchronize(void *s) { if (s && last_launch) last_launch->under_way = 0; line("S", ""); return 0; }
 
 err_t hipMalloc(void **p, size_t n) { *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
 err_t hipFree(void *p) { free(p); return 0; }

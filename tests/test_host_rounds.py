@@ -75,3 +75,20 @@ for n in (1, 20, 64):
     assert s["weight_bytes"] == 6 * wl + wh and s["kv_bytes"] == 6 * (n - 1) * kv, (n, s)
 C.close()
 """, PPD_FUSED="2", PPD_PREFILL_LAST=last)
+
+
+def test_a_round_is_waited_for_before_its_graph_goes(stand_in):
+    """A round returns on the word of its last kernel, which may still run: a captured round that is captured anew for a longer
+    sequence, or dropped with the rule it was captured for, is destroyed only once the stream has been waited for."""
+    run(stand_in, """
+for plain in (False, True):
+    C = Context(max_ctx=2100)
+    for n in (506, 1018, 2042):
+        C.prefill(n)
+        for t in range(12):                                        # (512, 1024 and 2048 positions: another grid of the attention)
+            C.step(plain, match=t % 3 - 1)
+    C.sample(1, 3, 1.0, 7)
+    assert counter("si_destroyed") > 0
+    assert counter("si_destroyed_under_way") == 0
+    C.close()
+""", PPD_FUSED="2")
