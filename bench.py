@@ -65,11 +65,22 @@ def kernel_bytes(cfg, pi, ctx, k):
     return out
 
 
+def prefill_rows(P, prompt):
+    """Prompt rows that ppd_prefill takes through the layers: all of them where x_0 goes along (the step behind it then runs one layer)."""
+    P.ppd_prefill(prompt)
+    P.ppd_set_profiling(2)
+    P.plain_greedy_step()
+    along = P.ppd_get_kernel_time()["gemm_qkv.g1"]["launches"] < P.cfg.n_layers
+    P.ppd_set_profiling(0)
+    return len(prompt) - (0 if along else 1)
+
+
 def prefill_report(cfg, pi, rows, secs, first_secs):
-    """The prompt pass against the MFMA roofline: multiply-adds of the linear layers (2 x rows x weights) and of
-    causal attention; bf16 models run every product twice (the rows as two bf16 terms), priced at the dense bf16 peak."""
-    lin = 2.0 * rows * (cfg.layer_weight_bytes() / cfg.wbytes) * cfg.n_layers
-    att = 4.0 * cfg.d_model * (rows * (rows + 1) / 2) * cfg.n_layers
+    """The prompt pass against the MFMA roofline: multiply-adds of the linear layers (2 x rows x weights) and of causal attention, as far as
+    the pass runs them (of the last layer only Q, K and V); bf16 models run every product twice (the rows as two bf16 terms), priced at
+    the dense bf16 peak."""
+    lin = 2.0 * rows * ((cfg.layer_weight_bytes() / cfg.wbytes) * (cfg.n_layers - 1) + 3 * cfg.d_model ** 2)
+    att = 4.0 * cfg.d_model * (rows * (rows + 1) / 2) * (cfg.n_layers - 1)
     out = {"positions": rows, "ms": round(secs * 1e3, 2), "first_call_ms": round(first_secs * 1e3, 2),
            "positions_per_s": round(rows / secs, 1), "useful_TFLOPs": round((lin + att) / secs / 1e12, 1)}
     if cfg.wdtype == pi.WD_BF16 and rows >= 32:
@@ -231,7 +242,7 @@ def main():
         round_hit.append(bool(info.matched))
 
     t = time.perf_counter()
-    P.ppd_prefill(prompt)                  # (synchronous) the prompt, all but its last token, fills the KV cache
+    P.ppd_prefill(prompt)                  # (synchronous) the prompt fills the KV cache
     prefill_first_s = time.perf_counter() - t      # (includes making the prompt pass's buffers)
     t = time.perf_counter()
     P.ppd_prefill(prompt)
@@ -243,8 +254,12 @@ def main():
     st = P.ppd_get_stats()
     ell = st["rounds"]
     p_hat = st["matches"] / ell
+    head_passes = (st["weight_bytes"] - (st["main_layer_rows"] + (cfg.n_layers - e) * ell) * cfg.layer_weight_bytes()) / cfg.head_weight_bytes() / ell
+    assert 1.0 <= head_passes <= 2.0, "the counters of bytes and of layer rows do not fit each other"
     # ---- plain greedy on the same kernels, same context
     wall_plain = timed(P, P.plain_greedy_step, W, K)
+
+    prompt_rows = prefill_rows(P, prompt)
 
     # ---- timing with HIP events on the library's own stream, separate short passes
     # (a) every kernel bracketed, plain greedy steps and PPD rounds: per-kernel durations of both launch shapes (one launch
@@ -276,7 +291,7 @@ def main():
                 kt[n] = v
         P.ppd_set_profiling(0)
         P.ppd_prefill(prompt)
-        for _ in range(W):
+        for _ in range(max(W, 1)):             # (a first round that goes on with the prompt pass's x_0 has no phases)
             P.ppd_step(want_info=False)
         P.ppd_set_profiling(1)
         s0, c0 = P.ppd_get_stats(), P.ppd_get_chain_rounds()
@@ -433,13 +448,12 @@ def main():
         "plain_greedy": {"tokens_per_s": round(K / wall_plain, 2), "ms_per_token": round(wall_plain / K * 1e3, 4)},
         "ppd_vs_plain_speed": round(wall_plain / wall_ppd, 4),
         "p_correct": round(p_hat, 4),
-        "lm_head_passes_per_round": round((st["weight_bytes"] - (st["main_layer_rows"] + (cfg.n_layers - e) * ell) * wl)
-                                          / (cfg.vocab * cfg.d_model * cfg.wbytes) / ell, 4),
+        "lm_head_passes_per_round": round(head_passes, 4),
         "layer_rows_per_token": {"measured_main": st["main_layer_rows"] / ell,
                                  "measured_total": (st["main_layer_rows"] + st["branch_layer_rows"]) / ell,
                                  "theorem_latency": tradeoff.expected_latency(d, e, ell, p_hat) / ell,
                                  "theorem_compute": tradeoff.expected_compute(d, e, ell, k, p_hat) / ell},
-        "prefill": prefill_report(cfg, pi, n_prompt - 1, prefill_s, prefill_first_s),
+        "prefill": prefill_report(cfg, pi, prompt_rows, prefill_s, prefill_first_s),
         "roofline": roof, "pipelined_step": pipe, "solo_phase": solo, "kernels": kernels, "time_model": model_fit, "cpu_baseline": cpu,
         "setup_s": {"generate_weights": round(t_gen, 1)},
     }
