@@ -638,8 +638,8 @@ __global__ __launch_bounds__(MG_THREADS) void sgemm_kernel(SGemmArgs a) {
 #pragma unroll
   for (int m = 0; m < MT; ++m) acc[m] = (f32x4){0.f, 0.f, 0.f, 0.f};
   for (int p = 0; p < np; ++p) {
-    // this phase's rows have arrived: they were requested before the newest SG_RING weight blocks; everybody is done with the other buffer
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(SG_RING) : "memory");
+    // this phase's rows have arrived: they were requested before the newest SG_RING weight blocks; everybody has read the other buffer
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(SG_RING) : "memory");
     if (p + 1 < np) stage(p + 1);
     const int n = nblk - p * SG_PB < SG_PB ? nblk - p * SG_PB : SG_PB;
     const char* const x = lds + (size_t)(p & 1) * SG_PB * 2 * MT * 1024 + lane * 16;
