@@ -27,25 +27,25 @@ hipError_t launch_gemm_small(hipStream_t stream, const GemmArgs& a, int ngroups,
   return launch_gemm_small_t<4>(stream, a, mmax, paired, grid);
 }
 #elif PPD_INST < 4 || PPD_INST == 6
-// Whether one row's gains are requested with the row.  (bf16 rows of up to 5120 elements are early_kernel's by now.)  It puts the weights off, which pays where a wave streams several sets of
-// rows of some length.  Measured (early prediction over bf16 weights, last / first, us): 2752 elements 32000 logits 47.5 / 46.2,
-// 12000 29.4 / 29.4, 5065 20.8 / 21.7, 1000 16.0 / 16.9; 4096 elements 59.5 / 58.9, 34.1 / 36.3, 25.2 / 26.6, 18.4 / 19.2; 1032
-// elements 34.7 / 34.7, 24.3 / 25.1, 18.3 / 18.9, 14.6 / 15.1.  fp32 weights: first everywhere (a plain token of a 3072-wide
-// model 654 / 641 us, 1000 to 50000 logits within 1 %).
-inline bool gains_first(const GemmArgs& a, unsigned grid) { return a.K >= 2048 && a.ntot > 2 * 4 * GEMM_WAVES * (int)grid; }
+// Whether one row's gains are requested with the row (bf16: rows of more than 5120 elements, the others are early_kernel's).  It puts the
+// weights off, which pays where a wave streams several sets of rows.  Measured (early prediction over bf16 weights, last / first, us, RMSNorm and
+// LayerNorm): 8192 elements 32000 logits 108.1 / 108.6 and 111.0 / 109.9, 12000 56.8 / 56.7 and 58.4 / 58.2, 5065 36.5 / 37.5 and 38.4 / 39.2, 1000
+// 22.4 / 23.1 and 24.6 / 24.7; 7168 elements 32000 84.9 / 85.6 and 87.1 / 86.4, 1000 21.0 / 21.8 and 23.0 / 23.3; 6144 elements 32000 77.3 / 77.4
+// and 78.6 / 78.6, 12000 43.9 / 44.8 and 45.5 / 45.8; 5128 elements 32000 71.5 / 71.4 and 72.7 / 73.0, 5065 28.9 / 29.4 and 30.8 / 31.2.
+// fp32 weights: first everywhere (a plain token of a 3072-wide model 654 / 641 us, 1000 to 50000 logits within 1 %).
+inline bool gains_first(const GemmArgs& a, unsigned grid) { return a.ntot > 2 * 4 * GEMM_WAVES * (int)grid; }
 // MA rows in group 0; MB rows in group 1 (0: single-group launch).  Launch shapes in use:
-// (1, 0) main token alone, (k, 0) the candidates alone, (1, k) both in one launch.
+// (1, 0) main token alone, (k, 0) the candidates alone, (1, k) both in one launch; bf16 weights: (1, 0).
 template <typename WT, bool PAIRED, int WR>
 hipError_t launch_gemm_t(hipStream_t stream, const GemmArgs& a, int MA, int MB, dim3 grid, size_t lds) {
 #define GO(ma, mb) hipLaunchKernelGGL((gemm_kernel<WT, ma, mb, PAIRED, WR>), grid, dim3(GEMM_THREADS), lds, stream, a)
-  if (MB == 0) {
+  if constexpr (sizeof(WT) == 2) {
+    if (MA != 1 || MB != 0) return hipErrorInvalidValue;
+    if (gains_first(a, grid.x)) GO(1, 0);
+    else hipLaunchKernelGGL((gemm_kernel<WT, 1, 0, PAIRED, WR, false>), grid, dim3(GEMM_THREADS), lds, stream, a);
+  } else if (MB == 0) {
     switch (MA) {
-      case 1:
-        if constexpr (sizeof(WT) == 2) {
-          if (!gains_first(a, grid.x)) { hipLaunchKernelGGL((gemm_kernel<WT, 1, 0, PAIRED, WR, false>), grid, dim3(GEMM_THREADS), lds, stream, a); break; }
-        }
-        GO(1, 0); break;
-      case 2: GO(2, 0); break; case 3: GO(3, 0); break; case 4: GO(4, 0); break;
+      case 1: GO(1, 0); break; case 2: GO(2, 0); break; case 3: GO(3, 0); break; case 4: GO(4, 0); break;
       case 5: GO(5, 0); break; case 6: GO(6, 0); break; case 7: GO(7, 0); break; case 8: GO(8, 0); break;
       default: return hipErrorInvalidValue;
     }

@@ -333,8 +333,7 @@ hipError_t early_topk_launch(const EarlyTopkPlan& p, int d_model, int vocab, int
   a.K = d_model; a.N[0] = vocab; a.ntot = vocab; a.ldx = d_model; a.ldy = vocab;
   a.norm = norm; a.eps = norm_eps; a.act = 0; a.KC = p.KC;
   a.topk = k; a.pk_val = pk_val; a.pk_idx = pk_idx;
-  hipError_t e = wdtype == 0 && gemm_small_fits(a, p.grid) ? launch_gemm_small(stream, a, 1, false, p.grid)
-               : wdtype == 0 ? launch_gemm_t<float, false, 4>(stream, a, 1, 0, dim3(p.grid, 1), p.lds)
+  hipError_t e = wdtype == 0 ? launch_gemm_t<float, false, 4>(stream, a, 1, 0, dim3(p.grid, 1), p.lds)
                              : launch_gemm_t<bf16_t, false, 4>(stream, a, 1, 0, dim3(p.grid, 1), p.lds);
   if (e != hipSuccess) return e;
   TopkMergeArgs t;
