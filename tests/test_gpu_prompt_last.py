@@ -1,6 +1,8 @@
 """x_0, the prompt's last token, goes through all layers but the last with the prompt's other rows; PPD_PREFILL_LAST=2 leaves it to
-the first round.  Prompts whose rows take the decode step's arithmetic (one chunk of a bf16 model; others stay as they were): the same bits, tokens,
-candidates and counters, over exit layers, numbers of candidates, and prompts of which x_0 is the last of a few rows, of a tile and of the chunk.  Longer prompts of bf16 models: close logits, and PPD == plain greedy bit for bit."""
+the first round.  Prompts whose rows take the decode step's arithmetic (one chunk of a bf16 model): the same bits, tokens,
+candidates and counters, over exit layers, numbers of candidates, and prompts of which x_0 is the last of a few rows, of a tile and of the chunk.  Prompts that
+leave x_0 to the first round (several chunks, fp32 models) are among them as they stood before.  Longer prompts of bf16 models: close
+logits, and PPD == plain greedy bit for bit.  Which of these prompts take x_0 along is what test_host_rounds.py checks, without a GPU."""
 import numpy as np
 import pytest
 
@@ -20,6 +22,8 @@ CASES = {
     "llama": small_cfg("llama", n_gen=4, max_ctx=160),
     "llama_late": small_cfg("llama", exit_layer=5, alpha=0.02, n_gen=4, max_ctx=160),
 }
+ONE_CHUNK = (1, 2, 3, 8, 9, 16, 17, 32)
+LONG = (33, 34, 63, 64, 65, 66, 100, 128, 129, 257, 590)      # (in the compute-bound pass; several chunks with PPD_PREFILL_TILED=2)
 
 
 def generate(cfg, dev, prompts, k, monkeypatch, **env):
@@ -46,7 +50,7 @@ def generate(cfg, dev, prompts, k, monkeypatch, **env):
 def test_x0_with_the_prompt_is_x0_by_itself_bit_exact(name, k, monkeypatch):
     cfg = CASES[name]
     dev = binding.upload_model(pi.make_model(cfg))
-    prompts = (1, 2, 3, 8, 9, 16, 17, 32) + ((33, 34, 64, 65, 66, 100) if cfg.max_ctx >= 120 else ())
+    prompts = ONE_CHUNK + ((33, 34, 64, 65, 66, 100) if cfg.max_ctx >= 120 else ())
     env = dict(PPD_PREFILL_TILED="2")
     got = generate(cfg, dev, prompts, k, monkeypatch, **env)
     ref = generate(cfg, dev, prompts, k, monkeypatch, PPD_PREFILL_LAST="2", **env)

@@ -6,6 +6,9 @@ import sys
 
 import pytest
 
+import ppd_inputs as pi
+from test_gpu_prompt_last import CASES, LONG, ONE_CHUNK
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -23,6 +26,55 @@ def run(stand_in, body, **env):
     r = subprocess.run([sys.executable, "-c", "from host_rounds import *\n" + body, stand_in], cwd=HERE, env=dict(e, **env),
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-4000:]
+
+
+def dims(cfg):
+    return {n: getattr(cfg, n) for n in ("n_layers", "d_model", "n_heads", "head_dim", "d_ff", "vocab", "max_ctx", "norm", "act", "pos", "has_bias", "wdtype")}
+
+
+# The first round's attention launches.  Where x_0 went along, one for it, elsewhere one a layer (a PPD round: up to the exit layer E); and one
+# for each layer of the candidates, with or without x_0.
+ALONG = """
+def attentions(C, n, plain):
+    C.prefill(n)
+    return sum(k.startswith("attn_kernel") or k.startswith("attn_whole") for k in C.step(plain)[1])
+def along(C, n):
+    plain, ppd = attentions(C, n, True), attentions(C, n, False) - (L - E)
+    assert (plain, ppd) in ((1, 1), (L, E)), (plain, ppd)
+    return plain == 1
+"""
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_where_x0_goes_with_the_prompt(stand_in, name):
+    """The prompts of test_gpu_prompt_last.py take the path that it compares: x_0 goes along behind one chunk and in the compute-bound
+    pass, not in fp32 models, not where several chunks go through the decode step's kernels, and not with PPD_PREFILL_LAST=2."""
+    cfg = CASES[name].replace(max_ctx=600)
+    body = f"""
+L, E, bf16 = {cfg.n_layers}, {cfg.exit_layer}, {cfg.wdtype == pi.WD_BF16}
+C = Context(3, {cfg.exit_layer}, **{dims(cfg)})
+{ALONG}
+for n in {ONE_CHUNK}:
+    assert along(C, n) == (ONE_CHUNK and bf16 and n > 1), n
+for n in {LONG}:
+    assert along(C, n) == (TILED and bf16), n
+C.close()
+"""
+    run(stand_in, "ONE_CHUNK = TILED = True\n" + body, PPD_FUSED="2")
+    run(stand_in, "ONE_CHUNK, TILED = True, False\n" + body, PPD_FUSED="2", PPD_PREFILL_TILED="2")
+    run(stand_in, "ONE_CHUNK = TILED = False\n" + body, PPD_FUSED="2", PPD_PREFILL_LAST="2")
+    run(stand_in, "ONE_CHUNK = TILED = False\n" + body, PPD_FUSED="2", PPD_PREFILL_CHUNK="1")
+
+
+def test_a_further_row_of_tiles_costs_wide_models_more_than_the_step(stand_in):
+    cfg = pi.CONFIGS["llama7b"].replace(n_layers=4, exit_layer=2, vocab=512, max_ctx=640)
+    run(stand_in, f"""
+L, E = {cfg.n_layers}, {cfg.exit_layer}
+C = Context(3, {cfg.exit_layer}, **{dims(cfg)})
+{ALONG}
+assert [n for n in (2, 32, 33, 64, 65, 128, 129, 256, 257, 258, 512, 513, 514) if not along(C, n)] == [257, 513]
+C.close()
+""", PPD_FUSED="2")
 
 
 @pytest.mark.parametrize("mode", [1, 2])
