@@ -34,7 +34,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # (paper_2307_05908_amd/ppd_pmc_probe), see profiles/.  A property of the kernel source it was collected on.
 MEASURED_TRAFFIC = {("llama7b", 3): 361.71e6}
 # sha1 of csrc/ppd_kernels.h when the counters were collected: a changed kernel source voids the figure (null is printed)
-TRAFFIC_KERNELS_SHA1 = "f37a0588b13279c6f0c7f0476c7bf2bc02dc59ca"
+TRAFFIC_KERNELS_SHA1 = "7bfe0ae5b2248a0fae0103303997252707774450"
 TRAFFIC_SOURCE = "profiles/llama7b_ppd_k3_traffic.txt"
 
 

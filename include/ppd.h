@@ -154,13 +154,17 @@ int ppd_reset(ppd_ctx *ctx);
  * bf16 models with prompts of more than 32 tokens: all prompt rows go through
  * a layer at once (tiled MFMA GEMMs on rows split into two bf16 terms,
  * causal attention on the same operands): products exact in fp32 as in
- * decoding, other summation order, so the cache is close to, not
- * bit-identical with, a token-by-token pass (every decode step after it is
- * the same arithmetic either way).  Otherwise, or with PPD_PREFILL_TILED=2 /
+ * decoding, other summation order, so the cache, and where x_0 goes along
+ * its row, are close to, not bit-identical with, those of a token-by-token
+ * pass: so are the first step's logits with x_0 along to those with x_0 by
+ * itself (which of the two a prompt gets depends on its length and the model's
+ * shape).  From the cache on, every decode step is the same arithmetic either
+ * way.  Otherwise, or with PPD_PREFILL_TILED=2 /
  * PPD_PREFILL_CHUNK=n in the environment at ppd_create, the prompt goes
  * through the decode kernels in chunks of 32 consecutive positions (n
- * lowers it): one pass over the weights per chunk, every row's arithmetic that of a one-token pass, the cache equal to
- * a token-by-token prefill bit for bit (n = 1 runs exactly that).
+ * lowers it): every row's arithmetic that of a one-token pass, the cache equal
+ * to a token-by-token prefill bit for bit (n = 1 runs exactly that).  bf16
+ * models read the weights once per chunk, fp32 models once per eight rows.
  * Buffers of the first kind are allocated at the first such prompt and grow
  * with the longest prompt seen (PPD_ENOMEM / PPD_EHIP if that fails). */
 int ppd_prefill(ppd_ctx *ctx, const int32_t *prompt, int n_prompt);

@@ -23,7 +23,9 @@ enum {
                         (hidden row + KV tails -> cache) */
   PPD_KC_COMMIT,     /* unused (adoption runs inside PPD_KC_SELECT) */
   PPD_KC_PHASE,      /* not a kernel: one bracket around a whole phase of a round (groups = 1: the
-                        main token alone up to the exit layer; groups = 2: the d-dbar pipelined steps) */
+                        main token alone up to the exit layer; groups = 2: the d-dbar pipelined steps).
+                        None in a first round whose x_0 went with the prompt: its last layer and the
+                        candidates' layers are single-group launches of their own */
   PPD_KC_COUNT
 };
 

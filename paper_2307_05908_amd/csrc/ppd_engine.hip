@@ -1226,6 +1226,11 @@ int prefill_tiled(ppd_ctx* c, int rows, bool last) {
 // 257 2776 / 2777 and 513 3964 / 3983 (by itself either way); 13B shape, 8 layers, 4096 rows 33.5 / 32.5 ms; OPT-125m shape, 9 rows
 // 796 / 641, 128 1043 / 784.  fp32 models, whose rounds are replayed launches of 2 - 4 us, gain nothing: 256 wide, 2 rows 212 / 235, 16
 // 370 / 369, a PPD round behind 16 401 / 431.
+// Prompts of several chunks are left out for a fault, not for speed: the first version took x_0 along there too, ran the first round launch by launch
+// between captured ones and moved the row by device-to-device copies, and one run of the tests ended in a segmentation fault of the host inside
+// ppd_step, in a context that had such prompts of 33 to 250 tokens.  The cause was not found, neither by reading nor over a stand-in for the
+// runtime with address and undefined-behaviour checks; those two kinds of calls are gone with the path (a first round is captured like any other, a
+// kernel moves the row), and captured rounds are waited for before they are destroyed, which they were not then.
 bool takes_x0(const ppd_ctx* c, int n_prompt, bool tiled) {
   if (!c->mfma || !c->prefill_last || n_prompt < 2) return false;
   if (!tiled) return n_prompt <= c->prefill_chunk;
@@ -1530,8 +1535,8 @@ int ppd_prefill(ppd_ctx* c, const int32_t* prompt, int n_prompt) {
   const WorkScope work(c);
   int prof = c->prof; c->prof = 0;
   c->chain = 0;
-  // positions 0 .. n_prompt-2 in chunks of consecutive positions: every row's arithmetic is that of a
-  // token-by-token pass (PPD_PREFILL_CHUNK=1 runs exactly that), the weights are streamed once per chunk
+  // positions 0 .. n_prompt-2, and x_0's where it goes along, in chunks of consecutive positions: every row's arithmetic is that of a
+  // token-by-token pass (PPD_PREFILL_CHUNK=1 runs exactly that); bf16 models stream the weights once per chunk
   const int chunk = c->prefill_chunk;
   const bool tiled = c->prefill_tiled && n_prompt - 1 >= PREFILL_TILED_MIN;
   const bool last = takes_x0(c, n_prompt, tiled);

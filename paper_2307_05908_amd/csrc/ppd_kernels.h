@@ -147,7 +147,6 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4* p, size_t
   for (; i < n16; i += stride) acc ^= ld_stream(p + i);
   if ((acc.x ^ acc.y ^ acc.z ^ acc.w) == 0x9e3779b9u) *sink = acc.x;   // keeps the loads alive; practically never taken
 }
-// take_next: the round about to start uses the candidates the previous round predicted for it
 __global__ void set_state_kernel(DevState* ds, int pos, int tok) {
   if (threadIdx.x == 0) { ds->pos = pos; if (tok >= 0) ds->next_tok = tok; }
 }
@@ -1298,8 +1297,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(MergeArgs a) 
 // Final prediction: arg max of the final logits (ties to the lowest id), verification against the
 // early candidates (Algorithm 2's comparison of each candidate with the final token), then adoption:
 // on a match the matching candidate's hidden row becomes the main row and its key/value tails of layers
-// 1..d-dbar become cache position t+1; without a match nothing is copied and the tails are overwritten
-// by the next round.
+// 1..d-dbar become cache position t+1; without a match the tails are overwritten by the next round, and
+// the main row becomes the token's embedding.  The workgroup that is done last leaves the next position.
 // Appendix B's sampling-based variants replace only the arg max: the token verified here is then the one
 // drawn by top-k sampling (inside this kernel, from the merged lists) or by the sampling kernel (top-p).
 struct SelectArgs {
@@ -1308,8 +1307,8 @@ struct SelectArgs {
   int k;
   int mode;             // 0: early top-k -> cand[0..k) + embed; 1: final arg max + verify + adopt
   DevState* ds;
-  int32_t* host_result; // device-visible pinned host memory: [0] token, [1] match_idx (mode 1), [2..2+k) candidates (mode 0),
-                        // [2 + MAXM] number of finished rounds, written after the rest (mode 1): the host polls it
+  int32_t* host_result; // device-visible pinned host memory: [0] token, [1] match_idx (mode 1), [2..2+k) candidates (mode 0, or
+                        // mode 1 where the round before predicted them), [2 + MAXM] number of finished rounds, written after the rest (mode 1): the host polls it
   EmbedArgs emb;        // candidate rows (mode 0; mode 1 with spec)
   EmbedArgs next;       // mode 1: row 0 of the next round, unless that one begins with an adopted row
   int take_next;        // mode 1: the round's candidates are those that the round before predicted (cand_next)
@@ -2124,9 +2123,10 @@ __global__ __launch_bounds__(MG_THREADS) void gemm_mfma_kernel(MGemmArgs a) {
   float* redB = redA + 16 * MG_WAVES;
   float* hlog = (float*)(lds + off_x);        // head launches: [M][HEAD_MAX_ROWS] logits, over the staged rows once those are done with
 
-  // ---- 1. input rows (and the norm's gain and bias) into LDS, fp32 as they are: wave w takes the
-  // kilobyte pieces w, w + 8, ... of every row.  These requests come first: a wave's loads return in order.
-  // With passes, a staged row is 8 runs (one per wave) of nbp blocks; float f of the row belongs to wave
+  // ---- 1. input rows (and the norm's gain and bias) into LDS, fp32 as they are.  These requests come first: a wave's loads return in
+  // order.  A wave brings exactly the share of every row that it multiplies (its eighth of the reduction length), and later converts that share
+  // alone: without a norm no barrier stands between the two, so nothing else may be read from the rows before the main loop is done.
+  // With passes (a barrier follows each), wave w takes the kilobyte pieces w, w + 8, ... of every row; a staged row is 8 runs (one per wave) of nbp blocks; float f of the row belongs to wave
   // f / (32 nbp)'s share, block (pass * nbp + (f / 32) % nbp) of it.  pass_col gives the input column, or -1.
   const int npass = MP ? a.passes : 1;
   const int nb8_ = (KT + MG_WAVES - 1) / MG_WAVES, nbp_ = mg_nbp(KT, npass);
